@@ -55,6 +55,20 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// The four lanes 16 apart (l % 16 alike) combined by `op` without a trip through LDS: two register
+// swaps, of odd with even 16-lane rows and of the wave's halves, leave each lane with its own
+// and its partner's value.
+template <class Op>
+__device__ __forceinline__ float rows16_reduce(float v, Op op) {
+  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+  const unsigned x = __float_as_uint(v);
+  const u2v a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  const float p = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const unsigned y = __float_as_uint(p);
+  const u2v b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // (value, index) minimum with ties to the lower index.
 __device__ __forceinline__ void argmin_merge(float& v, int& i, float v2, int i2) {
   if (v2 < v || (v2 == v && i2 < i)) {

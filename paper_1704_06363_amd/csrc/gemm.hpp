@@ -36,7 +36,7 @@ constexpr int kStageRowBytes = 128;  // K extent of one stage, in bytes
 template <typename T, int BM_, int BN_, int WM_, int WN_>
 struct Cfg {
   using type = T;
-  static constexpr bool DMA = false;  // register-staged engine
+  static constexpr bool DMA = false, PIPE = false, SPLIT = false;  // register-staged engine
   static constexpr bool TRANS = false;  // accumulator element (i, j, r) at row 16 i + 4 (l / 16) + r, col 16 j + l % 16
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int WAVES_N = BN / WN, WAVES_M = BM / WM;
@@ -299,7 +299,7 @@ template <typename T, int BM_, int BN_, int WM_, int WN_, int NS_>
 struct CfgD {
   using type = T;
   static constexpr bool F32 = sizeof(T) == 4;
-  static constexpr bool DMA = true;
+  static constexpr bool DMA = true, PIPE = false, SPLIT = false;
   static constexpr bool TRANS = true;  // accumulator element (i, j, r) at row 16 i + l % 16, col 16 j + 4 (l / 16) + r
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int WAVES_N = BN / WN, WAVES_M = BM / WM;
@@ -313,24 +313,6 @@ struct CfgD {
   static_assert(sizeof(T) == 2 || sizeof(T) == 4, "bf16 or fp32 operands");
 };
 
-// 256 x 256 tiles, eight waves of 128 x 64, a 4-stage ring (128 KB): 3 and 5 stages measured
-// slower for the decoder and expert GEMMs.
-typedef CfgD<bf16, 256, 256, 128, 64, 4> CfgDma;
-// The last row tile of a group with at most 128 rows (the short buckets of skewed routing) runs
-// at half height: 128 x 256, eight waves of 64 x 64, a 5-stage ring (120 KB, inside the
-// 256 x 256 tile's allocation), with half the MFMA work of the padded 256-row tile.  Such a
-// tile streams a whole weight panel for few rows: with one row per bucket, 1024 tiles read
-// their 1.07 GB of panels at ~4 TB/s whether the ring runs 4, 5 or 6 stages.
-typedef CfgD<bf16, 128, 256, 64, 64, 5> CfgDmaShort;
-template <class C>
-struct ShortTile {
-  using type = void;
-};
-template <>
-struct ShortTile<CfgDma> {
-  using type = CfgDmaShort;
-};
-typedef CfgD<float, 256, 256, 128, 64, 4> CfgDmaF32;        // fp32, K-contiguous operands
 // fp32 with at most 64 columns (the gater's assignment, K <= 64): 128 x 64 tiles of four waves
 // and a 3-stage ring (36 KB), four workgroups per CU -- measured against 256 x 64 (4 stages:
 // 11% slower; 3 stages: 15%), 128 x 64 with 2 or 4 stages (10%, 8%) and 64 x 64 (17%)
@@ -448,7 +430,7 @@ __device__ __forceinline__ void dma_read_frags(const lds<char>* bA, const lds<ch
 
 // The stage's MFMAs.  B is the MFMA's first operand: the 16 x 16 result is the transposed
 // sub-tile, so each lane ends up with four consecutive output columns of one row (see TRANS).
-// ROWNORM: xs[i] += squares of this lane's 8 elements of A fragment i, for the fragments
+// ROWNORM: xs[i / WAVES_N] += squares of this lane's 8 elements of A fragment i, for the fragments
 // i = wn (mod WAVES_N) that this wave is responsible for (the work is spread over the waves
 // that share the rows; each row's sum stays within one wave), as four packed bf16 dot products
 // (the squares of bf16 values are exact in fp32).
@@ -471,7 +453,7 @@ __device__ __forceinline__ void dma_mfmas(const bf16x8 (&a)[C::MI], const bf16x8
         if ((i % C::WAVES_N) == wn) {
           const floatx4 v = __builtin_bit_cast(floatx4, a[i]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) xs[i] = fmaf(v[e], v[e], xs[i]);
+          for (int e = 0; e < 4; ++e) xs[i / C::WAVES_N] = fmaf(v[e], v[e], xs[i / C::WAVES_N]);
         }
     }
     return;
@@ -489,7 +471,7 @@ __device__ __forceinline__ void dma_mfmas(const bf16x8 (&a)[C::MI], const bf16x8
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const bf16x2 v = {a[i][2 * e], a[i][2 * e + 1]};
-          xs[i] = __builtin_amdgcn_fdot2_f32_bf16(v, v, xs[i], false);
+          xs[i / C::WAVES_N] = __builtin_amdgcn_fdot2_f32_bf16(v, v, xs[i / C::WAVES_N], false);
         }
       }
   }
@@ -596,7 +578,7 @@ struct DmaTile {
     static_assert(!ROWNORM || A_KC, "row norms need a K-contiguous A");
     if constexpr (ROWNORM) {
 #pragma unroll
-      for (int i = 0; i < C::MI; ++i) xs[i] = 0.f;
+      for (int i = 0; i < (C::MI + C::WAVES_N - 1) / C::WAVES_N; ++i) xs[i] = 0.f;
     }
 #pragma unroll
     for (int i = 0; i < C::MI; ++i)
@@ -676,12 +658,503 @@ struct DmaTile {
   }
 };
 
+// ------------------------------------------------------------------ pipelined engine
+//
+// 256 x 256 tiles of eight waves (128 x 64 each) on a direct-to-LDS pipeline of 64-element
+// stages: 128-byte rows, so that every load instruction reads whole 128-byte lines.  (A ring of
+// 32-element stages, the same tile and waves, fetched every line twice, half at a time: on NT
+// products of 8192^3 / 65536 x 4096 x 2048 / 2^20 x 1024 x 2048 it ran at 1134 / 1075 / 1125
+// TFLOP/s against 1513 / 1339 / 1345 here; with a K-strided B, 65536 x 1024 x 50000, 1225
+// against 1454; with both K-strided 1174 against 1415.)
+//
+// A stage holds four half panels, each in a slot of its own, two stages in LDS (128 KB): half h
+// of A has rows 64 h .. 64 h + 63 of every 128-row wave strip, half h of B columns 32 h .. + 31
+// of every 64-column wave strip (SPLIT: the halves are contiguous, which keeps the lines of a
+// K-strided B whole; a wave then owns 32 columns of each half).  A wave computes its tile in
+// two phases per stage, 32 MFMAs and 12 fragment reads each:
+//   phase 0   reads A0(s), B1(s):     A0 B0, A0 B1        (B0(s) was read one phase earlier)
+//   phase 1   reads A1(s), B0(s + 1): A1 B0, A1 B1
+// The two wave groups (waves 0-3 and 4-7, one of each per SIMD) run one half phase apart, so
+// that one reads while the other feeds the matrix cores: every phase is [reads, loads, barrier,
+// MFMAs, barrier], and the offset is one extra barrier, taken by group 1 before the loop and by
+// group 0 after it.  Phase q issues the loads of the slots that phase q - 1 has read, three
+// phases before they are needed:
+//   phase 0 of s:  A1(s + 1), B0(s + 2)        phase 1 of s:  A0(s + 2), B1(s + 2)
+// Slot order: group 0's phase q lies between barriers 2q and 2q + 2 and group 1's between 2q + 1
+// and 2q + 3, each with its reads done (lgkmcnt) before its middle barrier, so every read of
+// phase q - 1 precedes barrier 2q and the loads that overwrite it follow.  Arrival: each wave
+// waits for its own loads of phase q before its middle barrier of phase q - 1, and the barrier
+// that starts group 0's phase q is no earlier than that; vmcnt counts in issue order, and the
+// events behind the one waited for are those of the last two phases.
+// Waves at raised priority around the MFMAs measured 1-3% slower.
+//
+// Offsets from a tile's base are 32-bit (one VGPR per load, the base in SGPRs): row widths must
+// be below kPipeMaxLd elements; wider rows take the register-staged engine.
+// fp32 operands (F32) run as 16-bit units, as on the ring engine.
+constexpr int64_t kPipeMaxLd = int64_t(1) << 23;  // 255 rows x 2 bytes x ld < 2^32
+
+template <typename T, int BM_, int BN_, int WM_, int WN_, bool SPLIT_>
+struct CfgP {
+  using type = T;
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr bool DMA = true, PIPE = true;
+  static constexpr bool TRANS = true;  // accumulator element (i, j, r) at row 16 i + l % 16, col 16 j + 4 (l / 16) + r
+  static constexpr bool SPLIT = SPLIT_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+  static constexpr int WAVES_N = BN / WN, WAVES_M = BM / WM;
+  static constexpr int WAVES = WAVES_M * WAVES_N;
+  static constexpr int THREADS = 64 * WAVES;
+  static constexpr int MI = WM / 16, NJ = WN / 16;
+  static constexpr int BK = 64;  // in 16-bit units (128-byte rows)
+  static constexpr int A_HALF = BM / 2 * BK * 2, B_HALF = BN / 2 * BK * 2;
+  static constexpr int STAGE = 2 * (A_HALF + B_HALF);
+  static constexpr int LDS = 2 * STAGE;
+  static_assert(sizeof(T) == 2 || sizeof(T) == 4, "bf16 or fp32 operands");
+  static_assert(WM % 64 == 0 && WN % 64 == 0, "half strips of whole swizzle periods");
+};
+typedef CfgP<bf16, 256, 256, 128, 64, false> CfgPipe;    // B K-contiguous
+typedef CfgP<bf16, 256, 256, 128, 64, true> CfgPipeKS;   // B K-strided
+typedef CfgP<float, 256, 256, 128, 64, false> CfgPipeF32;  // fp32, K-contiguous operands
+// The last row tile of a group with at most 128 rows (the short buckets of skewed routing) runs
+// at half height, with half the MFMA work of the padded 256-row tile.
+typedef CfgP<bf16, 128, 256, 64, 64, false> CfgPipeShort;
+typedef CfgP<bf16, 128, 256, 64, 64, true> CfgPipeShortKS;
+template <class C>
+struct ShortTile {
+  using type = void;
+};
+template <>
+struct ShortTile<CfgPipe> {
+  using type = CfgPipeShort;
+};
+template <>
+struct ShortTile<CfgPipeKS> {
+  using type = CfgPipeShortKS;
+};
+
+// threadIdx.x, computed with anew at each use: a persistent kernel's per-lane address terms are
+// otherwise hoisted out of its tile loop, where they crowd the K loop's registers into scratch.
+__device__ __forceinline__ int thread_id() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// A wave-uniform pointer as scalar registers (whatever the compiler keeps its inputs in).
+__device__ __forceinline__ const char* uniform(const char* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+
+// Half panels of an operand of R tile rows, W per wave strip.
+//   K-contiguous: slot [R / 2 rows][64 K], 16-byte chunk c of slot row r at c ^ ((r ^ (r >> 2)) & 7).
+//   K-strided:    slot [64 K][R / 2 rows], chunk swizzle of ks_off<R / 2>.
+template <int R, int W, int THREADS, bool KC, bool SPLIT>
+struct HalfPanels {
+  static constexpr int HR = R / 2;
+  static constexpr int NQ = HR * 128 / (THREADS * 16);  // loads per wave and half
+  static_assert(NQ * THREADS * 16 == HR * 128, "whole loads");
+  uint32_t off[2][NQ];  // byte offset of this lane's 16 bytes from the stage's base
+
+  // tile row of row q of half h
+  __device__ __forceinline__ static int tile_row(int h, int q) {
+    if constexpr (SPLIT) return h * HR + q;
+    constexpr int G = W / 2;
+    return (q / G) * W + h * G + q % G;
+  }
+  // byte offset and K position (within the stage) of 16-byte slot piece `piece` of half h; rows
+  // past the valid range take a valid row's bytes (they only feed outputs that are not stored)
+  __device__ __forceinline__ static uint32_t source(int h, int piece, int64_t ld, int rows_valid, int& kk) {
+    if constexpr (KC) {
+      const int r = piece >> 3, p = piece & 7;
+      const int c = p ^ ((r ^ (r >> 2)) & 7);
+      int tr = tile_row(h, r);
+      tr = tr < rows_valid ? tr : rows_valid - 1;
+      kk = c * 8;
+      return (uint32_t)((tr * ld + c * 8) * 2);
+    } else {
+      constexpr int CPR = HR / 8;
+      const int k = piece / CPR, p = piece % CPR;
+      const int sw = ((k & 3) | ((k >> 1) & 4)) << 1;
+      const int col = tile_row(h, (p ^ sw) * 8);
+      kk = k;
+      return (uint32_t)((k * ld + (col < rows_valid ? col : 0)) * 2);
+    }
+  }
+  __device__ __forceinline__ void init(int64_t ld, int rows_valid) {
+    const int t = thread_id();  // piece q THREADS + t of a half is this thread's
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        int kk;
+        off[h][q] = source(h, q * THREADS + t, ld, rows_valid, kk);
+      }
+  }
+  template <int H>
+  __device__ __forceinline__ void issue(const char* __restrict__ base, lds<char>* slot) const {
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      uint32_t o = off[H][q];
+      asm volatile("" : "+v"(o));  // keeps base + o an SGPR base with a 32-bit offset
+      __builtin_amdgcn_global_load_lds((const void*)(base + o), (lds<void>*)(slot + (q * (THREADS / 64) + w) * 1024),
+                                       16, 0, 0);
+    }
+  }
+  // The last, partial stage of k_left K positions, through registers; zero past them.
+  __device__ __forceinline__ static void tail(int h, const char* __restrict__ base, int64_t ld, int rows_valid,
+                                              int k_left, lds<char>* slot) {
+    const int t = thread_id();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int piece = q * THREADS + t;
+      int kk;
+      const uint32_t o = source(h, piece, ld, rows_valid, kk);
+      i32x4 v = i32x4{0, 0, 0, 0};
+      if (kk < k_left)
+        v = *reinterpret_cast<const __attribute__((address_space(1))) i32x4*>(
+            (const __attribute__((address_space(1))) char*)base + o);
+      *reinterpret_cast<lds<i32x4>*>(slot + piece * 16) = v;
+    }
+  }
+};
+
+// A lane's LDS addresses of the MFMA fragments in a half-panel slot: fragment i covers rows
+// row0 + 16 i .. + 15 (row0 a multiple of 32) and K 32 ks .. + 31.  `at` is the slot's offset.
+template <bool KC, int HR, int N>
+struct HalfFrags {
+  // KC: two addresses, the swizzle's bit 2 alternating with i and ks; KS: one per fragment row
+  static constexpr int NA = KC ? 2 : N;
+  int a[NA];
+  __device__ __forceinline__ void init(int row0, int lr, int lg) {
+    if constexpr (KC) {
+      const int f = (lr ^ (lr >> 2)) & 7;
+      a[0] = (row0 + lr) * 128 + ((lg ^ f) << 4);
+      a[1] = (row0 + lr) * 128 + (((lg + 4) ^ f) << 4);
+    } else {
+      const int k = 8 * lg + (lr >> 2);
+#pragma unroll
+      for (int i = 0; i < N; ++i) a[i] = ks_off<HR>(k, (row0 + 16 * i + 4 * (lr & 3)) * 2);
+    }
+  }
+  // moves every address by d bytes, in place: the other stage's addresses would otherwise be
+  // kept in registers of their own through the loop
+  __device__ __forceinline__ void move(int d) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      a[i] += d;
+      asm volatile("" : "+v"(a[i]));
+    }
+  }
+  __device__ __forceinline__ bf16x8 read(lds<char>* slot, int i, int ks) const {
+    if constexpr (KC) {
+      return *reinterpret_cast<const lds<bf16x8>*>(slot + a[(i ^ ks) & 1] + i * 2048);
+    } else {
+      typedef short s4 __attribute__((ext_vector_type(4)));
+      typedef short s8 __attribute__((ext_vector_type(8)));
+      // K advances by 4 and by 32 without touching the swizzle (bits 0, 1 and 3 of K)
+      lds<char>* p = slot + a[i] + ks * 32 * HR * 2;
+      const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds<s4>*)p);
+      const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds<s4>*)(p + 4 * HR * 2));
+      const s8 v = s8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      return __builtin_bit_cast(bf16x8, v);
+    }
+  }
+};
+
+// The K loop of one tile, split in two so that a persistent kernel can start the next tile's
+// loads before it runs the current tile's epilogue:
+//   prime()  issues the first loads of a tile (LDS must be free: after run()'s closing barrier,
+//            or at kernel start);
+//   run()    the main loop and a partial last stage; it ends with a barrier after which LDS is
+//            free again.  run<.., X>(.., after_prime) is for a caller that issued exactly X
+//            further memory operations (per wave) between prime() and run() when after_prime is
+//            true: the waits for the primed loads let those X stay in flight.
+// A_SW > 0: A is K-contiguous and stored slab-major -- K split into slabs of A_SW columns,
+// slab s of every row at A + s a_sstride, lda = A_SW within a slab (A_SW a multiple of BK).
+// Set the stride with slab_a() before prime().
+template <class C, bool A_KC, bool B_KC, int A_SW = 0>
+struct PipeTile {
+  using OA = HalfPanels<C::BM, C::WM, C::THREADS, A_KC, false>;
+  using OB = HalfPanels<C::BN, C::WN, C::THREADS, B_KC, C::SPLIT>;
+  static constexpr int AL = OA::NQ, BL = OB::NQ;
+  static constexpr int HI = C::MI / 2, HJ = C::NJ / 2;
+  static_assert(A_SW == 0 || (A_KC && A_SW % C::BK == 0), "slab-major A: K-contiguous, whole stages per slab");
+  static_assert(!C::F32 || (A_KC && B_KC), "fp32: K-contiguous operands only");
+  OA oa;
+  OB ob;
+  HalfFrags<A_KC, C::BM / 2, HI> fa;
+  HalfFrags<B_KC, C::BN / 2, HJ> fb;
+  const char* A;
+  const char* B;
+  int64_t lda, ldb, step_a, step_b;  // bytes per stage
+  int64_t slab_bytes = 0;
+  int a_rows, b_rows, k_len;
+
+  __device__ __forceinline__ void slab_a(int64_t stride) { slab_bytes = stride * 2; }
+  __device__ __forceinline__ const char* a_at(int k) const {  // stage k of A
+    const char* p;
+    if constexpr (A_SW > 0)
+      p = A + (k / (A_SW / C::BK)) * slab_bytes + (k % (A_SW / C::BK)) * (C::BK * 2);
+    else
+      p = A + k * step_a;
+    return uniform(p);
+  }
+  __device__ __forceinline__ const char* b_at(int k) const { return uniform(B + k * step_b); }
+  __device__ __forceinline__ static lds<char>* slot_a(lds<char>* smem, int par, int h) {
+    return smem + par * C::STAGE + h * C::A_HALF;
+  }
+  __device__ __forceinline__ static lds<char>* slot_b(lds<char>* smem, int par, int h) {
+    return smem + par * C::STAGE + 2 * C::A_HALF + h * C::B_HALF;
+  }
+
+  // LONG: the reduction has at least two whole stages (no branches among the loads)
+  template <bool LONG = false>
+  __device__ __forceinline__ void prime(const bf16* __restrict__ A_, int64_t lda_, int a_rows_,
+                                        const bf16* __restrict__ B_, int64_t ldb_, int b_rows_, int k_len_,
+                                        lds<char>* smem) {
+    A = uniform(reinterpret_cast<const char*>(A_));
+    B = uniform(reinterpret_cast<const char*>(B_));
+    lda = lda_;
+    ldb = ldb_;
+    a_rows = a_rows_;
+    b_rows = b_rows_;
+    k_len = __builtin_amdgcn_readfirstlane(k_len_);
+    step_a = A_KC ? C::BK * 2 : C::BK * 2 * lda;
+    step_b = B_KC ? C::BK * 2 : C::BK * 2 * ldb;
+    oa.init(lda, a_rows);
+    ob.init(ldb, b_rows);
+    const int nk = k_len / C::BK;
+    if (LONG || nk > 0) {
+      const char *pa = a_at(0), *pb = b_at(0);
+      ob.template issue<0>(pb, slot_b(smem, 0, 0));
+      oa.template issue<0>(pa, slot_a(smem, 0, 0));
+      ob.template issue<1>(pb, slot_b(smem, 0, 1));
+      oa.template issue<1>(pa, slot_a(smem, 0, 1));
+    }
+    if (LONG || nk > 1) {
+      const char *pa = a_at(1), *pb = b_at(1);
+      ob.template issue<0>(pb, slot_b(smem, 1, 0));
+      oa.template issue<0>(pa, slot_a(smem, 1, 0));
+      ob.template issue<1>(pb, slot_b(smem, 1, 1));
+    }
+  }
+
+  __device__ __forceinline__ void read_a(bf16x8 (&a)[HI][2], lds<char>* slot) const {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < HI; ++i) a[i][ks] = fa.read(slot, i, ks);
+  }
+  __device__ __forceinline__ void read_b(bf16x8 (&b)[HJ][2], lds<char>* slot) const {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < HJ; ++j) b[j][ks] = fb.read(slot, j, ks);
+  }
+
+  // Quadrant (QI, QJ) of the wave's tile.  B is the MFMA's first operand: the 16 x 16 result is
+  // the transposed sub-tile, so each lane ends up with four consecutive output columns of one row.
+  template <int QI, int QJ>
+  __device__ __forceinline__ static void mfmas(const bf16x8 (&a)[HI][2], const bf16x8 (&b)[HJ][2],
+                                               floatx4 (&acc)[C::MI][C::NJ]) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int q = 0; q < (C::F32 ? 4 : 1); ++q)
+#pragma unroll
+        for (int i = 0; i < HI; ++i)
+#pragma unroll
+          for (int j = 0; j < HJ; ++j) {
+            floatx4& c = acc[QI * HI + i][QJ * HJ + j];
+            if constexpr (C::F32)
+              c = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(floatx4, b[j][ks])[q],
+                                                       __builtin_bit_cast(floatx4, a[i][ks])[q], c, 0, 0, 0);
+            else
+              c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][ks], a[i][ks], c, 0, 0, 0);
+          }
+  }
+  // xs[i / WAVES_N] += squares of this lane's elements of A fragment i, for the fragments i = wn
+  // (mod WAVES_N) this wave is responsible for (each row's sum stays within one wave); bf16 as
+  // packed dot products (the squares of bf16 values are exact in fp32).
+  template <int QI>
+  __device__ __forceinline__ static void row_squares(const bf16x8 (&a)[HI][2], int wn, float* xs) {
+#pragma unroll
+    for (int i = 0; i < HI; ++i)
+      if (((QI * HI + i) % C::WAVES_N) == wn) {
+        float& x = xs[(QI * HI + i) / C::WAVES_N];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          if constexpr (C::F32) {
+            const floatx4 v = __builtin_bit_cast(floatx4, a[i][ks]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x = fmaf(v[e], v[e], x);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const bf16x2 v = {a[i][ks][2 * e], a[i][ks][2 * e + 1]};
+              x = __builtin_amdgcn_fdot2_f32_bf16(v, v, x, false);
+            }
+          }
+        }
+      }
+  }
+  __device__ __forceinline__ static void mid_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    wg_barrier_lds();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ static void end_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    wg_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // Stage s in parity PAR, `left` stages before the last (STEADY: at least two); b0 = B0(s) in
+  // registers, b0n receives B0(s + 1).  extra: the caller's X operations may still be in flight.
+  template <int PAR, bool STEADY, bool ROWNORM, int X>
+  __device__ __forceinline__ void stage(lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ], bf16x8 (&b0)[HJ][2],
+                                        bf16x8 (&b0n)[HJ][2], int s, int left, int wn, float* xs, bool extra) {
+    constexpr int kFlip = PAR == 0 ? C::STAGE : -C::STAGE;
+    bf16x8 a[HI][2], b1[HJ][2];
+    read_a(a, slot_a(smem, 0, 0));  // fa and fb carry the stage's parity
+    read_b(b1, slot_b(smem, 0, 1));
+    if (STEADY || left >= 1) oa.template issue<1>(a_at(s + 1), slot_a(smem, PAR ^ 1, 1));
+    if (STEADY || left >= 2) ob.template issue<0>(b_at(s + 2), slot_b(smem, PAR, 0));
+    if (X > 0 && extra) {
+      if (STEADY || left >= 2) wait_vmcnt<2 * AL + 2 * BL + X>();
+      else if (left == 1) wait_vmcnt<2 * AL + BL + X>();
+      else wait_vmcnt<X>();
+    } else {
+      if (STEADY || left >= 2) wait_vmcnt<2 * AL + 2 * BL>();
+      else if (left == 1) wait_vmcnt<2 * AL + BL>();
+      else wait_vmcnt<0>();
+    }
+    mid_barrier();
+    mfmas<0, 0>(a, b0, acc);
+    mfmas<0, 1>(a, b1, acc);
+    if constexpr (ROWNORM) row_squares<0>(a, wn, xs);
+    end_barrier();
+    read_a(a, slot_a(smem, 0, 1));
+    fa.move(kFlip);
+    fb.move(kFlip);
+    if (STEADY || left >= 1) read_b(b0n, slot_b(smem, 0, 0));
+    if (STEADY || left >= 2) {
+      oa.template issue<0>(a_at(s + 2), slot_a(smem, PAR, 0));
+      ob.template issue<1>(b_at(s + 2), slot_b(smem, PAR, 1));
+    }
+    if (X > 0 && extra) {
+      if (STEADY || left >= 2) wait_vmcnt<2 * AL + 2 * BL + X>();
+      else if (left == 1) wait_vmcnt<AL + X>();
+    } else {
+      if (STEADY || left >= 2) wait_vmcnt<2 * AL + 2 * BL>();
+      else if (left == 1) wait_vmcnt<AL>();
+    }
+    mid_barrier();
+    mfmas<1, 0>(a, b0, acc);
+    mfmas<1, 1>(a, b1, acc);
+    if constexpr (ROWNORM) row_squares<1>(a, wn, xs);
+    end_barrier();
+  }
+
+  // ZERO: the sums start at zero, otherwise at what acc holds
+  template <bool ROWNORM = false, int X = 0, bool ZERO = true>
+  __device__ __forceinline__ void run(lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ], float* xs = nullptr,
+                                      bool after_prime = false) {
+    static_assert(!ROWNORM || A_KC, "row norms need a K-contiguous A");
+    static_assert(2 * AL + 2 * BL + X <= 63, "vmcnt range");
+    if constexpr (ROWNORM) {
+#pragma unroll
+      for (int i = 0; i < (C::MI + C::WAVES_N - 1) / C::WAVES_N; ++i) xs[i] = 0.f;
+    }
+    if constexpr (ZERO) {
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int nk = k_len / C::BK;
+    const int l = thread_id() & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wm = w / C::WAVES_N, wn = w % C::WAVES_N;
+    fa.init(wm * (C::WM / 2), l & 15, l >> 4);
+    fb.init(wn * (C::WN / 2), l & 15, l >> 4);
+    const bool g1 = w >= C::WAVES / 2;
+    bf16x8 be[HJ][2], bo[HJ][2];  // B0 of even and odd stages
+    if (nk > 0) {
+      if (X > 0 && after_prime) {
+        if (nk > 1) wait_vmcnt<2 * AL + 2 * BL + X>(); else wait_vmcnt<AL + X>();
+      } else {
+        if (nk > 1) wait_vmcnt<2 * AL + 2 * BL>(); else wait_vmcnt<AL>();
+      }
+      wg_barrier();
+      read_b(be, slot_b(smem, 0, 0));
+      wg_barrier_lds();  // B0's slot of stage 0 is loaded again from phase 0 on
+      if (g1) wg_barrier();
+    }
+    int s = 0;
+    // a first stage with the caller's operations in flight; the compiler may not see that it is
+    // the first (it would make a copy of the loop body for it)
+    auto extra = [&]() {
+      int first = s;
+      asm volatile("" : "+s"(first));
+      return X > 0 && after_prime && first == 0;
+    };
+    for (; s + 3 < nk; s += 2) {
+      stage<0, true, ROWNORM, X>(smem, acc, be, bo, s, 0, wn, xs, extra());
+      stage<1, true, ROWNORM, 0>(smem, acc, bo, be, s + 1, 0, wn, xs, false);
+    }
+    for (; s < nk; s += 2) {
+      stage<0, false, ROWNORM, X>(smem, acc, be, bo, s, nk - 1 - s, wn, xs, extra());
+      if (s + 1 < nk) stage<1, false, ROWNORM, 0>(smem, acc, bo, be, s + 1, nk - 2 - s, wn, xs, false);
+    }
+    if (nk > 0 && !g1) wg_barrier();
+    if (nk * C::BK < k_len) {
+      bf16x8 a[HI][2];
+      const int left = k_len - nk * C::BK;
+      const char *pa = a_at(nk), *pb = b_at(nk);
+      fa.init(wm * (C::WM / 2), l & 15, l >> 4);
+      fb.init(wn * (C::WN / 2), l & 15, l >> 4);
+      wg_barrier_lds();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        OA::tail(h, pa, lda, a_rows, left, slot_a(smem, 0, h));
+        OB::tail(h, pb, ldb, b_rows, left, slot_b(smem, 0, h));
+      }
+      wg_barrier_lds();
+      read_b(be, slot_b(smem, 0, 0));
+      read_b(bo, slot_b(smem, 0, 1));
+      read_a(a, slot_a(smem, 0, 0));
+      mfmas<0, 0>(a, be, acc);
+      mfmas<0, 1>(a, bo, acc);
+      if constexpr (ROWNORM) row_squares<0>(a, wn, xs);
+      read_a(a, slot_a(smem, 0, 1));
+      mfmas<1, 0>(a, be, acc);
+      mfmas<1, 1>(a, bo, acc);
+      if constexpr (ROWNORM) row_squares<1>(a, wn, xs);
+    }
+    wg_barrier_lds();
+  }
+};
+
+// The tile loop of a direct-to-LDS configuration.
+template <class C, bool A_KC, bool B_KC, int A_SW = 0, bool PIPE = C::PIPE>
+struct TileLoop {
+  using type = PipeTile<C, A_KC, B_KC, A_SW>;
+};
+template <class C, bool A_KC, bool B_KC, int A_SW>
+struct TileLoop<C, A_KC, B_KC, A_SW, false> {
+  using type = DmaTile<C, A_KC, B_KC>;
+};
+
 template <class C, bool A_KC, bool B_KC, bool ROWNORM = false>
 __device__ __forceinline__ void gemm_tile_dma(const bf16* __restrict__ A, int64_t lda, int a_rows,
                                               const bf16* __restrict__ B, int64_t ldb, int b_rows, int k_len,
                                               lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ],
                                               float* xs = nullptr) {
-  DmaTile<C, A_KC, B_KC> t;
+  typename TileLoop<C, A_KC, B_KC>::type t;
   t.prime(A, lda, a_rows, B, ldb, b_rows, k_len, smem);
   t.template run<ROWNORM>(smem, acc, xs);
 }
@@ -723,8 +1196,21 @@ struct TileCoord {
   int n_cols;     // valid columns
   int64_t k0;     // first reduction index (grouped-K problems)
   int k_len;      // reduction length
-  bool valid;
+  int valid;      // not bool: whole registers, so that copies of a tile stay out of memory
 };
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+// The tile in scalar registers: its coordinates come out of 64-bit divisions, which leave them in
+// vector registers that a persistent kernel would hold (and spill for) through its K loop.
+__device__ __forceinline__ TileCoord uniform(const TileCoord& t) {
+  return TileCoord{uniform(t.group), uniform(t.m0), uniform(t.m_rows), uniform(t.n0),
+                   uniform(t.n_cols), uniform(t.k0), uniform(t.k_len), uniform(t.valid)};
+}
 
 // Plain problem: M x N tiles, bands of `band` m-tiles walked m-fastest so that concurrently
 // running workgroups share both operand tiles in the caches.
@@ -854,14 +1340,21 @@ struct Frag {
   static constexpr int NCOL = T ? C::NJ * 4 : C::NJ;
   int wm, wn, lr, lg;
   __device__ __forceinline__ Frag() {
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int l = thread_id() & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     wm = w / C::WAVES_N;
     wn = w % C::WAVES_N;
     lr = l & 15;
     lg = l >> 4;
   }
   __device__ __forceinline__ int row(int i, int r) const { return wm * C::WM + 16 * i + (T ? lr : 4 * lg + r); }
-  __device__ __forceinline__ int col(int j, int r) const { return wn * C::WN + 16 * j + (T ? 4 * lg + r : lr); }
+  // first column of the wave's 16-column block j
+  __device__ __forceinline__ int block(int j) const {
+    if constexpr (C::SPLIT)
+      return (j / (C::NJ / 2)) * (C::BN / 2) + wn * (C::WN / 2) + 16 * (j % (C::NJ / 2));
+    else
+      return wn * C::WN + 16 * j;
+  }
+  __device__ __forceinline__ int col(int j, int r) const { return block(j) + (T ? 4 * lg + r : lr); }
   __device__ __forceinline__ static constexpr int qidx(int j, int r) { return T ? 4 * j + r : j; }
   __device__ __forceinline__ int colq(int q) const { return T ? col(q >> 2, q & 3) : col(q, 0); }
 };
@@ -932,17 +1425,27 @@ __device__ __forceinline__ void store_tile(const TileCoord& tc, const floatx4 (&
 // direct_stores<C, O>() is the number of store instructions a wave issues for a full tile.
 template <class C, typename O>
 __device__ __forceinline__ constexpr bool direct_pairs() {
-  return sizeof(O) == 2 && C::NJ % 2 == 0;
+  return sizeof(O) == 2 && (C::SPLIT ? C::NJ % 4 == 0 : C::NJ % 2 == 0);
 }
 template <class C, typename O>
 __device__ __forceinline__ constexpr int direct_stores() {
   return direct_pairs<C, O>() ? C::MI * C::NJ / 2 : C::MI * C::NJ;
 }
-template <class C, typename O, class Elem, class RowMap, class Vec>
-__device__ __forceinline__ void store_direct(const TileCoord& tc, const floatx4 (&acc)[C::MI][C::NJ],
-                                             O* __restrict__ out, int64_t ldo, Elem elem, RowMap rowmap, Vec vec) {
+// FULL: every row and column of the tile is valid, and no store sits behind a branch.  The
+// destination rows are all fetched before the first store: fetched one by one between the
+// stores, a row map costs a memory latency per 16 rows.
+template <class C, typename O, bool FULL, class Elem, class RowMap, class Vec>
+__device__ __forceinline__ void store_direct_rows(const TileCoord& tc, const floatx4 (&acc)[C::MI][C::NJ],
+                                                  O* __restrict__ out, int64_t ldo, Elem elem, RowMap rowmap,
+                                                  Vec vec) {
   static_assert(C::TRANS, "direct stores need the transposed accumulator layout");
   const Frag<C> f;
+  int64_t dst[C::MI];
+#pragma unroll
+  for (int i = 0; i < C::MI; ++i) {
+    const int row = f.row(i, 0);
+    dst[i] = rowmap(FULL || row < tc.m_rows ? row : tc.m_rows - 1);
+  }
   if constexpr (direct_pairs<C, O>()) {
     typedef unsigned int u2v __attribute__((ext_vector_type(2)));
     typedef unsigned int u4v __attribute__((ext_vector_type(4)));
@@ -951,8 +1454,7 @@ __device__ __forceinline__ void store_direct(const TileCoord& tc, const floatx4 
 #pragma unroll
     for (int i = 0; i < C::MI; ++i) {
       const int row = f.row(i, 0);
-      const bool row_ok = row < tc.m_rows;  // the same for the two lanes of a swap
-      const int64_t dr = row_ok ? rowmap(row) : 0;
+      const bool row_ok = FULL || row < tc.m_rows;  // the same for the two lanes of a swap
 #pragma unroll
       for (int p = 0; p < C::NJ / 2; ++p) {
         vec4<O> va, vb;
@@ -966,29 +1468,36 @@ __device__ __forceinline__ void store_direct(const TileCoord& tc, const floatx4 
         const u2v s0 = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
         const u2v s1 = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
         const u4v w = u4v{s0[0], s1[0], s0[1], s1[1]};
-        const int col = f.wn * C::WN + 32 * p + cpos;
-        if (row_ok && col < tc.n_cols)
-          *reinterpret_cast<v8*>(out + dr * ldo + tc.n0 + col) = vec(dr, row, col, __builtin_bit_cast(v8, w));
+        const int col = f.block(2 * p) + cpos;
+        if (row_ok && (FULL || col < tc.n_cols))
+          *reinterpret_cast<v8*>(out + dst[i] * ldo + tc.n0 + col) = vec(dst[i], row, col, __builtin_bit_cast(v8, w));
       }
     }
   } else {
 #pragma unroll
     for (int i = 0; i < C::MI; ++i) {
       const int row = f.row(i, 0);
-      if (row >= tc.m_rows) continue;
-      const int64_t dr = rowmap(row);
-      O* orow = out + dr * ldo + tc.n0;
+      if (!FULL && row >= tc.m_rows) continue;
+      O* orow = out + dst[i] * ldo + tc.n0;
 #pragma unroll
       for (int j = 0; j < C::NJ; ++j) {
         const int col = f.col(j, 0);
-        if (col >= tc.n_cols) continue;
+        if (!FULL && col >= tc.n_cols) continue;
         vec4<O> v;
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = from_f32<O>(elem(i, j, r, acc[i][j][r]));
-        *reinterpret_cast<vec4<O>*>(orow + col) = vec(dr, row, col, v);
+        *reinterpret_cast<vec4<O>*>(orow + col) = vec(dst[i], row, col, v);
       }
     }
   }
+}
+template <class C, typename O, class Elem, class RowMap, class Vec>
+__device__ __forceinline__ void store_direct(const TileCoord& tc, const floatx4 (&acc)[C::MI][C::NJ],
+                                             O* __restrict__ out, int64_t ldo, Elem elem, RowMap rowmap, Vec vec) {
+  if (tc.m_rows == C::BM && tc.n_cols == C::BN)
+    store_direct_rows<C, O, true>(tc, acc, out, ldo, elem, rowmap, vec);
+  else
+    store_direct_rows<C, O, false>(tc, acc, out, ldo, elem, rowmap, vec);
 }
 
 // Destination row of a tile row for the plain case: m0 + r.
@@ -997,15 +1506,18 @@ struct RowId {
   __device__ __forceinline__ int64_t operator()(int r) const { return m0 + r; }
 };
 
-// Tile configuration per data type: bf16 runs the 256 x 256 direct-to-LDS engine, fp32 the
-// register-staged 128 x 128 one.
-template <typename T>
+// Tile configurations per data type, C for a K-contiguous B and CK for a K-strided one: bf16
+// runs the 256 x 256 pipelined engine, fp32 -- and bf16 rows too wide for the pipelined engine's
+// 32-bit offsets (WIDE) -- the register-staged 128 x 128 one.
+template <typename T, bool WIDE = false>
 struct Pick {
-  using C = CfgSmall<float>;
+  using C = CfgSmall<T>;
+  using CK = CfgSmall<T>;
 };
 template <>
-struct Pick<bf16> {
-  using C = CfgDma;
+struct Pick<bf16, false> {
+  using C = CfgPipe;
+  using CK = CfgPipeKS;
 };
 
 // The epilogue store for the configuration's orientation.

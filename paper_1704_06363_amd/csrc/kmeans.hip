@@ -12,15 +12,26 @@ namespace hmoe {
 
 // ------------------------------------------------------------------ centre norms
 
+// cn[k] = |c_k|^2, one wave per centre over 16-byte vectors (element by element a row of 2048
+// was 32 dependent trips to memory: 16 us, 5 us by vectors).
 template <typename T>
 __global__ void __launch_bounds__(256) k_cnorm(const T* __restrict__ C, int K, int d, float* __restrict__ cn) {
+  constexpr int EPV = 16 / sizeof(T);
   const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int l = threadIdx.x & 63;
   if (k >= K) return;
+  const T* row = C + (int64_t)k * d;
+  const int nv = d / EPV;  // row widths are multiples of 8
   float s = 0.f;
-  for (int j = l; j < d; j += 64) {
-    const float c = to_f32(C[(int64_t)k * d + j]);
-    s += c * c;
+#pragma unroll 4
+  for (int v = l; v < nv; v += 64) {
+    const i32x4 raw = *reinterpret_cast<const i32x4*>(row + (int64_t)v * EPV);
+    const T* e = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+    for (int z = 0; z < EPV; ++z) {
+      const float c = to_f32(e[z]);
+      s += c * c;
+    }
   }
   s = wave_sum(s);
   if (l == 0) cn[k] = s;
@@ -101,10 +112,34 @@ __global__ void __launch_bounds__(C::THREADS)
   }
 }
 
-// The same tile on the direct-to-LDS engine (bf16 with many centres, and fp32).  Each lane
-// holds four consecutive centres of one row per fragment; the row norms come from the A
+// (value, index) maximum with ties to the lower index over the four lanes 16 apart.
+__device__ __forceinline__ void rows16_argmax(float& v, int& i) {
+  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+  const auto merge = [&](u2v a, u2v b) {
+    const float v0 = __uint_as_float(a[0]), v1 = __uint_as_float(a[1]);
+    const int i0 = (int)b[0], i1 = (int)b[1];
+    const bool second = v1 > v0 || (v1 == v0 && i1 < i0);
+    v = second ? v1 : v0;
+    i = second ? i1 : i0;
+  };
+  merge(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false),
+        __builtin_amdgcn_permlane16_swap((unsigned)i, (unsigned)i, false, false));
+  merge(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false),
+        __builtin_amdgcn_permlane32_swap((unsigned)i, (unsigned)i, false, false));
+}
+
+// The same tile on the direct-to-LDS engines (bf16 with many centres, and fp32).  A row's nearest
+// centre is the maximum of x . c_k - |c_k|^2 / 2 = -dist' / 2 (the factor is exact): the epilogue
+// is a subtraction, a compare and two selects per element, in increasing centre order, where a
+// guarded (value, index) merge per element took 1.2 of 4.5 ms at 2^20 x 2048 rows and 1024
+// centres.  The tile's |c_k|^2 / 2 wait in LDS past the operands, +inf for absent centres.  Each
+// lane holds four consecutive centres of one row per fragment; the row norms come from the A
 // fragments the engine already reads (fragment i summed by wave i mod WAVES_N).  fp32 rows are
 // staged as 16-bit units (U per element).
+template <class C>
+constexpr int assign_lds() {
+  return C::LDS + C::BN * (int)sizeof(float);
+}
 template <class C>
 __global__ void __launch_bounds__(C::THREADS)
     k_assign_dma(const typename C::type* __restrict__ X, int64_t n, int d, const typename C::type* __restrict__ Cn,
@@ -117,19 +152,24 @@ __global__ void __launch_bounds__(C::THREADS)
   const TileCoord tc = tile_plain<C>(n, K, d);
   if (!tc.valid) return;
   floatx4 acc[C::MI][C::NJ];
-  float xs[C::MI];
+  float xs[(C::MI + C::WAVES_N - 1) / C::WAVES_N];
+  using F = Frag<C>;
   // only the first centre tile of a row block needs the row norms (min_dist = min + |x|^2)
   constexpr int U = C::F32 ? 2 : 1;
   const bf16* Xu = reinterpret_cast<const bf16*>(X);
   const bf16* Cu = reinterpret_cast<const bf16*>(Cn);
-  DmaTile<C, true, true> pipe;
+  typename TileLoop<C, true, true>::type pipe;
+  lds<float>* hn = reinterpret_cast<lds<float>*>(smem + C::LDS);  // [BN]
+  static_assert(C::BN <= C::THREADS, "one thread per centre");
+  float h = INFINITY;
+  if ((int)threadIdx.x < tc.n_cols) h = 0.5f * cn[tc.n0 + threadIdx.x];
   pipe.prime(Xu + tc.m0 * d * U, (int64_t)d * U, tc.m_rows, Cu + (int64_t)tc.n0 * d * U, (int64_t)d * U, tc.n_cols,
              d * U, smem);
+  if ((int)threadIdx.x < C::BN) hn[threadIdx.x] = h;  // read after the K loop's barriers
   if (tc.n0 == 0)
     pipe.template run<true>(smem, acc, xs);
   else
     pipe.template run<false>(smem, acc);
-  using F = Frag<C>;
   const F f;
   lds<float>* xn = reinterpret_cast<lds<float>*>(smem);  // [BM]
   lds<float>* rv = xn + C::BM;                           // [WAVES_N][BM]
@@ -137,54 +177,53 @@ __global__ void __launch_bounds__(C::THREADS)
 #pragma unroll
   for (int i = 0; i < C::MI; ++i)
     if (tc.n0 == 0 && (i % C::WAVES_N) == f.wn) {
-      float s = xs[i];
-      s += shfl_xor(s, 16);
-      s += shfl_xor(s, 32);
+      const float s = rows16_reduce(xs[i / C::WAVES_N], [](float a, float b) { return a + b; });
       if (f.lg == 0) xn[f.row(i, 0)] = s;
     }
-  float cv[F::NCOL];
+  floatx4 hv[C::NJ];
 #pragma unroll
-  for (int q = 0; q < F::NCOL; ++q) {
-    const int col = f.colq(q);
-    cv[q] = col < tc.n_cols ? cn[tc.n0 + col] : 0.f;
-  }
+  for (int j = 0; j < C::NJ; ++j) hv[j] = *reinterpret_cast<const lds<floatx4>*>(hn + f.col(j, 0));
+  float best[C::MI];
+  int bi[C::MI];
 #pragma unroll
   for (int i = 0; i < C::MI; ++i) {
-    float best = FLT_MAX;
-    int bi = INT_MAX;
+    best[i] = -0.5f * FLT_MAX;  // dist' below FLT_MAX
+    int o = -1;                 // 16 j + r of this lane's best
 #pragma unroll
     for (int j = 0; j < C::NJ; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int col = f.col(j, r);
-        if (col < tc.n_cols) argmin_merge(best, bi, cv[F::qidx(j, r)] - 2.f * acc[i][j][r], tc.n0 + col);
+        const float v = acc[i][j][r] - hv[j][r];
+        const bool gt = v > best[i];
+        best[i] = gt ? v : best[i];
+        o = gt ? f.col(j, r) - f.col(0, 0) : o;
       }
+    bi[i] = o < 0 ? INT_MAX : tc.n0 + f.col(0, 0) + o;
+  }
 #pragma unroll
-    for (int m = 16; m < 64; m <<= 1) {
-      const float v2 = shfl_xor(best, m);
-      const int i2 = shfl_xor(bi, m);
-      argmin_merge(best, bi, v2, i2);
-    }
-    if (f.lg == 0) {
-      rv[f.wn * C::BM + f.row(i, 0)] = best;
-      ri[f.wn * C::BM + f.row(i, 0)] = bi;
+  for (int i = 0; i < C::MI; ++i) rows16_argmax(best[i], bi[i]);
+  if (f.lg == 0) {
+#pragma unroll
+    for (int i = 0; i < C::MI; ++i) {
+      rv[f.wn * C::BM + f.row(i, 0)] = -2.f * best[i];
+      ri[f.wn * C::BM + f.row(i, 0)] = bi[i];
     }
   }
   __syncthreads();
   const int nt = (int)cdiv(K, C::BN);
   for (int q = threadIdx.x; q < tc.m_rows; q += C::THREADS) {
     float v = rv[q];
-    int bi = ri[q];
+    int b = ri[q];
 #pragma unroll
-    for (int w = 1; w < C::WAVES_N; ++w) argmin_merge(v, bi, rv[w * C::BM + q], ri[w * C::BM + q]);
+    for (int w = 1; w < C::WAVES_N; ++w) argmin_merge(v, b, rv[w * C::BM + q], ri[w * C::BM + q]);
     const int64_t row = tc.m0 + q;
     if (nt == 1) {
-      assign[row] = bi;
+      assign[row] = b;
       if (min_dist) min_dist[row] = fmaxf(v + xn[q], 0.f);
     } else {
       const int ti = tc.n0 / C::BN;
       part_v[(int64_t)ti * n + row] = v;
-      part_i[(int64_t)ti * n + row] = bi;
+      part_i[(int64_t)ti * n + row] = b;
       if (ti == 0) xnorm[row] = xn[q];
     }
   }
@@ -204,20 +243,21 @@ __global__ void __launch_bounds__(256) k_assign_merge(const float* __restrict__ 
 }
 
 // Centre-tile width of the assignment: up to 64 centres run the narrow 128 x 64 tiles of the
-// direct-to-LDS engine, fp32 above that and bf16 above 128 centres its 256 x 256 tiles, bf16
-// with 65 .. 128 centres the register-staged 128 x 128 tiles.
-// bf16 with more than 128 centres
-typedef CfgDma CfgAssignWide;
-
-static int assign_bn(hmoe_dtype_t dt, int32_t K) {
-  if (K <= 64) return 64;
-  if (dt != HMOE_BF16) return CfgDmaF32::BN;
-  return K > 128 ? CfgAssignWide::BN : 128;
+// ring engine, fp32 above that and bf16 above 128 centres the 256 x 256 tiles of the pipelined
+// engine, bf16 with 65 .. 128 centres the register-staged 128 x 128 tiles -- and so do rows too
+// wide for the pipelined engine.
+static bool assign_pipe(int64_t d, hmoe_dtype_t dt, int32_t K) {
+  return dt == HMOE_BF16 ? K > 128 && d < kPipeMaxLd : K > 64 && 2 * d < kPipeMaxLd;
 }
 
-static size_t assign_ws_bytes(int64_t n, int32_t K, hmoe_dtype_t dt) {
+static int assign_bn(int64_t d, hmoe_dtype_t dt, int32_t K) {
+  if (K <= 64) return 64;
+  return assign_pipe(d, dt, K) ? CfgPipe::BN : 128;
+}
+
+static size_t assign_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
   Workspace ws(nullptr, 0);
-  const int nt = (int)cdiv(K, assign_bn(dt, K));
+  const int nt = (int)cdiv(K, assign_bn(d, dt, K));
   ws.take<float>(K);
   if (nt > 1) {
     ws.take<float>((size_t)nt * n);
@@ -245,7 +285,7 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
   if (n == 0) return HMOE_OK;
   const int64_t tiles = cdiv(n, C::BM) * nt;
   if constexpr (C::DMA)
-    HMOE_LAUNCH("assign", k_assign_dma<C>, dim3((unsigned)tiles), dim3(C::THREADS), C::LDS, st, X, n, d, Cn, K, cn,
+    HMOE_LAUNCH("assign", k_assign_dma<C>, dim3((unsigned)tiles), dim3(C::THREADS), assign_lds<C>(), st, X, n, d, Cn, K, cn,
                 assign, min_dist, pv, pi, xn);
   else
     HMOE_LAUNCH("assign", k_assign<C>, dim3((unsigned)tiles), dim3(C::THREADS), C::LDS, st, X, n, d, Cn, K, cn,
@@ -258,16 +298,17 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
 
 int launch_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, const void* C, int32_t K, int32_t* assign,
                   float* min_dist, Workspace& ws, hipStream_t st) {
-  const int bn = assign_bn(dt, K);
+  const bool pipe = assign_pipe(d, dt, K);
   if (dt == HMOE_BF16) {
-    if (bn == 64) return assign_t<CfgDmaNarrow>((const bf16*)X, n, d, (const bf16*)C, K, assign, min_dist, ws, st);
-    if (K > 128)
-      return assign_t<CfgAssignWide>((const bf16*)X, n, d, (const bf16*)C, K, assign, min_dist, ws, st);
-    return assign_t<CfgSmall<bf16>>((const bf16*)X, n, d, (const bf16*)C, K, assign, min_dist, ws, st);
+    const bf16 *x = (const bf16*)X, *c = (const bf16*)C;
+    if (K <= 64) return assign_t<CfgDmaNarrow>(x, n, d, c, K, assign, min_dist, ws, st);
+    if (pipe) return assign_t<CfgPipe>(x, n, d, c, K, assign, min_dist, ws, st);
+    return assign_t<CfgSmall<bf16>>(x, n, d, c, K, assign, min_dist, ws, st);
   }
-  if (bn == 64)
-    return assign_t<CfgDmaF32Narrow>((const float*)X, n, d, (const float*)C, K, assign, min_dist, ws, st);
-  return assign_t<CfgDmaF32>((const float*)X, n, d, (const float*)C, K, assign, min_dist, ws, st);
+  const float *x = (const float*)X, *c = (const float*)C;
+  if (K <= 64) return assign_t<CfgDmaF32Narrow>(x, n, d, c, K, assign, min_dist, ws, st);
+  if (pipe) return assign_t<CfgPipeF32>(x, n, d, c, K, assign, min_dist, ws, st);
+  return assign_t<CfgSmall<float>>(x, n, d, c, K, assign, min_dist, ws, st);
 }
 
 // ------------------------------------------------------------------ k-means++ seeding
@@ -681,11 +722,11 @@ size_t fit_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
   ws.take<double>(n);                       // D^2 for k-means++
   ws.take<double>(cdiv(n, kKppRows));       // block sums
   ws.take<int32_t>(K);                      // picks when the caller passes none
-  size_t s = ws.off + update_scratch(n, d, K) + assign_ws_bytes(n, K, dt) + 4096;
+  size_t s = ws.off + update_scratch(n, d, K) + assign_ws_bytes(n, d, K, dt) + 4096;
   return s;
 }
 
-size_t assign_ws(int64_t n, int32_t K, hmoe_dtype_t dt) { return assign_ws_bytes(n, K, dt) + 256; }
+size_t assign_ws(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) { return assign_ws_bytes(n, d, K, dt) + 256; }
 
 template <typename T>
 static int fit_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t n_iter, const double* u, int32_t reseed,

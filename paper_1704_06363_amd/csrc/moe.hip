@@ -125,30 +125,42 @@ __device__ __forceinline__ void dec_row_stats(const TileCoord& tc, const floatx4
   const F f;
   constexpr float kLog2e = 1.4426950408889634f;
   if constexpr (F::T) {
-    // one row per i; its WN columns of this wave sit in lanes lr, lr + 16, lr + 32, lr + 48
+    // one row per i; its WN columns of this wave sit in lanes lr, lr + 16, lr + 32, lr + 48.  All
+    // rows take each step together: row by row, every cross-lane step waits for the one before.
+    float mx[C::MI], sm[C::MI];
+    const auto max2 = [](float a, float b) { return fmaxf(a, b); };
+    const auto add2 = [](float a, float b) { return a + b; };
 #pragma unroll
     for (int i = 0; i < C::MI; ++i) {
-      float mx = -FLT_MAX;
+      float m = -FLT_MAX;
 #pragma unroll
       for (int j = 0; j < C::NJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (FULL || f.col(j, r) < tc.n_cols) mx = fmaxf(mx, acc[i][j][r]);
-      mx = fmaxf(mx, shfl_xor(mx, 16));
-      mx = fmaxf(mx, shfl_xor(mx, 32));
-      if (mxo) mxo[4 * i] = mx;
-      const float mb = mx * kLog2e;
+          if (FULL || f.col(j, r) < tc.n_cols) m = fmaxf(m, acc[i][j][r]);
+      mx[i] = m;
+    }
+#pragma unroll
+    for (int i = 0; i < C::MI; ++i) {
+      mx[i] = rows16_reduce(mx[i], max2);
+      if (mxo) mxo[4 * i] = mx[i];
+    }
+#pragma unroll
+    for (int i = 0; i < C::MI; ++i) {
+      const float mb = mx[i] * kLog2e;
       float s = 0.f;
 #pragma unroll
       for (int j = 0; j < C::NJ; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (FULL || f.col(j, r) < tc.n_cols) s += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], kLog2e, -mb));
-      s += shfl_xor(s, 16);
-      s += shfl_xor(s, 32);
-      if (f.lg == 0) {
-        rm[f.wn * C::BM + f.row(i, 0)] = mx;
-        rs[f.wn * C::BM + f.row(i, 0)] = s;
+      sm[i] = rows16_reduce(s, add2);
+    }
+    if (f.lg == 0) {
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i) {
+        rm[f.wn * C::BM + f.row(i, 0)] = mx[i];
+        rs[f.wn * C::BM + f.row(i, 0)] = sm[i];
       }
     }
   } else {
@@ -194,7 +206,7 @@ __device__ __forceinline__ void dec_stats_merge(const TileCoord& tc, lds<float>*
   static_assert(C::WN == kAnchorCols && (kAnchorTile / C::BN) * C::BN == kAnchorTile, "anchor slots per tile");
   typedef float avec __attribute__((ext_vector_type(C::WAVES_N)));
   if constexpr (BARRIER) wg_barrier_lds();
-  for (int t = threadIdx.x; t < tc.m_rows; t += C::THREADS) {
+  for (int t = thread_id(); t < tc.m_rows; t += C::THREADS) {
     avec mw;
 #pragma unroll
     for (int w = 0; w < C::WAVES_N; ++w) mw[w] = rm[w * C::BM + t];
@@ -317,55 +329,68 @@ __global__ void __launch_bounds__(C::THREADS)
 // the next tile's epilogue, after that tile's K loop, whose barriers order the partials'
 // writes before the merge's reads and the merge's reads before the buffer is written again.
 constexpr int kDecStatLds = 2 * 4 * 256 * (int)sizeof(float);
+// This lane's bias of a tile, packed; the loads are unconditional (a column past the tile reads
+// the tile's first ones, for outputs that are neither stored nor counted).
 template <class C>
 __device__ __forceinline__ void dec_bias_packed(const TileCoord& tc, const bf16* __restrict__ bD,
                                                 uint2 (&bp)[C::NJ]) {
+  if (!bD) {
+#pragma unroll
+    for (int j = 0; j < C::NJ; ++j) bp[j] = uint2{0u, 0u};
+    return;
+  }
   const Frag<C> f;
 #pragma unroll
   for (int j = 0; j < C::NJ; ++j) {
     const int col = f.col(j, 0);  // four consecutive columns; n_cols is a multiple of 8
-    bp[j] = (bD && col < tc.n_cols) ? *reinterpret_cast<const uint2*>(bD + tc.n0 + col) : uint2{0u, 0u};
+    bp[j] = *reinterpret_cast<const uint2*>(bD + tc.n0 + (col < tc.n_cols ? col : 0));
   }
+}
+// Waits for the bias here: among loads that a fixed count can tell apart.  Behind the stores, of
+// which a ragged tile has fewer, it could only be told from them by draining everything.
+template <class C>
+__device__ __forceinline__ void dec_bias_arrived(uint2 (&bp)[C::NJ]) {
+#pragma unroll
+  for (int j = 0; j < C::NJ; ++j) asm volatile("" : "+v"(bp[j].x), "+v"(bp[j].y));
 }
 template <class C>
 __global__ void __launch_bounds__(C::THREADS)
     k_dec_fwd_stream(const bf16* __restrict__ H, const bf16* __restrict__ D, const bf16* __restrict__ bD, int64_t n,
                      int V, int o, float* __restrict__ pm, float* __restrict__ ps, bf16* __restrict__ L,
                      float* __restrict__ anc) {
-  static_assert(C::DMA && C::TRANS, "persistent decoder forward runs the direct-to-LDS engine");
+  static_assert(C::PIPE, "persistent decoder forward runs the pipelined engine");
   static_assert(2 * C::WAVES_N * C::BM * (int)sizeof(float) <= kDecStatLds, "statistics scratch");
   constexpr int STORES = direct_stores<C, bf16>();  // per wave, for a full tile
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds<char>* smem = (lds<char>*)smem_raw;
   lds<float>* rm0 = reinterpret_cast<lds<float>*>(smem + C::LDS);
   constexpr int SB = 2 * C::WAVES_N * C::BM;  // one statistics buffer (floats)
-  using F = Frag<C>;
-  const F f0;
   const int64_t tiles = cdiv(n, C::BM) * cdiv(V, C::BN);
   int64_t t = blockIdx.x;
   if (t >= tiles) return;
-  TileCoord tc = tile_plain_at<C>(n, V, o, t);
-  DmaTile<C, true, true> pipe;
-  pipe.prime(H + tc.m0 * o, o, tc.m_rows, D + (int64_t)tc.n0 * o, o, tc.n_cols, o, smem);
+  TileCoord tc = uniform(tile_plain_at<C>(n, V, o, t));
+  typename TileLoop<C, true, true>::type pipe;
+  pipe.template prime<true>(H + tc.m0 * o, o, tc.m_rows, D + (int64_t)tc.n0 * o, o, tc.n_cols, o, smem);
   uint2 bp[C::NJ];
   dec_bias_packed<C>(tc, bD, bp);
+  dec_bias_arrived<C>(bp);
   bool stores_pending = false;
   int buf = 0;
   TileCoord pc = tc;  // the previous tile, whose partials merge in this tile's epilogue
   bool have_prev = false;
   for (;;) {
+    // the sums start at the bias: nothing of it is held through the K loop or added after it
     floatx4 acc[C::MI][C::NJ];
-    pipe.template run<false, STORES>(smem, acc, nullptr, stores_pending);
-    lds<float>* rm = rm0 + buf * SB;
-    lds<float>* rs = rm + C::WAVES_N * C::BM;
-    float bias[F::NCOL];
 #pragma unroll
     for (int j = 0; j < C::NJ; ++j) {
-      bias[4 * j + 0] = __uint_as_float(bp[j].x << 16);
-      bias[4 * j + 1] = __uint_as_float(bp[j].x & 0xffff0000u);
-      bias[4 * j + 2] = __uint_as_float(bp[j].y << 16);
-      bias[4 * j + 3] = __uint_as_float(bp[j].y & 0xffff0000u);
+      const floatx4 b = {__uint_as_float(bp[j].x << 16), __uint_as_float(bp[j].x & 0xffff0000u),
+                         __uint_as_float(bp[j].y << 16), __uint_as_float(bp[j].y & 0xffff0000u)};
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i) acc[i][j] = b;
     }
+    pipe.template run<false, STORES, false>(smem, acc, nullptr, stores_pending);
+    lds<float>* rm = rm0 + buf * SB;
+    lds<float>* rs = rm + C::WAVES_N * C::BM;
     // the next tile's first stages go out before the statistics, so their loads land while
     // the epilogue runs (run() ends with every wave past its last read of the ring; the
     // statistics' partials stores are then younger than the primed loads, which can only make
@@ -374,28 +399,23 @@ __global__ void __launch_bounds__(C::THREADS)
     const bool more = tn < tiles;
     TileCoord nc = tc;
     if (more) {
-      nc = tile_plain_at<C>(n, V, o, tn);
+      nc = uniform(tile_plain_at<C>(n, V, o, tn));
       dec_bias_packed<C>(nc, bD, bp);
-      pipe.prime(H + nc.m0 * o, o, nc.m_rows, D + (int64_t)nc.n0 * o, o, nc.n_cols, o, smem);
+      pipe.template prime<true>(H + nc.m0 * o, o, nc.m_rows, D + (int64_t)nc.n0 * o, o, nc.n_cols, o, smem);
     }
-    add_bias<C>(acc, bias);
     // the waves' row partials, then the logits stores, then the previous tile's merge:
     // measured faster than merging before the stores.  The merge's stores are younger than
     // the logits stores, which only makes the next tile's waits stricter.
+    Anchored<C> an;
     if (tc.n_cols == C::BN)
-      dec_row_stats<C, true>(tc, acc, rm, rs);
+      dec_row_stats<C, true>(tc, acc, rm, rs, an.mx);
     else
-      dec_row_stats<C, false>(tc, acc, rm, rs);
+      dec_row_stats<C, false>(tc, acc, rm, rs, an.mx);
+    dec_bias_arrived<C>(bp);
     // nothing may move between the primed loads and the stores: the next waits count them
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    if (L) {
-      // the anchor of each row: this wave's row maximum, read back from the partials it has
-      // just written (a wave's LDS accesses complete in order; the registers are full here)
-      const lds<float>* rmw = rm + f0.wn * C::BM;
-      store_direct<C, bf16>(tc, acc, L, V, [&](int i, int, int, float v) { return v - rmw[f0.row(i, 0)]; },
-                            RowId{tc.m0}, NoVec{});
-    }
+    if (L) store_direct<C, bf16>(tc, acc, L, V, an, RowId{tc.m0}, NoVec{});
     __builtin_amdgcn_sched_barrier(0);
     // the previous tile's partials were written before this tile's K loop, whose barriers
     // order them; its buffer is rewritten only after the next K loop
@@ -879,8 +899,8 @@ __global__ void __launch_bounds__(C::THREADS)
   if (!tc.valid) return;
   floatx4 acc[C::MI][C::NJ];
   if constexpr (GW > 0) {
-    static_assert(C::DMA, "slab-major G on the direct-to-LDS engine");
-    DmaTile<C, true, false, GW> pipe;
+    static_assert(C::PIPE, "slab-major G on the pipelined engine");
+    PipeTile<C, true, false, GW> pipe;
     pipe.slab_a(n * GW);
     pipe.prime(G + tc.m0 * GW, GW, tc.m_rows, D + tc.n0, o, tc.n_cols, V, smem);
     pipe.run(smem, acc);
@@ -962,9 +982,9 @@ static int launch_tn_split(const char* label, const typename C::type* A, const t
   const int64_t R = tiles % slots;
   const int64_t t_full = tiles - R;
   int split = R > 0 ? (int)(slots / R) : 1;
-  // chunks of a multiple of 32 rows and at least 256 (fewer chunks when rows are few); split is
+  // chunks of a multiple of 64 rows and at least 256 (fewer chunks when rows are few); split is
   // then recounted so that no chunk is empty
-  int64_t chunk = cdiv(cdiv(rows, split), 32) * 32;
+  int64_t chunk = cdiv(cdiv(rows, split), 64) * 64;
   if (chunk < 256) chunk = 256;
   split = (int)cdiv(rows, chunk);
   HMOE_LAUNCH(label, k_gemm_tn_split<C>, dim3((unsigned)(t_full + R * split)), dim3(C::THREADS), C::LDS, st, A, B,
@@ -1063,9 +1083,12 @@ static MoeShape shape_of(const hmoe_moe_params_t* p, int64_t n) {
   return MoeShape{n, p->K, p->d_in, p->d_hid, p->d_out, p->vocab, p->decoders > 1 ? p->decoders : 1};
 }
 
-template <typename T>
+// Rows too wide for the pipelined engine's offsets (the vocabulary's are rows of g).
+static bool wide_rows(const MoeShape& s) { return s.d >= kPipeMaxLd || s.V >= kPipeMaxLd; }
+
+template <typename T, class P>
 static size_t fwd_ws(const MoeShape& s) {
-  using C = typename Pick<T>::C;
+  using C = typename P::C;
   Workspace ws(nullptr, 0);
   const int64_t ntv = cdiv(s.V, C::BN);
   ws.take<int32_t>(s.K + 1);
@@ -1076,14 +1099,14 @@ static size_t fwd_ws(const MoeShape& s) {
   return ws.off;
 }
 
-template <typename T>
+template <typename T, class P>
 static size_t bwd_ws(const MoeShape& s) {
-  using C = typename Pick<T>::C;
+  using C = typename P::C;
   Workspace ws(nullptr, 0);
   ws.take<int32_t>(s.K + 1);
   ws.take<int32_t>(s.K);
   constexpr int GW = 256 * (16 / (int)sizeof(T));  // G padded to whole slabs (backward_t)
-  ws.take<T>(sizeof(T) == 2 && s.nd == 1 ? (size_t)s.n * cdiv(s.V, GW) * GW : (size_t)s.n * s.V);
+  ws.take<T>(C::PIPE && s.nd == 1 ? (size_t)s.n * cdiv(s.V, GW) * GW : (size_t)s.n * s.V);
   ws.take<T>((size_t)s.n * s.o);
   ws.take<T>((size_t)s.n * s.h);
   const int64_t prow = cdiv(s.n, C::BM) > cdiv(s.n, kGradRows) ? cdiv(s.n, C::BM) : cdiv(s.n, kGradRows);
@@ -1099,16 +1122,25 @@ static size_t bwd_ws(const MoeShape& s) {
 
 size_t moe_ws_bytes(const hmoe_moe_params_t* p, int64_t n) {
   const MoeShape s = shape_of(p, n);
-  const size_t a = p->dt == HMOE_BF16 ? fwd_ws<bf16>(s) : fwd_ws<float>(s);
-  const size_t b = p->dt == HMOE_BF16 ? bwd_ws<bf16>(s) : bwd_ws<float>(s);
+  size_t a, b;
+  if (p->dt != HMOE_BF16) {
+    a = fwd_ws<float, Pick<float>>(s);
+    b = bwd_ws<float, Pick<float>>(s);
+  } else if (wide_rows(s)) {
+    a = fwd_ws<bf16, Pick<bf16, true>>(s);
+    b = bwd_ws<bf16, Pick<bf16, true>>(s);
+  } else {
+    a = fwd_ws<bf16, Pick<bf16>>(s);
+    b = bwd_ws<bf16, Pick<bf16>>(s);
+  }
   return a > b ? a : b;
 }
 
-template <typename T>
+template <typename T, class P>
 static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const int32_t* offsets, const int32_t* perm,
                      const hmoe_labels_t* y, T* H1s, T* H, T* Lg, float* anc, float* lse, float* loss,
                      float* loss_mean, Workspace& ws, hipStream_t st) {
-  using C = typename Pick<T>::C;
+  using C = typename P::C;
   const MoeShape s = shape_of(p, n);
   const int ntv = (int)cdiv(s.V, C::BN);
   int32_t* ts = ws.take<int32_t>(s.K + 1);
@@ -1136,30 +1168,36 @@ static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const i
                 (const T*)Hs, D, (const T*)p->bD, n, s.o, s.V, perm, offsets, s.K, y->row_ptr, y->tag, lse, loss);
     return launch_sum_f32(loss, n, 1.0 / (double)n, nullptr, loss_mean, ws, st);
   }
-  if constexpr (C::DMA) {
-    // persistent: one workgroup per resident slot
-    const int64_t tiles = cdiv(n, C::BM) * ntv;
-    constexpr int lds_bytes = C::LDS + 2 * kDecStatLds;
-    int64_t slots = (int64_t)device_cus() * ((160 * 1024) / lds_bytes);
-    if (slots > tiles) slots = tiles;
-    HMOE_LAUNCH("decoder forward", k_dec_fwd_stream<C>, dim3((unsigned)slots), dim3(C::THREADS), lds_bytes, st,
-                (const bf16*)H, (const bf16*)D, (const bf16*)p->bD, n, s.V, s.o, pm, ps, (bf16*)Lg, anc);
-  } else {
+  // persistent, one workgroup per resident slot, when a tile's reduction has the two stages its
+  // priming takes; shorter ones have no loop to hide an epilogue behind
+  bool streamed = false;
+  if constexpr (C::PIPE) {
+    if (s.o >= 2 * C::BK) {
+      const int64_t tiles = cdiv(n, C::BM) * ntv;
+      constexpr int lds_bytes = C::LDS + 2 * kDecStatLds;
+      int64_t slots = (int64_t)device_cus() * ((160 * 1024) / lds_bytes);
+      if (slots > tiles) slots = tiles;
+      HMOE_LAUNCH("decoder forward", k_dec_fwd_stream<C>, dim3((unsigned)slots), dim3(C::THREADS), lds_bytes, st,
+                  (const bf16*)H, (const bf16*)D, (const bf16*)p->bD, n, s.V, s.o, pm, ps, (bf16*)Lg, anc);
+      streamed = true;
+    }
+  }
+  if (!streamed)
     HMOE_LAUNCH("decoder forward", k_dec_fwd<C>, dim3((unsigned)(cdiv(n, C::BM) * ntv)), dim3(C::THREADS), C::LDS,
                 st, (const T*)H, D, (const T*)p->bD, n, s.V, s.o, pm, ps, Lg, anc);
-  }
   HMOE_LAUNCH("decoder loss", k_dec_loss<T>, dim3((unsigned)cdiv(n, kLossRows)), dim3(256), 0, st, pm, ps, ntv, (const T*)H, D,
               (const T*)p->bD, n, s.o, s.V, (const int32_t*)nullptr, (const int32_t*)nullptr, 0, y->row_ptr,
               y->tag, lse, loss);
   return launch_sum_f32(loss, n, 1.0 / (double)n, nullptr, loss_mean, ws, st);
 }
 
-template <typename T>
+template <typename T, class P>
 static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const int32_t* offsets, const int32_t* perm,
                       const int32_t* inv, const hmoe_labels_t* y, const T* H1s, const T* H, const T* Lg,
                       const float* anc, const float* lse, float* dW1, float* db1, float* dW2, float* db2, float* dD, float* dbD, T* dX,
                       Workspace& ws, hipStream_t st) {
-  using C = typename Pick<T>::C;
+  using C = typename P::C;
+  using CK = typename P::CK;  // K-strided second operand
   const MoeShape s = shape_of(p, n);
   int32_t* ts = ws.take<int32_t>(s.K + 1);
   int32_t* order = ws.take<int32_t>(s.K);
@@ -1167,7 +1205,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   // bf16 logits through the shared decoder: G slab-major, [V / GW slabs][n][GW] (see
   // k_dec_grad_elem), which the grad kernel writes contiguously; the last slab is padded.
   constexpr int GW = 256 * EPV;
-  const bool slab = sizeof(T) == 2 && Lg && s.nd == 1;
+  const bool slab = C::PIPE && Lg && s.nd == 1;
   T* G = ws.take<T>(slab ? (size_t)n * cdiv(s.V, GW) * GW : (size_t)n * s.V);
   T* dYs = ws.take<T>((size_t)n * s.o);
   T* dZ = ws.take<T>((size_t)n * s.h);
@@ -1202,10 +1240,10 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
                   st, pdb, gts, s.V, dbD);
     HMOE_TRY(launch_permute(H, Hs, perm, n, s.o, p->dt, st));
     // XCD-grouped tile order: the o / BN tiles of an m-tile share one G row block (V wide)
-    HMOE_LAUNCH("decoder dH", (k_expert_dgrad<C, false, true>),
+    HMOE_LAUNCH("decoder dH", (k_expert_dgrad<CK, false, true>),
                 dim3((unsigned)(cdiv(mt_bound, 64) * 64 * cdiv(s.o, C::BN))), dim3(C::THREADS), C::LDS, st,
                 (const T*)G, D, offsets, ts, s.K, s.o, s.V, (const T*)nullptr, (const int32_t*)nullptr, dYs);
-    HMOE_LAUNCH("decoder dD", k_expert_wgrad<C>,
+    HMOE_LAUNCH("decoder dD", k_expert_wgrad<CK>,
                 dim3((unsigned)((int64_t)s.K * cdiv(s.V, C::BM) * cdiv(s.o, C::BN))), dim3(C::THREADS), C::LDS, st,
                 (const T*)G, (const T*)Hs, offsets, order, s.K, s.V, s.o, dD);
   } else {
@@ -1223,33 +1261,33 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   if (dbD)
     HMOE_LAUNCH("decoder bias grad", k_colsum_final, dim3((unsigned)cdiv(s.V, 64)), dim3(256), 0, st, pdb, prow,
                 s.V, dbD);
-  if constexpr (sizeof(T) == 2) {
+  if constexpr (C::PIPE) {
     if (slab) {
-      HMOE_LAUNCH("decoder dH", (k_dec_dH<C, GW>), dim3((unsigned)(mt * cdiv(s.o, C::BN))), dim3(C::THREADS),
+      HMOE_LAUNCH("decoder dH", (k_dec_dH<CK, GW>), dim3((unsigned)(mt * cdiv(s.o, C::BN))), dim3(C::THREADS),
                   C::LDS, st, (const T*)G, D, n, s.V, s.o, inv, dYs);
-      HMOE_TRY(launch_tn_split<C>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st, n * GW, GW));
+      HMOE_TRY(launch_tn_split<CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st, n * GW, GW));
     }
   }
   if (!slab) {
-    HMOE_LAUNCH("decoder dH", k_dec_dH<C>, dim3((unsigned)(mt * cdiv(s.o, C::BN))), dim3(C::THREADS), C::LDS, st,
+    HMOE_LAUNCH("decoder dH", k_dec_dH<CK>, dim3((unsigned)(mt * cdiv(s.o, C::BN))), dim3(C::THREADS), C::LDS, st,
                 (const T*)G, D, n, s.V, s.o, inv, dYs);
-    HMOE_TRY(launch_tn_split<C>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st));
+    HMOE_TRY(launch_tn_split<CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st));
   }
   }
   // experts
   const size_t mark = ws.off;
   if (db2) HMOE_TRY(launch_segsum<T, float>(dYs, s.o, nullptr, offsets, s.K, s.o, n, db2, 0, ws, st));
   ws.off = mark;
-  HMOE_LAUNCH("expert dW2", k_expert_wgrad<C>, dim3((unsigned)((int64_t)s.K * cdiv(s.o, C::BM) * cdiv(s.h, C::BN))),
+  HMOE_LAUNCH("expert dW2", k_expert_wgrad<CK>, dim3((unsigned)((int64_t)s.K * cdiv(s.o, C::BM) * cdiv(s.h, C::BN))),
               dim3(C::THREADS), C::LDS, st, (const T*)dYs, H1s, offsets, order, s.K, s.o, s.h, dW2);
-  HMOE_LAUNCH("expert dH1", (k_expert_dgrad<C, true>), dim3((unsigned)(mt_bound * cdiv(s.h, C::BN))),
+  HMOE_LAUNCH("expert dH1", (k_expert_dgrad<CK, true>), dim3((unsigned)(mt_bound * cdiv(s.h, C::BN))),
               dim3(C::THREADS), C::LDS, st, (const T*)dYs, W2, offsets, ts, s.K, s.h, s.o, H1s, perm, dZ);
   if (db1) HMOE_TRY(launch_segsum<T, float>(dZ, s.h, nullptr, offsets, s.K, s.h, n, db1, 0, ws, st));
   ws.off = mark;
-  HMOE_LAUNCH("expert dW1", k_expert_wgrad<C>, dim3((unsigned)((int64_t)s.K * cdiv(s.h, C::BM) * cdiv(s.d, C::BN))),
+  HMOE_LAUNCH("expert dW1", k_expert_wgrad<CK>, dim3((unsigned)((int64_t)s.K * cdiv(s.h, C::BM) * cdiv(s.d, C::BN))),
               dim3(C::THREADS), C::LDS, st, (const T*)dZ, Xs, offsets, order, s.K, s.h, s.d, dW1);
   if (dX)
-    HMOE_LAUNCH("expert dX", (k_expert_dgrad<C, false>), dim3((unsigned)(mt_bound * cdiv(s.d, C::BN))),
+    HMOE_LAUNCH("expert dX", (k_expert_dgrad<CK, false>), dim3((unsigned)(mt_bound * cdiv(s.d, C::BN))),
                 dim3(C::THREADS), C::LDS, st, (const T*)dZ, W1, offsets, ts, s.K, s.d, s.h,
                 (const T*)nullptr, perm, dX);
   return HMOE_OK;
@@ -1269,14 +1307,14 @@ static __global__ void k_seg_one(int32_t* __restrict__ seg, int64_t rows) {
 // tiles alone would leave most of the chip idle.
 template <typename T>
 size_t gemm_tn_ws() {
-  using C = typename Pick<T>::C;
+  using C = typename Pick<T>::CK;
   return ((size_t)kMaxSplitItems * C::BM * C::BN) * sizeof(float) + 256;
 }
 
 template <typename T>
 int launch_gemm_tn(const T* A, const T* B, int64_t rows, int M, int N, float* out, Workspace& ws, hipStream_t st,
                    const char* label) {
-  using C = typename Pick<T>::C;
+  using C = typename Pick<T>::CK;
   float* part = ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   if (!ws.fits()) return HMOE_EWORKSPACE;
   if (rows <= 0) return launch_zero_f32(out, (int64_t)M * N, st);
@@ -1287,7 +1325,7 @@ int launch_gemm_tn(const T* A, const T* B, int64_t rows, int M, int N, float* ou
 // a single group.
 template <typename T>
 int launch_gemm_nn(const T* A, const T* W, int64_t rows, int Kd, int N, T* out, Workspace& ws, hipStream_t st) {
-  using C = typename Pick<T>::C;
+  using C = typename Pick<T>::CK;
   int32_t* seg = ws.take<int32_t>(2);
   int32_t* ts = ws.take<int32_t>(2);
   if (!ws.fits()) return HMOE_EWORKSPACE;
@@ -1309,10 +1347,12 @@ template int launch_gemm_nn<float>(const float*, const float*, int64_t, int, int
 int launch_moe_forward(const hmoe_moe_params_t* p, int64_t n, const void* Xs, const int32_t* offsets,
                        const int32_t* perm, const hmoe_labels_t* y, void* H1s, void* H, void* logits, float* anc,
                        float* lse, float* loss, float* loss_mean, Workspace& ws, hipStream_t st) {
-  if (p->dt == HMOE_BF16)
-    return forward_t<bf16>(p, n, (const bf16*)Xs, offsets, perm, y, (bf16*)H1s, (bf16*)H, (bf16*)logits, anc, lse,
+  if (p->dt == HMOE_BF16) {
+    const auto run = wide_rows(shape_of(p, n)) ? forward_t<bf16, Pick<bf16, true>> : forward_t<bf16, Pick<bf16>>;
+    return run(p, n, (const bf16*)Xs, offsets, perm, y, (bf16*)H1s, (bf16*)H, (bf16*)logits, anc, lse,
                            loss, loss_mean, ws, st);
-  return forward_t<float>(p, n, (const float*)Xs, offsets, perm, y, (float*)H1s, (float*)H, (float*)logits, anc, lse,
+  }
+  return forward_t<float, Pick<float>>(p, n, (const float*)Xs, offsets, perm, y, (float*)H1s, (float*)H, (float*)logits, anc, lse,
                           loss, loss_mean, ws, st);
 }
 
@@ -1321,10 +1361,12 @@ int launch_moe_backward(const hmoe_moe_params_t* p, int64_t n, const void* Xs, c
                         const void* H, const void* logits, const float* anc, const float* lse, float* dW1,
                         float* db1, float* dW2, float* db2, float* dD, float* dbD, void* dX, Workspace& ws,
                         hipStream_t st) {
-  if (p->dt == HMOE_BF16)
-    return backward_t<bf16>(p, n, (const bf16*)Xs, offsets, perm, inv, y, (const bf16*)H1s, (const bf16*)H,
+  if (p->dt == HMOE_BF16) {
+    const auto run = wide_rows(shape_of(p, n)) ? backward_t<bf16, Pick<bf16, true>> : backward_t<bf16, Pick<bf16>>;
+    return run(p, n, (const bf16*)Xs, offsets, perm, inv, y, (const bf16*)H1s, (const bf16*)H,
                             (const bf16*)logits, anc, lse, dW1, db1, dW2, db2, dD, dbD, (bf16*)dX, ws, st);
-  return backward_t<float>(p, n, (const float*)Xs, offsets, perm, inv, y, (const float*)H1s, (const float*)H,
+  }
+  return backward_t<float, Pick<float>>(p, n, (const float*)Xs, offsets, perm, inv, y, (const float*)H1s, (const float*)H,
                            (const float*)logits, anc, lse, dW1, db1, dW2, db2, dD, dbD, (float*)dX, ws, st);
 }
 
