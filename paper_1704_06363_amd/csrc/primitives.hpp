@@ -159,6 +159,7 @@ __global__ void __launch_bounds__(256) k_segsum_partial(const T* __restrict__ X,
   }
   double* dst = part + b * (int64_t)w;
   if (RG == 1) {
+    if (rg > 0) return;  // fewer than 256 vectors: the last threads have no column
 #pragma unroll
     for (int q = 0; q < kSegMaxVec; ++q) {
       const int v = v0 + q * 256;

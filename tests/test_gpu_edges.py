@@ -229,3 +229,20 @@ def test_vocabulary_padded_to_a_multiple_of_8(store, saved):
     assert_grad_close(g["dD"][:V], gr["dD"], gm["dD"], store, "dD")
     assert_grad_close(g["dbD"][:V], gr["dbD"], gm["dbD"], store, "dbD")
     assert torch.count_nonzero(g["dD"][V:]).item() == 0 and torch.count_nonzero(g["dbD"][V:]).item() == 0
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 1024), ("bf16", 1032), ("bf16", 1544), ("bf16", 2040), ("bf16", 2048),
+                                     ("f32", 512), ("f32", 520), ("f32", 1016), ("f32", 1024)])
+def test_column_sums_around_one_vector_per_thread(dtype, d):
+    # rows of 128 to 256 16-byte vectors: between the two, some of the workgroup's threads have
+    # no column of their own
+    n, K = 3000, 5
+    X = W.gmm_features(n, d, 8, seed=d, dtype=dtype, device="cuda")
+    a = torch.arange(n, dtype=torch.int32, device="cuda") % K
+    sums = torch.zeros(K, d, dtype=torch.float64, device="cuda")
+    counts = torch.zeros(K, dtype=torch.int64, device="cuda")
+    hmoe.kmeans_update(X, K, a, None, sums, counts, torch.zeros(K, d, device="cuda"), mode=hmoe.UPDATE_ACCUMULATE,
+                       reseed=False)
+    ref = torch.zeros_like(sums).index_add_(0, a.long(), X.double())
+    # fp64 sums of 600 terms: n eps times their magnitude
+    assert (sums - ref).abs().max() <= n * 2.0 ** -53 * X.double().abs().sum(0).max()
