@@ -11,10 +11,10 @@
 // below a wave-wide bound on the row's m-th value (the m-th largest of the lanes' maxima).
 // The row is read once: the kernel is bound by HBM.
 // k_topm_anchored (logits stored as offsets <= 0 from per-row anchors, one per 64 columns, as
-// the forward writes them; an entry is anchor + offset formed in fp32), one lane per row and
-// four waves per 64 rows: a block's anchor bounds all its entries, so the row's anchors (a few
-// KB) are read and only the blocks whose anchor can reach the row's m-th entry -- about m
-// blocks of 64 columns when every anchor is its block's maximum.
+// the forward writes them; an entry is anchor + offset formed in fp32), one wave per row: a
+// block's anchor bounds all its entries, so the row's anchors (a few KB) are read and only the
+// blocks whose anchor can reach the row's m-th entry -- a few more than m blocks of 64 columns
+// when every anchor is its block's maximum.
 //
 // k_topm_hits: one thread per row (p) and per draw (q); the rank of each matching tag in the
 // top-m list adds 1 to every m' above it.  Integer counts, summed through LDS and then with
@@ -72,13 +72,70 @@ __device__ __forceinline__ void emit_topm(float (&lv)[M], int (&li)[M], int m, i
   }
 }
 
-template <typename T, int M>
-__global__ void __launch_bounds__(256) k_topm(const T* __restrict__ L, int64_t n, int V, int m,
-                                              int32_t* __restrict__ idx, float* __restrict__ val) {
+// The m-th largest over the lanes of x (with multiplicity): a bitonic sort of the 64 lanes in
+// registers, each merge starting with the mirrored pair (so that every step keeps the larger
+// value in the lower lane).  About 90 instructions; m rounds of a wave maximum take 16 m.
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float mth_lane_value(float x, int m, int l) {
+  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+  const auto step = [&](float y, int bit) { x = (l & bit) ? fminf(x, y) : fmaxf(x, y); };
+  const auto xor1 = [&] { step(dpp_of<0xB1>(x), 1); };           // quad_perm [1,0,3,2]
+  const auto xor2 = [&] { step(dpp_of<0x4E>(x), 2); };           // quad_perm [2,3,0,1]
+  const auto xor4 = [&] { step(dpp_of<0x1B>(dpp_of<0x141>(x)), 4); };  // half mirror, quad mirror
+  const auto xor8 = [&] { step(dpp_of<0x128>(x), 8); };          // row_ror:8
+  const auto rows16 = [&](float y) {  // y from the lane 16 away
+    const u2v a = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return __uint_as_float((l & 16) ? a[0] : a[1]);
+  };
+  const auto rows32 = [&](float y) {  // y from the lane 32 away
+    const u2v a = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return __uint_as_float((l & 32) ? a[0] : a[1]);
+  };
+  xor1();
+  step(dpp_of<0x1B>(x), 2);  // quad mirror
+  xor1();
+  step(dpp_of<0x141>(x), 4);  // half mirror
+  xor2();
+  xor1();
+  step(dpp_of<0x140>(x), 8);  // row mirror
+  xor4();
+  xor2();
+  xor1();
+  step(rows16(dpp_of<0x140>(x)), 16);
+  xor8();
+  xor4();
+  xor2();
+  xor1();
+  step(rows16(rows32(dpp_of<0x140>(x))), 32);
+  step(rows16(x), 16);
+  xor8();
+  xor4();
+  xor2();
+  xor1();
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), m - 1));
+}
+
+// Set bits of `mask` below this lane.
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// Orders a wave's LDS writes before its later reads by other lanes of the same wave.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One row's t_m by one wave, reading the whole row: r its entries, arow its anchors' four-slot
+// tiles (tile t at arow[t n]; NULL: the stored values are the entries).  U vectors in flight.
+template <typename T, int M, int U>
+__device__ __forceinline__ void topm_row(const T* __restrict__ r, const floatx4* __restrict__ arow, int64_t n, int V,
+                                         int m, int l, int64_t row, int32_t* __restrict__ idx,
+                                         float* __restrict__ val) {
   constexpr int EPV = 16 / sizeof(T);
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
-  if (row >= n) return;
   float lv[M];
   int li[M];
 #pragma unroll
@@ -86,22 +143,28 @@ __global__ void __launch_bounds__(256) k_topm(const T* __restrict__ L, int64_t n
     lv[k] = -INFINITY;
     li[k] = 0x7fffffff;
   }
-  const T* r = L + row * (int64_t)V;
   const int nvec = V / EPV;
   // Wave-wide lower bound on the row's m-th largest value (the m-th largest of the lanes'
   // maxima: m entries are at least that large), so an entry below thr is not in t_m (entries
   // equal to it may be, and stay).  It closes in on the m-th value within a few steps, which
   // keeps the insertion branch -- taken by the wave when any lane takes it -- rare.
   float thr = -INFINITY;
-  constexpr int U = 4;  // vectors in flight per lane
   // the trip count is the same for every lane (the bound is a wave-wide shuffle reduction)
   int step = 0;
   for (int b0 = 0; b0 < nvec; b0 += 64 * U, ++step) {
     i32x4 raw[U];
+    float an[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int v = b0 + 64 * u + l;
-      if (v < nvec) raw[u] = *reinterpret_cast<const i32x4*>(r + (int64_t)v * EPV);
+      an[u] = 0.f;
+      if (v < nvec) {
+        raw[u] = *reinterpret_cast<const i32x4*>(r + (int64_t)v * EPV);
+        if (arow) {
+          const int c = v * EPV;
+          an[u] = reinterpret_cast<const float*>(arow + (int64_t)(c / kAnchorTile) * n)[(c % kAnchorTile) / kAnchorCols];
+        }
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -112,267 +175,185 @@ __global__ void __launch_bounds__(256) k_topm(const T* __restrict__ L, int64_t n
       float vmax = -INFINITY;
 #pragma unroll
       for (int z = 0; z < EPV; ++z) {
-        f[z] = to_f32(e[z]);
+        f[z] = arow ? an[u] + to_f32(e[z]) : to_f32(e[z]);
         vmax = fmaxf(vmax, f[z]);
       }
-      if (!(vmax >= thr && vmax > lv[M - 1])) continue;  // the common case: nothing here enters
+      // the common case: nothing here enters (an unfilled slot also takes a -inf entry of
+      // anchored logits, whose rows may have fewer than m finite ones)
+      const bool open = arow && li[M - 1] == 0x7fffffff;
+      if (!(vmax >= thr && (vmax > lv[M - 1] || open))) continue;
 #pragma unroll
       for (int z = 0; z < EPV; ++z)
-        if (f[z] >= thr && f[z] > lv[M - 1]) list_carry(lv, li, f[z], v * EPV + z);
+        if (f[z] >= thr && (f[z] > lv[M - 1] || (arow && f[z] == lv[M - 1] && li[M - 1] == 0x7fffffff)))
+          list_carry(lv, li, f[z], v * EPV + z);
     }
     // the m-th largest of the lanes' maxima: m lanes each hold an entry at least that large
     // (refreshed on the first steps, then every 4th: it settles quickly, and any value it
     // took is a valid bound)
     if (step >= 4 && (step & 3) != 0) continue;
-    float x = lv[0];
-    float t = -INFINITY;
-    for (int q = 0; q < m; ++q) {
-      t = wave_max(x);
-      const uint64_t hit = __ballot(x == t);
-      if (l == __ffsll((unsigned long long)hit) - 1) x = -INFINITY;  // drop one holder
-    }
-    thr = t;
+    thr = mth_lane_value(lv[0], m, l);
   }
   emit_topm(lv, li, m, l, row, idx, val);
 }
 
-constexpr int kTopmRows = 64;  // rows per workgroup (one per lane; four waves split the tiles)
-
-// The first m entries, in (value desc, index asc) order, of the union of the four sorted lists
-// of this lane's row held in LDS ([wave][k][lane]; si NULL: values only): the m-th value is
-// returned, and with gi given the m entries are written to gi[0 .. m) (and gv).
-template <int M>
-__device__ __forceinline__ float merge4(const float* sv, const int32_t* si, int m, int l,
-                                        int32_t* __restrict__ gi = nullptr, float* __restrict__ gv = nullptr) {
-  int h[4] = {0, 0, 0, 0};
-  float v = -INFINITY;
-  for (int q = 0; q < m; ++q) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff, bw = -1;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (h[w] >= M) continue;
-      const float cv = sv[(w * M + h[w]) * kTopmRows + l];
-      const int ci = si ? si[(w * M + h[w]) * kTopmRows + l] : 0;
-      if (bw < 0 || cv > bv || (cv == bv && ci < bi)) {
-        bv = cv;
-        bi = ci;
-        bw = w;
-      }
-    }
-#pragma unroll
-    for (int w = 0; w < 4; ++w) h[w] += (w == bw);
-    v = bv;
-    if (gi) gi[q] = bi;
-    if (gv) gv[q] = bv;
-  }
-  return v;
+template <typename T, int M>
+__global__ void __launch_bounds__(256) k_topm(const T* __restrict__ L, int64_t n, int V, int m,
+                                              int32_t* __restrict__ idx, float* __restrict__ val) {
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  topm_row<T, M, 4>(L + row * (int64_t)V, nullptr, n, V, m, threadIdx.x & 63, row, idx, val);
 }
 
-// Reads block b of a row (64 columns from r) and offers its entries >= lo, formed as anchor a
-// + stored value in fp32, to the (value desc, index asc) list; cnt counts the entries that
-// enter.  Nothing is read when `take` is false.
-template <typename T, int M>
-__device__ __forceinline__ void topm_block(const T* __restrict__ r, int V, int b, float a, float lo, bool take,
-                                           float (&lv)[M], int (&li)[M], int& cnt) {
+// Anchored logits, one wave per row and eight adjacent rows per workgroup.  Block b (columns
+// [64 b, 64 b + 64)) of row i has its anchor at anc[((b / 4) n + i) 4 + b % 4], and every entry
+// of it is at most that anchor; the four anchors of a 256-column tile are one 16-byte vector, and
+// the eight rows' vectors one 128-byte line, which the workgroup's waves read at about the same
+// time.
+//   1. Lane l reads the tiles l, l + 64, ... of its row.  t0 = the m-th largest of the lanes'
+//      largest anchors: at least m blocks have an anchor >= t0.  Those blocks are listed in LDS
+//      (a few more than m: a lane that holds two of the largest lowers t0 a little).
+//   2. The listed blocks are read, a 16-byte vector per lane, several blocks at once.  t1 = the
+//      m-th largest of the lanes' largest entries; the entries >= t1 (m and a few more) are
+//      collected in LDS, one per lane, and ranked by (value desc, index asc).
+//   3. Every entry outside the listed blocks is below t0, so t_m is among the listed ones when
+//      the m-th of them is >= t0.  With the forward's anchors (each its block's maximum, so each
+//      listed block holds an entry equal to its anchor) this is always the case.  Otherwise, and
+//      when the lists overflow (many equal anchors or entries), the wave reads the whole row.
+// The work per row is under a thousand vector instructions and two trips to memory (290 MB at
+// 65,536 x 50,000 bf16 logits and m = 10): 0.36 -> 0.11 ms there against a lane per row with
+// sorted lists of anchors, whose insertions every lane of a wave waits for, and 0.19 -> 0.01 ms
+// for 512 rows, which gave that kernel 8 workgroups.  Six waves per SIMD: four (no bound) take
+// 0.14 ms, eight 0.11 ms but spill the lists of the whole-row pass, which then takes 295 ms
+// instead of 2.5 on anchors above their blocks' entries (6.0 ms with sorted lists per lane).
+constexpr int kTopmWaves = 8;    // rows per workgroup
+constexpr int kTopmBlocks = 32;  // listed blocks at most
+constexpr int kTopmRegTiles = 4;  // anchor tiles a lane keeps between its two looks at them
+
+template <typename T>
+__global__ void __launch_bounds__(64 * kTopmWaves, 6)
+    k_topm_anchored(const T* __restrict__ L, const float* __restrict__ anc, int64_t n, int V, int m,
+                    int32_t* __restrict__ idx, float* __restrict__ val) {
   constexpr int EPV = 16 / sizeof(T);
-  constexpr int VPB = kAnchorCols / EPV;
-  const int c0 = b * kAnchorCols;
-  i32x4 raw[VPB];
-#pragma unroll
-  for (int v = 0; v < VPB; ++v)
-    if (take && c0 + v * EPV < V) raw[v] = *reinterpret_cast<const i32x4*>(r + c0 + v * EPV);
-  if (!take) return;
-  auto offer = [&](const i32x4& x, int cv0) {
-    const T* e = reinterpret_cast<const T*>(&x);
-#pragma unroll
-    for (int z = 0; z < EPV; ++z) {
-      const float cv = a + to_f32(e[z]);
-      if (cv >= lo && (cv > lv[M - 1] || (cv == lv[M - 1] && cv0 + z < li[M - 1]))) {
-        list_carry(lv, li, cv, cv0 + z);
-        ++cnt;
-      }
-    }
-  };
-  if constexpr (M <= 4) {
-#pragma unroll
-    for (int v = 0; v < VPB; ++v)
-      if (c0 + v * EPV < V) offer(raw[v], c0 + v * EPV);  // V is a multiple of 8: vectors are whole
-  } else {
-    // longer lists: one vector per trip, picked by selects.  Fully unrolled, the insertion code
-    // of a block is (64 entries x M steps) long: it compiled for minutes per list length, and
-    // past 12 entries the unroller gave up and indexed the vectors through scratch memory.
-#pragma unroll 1
-    for (int v = 0; v < VPB; ++v) {
-      if (c0 + v * EPV >= V) break;
-      i32x4 x = raw[0];
-#pragma unroll
-      for (int vv = 1; vv < VPB; ++vv) x = v == vv ? raw[vv] : x;
-      offer(x, c0 + v * EPV);
-    }
-  }
-}
-
-// One pass over this lane's tiles reading every block whose anchor is >= lo when `on`.
-template <typename T, int M, int TU>
-__device__ __forceinline__ void topm_scan(const T* __restrict__ r, const floatx4* __restrict__ arow, int64_t n,
-                                          int V, int nb, int nt, int w, float lo, bool on, float (&lv)[M],
-                                          int (&li)[M], int& cnt) {
-  for (int t0 = w; t0 < nt; t0 += 4 * TU) {
-    floatx4 q[TU];
-#pragma unroll
-    for (int u = 0; u < TU; ++u)
-      if (t0 + 4 * u < nt) q[u] = arow[(int64_t)(t0 + 4 * u) * n];
-    uint32_t mark = 0u;
-#pragma unroll
-    for (int u = 0; u < TU; ++u)
-#pragma unroll
-      for (int sl = 0; sl < 4; ++sl)
-        if (on && t0 + 4 * u < nt && (t0 + 4 * u) * 4 + sl < nb && q[u][sl] >= lo) mark |= 1u << (4 * u + sl);
-    while (mark) {
-      const int k = __ffs(mark) - 1;
-      mark &= mark - 1u;
-      float a = q[0][0];  // the block's anchor, selected without indexing the registers
-#pragma unroll
-      for (int kk = 1; kk < 4 * TU; ++kk) a = k == kk ? q[kk / 4][kk % 4] : a;
-      topm_block<T, M>(r, V, (t0 + 4 * (k / 4)) * 4 + k % 4, a, lo, true, lv, li, cnt);
-    }
-  }
-}
-
-// Anchored logits.  Block b (columns [64 b, 64 b + 64)) of row i has its anchor at
-// anc[((b / 4) n + i) 4 + b % 4], and every entry of it is at most that anchor; the four
-// anchors of a 256-column tile are one 16-byte vector.  A workgroup takes 64 rows, one per
-// lane, and its four waves split each row's tiles (wave w takes tiles w, w + 4, ...), so one
-// load instruction reads 1 KB of consecutive anchors.  Each lane keeps sorted register lists
-// over its share; the four shares of a row meet in LDS, where every lane merges them.
-//   1. Each lane keeps its m largest anchors with their blocks; merged, a_m = the row's m-th
-//      largest anchor (with multiplicity).  Every entry >= a_m lies in a block with anchor >=
-//      a_m, and those blocks are in the lanes' lists -- unless a lane's list ends at a_m and
-//      it dropped a block (then an anchor equal to a_m may be missing from its list, and the
-//      row rescans its anchors).
-//   2. The blocks with anchor >= a_m are read and their entries >= a_m enter the (value desc,
-//      index asc) lists of the row.  If the row has at least m such entries, its m-th largest
-//      entry is >= a_m and the lists hold t_m.  With the forward's anchors (each its block's
-//      maximum, so each of the m blocks holds an entry equal to its anchor) this is always the
-//      case: a row costs its anchors and about m blocks of 64 columns.
-//   3. Otherwise (anchors above their blocks' entries) the row's lists start again and every
-//      block is read.
-// The entries counted in pass 2 are distinct, and an entry >= a_m that does not enter a full
-// list ranks below m counted ones, so the count reaches m exactly when the row has m entries
-// >= a_m.  Entries reach a list out of index order, so an entry enters when it ranks above the
-// list's last by (value desc, index asc).
-template <typename T, int M>
-__global__ void __launch_bounds__(256) k_topm_anchored(const T* __restrict__ L, const float* __restrict__ anc,
-                                                       int64_t n, int V, int m, int32_t* __restrict__ idx,
-                                                       float* __restrict__ val) {
-  constexpr int TU = 4;  // a lane's anchor tiles in flight
-  static_assert(kAnchorSlots == 4 && 4 * TU <= 32, "one 16-byte anchor vector per tile, one mask bit per block");
-  __shared__ float s_v[4 * M * kTopmRows];
-  __shared__ int32_t s_i[4 * M * kTopmRows];
-  __shared__ int32_t s_c[4 * kTopmRows];
+  constexpr int VPB = kAnchorCols / EPV;           // vectors per block
+  constexpr int BPR = 64 / VPB;                    // blocks a wave reads at once
+  constexpr int ROUNDS = kTopmBlocks / BPR;
+  static_assert(kAnchorSlots == 4, "one 16-byte anchor vector per tile");
+  __shared__ int32_t s_blk[kTopmWaves][kTopmBlocks];
+  __shared__ float s_anc[kTopmWaves][kTopmBlocks];
+  __shared__ float s_val[kTopmWaves][64];
+  __shared__ int32_t s_idx[kTopmWaves][64];
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t row0 = (int64_t)blockIdx.x * kTopmRows + l;
-  const bool live = row0 < n;
-  const int64_t row = live ? row0 : n - 1;  // a spare lane shadows the last row, writes nothing
+  const int64_t row = (int64_t)blockIdx.x * kTopmWaves + w;
+  if (row >= n) return;
   const int nb = (int)cdiv(V, kAnchorCols);
   const int nt = (int)cdiv(V, kAnchorTile);
   const floatx4* arow = reinterpret_cast<const floatx4*>(anc) + row;  // tile t at arow[t n]
   const T* r = L + row * (int64_t)V;
-  // pass 1
-  float av[M];
-  int ab[M];
+  // a tile's anchors, absent blocks as -inf
+  auto tile = [&](int t) {
+    floatx4 q = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (t < nt) {
+      q = arow[(int64_t)t * n];
 #pragma unroll
-  for (int k = 0; k < M; ++k) {
-    av[k] = -INFINITY;
-    ab[k] = -1;
+      for (int sl = 0; sl < 4; ++sl)
+        if (4 * t + sl >= nb) q[sl] = -INFINITY;
+    }
+    return q;
+  };
+  floatx4 q[kTopmRegTiles];
+#pragma unroll
+  for (int u = 0; u < kTopmRegTiles; ++u) q[u] = tile(l + 64 * u);
+  float top = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < kTopmRegTiles; ++u) top = fmaxf(fmaxf(fmaxf(top, q[u][0]), fmaxf(q[u][1], q[u][2])), q[u][3]);
+  for (int t = 64 * kTopmRegTiles; t < nt; t += 64) {
+    const floatx4 x = tile(t + l);
+    top = fmaxf(fmaxf(fmaxf(top, x[0]), fmaxf(x[1], x[2])), x[3]);
   }
-  int seen = 0;  // blocks in this lane's share
-  for (int t0 = w; t0 < nt; t0 += 4 * TU) {
-    floatx4 q[TU];
+  const float t0 = mth_lane_value(top, m, l);
+  int listed = 0;  // wave-uniform
+  auto list = [&](const floatx4& x, int t) {
 #pragma unroll
-    for (int u = 0; u < TU; ++u)
-      if (t0 + 4 * u < nt) q[u] = arow[(int64_t)(t0 + 4 * u) * n];
+    for (int sl = 0; sl < 4; ++sl) {
+      const uint64_t hit = __ballot(4 * t + sl < nb && x[sl] >= t0);
+      if (hit == 0) continue;
+      const int at = listed + lanes_below(hit);
+      if (((hit >> l) & 1) && at < kTopmBlocks) {
+        s_blk[w][at] = 4 * t + sl;
+        s_anc[w][at] = x[sl];
+      }
+      listed += __popcll(hit);
+    }
+  };
 #pragma unroll
-    for (int u = 0; u < TU; ++u)
+  for (int u = 0; u < kTopmRegTiles; ++u) list(q[u], l + 64 * u);
+  for (int t = 64 * kTopmRegTiles; t < nt; t += 64) list(tile(t + l), t + l);
+  bool found = false;
+  if (listed <= kTopmBlocks) {
+    wave_lds_fence();
+    // the listed blocks, BPR at a time: lane l takes vector l % VPB of block l / VPB
+    float f[ROUNDS][EPV];
+    int c0[ROUNDS];
+    i32x4 raw[ROUNDS];
 #pragma unroll
-      for (int sl = 0; sl < 4; ++sl) {
-        const int b = (t0 + 4 * u) * 4 + sl;
-        if (t0 + 4 * u < nt && b < nb) {
-          ++seen;
-          float cv = q[u][sl];
-          int cb = b;
-          if (cv > av[M - 1]) {
+    for (int u = 0; u < ROUNDS; ++u) {
+      const int k = u * BPR + l / VPB;
+      c0[u] = V;
+      if (u * BPR < listed && k < listed) {
+        c0[u] = s_blk[w][k] * kAnchorCols + (l % VPB) * EPV;
+        if (c0[u] < V) raw[u] = *reinterpret_cast<const i32x4*>(r + c0[u]);
+      }
+    }
+    float best = -INFINITY;
 #pragma unroll
-            for (int k = 0; k < M; ++k) {
-              const bool gt = cv > av[k];
-              const float tv = av[k];
-              const int tb = ab[k];
-              av[k] = gt ? cv : tv;
-              ab[k] = gt ? cb : tb;
-              cv = gt ? tv : cv;
-              cb = gt ? tb : cb;
-            }
-          }
+    for (int u = 0; u < ROUNDS; ++u) {
+      if (u * BPR >= listed) break;
+      const int k = u * BPR + l / VPB;
+      const float a = k < listed ? s_anc[w][k] : 0.f;
+      const T* e = reinterpret_cast<const T*>(&raw[u]);
+#pragma unroll
+      for (int z = 0; z < EPV; ++z) {
+        f[u][z] = c0[u] < V ? a + to_f32(e[z]) : -INFINITY;
+        best = fmaxf(best, f[u][z]);
+      }
+    }
+    const float t1 = mth_lane_value(best, m, l);
+    int kept = 0;  // wave-uniform
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u) {
+      if (u * BPR >= listed) break;
+#pragma unroll
+      for (int z = 0; z < EPV; ++z) {
+        const uint64_t hit = __ballot(c0[u] < V && f[u][z] >= t1);
+        if (hit == 0) continue;
+        const int at = kept + lanes_below(hit);
+        if (((hit >> l) & 1) && at < 64) {
+          s_val[w][at] = f[u][z];
+          s_idx[w][at] = c0[u] + z;
         }
-      }
-  }
-#pragma unroll
-  for (int k = 0; k < M; ++k) s_v[(w * M + k) * kTopmRows + l] = av[k];
-  __syncthreads();
-  const float a_m = merge4<M>(s_v, nullptr, m, l);  // -inf when the row has fewer than m blocks
-  __syncthreads();
-  s_c[w * kTopmRows + l] = (seen > M && av[M - 1] >= a_m) ? 1 : 0;  // this lane may miss a block at a_m
-  __syncthreads();
-  const bool rescan = s_c[l] | s_c[kTopmRows + l] | s_c[2 * kTopmRows + l] | s_c[3 * kTopmRows + l];
-  __syncthreads();
-  float lv[M];
-  int li[M];
-#pragma unroll
-  for (int k = 0; k < M; ++k) {
-    lv[k] = -INFINITY;
-    li[k] = 0x7fffffff;
-  }
-  int cnt = 0;  // entries >= a_m that entered this lane's list (each entry enters at most once)
-  // pass 2: the listed blocks with anchor >= a_m (a prefix of the sorted list), two at a time
-  // from the head of the list, which then shifts by two (every register index stays static);
-  // an unfilled slot (block -1, anchor -inf) is never read, also when a_m is -inf
-  for (int k = 0; k < M; k += 2) {
-    const bool t0k = !rescan && ab[0] >= 0 && av[0] >= a_m;
-    const bool t1k = M > 1 && !rescan && ab[M > 1 ? 1 : 0] >= 0 && av[M > 1 ? 1 : 0] >= a_m;
-    if (!__any(t0k)) break;  // wave-uniform: the lists are sorted, nothing further qualifies
-    topm_block<T, M>(r, V, ab[0], av[0], a_m, t0k, lv, li, cnt);
-    if (M > 1) topm_block<T, M>(r, V, ab[M > 1 ? 1 : 0], av[M > 1 ? 1 : 0], a_m, t1k, lv, li, cnt);
-#pragma unroll
-    for (int q = 0; q < M; ++q) {
-      av[q] = q + 2 < M ? av[q + 2 < M ? q + 2 : q] : -INFINITY;
-      ab[q] = q + 2 < M ? ab[q + 2 < M ? q + 2 : q] : -1;
-    }
-  }
-  if (__any(rescan)) topm_scan<T, M, TU>(r, arow, n, V, nb, nt, w, a_m, rescan, lv, li, cnt);
-  // pass 3 for the rows with fewer than m entries >= a_m
-  s_c[w * kTopmRows + l] = cnt;
-  __syncthreads();
-  const int total = s_c[l] + s_c[kTopmRows + l] + s_c[2 * kTopmRows + l] + s_c[3 * kTopmRows + l];
-  if (__any(total < m)) {
-    const bool redo = total < m;
-    if (redo) {
-#pragma unroll
-      for (int k = 0; k < M; ++k) {
-        lv[k] = -INFINITY;
-        li[k] = 0x7fffffff;
+        kept += __popcll(hit);
       }
     }
-    topm_scan<T, M, TU>(r, arow, n, V, nb, nt, w, -INFINITY, redo, lv, li, cnt);
+    if (kept >= m && kept <= 64) {
+      wave_lds_fence();
+      const float v = l < kept ? s_val[w][l] : -INFINITY;
+      const int i = l < kept ? s_idx[w][l] : 0x7fffffff;
+      int rank = 0;
+      for (int k = 0; k < kept; ++k) {
+        const float ov = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), k));
+        const int oi = __builtin_amdgcn_readlane(i, k);
+        rank += (ov > v || (ov == v && oi < i)) ? 1 : 0;
+      }
+      // the m-th found entry settles whether anything outside the listed blocks could rank
+      const uint64_t last = __ballot(l < kept && rank == m - 1 && v >= t0);
+      found = last != 0;
+      if (found && l < kept && rank < m) {
+        idx[row * (int64_t)m + rank] = i;
+        if (val) val[row * (int64_t)m + rank] = v;
+      }
+    }
   }
-  // the four shares of each row, merged by wave 0
-#pragma unroll
-  for (int k = 0; k < M; ++k) {
-    s_v[(w * M + k) * kTopmRows + l] = lv[k];
-    s_i[(w * M + k) * kTopmRows + l] = li[k];
-  }
-  __syncthreads();
-  if (w == 0 && live) merge4<M>(s_v, s_i, m, l, idx + row * (int64_t)m, val ? val + row * (int64_t)m : nullptr);
+  if (!found) topm_row<T, 16, 1>(r, arow, n, V, m, l, row, idx, val);
 }
 
 // hits[0 .. m) for p, hits[m .. 2m) for q; must start at zero.
@@ -428,25 +409,14 @@ static int topm_launch(const T* L, int64_t n, int V, int m, int32_t* idx, float*
   return HMOE_OK;
 }
 
-// The anchored kernel keeps M >= m entries per list (it takes the m-th of the merged lists), so
-// four list lengths cover m = 1 .. 16.
-template <typename T, int M>
-static int topm_launch_anchored(const T* L, const float* anc, int64_t n, int V, int m, int32_t* idx, float* val,
-                                hipStream_t st) {
-  HMOE_LAUNCH("top-m", (k_topm_anchored<T, M>), dim3((unsigned)cdiv(n, kTopmRows)), dim3(256), 0, st, L, anc, n, V,
-              m, idx, val);
-  return HMOE_OK;
-}
-
 // The plain kernel's register lists hold exactly m entries (the insertion and the registers
 // scale with the list length: a 16-entry list for m = 10 ran 25% slower than a 12-entry one).
 template <typename T>
 static int topm_t(const T* L, const float* anc, int64_t n, int V, int m, int32_t* idx, float* val, hipStream_t st) {
   if (anc) {
-    if (m <= 4) return topm_launch_anchored<T, 4>(L, anc, n, V, m, idx, val, st);
-    if (m <= 8) return topm_launch_anchored<T, 8>(L, anc, n, V, m, idx, val, st);
-    if (m <= 12) return topm_launch_anchored<T, 12>(L, anc, n, V, m, idx, val, st);
-    return topm_launch_anchored<T, 16>(L, anc, n, V, m, idx, val, st);
+    HMOE_LAUNCH("top-m", k_topm_anchored<T>, dim3((unsigned)cdiv(n, kTopmWaves)), dim3(64 * kTopmWaves), 0, st, L, anc,
+                n, V, m, idx, val);
+    return HMOE_OK;
   }
   switch (m) {
     case 1: return topm_launch<T, 1>(L, n, V, m, idx, val, st);
