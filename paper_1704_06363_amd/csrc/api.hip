@@ -236,7 +236,7 @@ int hmoe_kmeans_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, con
 
 size_t hmoe_kmeans_fit_workspace(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
   if (n < 0 || K < 1 || d < 1) return 0;
-  return fit_ws_bytes(n, d, K, dt);
+  return fit_ws_bytes(n, d, K, dt) + fit_ws_copy_bytes(n, d, K, dt);
 }
 
 int hmoe_kmeans_fit(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t K, int32_t n_iter,

@@ -269,7 +269,7 @@ int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* 
   HMOE_TRY(launch_seg_tiles(seg, G, kSegPiece, ts, st));
   HMOE_LAUNCH("segsum partial", k_segsum_partial<T>, dim3((unsigned)pieces), dim3(256), 0, st, X, ld, rowmap, seg, ts, G,
                      w, part);
-  HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 256)), dim3(256), 0, st, part,
+  HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
                      ts, G, w, out, accumulate);
   return HMOE_OK;
 }

@@ -327,42 +327,163 @@ __global__ void k_kpp_first(const double* __restrict__ u, int64_t n, int32_t* __
   }
 }
 
-// D2[i] = min(D2[i], |x_i - X[idx[t]]|^2) (fp64 direct differences; t == 0 initialises) and
-// bsum[b] = sum of D2 over the block's kKppRows rows, in a fixed order.  16 lanes share a row
-// (16-byte loads, fp64 partial sums reduced over the 16 lanes), so each wave streams 4 rows at
-// once and the block 16.
+// |x - c|^2 in fp64 from direct differences, by the 16 lanes of a row group (16-byte loads, the
+// partial sums combined in a fixed order); in every lane.
 template <typename T>
+__device__ __forceinline__ double kpp_dist(const T* __restrict__ x, const T* __restrict__ c, int d, int lane) {
+  constexpr int EPV = 16 / sizeof(T);
+  const int vpr = d / EPV;
+  double s = 0.0;
+  for (int v = lane; v < vpr; v += 16) {
+    const i32x4 xr = *reinterpret_cast<const i32x4*>(x + v * EPV);
+    const i32x4 cr = *reinterpret_cast<const i32x4*>(c + v * EPV);
+    const T* xe = reinterpret_cast<const T*>(&xr);
+    const T* ce = reinterpret_cast<const T*>(&cr);
+#pragma unroll
+    for (int z = 0; z < EPV; ++z) {
+      const double df = (double)to_f32(xe[z]) - (double)to_f32(ce[z]);
+      s += df * df;
+    }
+  }
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) s += shfl_xor(s, m);
+  return s;
+}
+
+// bsum[block] = sum of the block's D2 in row order, split over the first wave: lane l adds rows
+// 4l..4l+3, then the lanes are combined by the wave's fixed butterfly.
+__device__ __forceinline__ void kpp_block_sum(const double* rowv, double* __restrict__ bsum) {
+  if (threadIdx.x < 64) {
+    double s = ((rowv[4 * threadIdx.x] + rowv[4 * threadIdx.x + 1]) + rowv[4 * threadIdx.x + 2]) +
+               rowv[4 * threadIdx.x + 3];
+    s = wave_sum(s);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = s;
+  }
+}
+
+// The D^2 pass over an 8-bit copy of the rows.  A pass over X for each centre is bound by reading X
+// (2^20 x 512 fp32 rows: 366 us at 5.9 TB/s), yet a new centre changes the D^2 of few rows.  So
+// the first pass also writes each row as x = s q + r with integers |q| <= 127 and e >= |r|, and a
+// later pass reads q instead of x: |x - c| >= |s q - s' q'| - e - e' (the triangle inequality; q . q'
+// is exact in integers), and a row whose bound lies above its D^2 keeps it.  Only the other rows
+// are read in full and measured as k_kpp_update does, so every D^2, and with it every pick, is the
+// same to the last bit: the margins below cover the rounding of the bound and of the distance.
+// Rows with entries that are not finite, or too large or small to square, have e = inf: they are
+// always measured.
+// 2^20 x 512 fp32, 64 centres: 23.4 ms -> 10.0 (142 us a pass, 1.06 ms for the first, which also writes
+// the copy).
+struct KppMeta {
+  float s, e;    // scale; upper bound of |x - s q|
+  int32_t qq;    // |q|^2
+  int32_t pad;
+};
+static_assert(sizeof(KppMeta) == 16, "one 16-byte load");
+
+__host__ __device__ __forceinline__ int64_t kpp_row_bytes(int d) { return (int64_t)((d + 15) & ~15); }
+
+// Sum over the 16 lanes of a row group, in every lane of it.
+__device__ __forceinline__ int row16_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror:8, 4, 2, 1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, true);
+  return v;
+}
+
+// Row i's 8-bit copy; 16 lanes of a wave share the row, lane taking vectors lane, lane + 16, ...
+// of 16 entries (absent ones 0, up to the padded row).
+template <typename T>
+__device__ __forceinline__ void kpp_quantise(const T* __restrict__ x, int64_t i, int d, int lane,
+                                             int8_t* __restrict__ Xq, KppMeta* __restrict__ meta) {
+  constexpr int EPV = 16 / sizeof(T);
+  constexpr int PER = 16 / EPV;  // source vectors per destination vector
+  const int vpr = d / EPV;
+  float amax = 0.f;
+  bool finite = true;
+  for (int v = lane; v < vpr; v += 16) {
+    const i32x4 raw = *reinterpret_cast<const i32x4*>(x + v * EPV);
+    const T* e = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+    for (int z = 0; z < EPV; ++z) {
+      const float a = fabsf(to_f32(e[z]));
+      finite = finite && a <= 1e15f;  // false for NaN
+      amax = fmaxf(amax, a);
+    }
+  }
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) amax = fmaxf(amax, shfl_xor(amax, m));
+  const uint64_t bad = __ballot(!finite) >> (threadIdx.x & 48) & 0xffff;
+  const bool ok = bad == 0 && (amax >= 1e-15f || amax == 0.f);
+  const float s = ok ? amax * (1.f / 127.f) : 0.f;
+  const float inv = ok && amax > 0.f ? 127.f / amax : 0.f;
+  const int qv = (int)(kpp_row_bytes(d) / 16);
+  int qq = 0;
+  double r2 = 0.0;
+  for (int v = lane; v < qv; v += 16) {
+    i32x4 out = i32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      if (!ok || v * PER + p >= vpr) continue;
+      const i32x4 raw = *reinterpret_cast<const i32x4*>(x + (v * PER + p) * EPV);
+      const T* e = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+      for (int z = 0; z < EPV; ++z) {
+        const float f = to_f32(e[z]);
+        int q = (int)rintf(f * inv);
+        q = q > 127 ? 127 : (q < -127 ? -127 : q);
+        qq += q * q;
+        const double r = (double)f - (double)s * (double)q;
+        r2 += r * r;
+        const int at = p * EPV + z;
+        out[at / 4] |= (q & 255) << (8 * (at % 4));
+      }
+    }
+    *reinterpret_cast<i32x4*>(Xq + i * kpp_row_bytes(d) + v * 16) = out;
+  }
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) r2 += shfl_xor(r2, m);
+  qq = row16_sum(qq);
+  if (lane == 0) {
+    KppMeta mt;
+    mt.s = s;
+    mt.e = ok ? (float)(sqrt(r2) * (1.0 + 1e-6)) : INFINITY;
+    mt.qq = qq;
+    mt.pad = 0;
+    meta[i] = mt;
+  }
+}
+
+// Whether the bound says that row x is farther from centre c than sqrt(D2): P = q . q'.
+__device__ __forceinline__ bool kpp_far(const KppMeta& x, const KppMeta& c, int P, double D2) {
+  const double sx = x.s, sc = c.s;
+  const double xx = sx * sx * (double)x.qq, cc = sc * sc * (double)c.qq;
+  const double d2 = xx + cc - 2.0 * (sx * sc * (double)P) - 1e-12 * (xx + cc);
+  const double lb = (double)sqrtf((float)fmax(d2, 0.0)) * (1.0 - 1e-6) - (double)x.e - (double)c.e;
+  return lb > 1e-12 && lb * lb * (1.0 - 1e-6) > D2;  // false where a bound is inf or NaN
+}
+
+// D2[i] = min(D2[i], |x_i - X[idx[t]]|^2) (fp64 direct differences; t == 0 initialises) and
+// bsum[b] = sum of D2 over the block's kKppRows rows, in a fixed order.  16 lanes share a row, so
+// each wave streams 4 rows at once and the block 16.  QUANT: also writes the rows' 8-bit copies.
+template <typename T, bool QUANT>
 __global__ void __launch_bounds__(256) k_kpp_update(const T* __restrict__ X, int64_t n, int d,
                                                     const int32_t* __restrict__ idx, int t,
-                                                    double* __restrict__ D2, double* __restrict__ bsum) {
-  constexpr int EPV = 16 / sizeof(T);
-  constexpr int G = 16;  // lanes per row
+                                                    double* __restrict__ D2, double* __restrict__ bsum,
+                                                    int8_t* __restrict__ Xq, KppMeta* __restrict__ meta) {
   __shared__ double rowv[kKppRows];
-  const int lane = threadIdx.x % G;         // position inside the row group
-  const int grp = threadIdx.x / G;          // 16 row groups per block
+  const int lane = threadIdx.x & 15;        // position inside the row group
+  const int grp = threadIdx.x >> 4;         // 16 row groups per block
   const T* c = X + (int64_t)idx[t] * d;
   const int64_t r0 = (int64_t)blockIdx.x * kKppRows;
-  const int vpr = d / EPV;                  // 16-byte vectors per row
+#pragma unroll 2
   for (int q = 0; q < kKppRows / 16; ++q) {
     const int lr = q * 16 + grp;
     const int64_t i = r0 + lr;
     double s = 0.0;
     if (i < n) {
-      const T* x = X + i * d;
-      for (int v = lane; v < vpr; v += G) {
-        const i32x4 xr = *reinterpret_cast<const i32x4*>(x + v * EPV);
-        const i32x4 cr = *reinterpret_cast<const i32x4*>(c + v * EPV);
-        const T* xe = reinterpret_cast<const T*>(&xr);
-        const T* ce = reinterpret_cast<const T*>(&cr);
-#pragma unroll
-        for (int z = 0; z < EPV; ++z) {
-          const double df = (double)to_f32(xe[z]) - (double)to_f32(ce[z]);
-          s += df * df;
-        }
-      }
+      s = kpp_dist(X + i * d, c, d, lane);
+      if constexpr (QUANT) kpp_quantise(X + i * d, i, d, lane, Xq, meta);
     }
-#pragma unroll
-    for (int m = 1; m < G; m <<= 1) s += shfl_xor(s, m);
     if (lane == 0) {
       double v = 0.0;
       if (i < n) {
@@ -377,14 +498,78 @@ __global__ void __launch_bounds__(256) k_kpp_update(const T* __restrict__ X, int
     }
   }
   __syncthreads();
-  // block sum in row order, split over the first wave: lane l adds rows 4l..4l+3, then the
-  // lanes are combined by the wave's fixed butterfly
-  if (threadIdx.x < 64) {
-    double s = ((rowv[4 * threadIdx.x] + rowv[4 * threadIdx.x + 1]) + rowv[4 * threadIdx.x + 2]) +
-               rowv[4 * threadIdx.x + 3];
-    s = wave_sum(s);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = s;
+  kpp_block_sum(rowv, bsum);
+}
+
+// Pass t > 0 over the copy: the block's rows are sifted first, four at a time by each group of 16
+// lanes, and those that remain are measured by all groups.
+template <typename T>
+__global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const int8_t* __restrict__ Xq,
+                                                  const KppMeta* __restrict__ meta, int64_t n, int d,
+                                                  const int32_t* __restrict__ idx, int t, double* __restrict__ D2,
+                                                  double* __restrict__ bsum) {
+  constexpr int U = 4;
+  __shared__ double rowv[kKppRows];
+  __shared__ int32_t list[kKppRows];
+  __shared__ int32_t left;
+  if (threadIdx.x == 0) left = 0;
+  __syncthreads();
+  const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * kKppRows;
+  const int64_t ci = idx[t];
+  const KppMeta cm = meta[ci];
+  const int64_t rb = kpp_row_bytes(d);
+  const int qv = (int)(rb / 16);
+  const int8_t* cq = Xq + ci * rb;
+  for (int q = 0; q < kKppRows / 16; q += U) {
+    const int mine = (q + (lane & (U - 1))) * 16 + grp;  // the row this lane decides on
+    const int64_t im = r0 + mine;
+    KppMeta xm = cm;
+    double old = 0.0;
+    if (im < n) {
+      xm = meta[im];
+      old = D2[im];
+    }
+    int acc[U] = {0, 0, 0, 0};
+    for (int v = lane; v < qv; v += 16) {
+      const i32x4 c = *reinterpret_cast<const i32x4*>(cq + v * 16);
+      i32x4 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = r0 + (q + u) * 16 + grp;
+        x[u] = *reinterpret_cast<const i32x4*>(Xq + (i < n ? i : ci) * rb + v * 16);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int z = 0; z < 4; ++z) acc[u] = __builtin_amdgcn_sdot4(x[u][z], c[z], acc[u], false);
+    }
+    int P = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int a = row16_sum(acc[u]);
+      P = (lane & (U - 1)) == u ? a : P;
+    }
+    if (lane < U) {
+      rowv[mine] = old;  // 0 past the last row
+      if (im < n && !kpp_far(xm, cm, P, old)) list[atomicAdd(&left, 1)] = mine;
+    }
   }
+  __syncthreads();
+  const int cnt = left;
+  const T* c = X + ci * d;
+  for (int q = grp; q < cnt; q += 16) {
+    const int lr = list[q];
+    const double s = kpp_dist(X + (r0 + lr) * d, c, d, lane);
+    if (lane == 0) {
+      const double old = rowv[lr];
+      const double v = old < s ? old : s;
+      D2[r0 + lr] = v;
+      rowv[lr] = v;
+    }
+  }
+  __syncthreads();
+  kpp_block_sum(rowv, bsum);
 }
 
 // Picks centre t: the first row whose running D^2 sum exceeds u[t] * total (lowest unchosen row
@@ -393,8 +578,9 @@ __global__ void __launch_bounds__(1024) k_kpp_select(const double* __restrict__ 
                                                      const double* __restrict__ bsum, int nb,
                                                      const double* __restrict__ u, int t,
                                                      int32_t* __restrict__ idx) {
-  __shared__ double sh[17];
+  __shared__ double sh[17], rowd[kKppRows], before;
   __shared__ int32_t pick;
+  __shared__ int who, block;
   const int per = (nb + 1023) / 1024;
   const int b0 = threadIdx.x * per;
   double s = 0.0;
@@ -406,31 +592,42 @@ __global__ void __launch_bounds__(1024) k_kpp_select(const double* __restrict__ 
   __syncthreads();
   if (S > 0.0) {
     const double target = u[t] * S;
-    // the thread whose run of blocks crosses the target walks its rows in order
-    if (ex <= target && target < ex + s) {
+    // the first thread whose run of blocks crosses the target finds the block, all threads fetch
+    // its rows, and one walks them in order (a trip to memory for each row took 20 us, now 7)
+    if (threadIdx.x == 0) who = INT_MAX;
+    __syncthreads();
+    if (ex <= target && target < ex + s) atomicMin(&who, (int)threadIdx.x);
+    __syncthreads();
+    if ((int)threadIdx.x == who) {
       double P = ex;
-      int32_t found = -1;
-      for (int q = 0; q < per && found < 0; ++q) {
-        const int b = b0 + q;
-        if (b >= nb) break;
-        if (P + bsum[b] <= target) {
-          P += bsum[b];
-          continue;
-        }
-        const int64_t r1 = ((int64_t)b + 1) * kKppRows < n ? ((int64_t)b + 1) * kKppRows : n;
-        for (int64_t i = (int64_t)b * kKppRows; i < r1; ++i) {
-          P += D2[i];
-          if (P > target) {
-            found = (int32_t)i;
-            break;
+      int b = b0;
+      while (b + 1 < nb && b + 1 < b0 + per && P + bsum[b] <= target) P += bsum[b++];
+      block = b;
+      before = P;
+    }
+    __syncthreads();
+    if (who != INT_MAX) {
+      const int64_t first = (int64_t)block * kKppRows;
+      if (threadIdx.x < kKppRows) rowd[threadIdx.x] = first + threadIdx.x < n ? D2[first + threadIdx.x] : 0.0;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double P = before;
+        int found = -1;
+        for (int i = 0; i < kKppRows && found < 0; i += 8) {
+          double v[8];
+#pragma unroll
+          for (int z = 0; z < 8; ++z) v[z] = rowd[i + z];
+#pragma unroll
+          for (int z = 0; z < 8; ++z) {
+            P += v[z];
+            if (found < 0 && P > target) found = i + z;
           }
         }
-        if (found < 0) {  // rounding left the crossing just past this block: take its last
-          for (int64_t i = r1 - 1; i >= (int64_t)b * kKppRows; --i)  // row with D2 > 0
-            if (D2[i] > 0.0) { found = (int32_t)i; break; }
-        }
+        // rounding left the crossing just past this block: take its last row with D2 > 0
+        for (int i = kKppRows - 1; i >= 0 && found < 0; --i)
+          if (rowd[i] > 0.0) found = i;
+        if (found >= 0) pick = (int32_t)(first + found);
       }
-      pick = found;
     }
     __syncthreads();
     if (threadIdx.x == 0 && pick < 0) {  // target beyond the rounded total: last row with D2 > 0
@@ -718,6 +915,17 @@ int launch_update(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t 
 
 size_t update_ws_bytes(int64_t n, int32_t d, int32_t K) { return update_scratch(n, d, K); }
 
+// The seeding's 8-bit copy pays where a pass over X is a trip to memory, and the copy is read at
+// least twice.  Below 32 MB a pass over X runs out of the caches and the copy's first pass costs more.
+static bool kpp_copies(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
+  return K >= 4 && n * d * (int64_t)dtype_size(dt) >= (int64_t(32) << 20);
+}
+
+// What a fit needs, and the 8-bit copy on top of it (a fit in a smaller workspace goes without).
+size_t fit_ws_copy_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
+  return kpp_copies(n, d, K, dt) ? (size_t)n * (kpp_row_bytes(d) + sizeof(KppMeta)) + 512 : 0;
+}
+
 size_t fit_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
   Workspace ws(nullptr, 0);
   ws.take<double>((size_t)K * d);           // sums
@@ -750,9 +958,27 @@ static int fit_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t n_iter, co
   const bool same = sizeof(T) == sizeof(float);  // fp32 data assigns against C itself
   const T* Cuse = same ? reinterpret_cast<const T*>(C) : Cd;
   if (u) {
+    // the copy lies past everything else in the workspace
+    int8_t* Xq = nullptr;
+    KppMeta* meta = nullptr;
+    if (fit_ws_copy_bytes(n, d, K, DT<T>::id) > 0) {
+      Workspace w(ws.base, ws.cap);
+      w.off = fit_ws_bytes(n, d, K, DT<T>::id);
+      Xq = w.take<int8_t>((size_t)n * kpp_row_bytes(d));
+      meta = w.take<KppMeta>(n);
+      if (!w.fits()) Xq = nullptr;
+    }
     HMOE_LAUNCH("kmeans++ first", k_kpp_first, dim3(1), dim3(64), 0, st, u, n, idx);
     for (int t = 0; t < K; ++t) {
-      HMOE_LAUNCH("kmeans++ D2", k_kpp_update<T>, dim3((unsigned)nb), dim3(256), 0, st, X, n, d, idx, t, D2, bsum);
+      if (Xq && t == 0)
+        HMOE_LAUNCH("kmeans++ D2", (k_kpp_update<T, true>), dim3((unsigned)nb), dim3(256), 0, st, X, n, d, idx, t, D2,
+                    bsum, Xq, meta);
+      else if (Xq)
+        HMOE_LAUNCH("kmeans++ D2", k_kpp_sift<T>, dim3((unsigned)nb), dim3(256), 0, st, X, (const int8_t*)Xq,
+                    (const KppMeta*)meta, n, d, idx, t, D2, bsum);
+      else
+        HMOE_LAUNCH("kmeans++ D2", (k_kpp_update<T, false>), dim3((unsigned)nb), dim3(256), 0, st, X, n, d, idx, t, D2,
+                    bsum, (int8_t*)nullptr, (KppMeta*)nullptr);
       if (t + 1 < K) {
         HMOE_LAUNCH("kmeans++ select", k_kpp_select, dim3(1), dim3(1024), 0, st, D2, n, bsum, nb, u, t + 1, idx);
       }
