@@ -52,6 +52,9 @@ struct Cfg {
 // fp32 GEMMs and narrow problems: 128 x 128 tiles, four waves of 64 x 64.
 template <typename T>
 using CfgSmall = Cfg<T, 128, 128, 64, 64>;
+// Problems of few tiles: a quarter of the tile, two waves of 32 x 64.
+template <typename T>
+using CfgQuarter = Cfg<T, 64, 64, 32, 64>;
 // Few columns (the gater's assignment with K <= 64 centres): 256 x 64 tiles, four waves of
 // 64 x 64 stacked along the rows, so no MFMA work is spent on absent centres.
 template <typename T>

@@ -164,4 +164,50 @@ inline bool sym_eigen(std::vector<double>& A, int n, std::vector<double>& w, std
   return hi <= 0;
 }
 
+// The QR steps of sym_eigen on the tridiagonal matrix alone (diagonal d, off-diagonal e, n entries
+// each; on return d holds the eigenvalues): every rotation of rows (k, k + 1) goes to
+// rotate(k, c, s), in order, and sweep(lo, hi) precedes those of a step (k = lo .. hi - 1).  The
+// rows of the identity, so rotated, are the eigenvectors.  False when the steps have not deflated
+// every entry within max_steps.
+template <class Sweep, class Rotate>
+inline bool tridiag_eigen(std::vector<double>& d, std::vector<double>& e, int n, Sweep sweep, Rotate rotate,
+                          int max_steps = -1) {
+  if (max_steps < 0) max_steps = 60 * n;
+  const double eps = 2.220446049250313e-16;
+  int hi = n - 1;
+  for (int guard = 0; hi > 0 && guard < max_steps;) {
+    if (fabs(e[hi - 1]) <= eps * (fabs(d[hi - 1]) + fabs(d[hi]))) {
+      e[hi - 1] = 0.0;
+      --hi;
+      continue;
+    }
+    int lo = hi - 1;
+    while (lo > 0 && fabs(e[lo - 1]) > eps * (fabs(d[lo - 1]) + fabs(d[lo]))) --lo;
+    ++guard;
+    sweep(lo, hi);
+    const double half = 0.5 * (d[hi - 1] - d[hi]);
+    const double eb = e[hi - 1];
+    const double mu = d[hi] - eb * eb / (half + (half >= 0.0 ? 1.0 : -1.0) * hypot(half, eb));
+    double x = d[lo] - mu, z = e[lo];
+    for (int k = lo; k < hi; ++k) {
+      const double r = sqrt(x * x + z * z);  // entries of an fp32 matrix: no overflow
+      const double ri = r == 0.0 ? 0.0 : 1.0 / r;
+      const double c = r == 0.0 ? 1.0 : x * ri, s = -z * ri;
+      if (k > lo) e[k - 1] = r;
+      const double ak = d[k], bk = d[k + 1], f = e[k];
+      d[k] = c * c * ak - 2.0 * c * s * f + s * s * bk;
+      d[k + 1] = s * s * ak + 2.0 * c * s * f + c * c * bk;
+      e[k] = c * s * (ak - bk) + (c * c - s * s) * f;
+      if (k + 1 < hi) {
+        const double g = e[k + 1];
+        z = -s * g;
+        e[k + 1] = c * g;
+      }
+      x = e[k];
+      rotate(k, c, s);
+    }
+  }
+  return hi <= 0;
+}
+
 }  // namespace hmoe

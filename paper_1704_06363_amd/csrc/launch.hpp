@@ -21,7 +21,9 @@ template <typename T>
 int launch_gemm_tn(const T* A, const T* B, int64_t rows, int M, int N, float* out, Workspace& ws, hipStream_t st,
                    const char* label = "gemm tn");
 template <typename T>
-int launch_gemm_nn(const T* A, const T* W, int64_t rows, int Kd, int N, T* out, Workspace& ws, hipStream_t st);
+int launch_gemm_nn(const T* A, const T* W, int64_t rows, int Kd, int N, T* out, hipStream_t st);
+template <typename T>
+int launch_gram(const T* A, int64_t rows, int M, float* out, Workspace& ws, hipStream_t st, const char* label);
 size_t pca_fit_ws(int64_t n, int d, int r, hmoe_dtype_t dt);
 size_t pca_project_ws(int d, int r, hmoe_dtype_t dt);
 int launch_pca_fit(const void* X, hmoe_dtype_t dt, int64_t n, int d, int r, int n_iter, uint64_t seed, float* mean,

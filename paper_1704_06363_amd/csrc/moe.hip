@@ -916,16 +916,44 @@ __global__ void __launch_bounds__(C::THREADS)
 // tiles are split over K instead: tiles b < t_full run whole, tile t_full + r (r < R) is computed
 // as `split` K-chunks of `chunk` rows (work items t_full + r * split + c, every chunk non-empty)
 // whose fp32 partials go to part[r * split + c] and are added in chunk order by k_split_reduce.
+// SYM (A = B, M = N): only the tiles on and below the diagonal, numbered row by row.
 constexpr int kMaxSplitItems = 512;
 
-template <class C>
+template <class C, bool SYM>
+__device__ __host__ __forceinline__ int64_t tn_tiles(int M, int N) {
+  const int64_t mt = cdiv(M, C::BM);
+  return SYM ? mt * (mt + 1) / 2 : mt * cdiv(N, C::BN);
+}
+template <class C, bool SYM>
+__device__ __forceinline__ TileCoord tn_tile_at(int M, int N, int rows, int64_t t) {
+  if constexpr (SYM) {
+    static_assert(C::BM == C::BN, "square tiles");
+    int mi = 0;
+    while ((int64_t)(mi + 1) * (mi + 2) / 2 <= t) ++mi;
+    const int ni = (int)(t - (int64_t)mi * (mi + 1) / 2);
+    TileCoord tc;
+    tc.group = 0;
+    tc.m0 = (int64_t)mi * C::BM;
+    tc.n0 = ni * C::BN;
+    tc.m_rows = (int)(M - tc.m0 < C::BM ? M - tc.m0 : C::BM);
+    tc.n_cols = N - tc.n0 < C::BN ? N - tc.n0 : C::BN;
+    tc.k0 = 0;
+    tc.k_len = rows;
+    tc.valid = tc.m_rows > 0;
+    return tc;
+  } else {
+    return tile_plain_at<C>(M, N, rows, t);
+  }
+}
+
+template <class C, bool SYM>
 __global__ void __launch_bounds__(C::THREADS)
     k_gemm_tn_split(const typename C::type* __restrict__ A, const typename C::type* __restrict__ B, int64_t rows,
                     int M, int N, float* __restrict__ out, int64_t t_full, int split, int64_t chunk,
                     float* __restrict__ part, int64_t a_sstride, int a_sw) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds<char>* smem = (lds<char>*)smem_raw;
-  const int64_t T = cdiv(M, C::BM) * cdiv(N, C::BN);
+  const int64_t T = tn_tiles<C, SYM>(M, N);
   const int64_t b = blockIdx.x;
   // A's columns m0 .. of a tile: row-major (ld M), or slab-major (a_sw > 0: a tile lies in one
   // slab of a_sw columns, rows a_sw apart)
@@ -933,7 +961,7 @@ __global__ void __launch_bounds__(C::THREADS)
   const int64_t lda = a_sw ? a_sw : M;
   floatx4 acc[C::MI][C::NJ];
   if (b < t_full) {
-    const TileCoord tc = tile_plain_at<C>(M, N, (int)rows, b);
+    const TileCoord tc = tn_tile_at<C, SYM>(M, N, (int)rows, b);
     if (!tc.valid) return;
     gemm_tile<C, false, false>(a_at(tc.m0), lda, tc.m_rows, B + tc.n0, N, tc.n_cols, (int)rows, smem, acc);
     store_out<C, float>(tc, acc, smem, out, N, Ident{}, RowId{tc.m0}, NoVec{});
@@ -943,7 +971,7 @@ __global__ void __launch_bounds__(C::THREADS)
   const int64_t t = t_full + q / split;
   if (t >= T) return;
   const int c = (int)(q % split);
-  const TileCoord tc = tile_plain_at<C>(M, N, (int)rows, t);
+  const TileCoord tc = tn_tile_at<C, SYM>(M, N, (int)rows, t);
   const int64_t k0 = c * chunk;
   const int klen = (int)(rows - k0 < chunk ? rows - k0 : chunk);
   gemm_tile<C, false, false>(a_at(tc.m0) + k0 * lda, lda, tc.m_rows, B + tc.n0 + k0 * N, N, tc.n_cols, klen, smem,
@@ -954,7 +982,7 @@ __global__ void __launch_bounds__(C::THREADS)
   store_out<C, float>(lt, acc, smem, part + q * (int64_t)(C::BM * C::BN), C::BN, Ident{}, RowId{0}, NoVec{});
 }
 
-template <class C>
+template <class C, bool SYM>
 __global__ void __launch_bounds__(256) k_split_reduce(const float* __restrict__ part, int64_t rows, int M, int N,
                                                       int64_t t_full, int split, int R, float* __restrict__ out) {
   constexpr int TE = C::BM * C::BN;
@@ -962,7 +990,7 @@ __global__ void __launch_bounds__(256) k_split_reduce(const float* __restrict__ 
   if (idx >= (int64_t)R * TE) return;
   const int r = (int)(idx / TE), e = (int)(idx % TE);
   const int i = e / C::BN, j = e % C::BN;
-  const TileCoord tc = tile_plain_at<C>(M, N, (int)rows, t_full + r);
+  const TileCoord tc = tn_tile_at<C, SYM>(M, N, (int)rows, t_full + r);
   if (i >= tc.m_rows || j >= tc.n_cols) return;
   float s = 0.f;
   for (int c = 0; c < split; ++c) s += part[((int64_t)r * split + c) * TE + e];
@@ -971,12 +999,12 @@ __global__ void __launch_bounds__(256) k_split_reduce(const float* __restrict__ 
 
 // Launches k_gemm_tn_split (and its reduction) for out = A^T B; `part` holds kMaxSplitItems
 // tiles of fp32 partials.  rows > 0.  a_sw > 0: A is slab-major (see k_gemm_tn_split).
-template <class C>
+template <class C, bool SYM = false>
 static int launch_tn_split(const char* label, const typename C::type* A, const typename C::type* B, int64_t rows,
                            int M, int N, float* out, float* part, hipStream_t st, int64_t a_sstride = 0,
                            int a_sw = 0) {
   // rounds of `slots` concurrent tiles (one workgroup per 160 KB of LDS per CU)
-  const int64_t tiles = cdiv(M, C::BM) * cdiv(N, C::BN);
+  const int64_t tiles = tn_tiles<C, SYM>(M, N);
   int64_t slots = (int64_t)device_cus() * ((160 * 1024) / C::LDS);
   if (slots > kMaxSplitItems) slots = kMaxSplitItems;
   const int64_t R = tiles % slots;
@@ -987,10 +1015,10 @@ static int launch_tn_split(const char* label, const typename C::type* A, const t
   int64_t chunk = cdiv(cdiv(rows, split), 64) * 64;
   if (chunk < 256) chunk = 256;
   split = (int)cdiv(rows, chunk);
-  HMOE_LAUNCH(label, k_gemm_tn_split<C>, dim3((unsigned)(t_full + R * split)), dim3(C::THREADS), C::LDS, st, A, B,
+  HMOE_LAUNCH(label, (k_gemm_tn_split<C, SYM>), dim3((unsigned)(t_full + R * split)), dim3(C::THREADS), C::LDS, st, A, B,
               rows, M, N, out, t_full, split, chunk, part, a_sstride, a_sw);
   if (R > 0)
-    HMOE_LAUNCH("split-K reduce", k_split_reduce<C>, dim3((unsigned)cdiv(R * C::BM * C::BN, 256)), dim3(256), 0, st,
+    HMOE_LAUNCH("split-K reduce", (k_split_reduce<C, SYM>), dim3((unsigned)cdiv(R * C::BM * C::BN, 256)), dim3(256), 0, st,
                 (const float*)part, rows, M, N, t_full, split, (int)R, out);
   return HMOE_OK;
 }
@@ -1295,12 +1323,18 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
 
 // ------------------------------------------------------------------ plain products (the PCA)
 
-// seg = {0, rows}: one group for the grouped kernels below.
-static __global__ void k_seg_one(int32_t* __restrict__ seg, int64_t rows) {
-  if (threadIdx.x == 0) {
-    seg[0] = 0;
-    seg[1] = (int32_t)rows;
-  }
+// out [rows][N] = A W (A [rows][Kd], W [Kd][N]).
+template <class C>
+__global__ void __launch_bounds__(C::THREADS)
+    k_gemm_nn(const typename C::type* __restrict__ A, const typename C::type* __restrict__ W, int64_t rows, int Kd,
+              int N, typename C::type* __restrict__ out) {
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  lds<char>* smem = (lds<char>*)smem_raw;
+  const TileCoord tc = tile_plain<C>(rows, N, Kd);
+  if (!tc.valid) return;
+  floatx4 acc[C::MI][C::NJ];
+  gemm_tile<C, true, false>(A + tc.m0 * Kd, Kd, tc.m_rows, W + tc.n0, N, tc.n_cols, Kd, smem, acc);
+  store_out<C, typename C::type>(tc, acc, smem, out, N, Ident{}, RowId{tc.m0}, NoVec{});
 }
 
 // out [M][N] fp32 = A^T B over `rows` rows (A [rows][M], B [rows][N]), split over K when the
@@ -1318,31 +1352,52 @@ int launch_gemm_tn(const T* A, const T* B, int64_t rows, int M, int N, float* ou
   float* part = ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   if (!ws.fits()) return HMOE_EWORKSPACE;
   if (rows <= 0) return launch_zero_f32(out, (int64_t)M * N, st);
+  if constexpr (sizeof(T) == 4) {
+    // a short reduction over few tiles (the PCA's Gram matrices: 4 tiles, two chunks): quarter
+    // tiles in the same chunks, so the same sums
+    if (rows <= 4096 && cdiv(M, C::BM) * cdiv(N, C::BN) * cdiv(rows, 256) < device_cus())
+      return launch_tn_split<CfgQuarter<T>>(label, A, B, rows, M, N, out, part, st);
+  }
   return launch_tn_split<C>(label, A, B, rows, M, N, out, part, st);
 }
 
-// out [rows][N] = A W (A [rows][Kd], W [Kd][N]), in the data dtype: the row-grouped kernel with
-// a single group.
+// The lower triangle (whole tiles) of out [M][M] fp32 = A^T A.
 template <typename T>
-int launch_gemm_nn(const T* A, const T* W, int64_t rows, int Kd, int N, T* out, Workspace& ws, hipStream_t st) {
+int launch_gram(const T* A, int64_t rows, int M, float* out, Workspace& ws, hipStream_t st, const char* label) {
   using C = typename Pick<T>::CK;
-  int32_t* seg = ws.take<int32_t>(2);
-  int32_t* ts = ws.take<int32_t>(2);
+  float* part = ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   if (!ws.fits()) return HMOE_EWORKSPACE;
-  HMOE_LAUNCH("one segment", k_seg_one, dim3(1), dim3(64), 0, st, seg, rows);
-  HMOE_TRY(launch_seg_tiles(seg, 1, C::BM, ts, st));
-  HMOE_LAUNCH("gemm nn", (k_expert_dgrad<C, false>), dim3((unsigned)((cdiv(rows, C::BM) + 1) * cdiv(N, C::BN))),
-              dim3(C::THREADS), C::LDS, st, A, W, seg, ts, 1, N, Kd, (const T*)nullptr, (const int32_t*)nullptr, out);
+  if (rows <= 0) return launch_zero_f32(out, (int64_t)M * M, st);
+  return launch_tn_split<C, true>(label, A, A, rows, M, M, out, part, st);
+}
+
+// out [rows][N] = A W (A [rows][Kd], W [Kd][N]), in the data dtype.  Fewer tiles than CUs (the
+// PCA's d x d x r products, 8 of them): a quarter of the tile, four times the workgroups; an
+// element's sum runs in the same order (512 x 256 x 512 fp32: 34 us with a segment table built
+// for each product, 20 now).
+template <typename T>
+int launch_gemm_nn(const T* A, const T* W, int64_t rows, int Kd, int N, T* out, hipStream_t st) {
+  static_assert(sizeof(T) == 4, "fp32 products");
+  using C = typename Pick<T>::CK;
+  using S = CfgQuarter<T>;
+  if (cdiv(rows, C::BM) * cdiv(N, C::BN) < device_cus())
+    HMOE_LAUNCH("gemm nn", k_gemm_nn<S>, dim3((unsigned)(cdiv(rows, S::BM) * cdiv(N, S::BN))), dim3(S::THREADS),
+                S::LDS, st, A, W, rows, Kd, N, out);
+  else
+    HMOE_LAUNCH("gemm nn", k_gemm_nn<C>, dim3((unsigned)(cdiv(rows, C::BM) * cdiv(N, C::BN))), dim3(C::THREADS),
+                C::LDS, st, A, W, rows, Kd, N, out);
   return HMOE_OK;
 }
 
+template int launch_gram<float>(const float*, int64_t, int, float*, Workspace&, hipStream_t, const char*);
+template int launch_gram<bf16>(const bf16*, int64_t, int, float*, Workspace&, hipStream_t, const char*);
 template size_t gemm_tn_ws<float>();
 template size_t gemm_tn_ws<bf16>();
 template int launch_gemm_tn<float>(const float*, const float*, int64_t, int, int, float*, Workspace&, hipStream_t,
                                    const char*);
 template int launch_gemm_tn<bf16>(const bf16*, const bf16*, int64_t, int, int, float*, Workspace&, hipStream_t,
                                   const char*);
-template int launch_gemm_nn<float>(const float*, const float*, int64_t, int, int, float*, Workspace&, hipStream_t);
+template int launch_gemm_nn<float>(const float*, const float*, int64_t, int, int, float*, hipStream_t);
 
 int launch_moe_forward(const hmoe_moe_params_t* p, int64_t n, const void* Xs, const int32_t* offsets,
                        const int32_t* perm, const hmoe_labels_t* y, void* H1s, void* H, void* logits, float* anc,

@@ -2,12 +2,13 @@
 // to their first 256 principal directions before the clustering).
 //
 // Fit: the sample mean (fp64 column sums), the covariance C = (X^T X - n m m^T) / (n - 1) with
-// X^T X on the tile engines (fp32 accumulation, the correction in fp64), and the r leading
-// eigenpairs of C by subspace iteration: Q <- orth(C Q), n_iter times from a seeded start, then
-// Rayleigh-Ritz (the eigenpairs of Q^T C Q, rotated back by Q).  The d x d x r and d x r x r
-// products run on the GPU; the r x r steps -- the Cholesky factor behind each orthonormalisation
-// (CholeskyQR) and the final symmetric eigensolve (Householder tridiagonalisation and implicit
-// QR steps) -- run on the host in fp64, so a fit synchronises its stream.
+// the lower triangle of X^T X on the tile engines (fp32 accumulation, the correction in fp64), and
+// the r leading eigenpairs of C by subspace iteration: Q <- orth(C Q), n_iter times from a seeded
+// start, then Rayleigh-Ritz (the eigenpairs of Q^T C Q, rotated back by Q).  The r x r steps -- the
+// Cholesky factor behind each orthonormalisation (CholeskyQR) and the final symmetric eigensolve
+// (Householder tridiagonalisation and implicit QR steps) -- are in fp64: for r <= kSmallN on the GPU
+// but for the QR steps' scalars, for larger r, and where the block loses rank, on the host.  A fit
+// synchronises its stream.
 // Projection: Z = (X - m) U^T on the tile engine, the mean folded into an fp32 column bias.
 #include <math.h>
 
@@ -18,6 +19,7 @@
 #include "host_linalg.hpp"
 #include "launch.hpp"
 #include "primitives.hpp"
+#include "small_linalg.hpp"
 
 namespace hmoe {
 
@@ -28,14 +30,18 @@ static __global__ void k_pca_seg(int32_t* __restrict__ seg, int64_t rows) {
   }
 }
 
-// C = (C - s s^T / n) / (n - 1) in place (C holds X^T X, s the fp64 column sums), mean = s / n.
+// C = (C - s s^T / n) / (n - 1) in place (C holds X^T X on and below the diagonal, s the fp64 column
+// sums), both triangles; mean = s / n.
 static __global__ void __launch_bounds__(256) k_cov_finalize(float* __restrict__ C, const double* __restrict__ s,
                                                              int64_t n, int d, float* __restrict__ mean) {
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q < d) mean[q] = (float)(s[q] / (double)n);
   if (q >= (int64_t)d * d) return;
   const int i = (int)(q / d), j = (int)(q % d);
-  C[q] = (float)(((double)C[q] - s[i] * s[j] / (double)n) / (double)(n - 1));
+  if (j > i) return;
+  const float c = (float)(((double)C[q] - s[i] * s[j] / (double)n) / (double)(n - 1));
+  C[q] = c;
+  C[(int64_t)j * d + i] = c;
 }
 
 // A seeded start for the subspace iteration: uniform in [-1, 1) from SplitMix64 of seed + index.
@@ -159,9 +165,9 @@ static int h2d(void* dst, const void* src, size_t bytes, hipStream_t st) {
 // eigenpairs (w_j, v_j) of Q^T Q -- column j = Q v_j / sqrt(w_j) where w_j stays above that
 // level, a fresh seeded random column where it does not -- and the passes start again.  The
 // kept columns span what Q determined; the fresh ones lie outside it with probability 1.
+constexpr double kRank = 1e-9;
 static int orthonormalise(float*& Q, float*& Z, int d, int r, float* S, float* Rinv, int passes, uint64_t seed,
                           Workspace& ws, hipStream_t st) {
-  constexpr double kRank = 1e-9;
   std::vector<float> hs((size_t)r * r);
   std::vector<double> Sd((size_t)r * r), Ri;
   int refills = 0;
@@ -190,7 +196,7 @@ static int orthonormalise(float*& Q, float*& Z, int d, int r, float* S, float* R
         flags[j] = keep ? 0 : 1;
       }
       HMOE_TRY(h2d(Rinv, hs.data(), hs.size() * sizeof(float), st));
-      HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, ws, st));
+      HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, st));
       ws.off = mark;
       HMOE_TRY(h2d(S, flags.data(), flags.size() * sizeof(int32_t), st));  // S is free until the next pass
       HMOE_LAUNCH("pca refill", k_pca_refill, dim3((unsigned)cdiv((int64_t)d * r, 256)), dim3(256), 0, st, Z, d, r,
@@ -201,10 +207,93 @@ static int orthonormalise(float*& Q, float*& Z, int d, int r, float* S, float* R
     }
     for (size_t i = 0; i < hs.size(); ++i) hs[i] = (float)Ri[i];
     HMOE_TRY(h2d(Rinv, hs.data(), hs.size() * sizeof(float), st));
-    HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, ws, st));
+    HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, st));
     ws.off = mark;
     std::swap(Q, Z);
   }
+  return HMOE_OK;
+}
+
+// The fp64 scratch of the r x r steps on the GPU, over the products' partial sums: free whenever one
+// of them runs (gemm_tn_ws() of either type holds it).
+struct SmallBufs {
+  double *U, *dinv, *W, *de;  // kSmallN^2, kSmallN, kSmallN^2, 2 kSmallN
+  SmallRot* rot;              // kRotGroups groups
+  int32_t *k0, *order;
+  static constexpr int kRotGroups = 16384;
+  explicit SmallBufs(Workspace ws)
+      : U(ws.take<double>(kSmallN * kSmallN)), dinv(ws.take<double>(kSmallN)), W(ws.take<double>(kSmallN * kSmallN)),
+        de(ws.take<double>(2 * kSmallN)), rot(ws.take<SmallRot>((size_t)kRotGroups * kRotGroup)),
+        k0(ws.take<int32_t>(kRotGroups)), order(ws.take<int32_t>(kSmallN)), fits(ws.fits()) {}
+  bool fits;
+};
+
+// orthonormalise() without a trip to the host, r <= kSmallN: a block that loses rank sets *flag
+// (and leaves Q undefined).  r = 256, d = 512: 0.35 ms a pass (1.0 with the factor and the inverse on the host).
+static int orthonormalise_gpu(float*& Q, float*& Z, int d, int r, float* S, float* Rinv, int passes, int32_t* flag,
+                              Workspace& ws, hipStream_t st) {
+  const SmallBufs b(ws);
+  if (!b.fits) return HMOE_EWORKSPACE;
+  for (int pass = 0; pass < passes; ++pass) {
+    const size_t mark = ws.off;
+    HMOE_TRY(launch_gemm_tn<float>(Q, Q, d, r, r, S, ws, st));
+    ws.off = mark;
+    HMOE_LAUNCH("pca cholesky", k_small_chol, dim3(1), dim3(1024), 0, st, (const float*)S, r, kRank, b.U, b.dinv, flag);
+    HMOE_LAUNCH("pca triangular inverse", k_small_tri_inverse, dim3((unsigned)cdiv(r, 4)), dim3(256), 0, st,
+                (const double*)b.U, (const double*)b.dinv, r, Rinv);
+    HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, st));
+    std::swap(Q, Z);
+  }
+  return HMOE_OK;
+}
+
+// The eigenvectors of (S + S^T) / 2, r <= kSmallN, as the columns of V (fp32, r x r) in decreasing
+// order of their eigenvalues, which go to eigvals.  r = 256: 3.9 ms, 0.8 of it on the host (16 ms there).
+static int ritz_gpu(const float* S, int r, float* V, float* eigvals, Workspace& ws, hipStream_t st) {
+  const SmallBufs b(ws);
+  if (!b.fits) return HMOE_EWORKSPACE;
+  HMOE_LAUNCH("pca tridiagonal", k_small_tridiag, dim3(1), dim3(1024), 0, st, S, r, b.U, b.de);
+  std::vector<double> de(2 * kSmallN);
+  HMOE_TRY(d2h(de.data(), b.de, de.size() * sizeof(double), st));
+  std::vector<double> d(de.begin(), de.begin() + r), e(r, 0.0);
+  for (int i = 0; i + 1 < r; ++i) e[i] = de[kSmallN + i];
+  std::vector<SmallRot> rot;
+  std::vector<int32_t> k0;
+  rot.reserve((size_t)r * r * 2);
+  const auto close = [&] { rot.resize(k0.size() * kRotGroup, SmallRot{1.0, 0.0}); };
+  const bool ok = tridiag_eigen(
+      d, e, r, [&](int, int) { close(); },
+      [&](int k, double c, double s) {
+        if (rot.size() == k0.size() * kRotGroup) k0.push_back(k);
+        rot.push_back(SmallRot{c, s});
+      });
+  if (!ok) {
+    set_error("pca: the eigensolve of the %d x %d Rayleigh-Ritz matrix did not converge", r, r);
+    return HMOE_ENUMERIC;
+  }
+  close();
+  constexpr int kRotLds = (kSmallN + kRotGroup) * 64 * (int)sizeof(double);
+  const size_t groups = k0.size();
+  size_t g = 0;
+  do {
+    const int m = (int)std::min(groups - g, (size_t)SmallBufs::kRotGroups);
+    if (m > 0) {
+      HMOE_TRY(h2d(b.rot, rot.data() + g * kRotGroup, (size_t)m * kRotGroup * sizeof(SmallRot), st));
+      HMOE_TRY(h2d(b.k0, k0.data() + g, (size_t)m * sizeof(int32_t), st));
+    }
+    HMOE_LAUNCH("pca rotations", k_small_rotate, dim3(kSmallN / 64), dim3(64), kRotLds, st, (const SmallRot*)b.rot,
+                (const int32_t*)b.k0, m, r, (int)(g == 0), b.W);
+    g += m;
+  } while (g < groups);
+  std::vector<int32_t> ord(r);
+  for (int i = 0; i < r; ++i) ord[i] = i;
+  std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return d[x] > d[y]; });
+  std::vector<float> hw(r);
+  for (int j = 0; j < r; ++j) hw[j] = (float)d[ord[j]];
+  HMOE_TRY(h2d(b.order, ord.data(), (size_t)r * sizeof(int32_t), st));
+  HMOE_TRY(h2d(eigvals, hw.data(), hw.size() * sizeof(float), st));
+  HMOE_LAUNCH("pca eigenvectors", k_small_back, dim3((unsigned)cdiv(r, 4)), dim3(256), 0, st, (const double*)b.W,
+              (const double*)b.U, (const int32_t*)b.order, r, V);
   return HMOE_OK;
 }
 
@@ -237,27 +326,55 @@ static int pca_fit_t(const T* X, int64_t n, int d, int r, int n_iter, uint64_t s
   HMOE_LAUNCH("pca segment", k_pca_seg, dim3(1), dim3(64), 0, st, seg, n);
   HMOE_TRY(launch_segsum<T, double>(X, d, nullptr, seg, 1, d, n, msum, 0, ws, st));
   ws.off = mark;
-  HMOE_TRY(launch_gemm_tn<T>(X, X, n, d, d, Cv, ws, st, "pca X^T X"));
+  HMOE_TRY(launch_gram<T>(X, n, d, Cv, ws, st, "pca X^T X"));
   ws.off = mark;
   HMOE_LAUNCH("pca covariance", k_cov_finalize, dim3((unsigned)cdiv((int64_t)d * d, 256)), dim3(256), 0, st, Cv, msum,
               n, d, mean);
-  HMOE_LAUNCH("pca start", k_pca_start, dim3((unsigned)cdiv((int64_t)d * r, 256)), dim3(256), 0, st, Q,
-              (int64_t)d * r, seed);
   // one CholeskyQR pass per iteration keeps the subspace; the basis that enters Rayleigh-Ritz
   // gets two
-  HMOE_TRY(orthonormalise(Q, Z, d, r, S, Rinv, n_iter == 0 ? 2 : 1, seed ^ 0xA5A5A5A5u, ws, st));
-  for (int it = 0; it < n_iter; ++it) {
-    HMOE_TRY(launch_gemm_nn<float>(Cv, Q, d, d, r, Z, ws, st));
-    ws.off = mark;
-    std::swap(Q, Z);
-    HMOE_TRY(orthonormalise(Q, Z, d, r, S, Rinv, it == n_iter - 1 ? 2 : 1, seed + 0x9E3779B9u * (uint64_t)(it + 1), ws,
-                            st));
+  const auto iterate = [&](bool gpu, bool& lost) -> int {
+    HMOE_LAUNCH("pca start", k_pca_start, dim3((unsigned)cdiv((int64_t)d * r, 256)), dim3(256), 0, st, Q,
+                (int64_t)d * r, seed);
+    const auto orth = [&](int passes, uint64_t s) {
+      return gpu ? orthonormalise_gpu(Q, Z, d, r, S, Rinv, passes, seg, ws, st)
+                 : orthonormalise(Q, Z, d, r, S, Rinv, passes, s, ws, st);
+    };
+    HMOE_TRY(orth(n_iter == 0 ? 2 : 1, seed ^ 0xA5A5A5A5u));
+    for (int it = 0; it < n_iter; ++it) {
+      HMOE_TRY(launch_gemm_nn<float>(Cv, Q, d, d, r, Z, st));
+      std::swap(Q, Z);
+      HMOE_TRY(orth(it == n_iter - 1 ? 2 : 1, seed + 0x9E3779B9u * (uint64_t)(it + 1)));
+      // a covariance of rank below r shows in the first product
+      if (gpu && (it == 0 || it == n_iter - 1)) {
+        int32_t flag = 0;
+        HMOE_TRY(d2h(&flag, seg, sizeof flag, st));
+        if ((lost = flag != 0)) return HMOE_OK;
+      }
+    }
+    if (gpu && n_iter == 0) {
+      int32_t flag = 0;
+      HMOE_TRY(d2h(&flag, seg, sizeof flag, st));
+      lost = flag != 0;
+    }
+    return HMOE_OK;
+  };
+  bool lost = false;
+  const bool small = r <= kSmallN;
+  if (small) {
+    HMOE_LAUNCH("pca segment", k_pca_seg, dim3(1), dim3(64), 0, st, seg, (int64_t)0);  // seg[0] = 0: the flag
+    HMOE_TRY(iterate(true, lost));
   }
+  if (!small || lost) HMOE_TRY(iterate(false, lost));
   // Rayleigh-Ritz: the eigenpairs of Q^T C Q, sorted by decreasing eigenvalue
-  HMOE_TRY(launch_gemm_nn<float>(Cv, Q, d, d, r, Z, ws, st));
-  ws.off = mark;
+  HMOE_TRY(launch_gemm_nn<float>(Cv, Q, d, d, r, Z, st));
   HMOE_TRY(launch_gemm_tn<float>(Q, Z, d, r, r, S, ws, st));
   ws.off = mark;
+  if (small) {
+    HMOE_TRY(ritz_gpu(S, r, Rinv, eigvals, ws, st));
+    HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, st));
+    HMOE_LAUNCH("pca components", k_pca_comps, dim3((unsigned)r), dim3(256), 0, st, (const float*)Z, d, r, comps);
+    return HMOE_OK;
+  }
   std::vector<float> hs((size_t)r * r);
   HMOE_TRY(d2h(hs.data(), S, hs.size() * sizeof(float), st));
   std::vector<double> Tm((size_t)r * r), w, VT;
@@ -276,8 +393,7 @@ static int pca_fit_t(const T* X, int64_t n, int d, int r, int n_iter, uint64_t s
   for (int j = 0; j < r; ++j) hw[j] = (float)w[ord[j]];
   HMOE_TRY(h2d(Rinv, hs.data(), hs.size() * sizeof(float), st));
   HMOE_TRY(h2d(eigvals, hw.data(), hw.size() * sizeof(float), st));
-  HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, ws, st));
-  ws.off = mark;
+  HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, st));
   HMOE_LAUNCH("pca components", k_pca_comps, dim3((unsigned)r), dim3(256), 0, st, (const float*)Z, d, r, comps);
   return HMOE_OK;
 }

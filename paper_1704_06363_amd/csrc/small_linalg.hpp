@@ -1,0 +1,365 @@
+// small_linalg.hpp -- the r x r steps of the PCA fit on the GPU, in fp64, for r <= 256: the Cholesky
+// factor of a Gram matrix with the inverse behind CholeskyQR, and the symmetric eigensolve's
+// tridiagonalisation and eigenvectors (its scalar QR steps run on the host, host_linalg.hpp).
+// The serial chains of both sit in one workgroup that holds the matrix in registers: thread
+// (ty, tx) of 32 x 32 has the elements (ty + 32 a, tx + 32 b), b <= a, of the lower triangle in
+// 32 x 32 blocks (the diagonal blocks whole), 72 of its 128 registers.
+#pragma once
+#include "common.hpp"
+
+namespace hmoe {
+
+constexpr int kSmallN = 256;  // largest r, and the leading dimension of the fp64 scratch matrices
+constexpr int kSmallB = kSmallN / 32;
+
+// Sums over 16 lanes (DPP rotations) and over a wave (register swaps), without trips through LDS.
+__device__ __forceinline__ double small_pair(double v, uint32_t lo, uint32_t hi) {
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double small_ror(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return small_pair(v, __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true),
+                    __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double small_sum32(double v) {  // over 32 lanes, in each of them
+  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+  v = small_ror<0x128>(v);  // row_ror:8, 4, 2, 1
+  v = small_ror<0x124>(v);
+  v = small_ror<0x122>(v);
+  v = small_ror<0x121>(v);
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const u2v lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  const u2v hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  return small_pair(__builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]), lo[1], hi[1]);
+}
+__device__ __forceinline__ double small_halves(double v) {  // lanes l and l ^ 32
+  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const u2v lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+  const u2v hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  return small_pair(__builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]), lo[1], hi[1]);
+}
+__device__ __forceinline__ double small_sum64(double v) { return small_halves(small_sum32(v)); }
+
+__device__ __forceinline__ double small_lane(double v, int lane) {  // `lane` wave-uniform
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// S (r x r, fp32) + shift I = L L^T, the shift 1e-12 of the mean diagonal: U[k][i] = L[i][k] (fp64,
+// ld kSmallN, 0 for i <= k and past r), dinv[k] = 1 / L[k][k].  A pivot (before its square root)
+// that is not above min_rel_pivot of the largest diagonal entry ends the factorisation and sets
+// *flag.  One workgroup, right-looking, a barrier per column; bound by that chain and by the LDS
+// reads of the column.  r = 256: 216 us.
+static __global__ void __launch_bounds__(1024) k_small_chol(const float* __restrict__ S, int r, double min_rel_pivot,
+                                                            double* __restrict__ U, double* __restrict__ dinv,
+                                                            int32_t* __restrict__ flag) {
+  __shared__ double col[2][kSmallN];
+  __shared__ double s_tr, s_max;
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
+  if (t < 64) {
+    double tr = 0.0, mx = 0.0;
+    for (int i = t; i < r; i += 64) {
+      const double v = (double)S[(int64_t)i * r + i];
+      tr += v;
+      mx = fmax(mx, v);
+    }
+    tr = wave_sum(tr);
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) mx = fmax(mx, shfl_xor(mx, m));
+    if (t == 0) {
+      s_tr = tr;
+      s_max = mx;
+    }
+  }
+  __syncthreads();
+  const double shift = 1e-12 * s_tr / r, least = min_rel_pivot * s_max;
+  double A[kSmallB][kSmallB];
+#pragma unroll
+  for (int a = 0; a < kSmallB; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int i = ty + 32 * a, j = tx + 32 * b;
+      double v = 0.0;
+      if (i < r && j < r) v = (double)S[(int64_t)(i > j ? i : j) * r + (i > j ? j : i)];
+      A[a][b] = i == j ? v + shift : v;
+    }
+#pragma unroll
+  for (int kb = 0; kb < kSmallB; ++kb)
+    for (int kr = 0; kr < 32; ++kr) {
+      const int k = 32 * kb + kr;
+      if (k >= r) return;
+      double* c = col[k & 1];
+      if (tx == kr) {
+#pragma unroll
+        for (int a = kb; a < kSmallB; ++a) c[ty + 32 * a] = A[a][kb];
+      }
+      __syncthreads();  // the other buffer's readers are one barrier behind at most
+      const double piv = c[k];
+      if (!(piv > 0.0) || !(piv > least)) {
+        if (t == 0) *flag = 1;
+        return;
+      }
+      const double root = sqrt(piv);
+      if (t < kSmallN) U[(int64_t)k * kSmallN + t] = t > k ? c[t] / root : 0.0;
+      if (t == 0) dinv[k] = 1.0 / root;
+      const double w = 1.0 / piv;
+      double cj[kSmallB];
+#pragma unroll
+      for (int b = kb; b < kSmallB; ++b) cj[b] = c[tx + 32 * b];
+#pragma unroll
+      for (int a = kb; a < kSmallB; ++a) {
+        const double ci = -c[ty + 32 * a] * w;
+#pragma unroll
+        for (int b = kb; b <= a; ++b) A[a][b] = fma(ci, cj[b], A[a][b]);
+      }
+    }
+}
+
+// Rinv (fp32, r x r) = R^-1 for R = L^T: its row j is column j of L^-1, by a wave each, lane l
+// holding entries l, l + 64, ... of the forward solve, a column of L at a time.
+static __global__ void __launch_bounds__(256) k_small_tri_inverse(const double* __restrict__ U,
+                                                                  const double* __restrict__ dinv, int r,
+                                                                  float* __restrict__ Rinv) {
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
+  if (j >= r) return;
+  double x[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = l + 64 * q == j ? 1.0 : 0.0;
+#pragma unroll
+  for (int kq = 0; kq < 4; ++kq) {
+    const int k1 = r - 64 * kq < 64 ? r - 64 * kq : 64;
+#pragma unroll 8
+    for (int kl = 0; kl < k1; ++kl) {
+      const int k = 64 * kq + kl;
+      const double xk = small_lane(x[kq], kl) * dinv[k];  // 0 until k = j
+#pragma unroll
+      for (int q = kq; q < 4; ++q) x[q] = fma(-U[(int64_t)k * kSmallN + l + 64 * q], xk, x[q]);
+      if (l == kl) x[kq] = xk;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (l + 64 * q < r) Rinv[(int64_t)j * r + l + 64 * q] = (float)x[q];
+}
+
+// Householder reduction of A = (S + S^T) / 2 (r x r, fp32 in) to tridiagonal form, as sym_eigen in
+// host_linalg.hpp: the reflection of step k is I - u u^T with u in refl[k][k + 1 ..] (zeros before
+// and past r; all zeros where nothing is to be done), the diagonal and off-diagonal in de[0 .. r)
+// and de[kSmallN ..].  One workgroup; a step multiplies the trailing block by u from the lower
+// triangle (row sums over the 32 lanes, column sums over the 16 waves) and updates it.
+// r = 256: 787 us.
+struct TridiagLds {
+  double u[kSmallN], q[kSmallN], row[kSmallN], col[16][kSmallN], half;
+};
+
+// The steps whose column lies in block KB (a constant, so that A stays in registers).
+template <int kb>
+__device__ __forceinline__ void tridiag_block(double (&A)[kSmallB][kSmallB], int r, double* __restrict__ refl,
+                                              double* __restrict__ de, TridiagLds& m) {
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5, w = t >> 6, l = t & 63;
+  for (int kr = 0; kr < 32; ++kr) {
+    const int k = 32 * kb + kr;
+    if (k >= r) return;
+    // column k from the diagonal down
+    if (tx == kr) {
+#pragma unroll
+      for (int a = kb; a < kSmallB; ++a) m.u[ty + 32 * a] = A[a][kb];
+    }
+    __syncthreads();
+    if (t == 0) de[k] = m.u[k];
+    if (k + 1 >= r) continue;
+    // u by the first wave: lane l has entries l, l + 64, ...
+    if (w == 0) {
+      double x[4], s = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = l + 64 * q;
+        x[q] = i > k && i < r ? m.u[i] : 0.0;
+        s += x[q] * x[q];
+      }
+      const double x0 = m.u[k + 1];
+      const double xn = sqrt(small_sum64(s));
+      if (k + 2 >= r) {  // the last off-diagonal entry as it is
+        if (l == 0) de[kSmallN + k] = x0;
+      } else {
+        const double alpha = x0 > 0.0 ? -xn : xn;
+        s = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (l + 64 * q == k + 1) x[q] -= alpha;
+          s += x[q] * x[q];
+        }
+        s = small_sum64(s);
+        const double sc = xn == 0.0 ? 0.0 : sqrt(2.0 / s);
+        if (l == 0) de[kSmallN + k] = xn == 0.0 ? 0.0 : alpha;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = l + 64 * q;
+          const double u = xn == 0.0 ? 0.0 : x[q] * sc;
+          m.u[i] = u;
+          refl[(int64_t)k * kSmallN + i] = u;
+        }
+      }
+    }
+    __syncthreads();
+    if (k + 2 >= r) continue;
+    // p = A u: row sums of the stored blocks, column sums of those below the diagonal
+    double uj[kSmallB], cs[kSmallB];
+#pragma unroll
+    for (int b = kb; b < kSmallB; ++b) {
+      uj[b] = m.u[tx + 32 * b];
+      cs[b] = 0.0;
+    }
+#pragma unroll
+    for (int a = kb; a < kSmallB; ++a) {
+      const double ui = m.u[ty + 32 * a];
+      double rs = 0.0;
+#pragma unroll
+      for (int b = kb; b <= a; ++b) {
+        rs = fma(A[a][b], uj[b], rs);
+        if (b < a) cs[b] = fma(A[a][b], ui, cs[b]);
+      }
+      rs = small_sum32(rs);
+      if (tx == 0) m.row[ty + 32 * a] = rs;
+    }
+#pragma unroll
+    for (int b = kb; b < kSmallB; ++b) {
+      cs[b] = small_halves(cs[b]);  // the wave's two rows ty
+      if (l < 32) m.col[w][tx + 32 * b] = cs[b];
+    }
+    __syncthreads();
+    // q = p - (u . p / 2) u by the first four waves
+    if (t < kSmallN && t >= 32 * kb) {
+      double p = m.row[t];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) p += m.col[v][t];
+      m.q[t] = p;
+    }
+    __syncthreads();
+    if (w == 0) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (l + 64 * q >= 32 * kb) s = fma(m.u[l + 64 * q], m.q[l + 64 * q], s);
+      s = small_sum64(s);
+      if (l == 0) m.half = 0.5 * s;
+    }
+    __syncthreads();
+    const double half = m.half;
+    double qj[kSmallB];
+#pragma unroll
+    for (int b = kb; b < kSmallB; ++b) {
+      uj[b] = m.u[tx + 32 * b];
+      qj[b] = fma(-half, uj[b], m.q[tx + 32 * b]);
+    }
+#pragma unroll
+    for (int a = kb; a < kSmallB; ++a) {
+      const double ui = m.u[ty + 32 * a];
+      const double qi = fma(-half, ui, m.q[ty + 32 * a]);
+#pragma unroll
+      for (int b = kb; b <= a; ++b) A[a][b] = A[a][b] - fma(ui, qj[b], qi * uj[b]);
+    }
+    __syncthreads();  // m.u is rewritten by the next step
+  }
+  if constexpr (kb + 1 < kSmallB) tridiag_block<kb + 1>(A, r, refl, de, m);
+}
+
+static __global__ void __launch_bounds__(1024) k_small_tridiag(const float* __restrict__ S, int r,
+                                                               double* __restrict__ refl, double* __restrict__ de) {
+  __shared__ TridiagLds m;
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
+  double A[kSmallB][kSmallB];
+#pragma unroll
+  for (int a = 0; a < kSmallB; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int i = ty + 32 * a, j = tx + 32 * b;
+      A[a][b] = i < r && j < r ? 0.5 * ((double)S[(int64_t)i * r + j] + (double)S[(int64_t)j * r + i]) : 0.0;
+    }
+  tridiag_block<0>(A, r, refl, de, m);
+}
+
+// A rotation of rows (k, k + 1): row k <- c row k - s row k+1, row k+1 <- s row k + c row k+1.
+struct SmallRot {
+  double c, s;
+};
+constexpr int kRotGroup = 8;  // rotations come in groups of consecutive k, the first k of each in k0
+
+// Applies `groups` groups of rotations to the rows of V ([r][kSmallN], row k of column j at lane
+// j); `first` starts from the identity.  A wave per 64 columns, which sit in LDS; the rows past
+// r absorb the identity rotations that fill a group.
+static __global__ void __launch_bounds__(64) k_small_rotate(const SmallRot* __restrict__ rot,
+                                                            const int32_t* __restrict__ k0, int groups, int r,
+                                                            int first, double* __restrict__ V) {
+  extern __shared__ __attribute__((aligned(16))) char small_smem[];
+  double* v = reinterpret_cast<double*>(small_smem);  // [kSmallN + kRotGroup][64]
+  const int l = threadIdx.x, j = blockIdx.x * 64 + l;
+  for (int k = 0; k < kSmallN + kRotGroup; ++k)
+    v[k * 64 + l] = first ? (k == j ? 1.0 : 0.0) : (k < r ? V[(int64_t)k * kSmallN + j] : 0.0);
+  // the next group's rotations are fetched ahead, as vector loads (the same address in every
+  // lane): scalar ones could only be waited for together with the LDS reads
+  int zero = 0;
+  asm volatile("" : "+v"(zero));
+  rot += zero;
+  k0 += zero;
+  SmallRot nq[kRotGroup];
+#pragma unroll
+  for (int z = 0; z < kRotGroup; ++z) nq[z] = rot[z];
+  int nk = k0[0];
+  for (int g = 0; g < groups; ++g) {
+    SmallRot q[kRotGroup];
+#pragma unroll
+    for (int z = 0; z < kRotGroup; ++z) q[z] = nq[z];
+    double* row = v + nk * 64 + l;
+    double x[kRotGroup + 1];
+#pragma unroll
+    for (int z = 0; z <= kRotGroup; ++z) x[z] = row[z * 64];
+    const int gn = g + 1 < groups ? g + 1 : g;
+#pragma unroll
+    for (int z = 0; z < kRotGroup; ++z) nq[z] = rot[(int64_t)gn * kRotGroup + z];
+    nk = k0[gn];
+#pragma unroll
+    for (int z = 0; z < kRotGroup; ++z) {
+      const double a = x[z], b = x[z + 1];
+      row[z * 64] = q[z].c * a - q[z].s * b;
+      x[z + 1] = q[z].s * a + q[z].c * b;
+    }
+    row[kRotGroup * 64] = x[kRotGroup];
+  }
+  for (int k = 0; k < r; ++k) V[(int64_t)k * kSmallN + j] = v[k * 64 + l];
+}
+
+// Column order[j] of the eigenvector matrix: H_0 (H_1 ( ... W[:, order[j]])) with the reflections
+// of k_small_tridiag, as column j of out (fp32, r x r).  W [r][kSmallN] holds the tridiagonal
+// matrix's eigenvectors as rows.  A wave per column.
+static __global__ void __launch_bounds__(256) k_small_back(const double* __restrict__ W,
+                                                           const double* __restrict__ refl,
+                                                           const int32_t* __restrict__ order, int r,
+                                                           float* __restrict__ out) {
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
+  if (j >= r) return;
+  double x[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = l + 64 * q < r ? W[(int64_t)order[j] * kSmallN + l + 64 * q] : 0.0;
+#pragma unroll 4
+  for (int k = r - 3; k >= 0; --k) {
+    double u[4], s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      u[q] = refl[(int64_t)k * kSmallN + l + 64 * q];
+      s = fma(u[q], x[q], s);
+    }
+    s = small_sum64(s);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = fma(-u[q], s, x[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (l + 64 * q < r) out[(int64_t)(l + 64 * q) * r + j] = (float)x[q];
+}
+
+}  // namespace hmoe
