@@ -249,24 +249,26 @@ int launch_permute(const void* in, void* out, const int32_t* index, int64_t n, i
   return HMOE_OK;
 }
 
-int launch_seg_tiles(const int32_t* seg, int G, int tile, int32_t* tile_start, hipStream_t st) {
-  HMOE_LAUNCH("segment tiles", k_seg_tiles, dim3(1), dim3(1024), 0, st, seg, G, tile, tile_start);
-  return HMOE_OK;
-}
-
-int launch_seg_order(const int32_t* seg, int G, int32_t* order, hipStream_t st) {
-  HMOE_LAUNCH("segment order", k_seg_order, dim3((unsigned)cdiv(G, 256)), dim3(256), 0, st, seg, G, order);
+int launch_seg_plan(const int32_t* seg, int G, SegPlan plan, hipStream_t st) {
+  int32_t* order = plan.order;
+  if (G > 256) plan.order = nullptr;
+  HMOE_LAUNCH("segment plan", k_seg_plan, dim3(1), dim3(1024), 0, st, seg, G, plan);
+  if (order && G > 256)
+    HMOE_LAUNCH("segment order", k_seg_order, dim3((unsigned)cdiv(G, 256)), dim3(256), 0, st, seg, G, order);
   return HMOE_OK;
 }
 
 template <typename T, typename O>
 int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* seg, int G, int w,
-                  int64_t n, O* out, int accumulate, Workspace& ws, hipStream_t st) {
+                  int64_t n, O* out, int accumulate, Workspace& ws, hipStream_t st, const int32_t* ts) {
   const int64_t pieces = cdiv(n, kSegPiece) + G;
-  int32_t* ts = ws.take<int32_t>(G + 1);
+  int32_t* own = ws.take<int32_t>(G + 1);
   double* part = ws.take<double>((size_t)pieces * w);
   if (!ws.fits()) return HMOE_EWORKSPACE;
-  HMOE_TRY(launch_seg_tiles(seg, G, kSegPiece, ts, st));
+  if (!ts) {
+    HMOE_TRY(launch_seg_plan(seg, G, SegPlan{{kSegPiece}, {own}, nullptr}, st));
+    ts = own;
+  }
   HMOE_LAUNCH("segsum partial", k_segsum_partial<T>, dim3((unsigned)pieces), dim3(256), 0, st, X, ld, rowmap, seg, ts, G,
                      w, part);
   HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
@@ -282,13 +284,13 @@ size_t segsum_ws(int64_t n, int G, int w) {
 }
 
 template int launch_segsum<float, double>(const float*, int64_t, const int32_t*, const int32_t*, int, int,
-                                          int64_t, double*, int, Workspace&, hipStream_t);
+                                          int64_t, double*, int, Workspace&, hipStream_t, const int32_t*);
 template int launch_segsum<bf16, double>(const bf16*, int64_t, const int32_t*, const int32_t*, int, int,
-                                         int64_t, double*, int, Workspace&, hipStream_t);
+                                         int64_t, double*, int, Workspace&, hipStream_t, const int32_t*);
 template int launch_segsum<float, float>(const float*, int64_t, const int32_t*, const int32_t*, int, int,
-                                         int64_t, float*, int, Workspace&, hipStream_t);
+                                         int64_t, float*, int, Workspace&, hipStream_t, const int32_t*);
 template int launch_segsum<bf16, float>(const bf16*, int64_t, const int32_t*, const int32_t*, int, int,
-                                        int64_t, float*, int, Workspace&, hipStream_t);
+                                        int64_t, float*, int, Workspace&, hipStream_t, const int32_t*);
 
 int launch_zero_f32(float* x, int64_t n, hipStream_t st) {
   if (n <= 0) return HMOE_OK;

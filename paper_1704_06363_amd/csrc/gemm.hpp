@@ -55,11 +55,6 @@ using CfgSmall = Cfg<T, 128, 128, 64, 64>;
 // Problems of few tiles: a quarter of the tile, two waves of 32 x 64.
 template <typename T>
 using CfgQuarter = Cfg<T, 64, 64, 32, 64>;
-// Few columns (the gater's assignment with K <= 64 centres): 256 x 64 tiles, four waves of
-// 64 x 64 stacked along the rows, so no MFMA work is spent on absent centres.
-template <typename T>
-using CfgNarrow = Cfg<T, 256, 64, 64, 64>;
-
 __device__ __forceinline__ int swz(int row, int chunk) {
   return row * kStageRowBytes + ((chunk ^ ((row ^ (row >> 2)) & 7)) << 4);
 }
@@ -321,6 +316,11 @@ struct CfgD {
 // 11% slower; 3 stages: 15%), 128 x 64 with 2 or 4 stages (10%, 8%) and 64 x 64 (17%)
 typedef CfgD<float, 128, 64, 32, 64, 3> CfgDmaF32Narrow;
 typedef CfgD<bf16, 128, 64, 32, 64, 3> CfgDmaNarrow;
+// The same with fewer such tiles than CUs, where a tile's chain of stages is all there is: half the
+// rows, so twice the workgroups, and four stages in flight instead of two (512 x 2048 bf16, K = 16:
+// 30 us, 25)
+typedef CfgD<float, 64, 64, 32, 32, 5> CfgDmaF32NarrowFew;
+typedef CfgD<bf16, 64, 64, 32, 32, 5> CfgDmaNarrowFew;
 
 // 16-byte chunk swizzle of the 64-byte K-contiguous rows (used by the DMA slot mapping and the
 // operand reads alike).  Measured with the LDS bank-conflict counter on gfx950 for the MFMA
@@ -1511,14 +1511,16 @@ struct RowId {
 
 // Tile configurations per data type, C for a K-contiguous B and CK for a K-strided one: bf16
 // runs the 256 x 256 pipelined engine, fp32 -- and bf16 rows too wide for the pipelined engine's
-// 32-bit offsets (WIDE) -- the register-staged 128 x 128 one.
-template <typename T, bool WIDE = false>
+// 32-bit offsets -- the register-staged 128 x 128 one.
+template <typename T, bool WIDE_ = false>
 struct Pick {
+  static constexpr bool WIDE = true;
   using C = CfgSmall<T>;
   using CK = CfgSmall<T>;
 };
 template <>
 struct Pick<bf16, false> {
+  static constexpr bool WIDE = false;
   using C = CfgPipe;
   using CK = CfgPipeKS;
 };

@@ -304,13 +304,16 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
 int launch_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, const void* C, int32_t K, int32_t* assign,
                   float* min_dist, Workspace& ws, hipStream_t st) {
   const bool pipe = assign_pipe(d, dt, K);
+  const bool few = cdiv(n, CfgDmaNarrow::BM) < device_cus();
   if (dt == HMOE_BF16) {
     const bf16 *x = (const bf16*)X, *c = (const bf16*)C;
+    if (K <= 64 && few) return assign_t<CfgDmaNarrowFew>(x, n, d, c, K, assign, min_dist, ws, st);
     if (K <= 64) return assign_t<CfgDmaNarrow>(x, n, d, c, K, assign, min_dist, ws, st);
     if (pipe) return assign_t<CfgPipe>(x, n, d, c, K, assign, min_dist, ws, st);
     return assign_t<CfgSmall<bf16>>(x, n, d, c, K, assign, min_dist, ws, st);
   }
   const float *x = (const float*)X, *c = (const float*)C;
+  if (K <= 64 && few) return assign_t<CfgDmaF32NarrowFew>(x, n, d, c, K, assign, min_dist, ws, st);
   if (K <= 64) return assign_t<CfgDmaF32Narrow>(x, n, d, c, K, assign, min_dist, ws, st);
   if (pipe) return assign_t<CfgPipeF32>(x, n, d, c, K, assign, min_dist, ws, st);
   return assign_t<CfgSmall<float>>(x, n, d, c, K, assign, min_dist, ws, st);

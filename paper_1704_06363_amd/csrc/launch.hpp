@@ -13,8 +13,8 @@ int launch_dispatch(const int32_t* e, int64_t n, int32_t K, int32_t* counts, int
                     int32_t* perm, int32_t* inv, Workspace& ws, hipStream_t st);
 int launch_permute(const void* in, void* out, const int32_t* index, int64_t n, int32_t w,
                    hmoe_dtype_t dt, hipStream_t st);
-int launch_seg_tiles(const int32_t* seg, int G, int tile, int32_t* tile_start, hipStream_t st);
-int launch_seg_order(const int32_t* seg, int G, int32_t* order, hipStream_t st);
+struct SegPlan;
+int launch_seg_plan(const int32_t* seg, int G, SegPlan plan, hipStream_t st);
 template <typename T>
 size_t gemm_tn_ws();
 template <typename T>
@@ -39,7 +39,8 @@ int launch_topm_hits(const int32_t* idx, int64_t n, int m, const hmoe_labels_t* 
 size_t segsum_ws(int64_t n, int G, int w);
 template <typename T, typename O>
 int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* seg, int G, int w,
-                  int64_t n, O* out, int accumulate, Workspace& ws, hipStream_t st);
+                  int64_t n, O* out, int accumulate, Workspace& ws, hipStream_t st,
+                  const int32_t* tile_start = nullptr);  // of kSegPiece rows, when it is there already
 int launch_zero_f32(float* x, int64_t n, hipStream_t st);
 int launch_sum_f32(const float* x, int64_t n, double scale, double* out_f64, float* out_f32,
                    Workspace& ws, hipStream_t st);

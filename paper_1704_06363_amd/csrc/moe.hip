@@ -436,20 +436,22 @@ __global__ void __launch_bounds__(C::THREADS)
   }
 }
 
-// lse = merge of the tile partials; loss = lse - mean positive logit.  A block takes 64 rows.
-// The merge reads the partials [tile][row] coalesced: lane l of wave w takes row r0 + l and the
-// tiles t = w, w + 4, ... with an online (max, sum) merge, and the four waves' pairs are merged
-// in wave order.  The positive logits are (row, tag) tasks, numbered row by row in tag order:
+// lse = merge of the tile partials; loss = lse - mean positive logit.  A block takes R rows.
+// The merge reads the partials [tile][row] coalesced: with S = 64 / R, lane l of wave w takes row
+// r0 + l % R and the tiles t = S w + l / R, + 4 S, ... with an online (max, sum) merge, and a row's
+// 4 S pairs are merged in order of their first tile.  R is 64 where that fills the chip and 16
+// otherwise: a walk over the tiles is a chain of memory latencies, and 512 rows x 196 tiles made
+// 8 blocks of 49 steps (44 us; 17 with R = 16).  The positive logits are (row, tag) tasks, numbered row by row in tag order:
 // 8 lanes per task each take every 8th 16-byte vector of the H row and the D row (row widths
 // are multiples of 8, so o / (16 / sizeof(T)) vectors cover a row exactly), the 8 partial sums
 // are combined by lane shuffles, and each row adds its tasks' dots in task order.
 // With per-expert decoders the rows (partials and H) are in slot order: row r is sample
 // perm[r], decoded by D_e, bD_e of the expert e whose segment of `seg` holds r; lse and loss
 // are written in sample order.  Shared decoder: perm = seg = NULL.
-constexpr int kLossRows = 64;
+constexpr int kLossRows = 64, kLossRowsFew = 16;
 constexpr int kLossTasks = 512;  // tasks staged in LDS at a time
 
-template <typename T>
+template <typename T, int R>
 __global__ void __launch_bounds__(256) k_dec_loss(const float* __restrict__ pm, const float* __restrict__ ps,
                                                   int nt, const T* __restrict__ H, const T* __restrict__ D,
                                                   const T* __restrict__ bD, int64_t n, int o, int V,
@@ -458,30 +460,33 @@ __global__ void __launch_bounds__(256) k_dec_loss(const float* __restrict__ pm, 
                                                   const int32_t* __restrict__ tag, float* __restrict__ lse,
                                                   float* __restrict__ loss) {
   constexpr int EPV = 16 / sizeof(T);
-  __shared__ float s_m[4][kLossRows], s_s[4][kLossRows], s_pos[kLossRows];
-  __shared__ int32_t s_first[kLossRows + 1];  // first task of each row (exclusive prefix)
-  __shared__ int32_t s_p0[kLossRows], s_exp[kLossRows];
+  constexpr int S = 64 / R;
+  __shared__ float s_m[4 * S][R], s_s[4 * S][R], s_pos[R];
+  __shared__ int32_t s_first[R + 1];  // first task of each row (exclusive prefix)
+  __shared__ int32_t s_p0[R], s_exp[R];
   __shared__ int32_t s_trow[kLossTasks], s_ttag[kLossTasks];
   __shared__ float s_dot[kLossTasks];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int64_t r0 = (int64_t)blockIdx.x * kLossRows;
-  const int rows = (int)(n - r0 < kLossRows ? n - r0 : kLossRows);
+  const int64_t r0 = (int64_t)blockIdx.x * R;
+  const int rows = (int)(n - r0 < R ? n - r0 : R);
   {
-    float M = -FLT_MAX, S = 0.f;
-    if (l < rows)
-      for (int t = w; t < nt; t += 4) {
-        const float m = pm[(int64_t)t * n + r0 + l], sv = ps[(int64_t)t * n + r0 + l];
+    float M = -FLT_MAX, sum = 0.f;
+    const int lr = l % R, ls = l / R;
+    if (lr < rows)
+#pragma unroll 4
+      for (int t = S * w + ls; t < nt; t += 4 * S) {
+        const float m = pm[(int64_t)t * n + r0 + lr], sv = ps[(int64_t)t * n + r0 + lr];
         if (m > M) {
-          S = S * __expf(M - m) + sv;
+          sum = sum * __expf(M - m) + sv;
           M = m;
         } else {
-          S += sv * __expf(m - M);
+          sum += sv * __expf(m - M);
         }
       }
-    s_m[w][l] = M;
-    s_s[w][l] = S;
+    s_m[S * w + ls][lr] = M;
+    s_s[S * w + ls][lr] = sum;
   }
-  if (threadIdx.x < kLossRows) {
+  if (threadIdx.x < R) {
     const int t = threadIdx.x;
     int32_t cnt = 0;
     if (t < rows) {
@@ -498,10 +503,10 @@ __global__ void __launch_bounds__(256) k_dec_loss(const float* __restrict__ pm, 
   __syncthreads();
   if (threadIdx.x == 0) {
     s_first[0] = 0;
-    for (int t = 0; t < kLossRows; ++t) s_first[t + 1] += s_first[t];
+    for (int t = 0; t < R; ++t) s_first[t + 1] += s_first[t];
   }
   __syncthreads();
-  const int total = s_first[kLossRows];
+  const int total = s_first[R];
   const int g = l >> 3, gl = l & 7;
   const int vpr = o / EPV;
   for (int c0 = 0; c0 < total; c0 += kLossTasks) {
@@ -573,18 +578,18 @@ __global__ void __launch_bounds__(256) k_dec_loss(const float* __restrict__ pm, 
   }
   if (threadIdx.x < rows) {
     const int t = threadIdx.x;
-    float M = s_m[0][t], S = s_s[0][t];
+    float M = s_m[0][t], sum = s_s[0][t];
 #pragma unroll
-    for (int q = 1; q < 4; ++q) {
+    for (int q = 1; q < 4 * S; ++q) {
       const float m = s_m[q][t], sv = s_s[q][t];
       if (m > M) {
-        S = S * __expf(M - m) + sv;
+        sum = sum * __expf(M - m) + sv;
         M = m;
       } else {
-        S += sv * __expf(m - M);
+        sum += sv * __expf(m - M);
       }
     }
-    const float Lv = M + __logf(S);
+    const float Lv = M + __logf(sum);
     const int64_t smp = perm ? perm[r0 + t] : r0 + t;
     lse[smp] = Lv;
     loss[smp] = Lv - s_pos[t] / (float)(s_first[t + 1] - s_first[t]);
@@ -721,7 +726,7 @@ __global__ void __launch_bounds__(C::THREADS)
 
 // Saved-logits path: g = (exp(anchor + L - lse) - y) / n elementwise over [n x V] (L holds the
 // logits as offsets from their anchors, anc, one per row and 64 columns); each thread owns one
-// 16-byte column vector over kGradRows rows, whose anchors are one per row (a vector never
+// 16-byte column vector over the block's rows, whose anchors are one per row (a vector never
 // straddles a 64-column block), and writes its column sums to part_db[rowblock][V].
 // A block covers a slab of 256 x EPV columns; per row it keeps (in LDS) only the tags that fall
 // inside its slab, so the per-element work is an fma and an exp, and a tag costs one compare
@@ -729,10 +734,11 @@ __global__ void __launch_bounds__(C::THREADS)
 // (flag -1) reads its tags from global memory instead.  g is stored non-temporally: it is only
 // read back by the next kernels, long after it has left the caches (measured 3.07 -> 2.91 ms).
 // Per-expert decoders: the rows (L, g) are in slot order, row r being sample perm[r], and a
-// block takes a piece of at most kGradRows rows of one expert (pieces numbered by
+// block takes a piece of at most `brows` rows of one expert (pieces numbered by
 // piece_start, as in the segmented sums), so its column sums belong to one decoder's dbD.
-// Shared decoder: perm = piece_start = NULL and block b takes rows [b, b + 1) * kGradRows.
-constexpr int kGradRows = 256;
+// Shared decoder: perm = piece_start = NULL and block b takes rows [b, b + 1) * brows.
+// `brows` rows per block: kGradRows, or fewer where those blocks would leave CUs idle (grad_rows()).
+constexpr int kGradRows = 256, kGradRowsFew = 16;
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_dec_grad_elem(const T* __restrict__ L, const float* __restrict__ anc,
@@ -742,7 +748,7 @@ __global__ void __launch_bounds__(256) k_dec_grad_elem(const T* __restrict__ L, 
                                                        float inv_n, const int32_t* __restrict__ perm,
                                                        const int32_t* __restrict__ seg,
                                                        const int32_t* __restrict__ piece_start, int NG,
-                                                       T* __restrict__ G, float* __restrict__ part_db, int slab) {
+                                                       T* __restrict__ G, float* __restrict__ part_db, int slab, int brows) {
   constexpr int EPV = 16 / sizeof(T);
   constexpr int MAXT = 16;
   constexpr float kLog2e = 1.4426950408889634f;
@@ -753,13 +759,13 @@ __global__ void __launch_bounds__(256) k_dec_grad_elem(const T* __restrict__ L, 
   if (piece_start) {
     if ((int64_t)blockIdx.x >= piece_start[NG]) return;
     const int e = find_segment(piece_start, NG, blockIdx.x);
-    r0 = seg[e] + (int64_t)(blockIdx.x - piece_start[e]) * kGradRows;
+    r0 = seg[e] + (int64_t)(blockIdx.x - piece_start[e]) * brows;
     rend = seg[e + 1];
   } else {
-    r0 = (int64_t)blockIdx.x * kGradRows;
+    r0 = (int64_t)blockIdx.x * brows;
     rend = n;
   }
-  const int rows = (int)((rend - r0) < kGradRows ? (rend - r0) : kGradRows);
+  const int rows = (int)((rend - r0) < brows ? (rend - r0) : brows);
   const int slab0 = blockIdx.y * 256 * EPV;
   for (int t = threadIdx.x; t < rows; t += 256) {
     const int64_t smp = perm ? perm[r0 + t] : r0 + t;
@@ -862,7 +868,7 @@ __global__ void __launch_bounds__(256) k_piece_colsum(const float* __restrict__ 
 }
 
 // out[v] = sum over the rows of part[row][v] (the decoder bias gradient from per-block column
-// partials).  A block takes 64 columns; its four waves sum a quarter of the rows each (in row order, four
+// partials).  A block takes 64 columns; its four waves sum a quarter of the rows each (in row order, sixteen
 // rows in flight) and the quarters are added in order, so the result does not depend on timing.
 __global__ void __launch_bounds__(256) k_colsum_final(const float* __restrict__ part, int rows, int V,
                                                       float* __restrict__ out) {
@@ -874,10 +880,12 @@ __global__ void __launch_bounds__(256) k_colsum_final(const float* __restrict__ 
   float s = 0.f;
   if (c < V) {
     int q = q0;
-    for (; q + 4 <= q1; q += 4) {
-      const float a = part[(int64_t)q * V + c], b = part[(int64_t)(q + 1) * V + c];
-      const float d = part[(int64_t)(q + 2) * V + c], e = part[(int64_t)(q + 3) * V + c];
-      s = (((s + a) + b) + d) + e;
+    for (; q + 16 <= q1; q += 16) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(q + u) * V + c];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += v[u];
     }
     for (; q < q1; ++q) s += part[(int64_t)q * V + c];
   }
@@ -1114,11 +1122,23 @@ static MoeShape shape_of(const hmoe_moe_params_t* p, int64_t n) {
 // Rows too wide for the pipelined engine's offsets (the vocabulary's are rows of g).
 static bool wide_rows(const MoeShape& s) { return s.d >= kPipeMaxLd || s.V >= kPipeMaxLd; }
 
+// Rows per block of k_dec_grad_elem: a block's rows are a chain of memory latencies (64 groups of four,
+// 161 us, for the 16 blocks of 4096 x 1000 fp32; 15 in 16 rows each), so they are halved until
+// there are two blocks per CU.
+template <typename T>
+static int grad_rows(int64_t n, int V) {
+  const int64_t slabs = cdiv(V, 256 * (16 / (int)sizeof(T)));
+  int rows = kGradRows;
+  while (rows > kGradRowsFew && cdiv(n, rows) * slabs < 2 * device_cus()) rows /= 2;
+  return rows;
+}
+
 template <typename T, class P>
 static size_t fwd_ws(const MoeShape& s) {
   using C = typename P::C;
   Workspace ws(nullptr, 0);
   const int64_t ntv = cdiv(s.V, C::BN);
+  ws.take<int32_t>(s.K + 1);
   ws.take<int32_t>(s.K + 1);
   ws.take<float>((size_t)ntv * s.n);
   ws.take<float>((size_t)ntv * s.n);
@@ -1132,12 +1152,15 @@ static size_t bwd_ws(const MoeShape& s) {
   using C = typename P::C;
   Workspace ws(nullptr, 0);
   ws.take<int32_t>(s.K + 1);
+  ws.take<int32_t>(s.K + 1);
+  ws.take<int32_t>(s.K + 1);
   ws.take<int32_t>(s.K);
   constexpr int GW = 256 * (16 / (int)sizeof(T));  // G padded to whole slabs (backward_t)
   ws.take<T>(C::PIPE && s.nd == 1 ? (size_t)s.n * cdiv(s.V, GW) * GW : (size_t)s.n * s.V);
   ws.take<T>((size_t)s.n * s.o);
   ws.take<T>((size_t)s.n * s.h);
-  const int64_t prow = cdiv(s.n, C::BM) > cdiv(s.n, kGradRows) ? cdiv(s.n, C::BM) : cdiv(s.n, kGradRows);
+  const int64_t gr = cdiv(s.n, grad_rows<T>(s.n, s.V));
+  const int64_t prow = cdiv(s.n, C::BM) > gr ? cdiv(s.n, C::BM) : gr;
   ws.take<float>((size_t)(prow + s.K) * s.V);
   ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   if (s.nd > 1) {
@@ -1164,6 +1187,31 @@ size_t moe_ws_bytes(const hmoe_moe_params_t* p, int64_t n) {
   return a > b ? a : b;
 }
 
+// fp32 products of few tiles run quarter tiles (CfgQuarter): with fewer tiles than CUs a product
+// lasts as long as one tile's reduction, and a quarter of the tile takes a quarter of the time per
+// stage on four times the CUs; each element's sum runs in the same order.  4096 x 64 -> 128 -> 64,
+// V = 1000, 8 experts: dH 83 -> 50 us, the weight gradients 99 -> 61.  Measured at up to a tile per CU; with more the larger tile
+// reads less.  body(configuration) launches; `tiles` counts C's.
+template <typename T, class C, class Body>
+static int by_tile_count(int64_t tiles, Body body) {
+  if constexpr (sizeof(T) == 4)
+    if (tiles < device_cus()) return body(CfgQuarter<T>{});
+  return body(C{});
+}
+
+template <typename T>
+static int launch_loss(const float* pm, const float* ps, int nt, const T* H, const T* D, const T* bD, int64_t n, int o,
+                       int V, const int32_t* perm, const int32_t* seg, int G, const hmoe_labels_t* y, float* lse,
+                       float* loss, hipStream_t st) {
+  if (cdiv(n, kLossRows) < device_cus())
+    HMOE_LAUNCH("decoder loss", (k_dec_loss<T, kLossRowsFew>), dim3((unsigned)cdiv(n, kLossRowsFew)), dim3(256), 0, st,
+                pm, ps, nt, H, D, bD, n, o, V, perm, seg, G, y->row_ptr, y->tag, lse, loss);
+  else
+    HMOE_LAUNCH("decoder loss", (k_dec_loss<T, kLossRows>), dim3((unsigned)cdiv(n, kLossRows)), dim3(256), 0, st, pm,
+                ps, nt, H, D, bD, n, o, V, perm, seg, G, y->row_ptr, y->tag, lse, loss);
+  return HMOE_OK;
+}
+
 template <typename T, class P>
 static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const int32_t* offsets, const int32_t* perm,
                      const hmoe_labels_t* y, T* H1s, T* H, T* Lg, float* anc, float* lse, float* loss,
@@ -1172,6 +1220,7 @@ static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const i
   const MoeShape s = shape_of(p, n);
   const int ntv = (int)cdiv(s.V, C::BN);
   int32_t* ts = ws.take<int32_t>(s.K + 1);
+  int32_t* tsq = ws.take<int32_t>(s.K + 1);  // of quarter tiles
   float* pm = ws.take<float>((size_t)ntv * n);
   float* ps = ws.take<float>((size_t)ntv * n);
   T* Hs = s.nd > 1 ? ws.take<T>((size_t)n * s.o) : nullptr;  // H in slot order
@@ -1180,20 +1229,29 @@ static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const i
   const T* W2 = (const T*)p->W2;
   const T* D = (const T*)p->D;
   if (!Lg) anc = nullptr;
-  HMOE_TRY(launch_seg_tiles(offsets, s.K, C::BM, ts, st));
+  HMOE_TRY(launch_seg_plan(offsets, s.K, SegPlan{{C::BM, CfgQuarter<T>::BM}, {ts, sizeof(T) == 4 ? tsq : nullptr}, nullptr},
+                           st));
   const int64_t mt_bound = cdiv(n, C::BM) + s.K;
-  HMOE_LAUNCH("expert layer 1", (k_expert_fwd<C, 1>), dim3((unsigned)(mt_bound * cdiv(s.h, C::BN))),
-              dim3(C::THREADS), C::LDS, st, Xs, W1, (const T*)p->b1, offsets, ts, s.K, s.h, s.d, perm, H1s);
-  HMOE_LAUNCH("expert layer 2", (k_expert_fwd<C, 2>), dim3((unsigned)(mt_bound * cdiv(s.o, C::BN))),
-              dim3(C::THREADS), C::LDS, st, (const T*)H1s, W2, (const T*)p->b2, offsets, ts, s.K, s.o, s.h,
-              perm, H);
+  HMOE_TRY(by_tile_count<T, C>(mt_bound * cdiv(s.h, C::BN), [&](auto cfg) -> int {
+    using F = decltype(cfg);
+    HMOE_LAUNCH("expert layer 1", (k_expert_fwd<F, 1>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.h, F::BN))),
+                dim3(F::THREADS), F::LDS, st, Xs, W1, (const T*)p->b1, offsets, F::BM == C::BM ? ts : tsq, s.K, s.h,
+                s.d, perm, H1s);
+    return HMOE_OK;
+  }));
+  HMOE_TRY(by_tile_count<T, C>(mt_bound * cdiv(s.o, C::BN), [&](auto cfg) -> int {
+    using F = decltype(cfg);
+    HMOE_LAUNCH("expert layer 2", (k_expert_fwd<F, 2>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.o, F::BN))),
+                dim3(F::THREADS), F::LDS, st, (const T*)H1s, W2, (const T*)p->b2, offsets, F::BM == C::BM ? ts : tsq,
+                s.K, s.o, s.h, perm, H);
+    return HMOE_OK;
+  }));
   if (s.nd > 1) {
     // one decoder per expert: decode in slot order
     HMOE_TRY(launch_permute(H, Hs, perm, n, s.o, p->dt, st));
     HMOE_LAUNCH("decoder forward", k_dec_fwd_grouped<C>, dim3((unsigned)(mt_bound * ntv)), dim3(C::THREADS), C::LDS,
                 st, (const T*)Hs, D, (const T*)p->bD, offsets, ts, s.K, n, s.V, s.o, pm, ps, Lg, anc);
-    HMOE_LAUNCH("decoder loss", k_dec_loss<T>, dim3((unsigned)cdiv(n, kLossRows)), dim3(256), 0, st, pm, ps, ntv,
-                (const T*)Hs, D, (const T*)p->bD, n, s.o, s.V, perm, offsets, s.K, y->row_ptr, y->tag, lse, loss);
+    HMOE_TRY(launch_loss<T>(pm, ps, ntv, Hs, D, (const T*)p->bD, n, s.o, s.V, perm, offsets, s.K, y, lse, loss, st));
     return launch_sum_f32(loss, n, 1.0 / (double)n, nullptr, loss_mean, ws, st);
   }
   // persistent, one workgroup per resident slot, when a tile's reduction has the two stages its
@@ -1213,9 +1271,7 @@ static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const i
   if (!streamed)
     HMOE_LAUNCH("decoder forward", k_dec_fwd<C>, dim3((unsigned)(cdiv(n, C::BM) * ntv)), dim3(C::THREADS), C::LDS,
                 st, (const T*)H, D, (const T*)p->bD, n, s.V, s.o, pm, ps, Lg, anc);
-  HMOE_LAUNCH("decoder loss", k_dec_loss<T>, dim3((unsigned)cdiv(n, kLossRows)), dim3(256), 0, st, pm, ps, ntv, (const T*)H, D,
-              (const T*)p->bD, n, s.o, s.V, (const int32_t*)nullptr, (const int32_t*)nullptr, 0, y->row_ptr,
-              y->tag, lse, loss);
+  HMOE_TRY(launch_loss<T>(pm, ps, ntv, H, D, (const T*)p->bD, n, s.o, s.V, nullptr, nullptr, 0, y, lse, loss, st));
   return launch_sum_f32(loss, n, 1.0 / (double)n, nullptr, loss_mean, ws, st);
 }
 
@@ -1228,6 +1284,8 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   using CK = typename P::CK;  // K-strided second operand
   const MoeShape s = shape_of(p, n);
   int32_t* ts = ws.take<int32_t>(s.K + 1);
+  int32_t* tsq = ws.take<int32_t>(s.K + 1);  // of quarter tiles
+  int32_t* tss = ws.take<int32_t>(s.K + 1);  // of the segmented sums' pieces
   int32_t* order = ws.take<int32_t>(s.K);
   constexpr int EPV = 16 / sizeof(T);
   // bf16 logits through the shared decoder: G slab-major, [V / GW slabs][n][GW] (see
@@ -1238,7 +1296,8 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   T* dYs = ws.take<T>((size_t)n * s.o);
   T* dZ = ws.take<T>((size_t)n * s.h);
   const int mt = (int)cdiv(n, C::BM);
-  const int gr = (int)cdiv(n, kGradRows);
+  const int brows = grad_rows<T>(n, s.V);
+  const int gr = (int)cdiv(n, brows);
   float* pdb = ws.take<float>((size_t)((mt > gr ? mt : gr) + s.K) * s.V);
   float* split_part = ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   T* Hs = nullptr;
@@ -1253,16 +1312,22 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   const T* D = (const T*)p->D;
   const int ntv = (int)cdiv(s.V, C::BN);
   const int64_t mt_bound = cdiv(n, C::BM) + s.K;
-  HMOE_TRY(launch_seg_tiles(offsets, s.K, C::BM, ts, st));
-  HMOE_TRY(launch_seg_order(offsets, s.K, order, st));
+  // bf16 tiles are as high as the sums' pieces and have no quarters
+  static_assert(sizeof(T) == 4 || P::WIDE || C::BM == kSegPiece, "one table for both");
+  if (C::BM == kSegPiece) tss = ts;
+  HMOE_TRY(launch_seg_plan(offsets, s.K,
+                           SegPlan{{C::BM, CfgQuarter<T>::BM, kSegPiece},
+                                   {ts, sizeof(T) == 4 ? tsq : nullptr, tss != ts ? tss : nullptr},
+                                   order},
+                           st));
   if (s.nd > 1) {
     // One decoder per expert, everything in slot order (the API guarantees saved logits):
     // g from the stored logits in pieces that stay within one expert, dbD_e from the pieces'
     // column sums, dH = g D_e (row-grouped), dD_e = g_e^T H_e (reduction-grouped).
-    HMOE_TRY(launch_seg_tiles(offsets, s.K, kGradRows, gts, st));
+    HMOE_TRY(launch_seg_plan(offsets, s.K, SegPlan{{brows}, {gts}, nullptr}, st));
     HMOE_LAUNCH("decoder grad", k_dec_grad_elem<T>, dim3((unsigned)(gr + s.K), (unsigned)cdiv(s.V, 256 * EPV)),
                 dim3(256), 0, st, Lg, anc, lse, y->row_ptr, y->tag, n, s.V, (float)(1.0 / (double)n), perm, offsets,
-                gts, s.K, G, pdb, 0);
+                gts, s.K, G, pdb, 0, brows);
     if (dbD)
       HMOE_LAUNCH("decoder bias grad", k_piece_colsum, dim3((unsigned)cdiv(s.V, 256), (unsigned)s.K), dim3(256), 0,
                   st, pdb, gts, s.V, dbD);
@@ -1279,7 +1344,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   if (Lg) {
     HMOE_LAUNCH("decoder grad", k_dec_grad_elem<T>, dim3((unsigned)gr, (unsigned)cdiv(s.V, 256 * EPV)), dim3(256),
                 0, st, Lg, anc, lse, y->row_ptr, y->tag, n, s.V, (float)(1.0 / (double)n), (const int32_t*)nullptr,
-                (const int32_t*)nullptr, (const int32_t*)nullptr, 0, G, pdb, (int)slab);
+                (const int32_t*)nullptr, (const int32_t*)nullptr, 0, G, pdb, (int)slab, brows);
     prow = gr;
   } else {
     HMOE_LAUNCH("decoder grad", k_dec_grad<C>, dim3((unsigned)(mt * ntv)), dim3(C::THREADS), C::LDS, st, H, D,
@@ -1297,27 +1362,46 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
     }
   }
   if (!slab) {
-    HMOE_LAUNCH("decoder dH", k_dec_dH<CK>, dim3((unsigned)(mt * cdiv(s.o, C::BN))), dim3(C::THREADS), C::LDS, st,
-                (const T*)G, D, n, s.V, s.o, inv, dYs);
+    HMOE_TRY(by_tile_count<T, CK>((int64_t)mt * cdiv(s.o, C::BN), [&](auto cfg) -> int {
+      using F = decltype(cfg);
+      HMOE_LAUNCH("decoder dH", k_dec_dH<F>, dim3((unsigned)(cdiv(n, F::BM) * cdiv(s.o, F::BN))), dim3(F::THREADS),
+                  F::LDS, st, (const T*)G, D, n, s.V, s.o, inv, dYs);
+      return HMOE_OK;
+    }));
     HMOE_TRY(launch_tn_split<CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st));
   }
   }
   // experts
   const size_t mark = ws.off;
-  if (db2) HMOE_TRY(launch_segsum<T, float>(dYs, s.o, nullptr, offsets, s.K, s.o, n, db2, 0, ws, st));
+  const auto wgrad = [&](const char* label, const T* A, int M, const T* B, int N, float* out) -> int {
+    return by_tile_count<T, CK>((int64_t)s.K * cdiv(M, C::BM) * cdiv(N, C::BN), [&](auto cfg) -> int {
+      using F = decltype(cfg);
+      HMOE_LAUNCH(label, k_expert_wgrad<F>, dim3((unsigned)((int64_t)s.K * cdiv(M, F::BM) * cdiv(N, F::BN))),
+                  dim3(F::THREADS), F::LDS, st, A, B, offsets, order, s.K, M, N, out);
+      return HMOE_OK;
+    });
+  };
+  if (db2) HMOE_TRY(launch_segsum<T, float>(dYs, s.o, nullptr, offsets, s.K, s.o, n, db2, 0, ws, st, tss));
   ws.off = mark;
-  HMOE_LAUNCH("expert dW2", k_expert_wgrad<CK>, dim3((unsigned)((int64_t)s.K * cdiv(s.o, C::BM) * cdiv(s.h, C::BN))),
-              dim3(C::THREADS), C::LDS, st, (const T*)dYs, H1s, offsets, order, s.K, s.o, s.h, dW2);
-  HMOE_LAUNCH("expert dH1", (k_expert_dgrad<CK, true>), dim3((unsigned)(mt_bound * cdiv(s.h, C::BN))),
-              dim3(C::THREADS), C::LDS, st, (const T*)dYs, W2, offsets, ts, s.K, s.h, s.o, H1s, perm, dZ);
-  if (db1) HMOE_TRY(launch_segsum<T, float>(dZ, s.h, nullptr, offsets, s.K, s.h, n, db1, 0, ws, st));
+  HMOE_TRY(wgrad("expert dW2", dYs, s.o, H1s, s.h, dW2));
+  HMOE_TRY(by_tile_count<T, CK>(mt_bound * cdiv(s.h, C::BN), [&](auto cfg) -> int {
+    using F = decltype(cfg);
+    HMOE_LAUNCH("expert dH1", (k_expert_dgrad<F, true>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.h, F::BN))),
+                dim3(F::THREADS), F::LDS, st, (const T*)dYs, W2, offsets, F::BM == C::BM ? ts : tsq, s.K, s.h, s.o,
+                H1s, perm, dZ);
+    return HMOE_OK;
+  }));
+  if (db1) HMOE_TRY(launch_segsum<T, float>(dZ, s.h, nullptr, offsets, s.K, s.h, n, db1, 0, ws, st, tss));
   ws.off = mark;
-  HMOE_LAUNCH("expert dW1", k_expert_wgrad<CK>, dim3((unsigned)((int64_t)s.K * cdiv(s.h, C::BM) * cdiv(s.d, C::BN))),
-              dim3(C::THREADS), C::LDS, st, (const T*)dZ, Xs, offsets, order, s.K, s.h, s.d, dW1);
+  HMOE_TRY(wgrad("expert dW1", dZ, s.h, Xs, s.d, dW1));
   if (dX)
-    HMOE_LAUNCH("expert dX", (k_expert_dgrad<CK, false>), dim3((unsigned)(mt_bound * cdiv(s.d, C::BN))),
-                dim3(C::THREADS), C::LDS, st, (const T*)dZ, W1, offsets, ts, s.K, s.d, s.h,
-                (const T*)nullptr, perm, dX);
+    HMOE_TRY(by_tile_count<T, CK>(mt_bound * cdiv(s.d, C::BN), [&](auto cfg) -> int {
+      using F = decltype(cfg);
+      HMOE_LAUNCH("expert dX", (k_expert_dgrad<F, false>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.d, F::BN))),
+                  dim3(F::THREADS), F::LDS, st, (const T*)dZ, W1, offsets, F::BM == C::BM ? ts : tsq, s.K, s.d, s.h,
+                  (const T*)nullptr, perm, dX);
+      return HMOE_OK;
+    }));
   return HMOE_OK;
 }
 

@@ -38,30 +38,46 @@ __device__ __forceinline__ V block_excl_scan(V v, V* sh, V* total) {
   return res;
 }
 
-// tile_start[e] = sum_{e' < e} ceil((seg[e'+1] - seg[e']) / tile), e = 0..G.  One block of
-// 1024 threads; G <= 4096.
-static __global__ void __launch_bounds__(1024) k_seg_tiles(const int32_t* __restrict__ seg, int G, int tile,
-                                                    int32_t* __restrict__ tile_start) {
+// What the grouped kernels need to know of the segments, in one launch: for each of up to three tile
+// heights tile_start[q][e] = sum_{e' < e} ceil((seg[e'+1] - seg[e']) / tile[q]), e = 0..G, and the
+// order of k_seg_order (G <= 256; NULL: not wanted).  One block of 1024 threads; G <= 4096.
+struct SegPlan {
+  int tile[3];
+  int32_t* tile_start[3];
+  int32_t* order;
+};
+static __global__ void __launch_bounds__(1024) k_seg_plan(const int32_t* __restrict__ seg, int G, SegPlan plan) {
   __shared__ int32_t sh[17];
+  __shared__ int32_t len_s[256];
   const int per = (G + 1023) / 1024;
   const int e0 = threadIdx.x * per;
-  int32_t loc[4];
-  int32_t s = 0;
-  for (int q = 0; q < per && q < 4; ++q) {
-    const int e = e0 + q;
-    int32_t c = 0;
-    if (e < G) c = (seg[e + 1] - seg[e] + tile - 1) / tile;
-    loc[q] = c;
-    s += c;
+  int32_t len[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) len[q] = q < per && e0 + q < G ? seg[e0 + q + 1] - seg[e0 + q] : 0;
+  for (int z = 0; z < 3; ++z) {
+    int32_t* out = plan.tile_start[z];
+    if (!out) continue;
+    const int tile = plan.tile[z];
+    int32_t s = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s += (len[q] + tile - 1) / tile;
+    int32_t total;
+    int32_t ex = block_excl_scan<int32_t>(s, sh, &total);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < per && e0 + q < G) out[e0 + q] = ex;
+      ex += (len[q] + tile - 1) / tile;
+    }
+    if (threadIdx.x == 0) out[G] = total;
   }
-  int32_t total;
-  int32_t ex = block_excl_scan<int32_t>(s, sh, &total);
-  for (int q = 0; q < per && q < 4; ++q) {
-    const int e = e0 + q;
-    if (e < G) tile_start[e] = ex;
-    ex += loc[q];
-  }
-  if (threadIdx.x == 0) tile_start[G] = total;
+  if (!plan.order) return;
+  const int e = threadIdx.x;  // per = 1
+  if (e < G) len_s[e] = len[0];
+  __syncthreads();
+  if (e >= G) return;
+  int rank = 0;
+  for (int f = 0; f < G; ++f) rank += (len_s[f] > len[0]) || (len_s[f] == len[0] && f < e);
+  plan.order[rank] = e;
 }
 
 // order[r] = the segment of rank r when segments are ranked by length, longest first, equal
