@@ -199,6 +199,72 @@ __global__ void __launch_bounds__(256) k_dispatch_scatter(const int32_t* __restr
   }
 }
 
+// The whole sort in one workgroup, for few ids (n <= kSortSmall) and buckets (K <= kSortBuckets): wave
+// w of 16 takes a contiguous run of the ids in chunks of 64, the waves' bucket counts meet in LDS,
+// and each wave scatters its run from its own running slots.  With `pieces`, the segments' table
+// of kSegPiece-row pieces as well (see k_seg_plan).  One launch instead of three or four (4096 ids,
+// 8 buckets: 13 us and two gaps -> 8); above 8192 ids the sixteen waves' serial chunks take longer than that saves.
+constexpr int64_t kSortSmall = 8192;
+constexpr int kSortBuckets = 512;
+__global__ void __launch_bounds__(1024) k_dispatch_small(const int32_t* __restrict__ e, int n, int K, int bits,
+                                                         int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                         int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                         int32_t* __restrict__ pieces) {
+  __shared__ int32_t slot[16][kSortBuckets + 1];
+  __shared__ int32_t sh[17];
+  const int t = threadIdx.x, w = t >> 6, l = t & 63;
+  const int KB = K + 1;
+  for (int k = t; k < 16 * KB; k += 1024) slot[k / KB][k % KB] = 0;
+  __syncthreads();
+  const int per = (n + 16 * 64 - 1) / (16 * 64) * 64;
+  const int i0 = w * per, i1 = i0 + per < n ? i0 + per : n;
+  const auto bucket = [&](int i, bool& valid) {
+    valid = i < i1;
+    const int id = valid ? e[i] : 0;
+    return (unsigned)id < (unsigned)K ? id : K;
+  };
+  for (int c = i0; c < i1; c += 64) {
+    bool valid;
+    const int id = bucket(c + l, valid);
+    const uint64_t peers = peer_mask(valid ? id : 0, valid, bits);
+    if (valid && lane_rank(peers) == 0) atomicAdd(&slot[w][id], (int32_t)__popcll(peers));
+  }
+  __syncthreads();
+  int32_t cnt = 0;
+  if (t < KB)
+    for (int v = 0; v < 16; ++v) cnt += slot[v][t];
+  int32_t total;
+  const int32_t first = block_excl_scan<int32_t>(cnt, sh, &total);
+  if (t < KB) {
+    int32_t run = first;
+    for (int v = 0; v < 16; ++v) {
+      const int32_t c = slot[v][t];
+      slot[v][t] = run;
+      run += c;
+    }
+    offsets[t] = first;  // offsets[K]: the out-of-range bucket starts where the experts end
+    if (t < K) counts[t] = cnt;
+  }
+  if (pieces) {
+    const int32_t pc = t < K ? (cnt + kSegPiece - 1) / kSegPiece : 0;
+    const int32_t at = block_excl_scan<int32_t>(pc, sh, &total);
+    if (t < KB) pieces[t] = at;
+  }
+  __syncthreads();
+  for (int c = i0; c < i1; c += 64) {
+    bool valid;
+    const int id = bucket(c + l, valid);
+    const uint64_t peers = peer_mask(valid ? id : 0, valid, bits);
+    if (valid) {
+      const int rank = lane_rank(peers);
+      const int32_t at = slot[w][id] + rank;
+      perm[at] = c + l;
+      inv[c + l] = at;
+      if (rank == 0) atomicAdd(&slot[w][id], (int32_t)__popcll(peers));  // after the peers' reads (same wave)
+    }
+  }
+}
+
 static int id_bits(int K) {
   int b = 0;
   while ((1 << b) < K) ++b;
@@ -213,12 +279,17 @@ size_t dispatch_ws(int64_t n, int32_t K) {
 }
 
 int launch_dispatch(const int32_t* e, int64_t n, int32_t K, int32_t* counts, int32_t* offsets,
-                    int32_t* perm, int32_t* inv, Workspace& ws, hipStream_t st) {
+                    int32_t* perm, int32_t* inv, Workspace& ws, hipStream_t st, int32_t* pieces) {
   const int64_t nb = cdiv(n, kIdsPerBlock);
   int32_t* bc = ws.take<int32_t>((size_t)(nb > 0 ? nb : 1) * (K + 1));
   if (!ws.fits()) return HMOE_EWORKSPACE;
   const int bits = id_bits(K + 1);  // ids 0 .. K (K: out of range)
   const size_t lds = 4 * (size_t)(K + 1) * sizeof(int32_t);
+  if (n <= kSortSmall && K <= kSortBuckets) {
+    HMOE_LAUNCH("dispatch", k_dispatch_small, dim3(1), dim3(1024), 0, st, e, (int)n, K, bits, counts, offsets, perm,
+                inv, pieces);
+    return HMOE_OK;
+  }
   if (nb > 0) {
     HMOE_LAUNCH("dispatch hist", k_dispatch_hist, dim3((unsigned)nb), dim3(256), lds, st, e, n, K, bits, bc,
                        (int32_t*)nullptr);
@@ -234,6 +305,7 @@ int launch_dispatch(const int32_t* e, int64_t n, int32_t K, int32_t* counts, int
     HMOE_LAUNCH("dispatch scatter", k_dispatch_scatter, dim3((unsigned)nb), dim3(256), lds, st, e, n, K, bits, bc,
                        offsets, perm, inv);
   }
+  if (pieces) HMOE_TRY(launch_seg_plan(offsets, K, SegPlan{{kSegPiece}, {pieces}, nullptr}, st));
   return HMOE_OK;
 }
 
@@ -304,6 +376,11 @@ int launch_sum_f32(const float* x, int64_t n, double scale, double* out_f64, flo
                    hipStream_t st) {
   double* part = ws.take<double>(kSumBlocks);
   if (!ws.fits()) return HMOE_EWORKSPACE;
+  if (n <= kSumSmall && !(out_f64 && out_f32)) {
+    if (out_f64) HMOE_LAUNCH("sum", (k_sum_small<float, double>), dim3(1), dim3(1024), 0, st, x, (int)n, scale, out_f64);
+    if (out_f32) HMOE_LAUNCH("sum", (k_sum_small<float, float>), dim3(1), dim3(1024), 0, st, x, (int)n, scale, out_f32);
+    return HMOE_OK;
+  }
   HMOE_LAUNCH("sum partial", k_sum_partial<float>, dim3(kSumBlocks), dim3(256), 0, st, x, n, part);
   if (out_f64) HMOE_LAUNCH("sum final", k_sum_final<double>, dim3(1), dim3(64), 0, st, part, scale, out_f64);
   if (out_f32) HMOE_LAUNCH("sum final", k_sum_final<float>, dim3(1), dim3(64), 0, st, part, scale, out_f32);

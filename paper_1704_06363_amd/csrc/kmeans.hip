@@ -16,6 +16,7 @@ namespace hmoe {
 // loads in flight (one at a time a row of 2048 was 32 dependent trips to memory: 16 us, 5 us now).
 // The order stays: a row between two centres goes to either with the last bit of a norm, and over
 // Lloyd iterations whole clusters go with it.
+// k_finalize_norm forms the same sum while it writes the centres.
 template <typename T>
 __global__ void __launch_bounds__(256) k_cnorm(const T* __restrict__ C, int K, int d, float* __restrict__ cn) {
   const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -274,10 +275,11 @@ static size_t assign_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) 
 
 template <class C>
 static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typename C::type* Cn, int32_t K,
-                    int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st) {
+                    int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st, const float* norms) {
   using T = typename C::type;
   const int nt = (int)cdiv(K, C::BN);
-  float* cn = ws.take<float>(K);
+  float* own = ws.take<float>(K);
+  const float* cn = norms ? norms : own;
   float *pv = nullptr, *xn = nullptr;
   int32_t* pi = nullptr;
   if (nt > 1) {
@@ -286,7 +288,8 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
     xn = ws.take<float>(n);
   }
   if (!ws.fits()) return HMOE_EWORKSPACE;
-  HMOE_LAUNCH("centre norms", k_cnorm<T>, dim3((unsigned)cdiv(K, 4)), dim3(256), 0, st, Cn, K, d, cn);
+  if (!norms)
+    HMOE_LAUNCH("centre norms", k_cnorm<T>, dim3((unsigned)cdiv(K, 4)), dim3(256), 0, st, Cn, K, d, own);
   if (n == 0) return HMOE_OK;
   const int64_t tiles = cdiv(n, C::BM) * nt;
   if constexpr (C::DMA)
@@ -302,21 +305,21 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
 }
 
 int launch_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, const void* C, int32_t K, int32_t* assign,
-                  float* min_dist, Workspace& ws, hipStream_t st) {
+                  float* min_dist, Workspace& ws, hipStream_t st, const float* norms) {
   const bool pipe = assign_pipe(d, dt, K);
   const bool few = cdiv(n, CfgDmaNarrow::BM) < device_cus();
   if (dt == HMOE_BF16) {
     const bf16 *x = (const bf16*)X, *c = (const bf16*)C;
-    if (K <= 64 && few) return assign_t<CfgDmaNarrowFew>(x, n, d, c, K, assign, min_dist, ws, st);
-    if (K <= 64) return assign_t<CfgDmaNarrow>(x, n, d, c, K, assign, min_dist, ws, st);
-    if (pipe) return assign_t<CfgPipe>(x, n, d, c, K, assign, min_dist, ws, st);
-    return assign_t<CfgSmall<bf16>>(x, n, d, c, K, assign, min_dist, ws, st);
+    if (K <= 64 && few) return assign_t<CfgDmaNarrowFew>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+    if (K <= 64) return assign_t<CfgDmaNarrow>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+    if (pipe) return assign_t<CfgPipe>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+    return assign_t<CfgSmall<bf16>>(x, n, d, c, K, assign, min_dist, ws, st, norms);
   }
   const float *x = (const float*)X, *c = (const float*)C;
-  if (K <= 64 && few) return assign_t<CfgDmaF32NarrowFew>(x, n, d, c, K, assign, min_dist, ws, st);
-  if (K <= 64) return assign_t<CfgDmaF32Narrow>(x, n, d, c, K, assign, min_dist, ws, st);
-  if (pipe) return assign_t<CfgPipeF32>(x, n, d, c, K, assign, min_dist, ws, st);
-  return assign_t<CfgSmall<float>>(x, n, d, c, K, assign, min_dist, ws, st);
+  if (K <= 64 && few) return assign_t<CfgDmaF32NarrowFew>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+  if (K <= 64) return assign_t<CfgDmaF32Narrow>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+  if (pipe) return assign_t<CfgPipeF32>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+  return assign_t<CfgSmall<float>>(x, n, d, c, K, assign, min_dist, ws, st, norms);
 }
 
 // ------------------------------------------------------------------ k-means++ seeding
@@ -845,18 +848,49 @@ __global__ void __launch_bounds__(256) k_finalize(const double* __restrict__ sum
   if (Cd) Cd[q] = from_f32<T>(c);
 }
 
+// The same for a fit's next assignment, with the centres' norms (of the data-precision copy, in
+// k_cnorm's order): one wave per centre.
+template <typename T>
+__global__ void __launch_bounds__(256) k_finalize_norm(const double* __restrict__ sums,
+                                                       const int64_t* __restrict__ counts, int K, int d,
+                                                       float* __restrict__ C, T* __restrict__ Cd,
+                                                       float* __restrict__ cn) {
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int l = threadIdx.x & 63;
+  if (k >= K) return;
+  const int64_t cnt = counts[k];
+  float s = 0.f;
+#pragma unroll 4
+  for (int j = l; j < d; j += 64) {
+    const int64_t q = (int64_t)k * d + j;
+    float c = C[q];
+    if (cnt > 0) c = (float)(sums[q] / (double)cnt);
+    C[q] = c;
+    const T lo = from_f32<T>(c);
+    if (Cd) Cd[q] = lo;
+    const float f = to_f32(lo);
+    s += f * f;
+  }
+  s = wave_sum(s);
+  if (l == 0) cn[k] = s;
+}
+
 // ------------------------------------------------------------------ fit / update drivers
 
 struct UpdateBufs {
-  int32_t *counts32, *offsets, *perm, *inv;
+  int32_t *counts32, *offsets, *perm, *inv, *pieces;
 };
+
+// Rows above which the reseeding's first search runs over the grid: one workgroup looks through
+// fewer in less than that launch takes, and only when a cluster is empty.
+constexpr int64_t kReseedGrid = 16384;
 
 template <typename T>
 static int update_core(const T* X, int64_t n, int32_t d, int32_t K, int32_t* assign, const float* d1,
                        double* sums, int64_t* counts64, int accumulate, int reseed, const UpdateBufs& b,
                        Workspace& ws, hipStream_t st) {
-  HMOE_TRY(launch_dispatch(assign, n, K, b.counts32, b.offsets, b.perm, b.inv, ws, st));
-  HMOE_TRY(launch_segsum<T, double>(X, d, b.perm, b.offsets, K, d, n, sums, accumulate, ws, st));
+  HMOE_TRY(launch_dispatch(assign, n, K, b.counts32, b.offsets, b.perm, b.inv, ws, st, b.pieces));
+  HMOE_TRY(launch_segsum<T, double>(X, d, b.perm, b.offsets, K, d, n, sums, accumulate, ws, st, b.pieces));
   if (accumulate) {
     HMOE_LAUNCH("add counts", k_add_counts, dim3((unsigned)cdiv(K, 256)), dim3(256), 0, st, b.counts32, K, counts64);
     return HMOE_OK;
@@ -864,7 +898,7 @@ static int update_core(const T* X, int64_t n, int32_t d, int32_t K, int32_t* ass
   float* pv = nullptr;
   int64_t* pi = nullptr;
   int np = 0;
-  if (reseed && n > 0) {
+  if (reseed && n > kReseedGrid) {
     np = (int)(cdiv(n, (int64_t)4096) < kReseedBlocks ? cdiv(n, (int64_t)4096) : kReseedBlocks);
     pv = ws.take<float>(np);
     pi = ws.take<int64_t>(np);
@@ -881,6 +915,7 @@ static size_t update_scratch(int64_t n, int32_t d, int32_t K) {
   Workspace ws(nullptr, 0);
   ws.take<int32_t>(K);
   ws.take<int32_t>(K + 1);
+  ws.take<int32_t>(K + 1);
   ws.take<int32_t>(n);
   ws.take<int32_t>(n);
   size_t s = ws.off + dispatch_ws(n, K) + segsum_ws(n, K, d) +
@@ -894,6 +929,7 @@ static int update_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t* assign
   UpdateBufs b;
   b.counts32 = ws.take<int32_t>(K);
   b.offsets = ws.take<int32_t>(K + 1);
+  b.pieces = ws.take<int32_t>(K + 1);
   b.perm = ws.take<int32_t>(n);
   b.inv = ws.take<int32_t>(n);
   if (!ws.fits()) return HMOE_EWORKSPACE;
@@ -938,6 +974,7 @@ size_t fit_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
   ws.take<double>(n);                       // D^2 for k-means++
   ws.take<double>(cdiv(n, kKppRows));       // block sums
   ws.take<int32_t>(K);                      // picks when the caller passes none
+  ws.take<float>(K);                        // centre norms
   size_t s = ws.off + update_scratch(n, d, K) + assign_ws_bytes(n, d, K, dt) + 4096;
   return s;
 }
@@ -997,18 +1034,20 @@ static int fit_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t n_iter, co
   Workspace* wsp = &ws;
   b.counts32 = wsp->take<int32_t>(K);
   b.offsets = wsp->take<int32_t>(K + 1);
+  b.pieces = wsp->take<int32_t>(K + 1);
   b.perm = wsp->take<int32_t>(n);
   b.inv = wsp->take<int32_t>(n);
   if (!ws.fits()) return HMOE_EWORKSPACE;
+  float* norms = ws.take<float>(K);
   const size_t mark = ws.off;
   for (int t = 0; t <= n_iter; ++t) {
     ws.off = mark;
-    HMOE_TRY(launch_assign(X, DT<T>::id, n, d, Cuse, K, assign, d1, ws, st));
+    HMOE_TRY(launch_assign(X, DT<T>::id, n, d, Cuse, K, assign, d1, ws, st, t > 0 ? norms : nullptr));
     if (objective) HMOE_TRY(launch_sum_f32(d1, n, 1.0, objective + t, nullptr, ws, st));
     if (t == n_iter) break;
     HMOE_TRY(update_core<T>(X, n, d, K, assign, d1, sums, c64, 0, reseed, b, ws, st));
-    HMOE_LAUNCH("finalize centres", (k_finalize<T, int64_t>), dim3((unsigned)cdiv(Kd, 256)), dim3(256), 0, st, sums, c64, K, d,
-                       C, same ? (T*)nullptr : Cd);
+    HMOE_LAUNCH("finalize centres", k_finalize_norm<T>, dim3((unsigned)cdiv(K, 4)), dim3(256), 0, st,
+                (const double*)sums, (const int64_t*)c64, K, d, C, same ? (T*)nullptr : Cd, norms);
   }
   if (counts) {
     ws.off = mark;

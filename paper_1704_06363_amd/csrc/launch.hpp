@@ -10,7 +10,8 @@ typedef __bf16 bf16;
 // dispatch.hip
 size_t dispatch_ws(int64_t n, int32_t K);
 int launch_dispatch(const int32_t* e, int64_t n, int32_t K, int32_t* counts, int32_t* offsets,
-                    int32_t* perm, int32_t* inv, Workspace& ws, hipStream_t st);
+                    int32_t* perm, int32_t* inv, Workspace& ws, hipStream_t st,
+                    int32_t* pieces = nullptr);  // K + 1: the buckets' table of kSegPiece-row pieces
 int launch_permute(const void* in, void* out, const int32_t* index, int64_t n, int32_t w,
                    hmoe_dtype_t dt, hipStream_t st);
 struct SegPlan;
@@ -51,7 +52,8 @@ size_t fit_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt);
 size_t fit_ws_copy_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt);
 size_t update_ws_bytes(int64_t n, int32_t d, int32_t K);
 int launch_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, const void* C, int32_t K,
-                  int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st);
+                  int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st,
+                  const float* norms = nullptr);  // |c_k|^2 as k_cnorm gives it
 int launch_fit(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t K, int32_t n_iter,
                const double* u, int32_t reseed, float* C, int32_t* assign, float* min_dist,
                int32_t* counts, double* objective, int32_t* init_idx, Workspace& ws, hipStream_t st);

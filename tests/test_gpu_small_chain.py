@@ -1,0 +1,56 @@
+"""The one-launch forms of short steps on both sides of the sizes where they end: the counting sort
+(8192 ids, 512 buckets), the objective's sum (16,384 rows), the reseeding's search (16,384 rows)
+and the centre norms that a fit's update leaves for its next assignment."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_1704_06363_amd import hmoe
+from paper_1704_06363_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 1023, 1025, 4096, 8191, 8192, 8193])
+@pytest.mark.parametrize("K", [1, 2, 50, 511, 512, 513])
+def test_dispatch(n, K):
+    ids = np.random.default_rng(n + K).integers(0, K, n).astype(np.int32)
+    if K > 1:
+        ids[ids == K // 2] = 0  # an empty bucket
+    out = hmoe.moe_dispatch(torch.from_numpy(ids).cuda(), K)
+    for got, ref in zip((out["counts"], out["offsets"], out["perm"], out["inv"]), O.dispatch(ids, K)):
+        assert np.array_equal(got.cpu().numpy(), ref)
+    # ids out of range follow every expert, in order
+    bad = ids.copy()
+    bad[:: 7] = np.where(np.arange(len(bad[:: 7])) % 2, -5, K + 3)
+    out = hmoe.moe_dispatch(torch.from_numpy(bad).cuda(), K)
+    key = np.where((bad < 0) | (bad >= K), K, bad)
+    assert np.array_equal(out["perm"].cpu().numpy(), np.argsort(key, kind="stable"))
+    assert np.array_equal(out["counts"].cpu().numpy(), np.bincount(key, minlength=K + 1)[:K])
+    assert int(out["offsets"][K]) == int((key < K).sum())
+
+
+@pytest.mark.parametrize("n,d,K,dtype", [(40, 16, 9, "f32"), (8192, 72, 50, "bf16"), (8193, 64, 300, "f32"),
+                                         (16384, 40, 64, "f32"), (16385, 40, 600, "bf16"), (20000, 1032, 3, "bf16")])
+def test_fit_is_its_steps(n, d, K, dtype):
+    """A fit and the same iterations through assign and update: the same bits (reseeding included: two
+    centres start far from every row)."""
+    X = W.gmm_features(n, d, 40, seed=n, dtype=dtype, device="cuda")
+    C = X[torch.randperm(n, generator=torch.Generator().manual_seed(1))[:K].cuda()].float().contiguous()
+    if K > 4:
+        C[1] = 1e3
+        C[3] = 2e3
+    out = hmoe.kmeans_fit(X, K, 3, C=C)
+    C2, obj = C.clone(), []
+    sums = torch.empty(K, d, dtype=torch.float64, device="cuda")
+    counts = torch.empty(K, dtype=torch.int64, device="cuda")
+    for t in range(4):
+        a, md = hmoe.kmeans_assign(X, C2.to(X.dtype))
+        obj.append(md.double().sum().item())
+        if t < 3:
+            hmoe.kmeans_update(X, K, a, md, sums, counts, C2)
+    assert torch.equal(out["C"], C2) and torch.equal(out["assign"], a) and torch.equal(out["min_dist"], md)
+    assert torch.equal(out["counts"].long(), torch.bincount(a.long(), minlength=K))
+    # sums of n non-negative terms in fp64, in two orders
+    assert np.allclose(out["objective"].cpu().numpy(), obj, rtol=n * 2.0 ** -52)
