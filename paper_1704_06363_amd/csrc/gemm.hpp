@@ -52,9 +52,10 @@ struct Cfg {
 // fp32 GEMMs and narrow problems: 128 x 128 tiles, four waves of 64 x 64.
 template <typename T>
 using CfgSmall = Cfg<T, 128, 128, 64, 64>;
-// Problems of few tiles: a quarter of the tile, two waves of 32 x 64.
+// Problems of few tiles: a quarter of the tile, four waves of 32 x 32 (two of 32 x 64 leave half of
+// a CU's matrix cores idle).
 template <typename T>
-using CfgQuarter = Cfg<T, 64, 64, 32, 64>;
+using CfgQuarter = Cfg<T, 64, 64, 32, 32>;
 __device__ __forceinline__ int swz(int row, int chunk) {
   return row * kStageRowBytes + ((chunk ^ ((row ^ (row >> 2)) & 7)) << 4);
 }
@@ -70,9 +71,11 @@ struct Stager {
   // K-contiguous: ROWS * 8 vectors of 16 bytes.
   // K-strided bf16: ROWS / 4 * 8 pieces of 8 K-rows x 4 rows, loaded as 8-byte rows.
   // K-strided fp32: ROWS / 4 * 8 blocks of 4 K-rows x 4 rows, loaded as 16-byte rows.
-  static constexpr int NPIECE = KCONTIG ? 0 : (ROWS / 4) * 8 / THREADS;
+  static constexpr int PIECES = (ROWS / 4) * 8;
+  static constexpr bool SPARE = PIECES < THREADS;  // the last threads have none
+  static constexpr int NPIECE = KCONTIG ? 0 : (SPARE ? 1 : PIECES / THREADS);
   static constexpr int NV = KCONTIG ? ROWS * 8 / THREADS : (BF ? NPIECE * 4 : NPIECE * 4);
-  static_assert(KCONTIG ? (ROWS * 8) % THREADS == 0 : ((ROWS / 4) * 8) % THREADS == 0, "tile/threads");
+  static_assert(KCONTIG ? (ROWS * 8) % THREADS == 0 : SPARE || PIECES % THREADS == 0, "tile/threads");
   i32x4 v[NV];
 
   // K-contiguous: element (r, k) at base + r * ld + k (k_valid a multiple of EPV).
@@ -96,6 +99,7 @@ struct Stager {
 #pragma unroll
       for (int q = 0; q < NPIECE; ++q) {
         const int pc = t + THREADS * q;
+        if (SPARE && pc >= PIECES) continue;
         const int r = (pc % RQ) * 4;
         const int kb = pc / RQ;  // which 16-byte chunk of the stage
         if constexpr (BF) {
@@ -135,6 +139,7 @@ struct Stager {
 #pragma unroll
       for (int q = 0; q < NPIECE; ++q) {
         const int pc = t + THREADS * q;
+        if (SPARE && pc >= PIECES) continue;
         const int r0 = (pc % RQ) * 4;
         const int kb = pc / RQ;
         if constexpr (BF) {

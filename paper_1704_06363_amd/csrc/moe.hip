@@ -895,27 +895,65 @@ __global__ void __launch_bounds__(256) k_colsum_final(const float* __restrict__ 
 }
 
 // dH = G D, written to expert order: dYs[inv[i]] = (G D)[i].  GW > 0: G is slab-major, [V / GW
-// slabs][n][GW] (direct-to-LDS engine only).
+// slabs][n][GW] (direct-to-LDS engine only).  split > 1: workgroup b takes chunk b % split of tile
+// b / split's reduction (`chunk` columns of G each, a multiple of the stage and of GW, none empty),
+// whose fp32 sums go to part[b] and are added in chunk order by k_dec_dH_reduce.
 template <class C, int GW = 0>
 __global__ void __launch_bounds__(C::THREADS)
     k_dec_dH(const typename C::type* __restrict__ G, const typename C::type* __restrict__ D, int64_t n, int V, int o,
-             const int32_t* __restrict__ inv, typename C::type* __restrict__ dYs) {
+             const int32_t* __restrict__ inv, typename C::type* __restrict__ dYs, int split, int chunk,
+             float* __restrict__ part) {
   using T = typename C::type;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds<char>* smem = (lds<char>*)smem_raw;
-  const TileCoord tc = tile_plain<C>(n, o, V);
+  const int64_t t = blockIdx.x / (unsigned)split;
+  const TileCoord tc = tile_plain_at<C>(n, o, V, t);
   if (!tc.valid) return;
+  const int v0 = (int)(blockIdx.x - t * split) * chunk;
+  const int vn = V - v0 < chunk ? V - v0 : chunk;
   floatx4 acc[C::MI][C::NJ];
   if constexpr (GW > 0) {
     static_assert(C::PIPE, "slab-major G on the pipelined engine");
     PipeTile<C, true, false, GW> pipe;
     pipe.slab_a(n * GW);
-    pipe.prime(G + tc.m0 * GW, GW, tc.m_rows, D + tc.n0, o, tc.n_cols, V, smem);
+    pipe.prime(G + (int64_t)(v0 / GW) * n * GW + tc.m0 * GW, GW, tc.m_rows, D + (int64_t)v0 * o + tc.n0, o, tc.n_cols,
+               vn, smem);
     pipe.run(smem, acc);
   } else {
-    gemm_tile<C, true, false>(G + tc.m0 * V, V, tc.m_rows, D + tc.n0, o, tc.n_cols, V, smem, acc);
+    gemm_tile<C, true, false>(G + tc.m0 * V + v0, V, tc.m_rows, D + (int64_t)v0 * o + tc.n0, o, tc.n_cols, vn, smem,
+                              acc);
   }
-  store_out<C, T>(tc, acc, smem, dYs, o, Ident{}, RowVia{inv, tc.m0}, NoVec{});
+  if (split > 1) {
+    TileCoord lt = tc;
+    lt.m0 = 0;
+    lt.n0 = 0;
+    store_out<C, float>(lt, acc, smem, part + (int64_t)blockIdx.x * (C::BM * C::BN), C::BN, Ident{}, RowId{0}, NoVec{});
+  } else {
+    store_out<C, T>(tc, acc, smem, dYs, o, Ident{}, RowVia{inv, tc.m0}, NoVec{});
+  }
+}
+
+// A thread per four columns.
+template <class C>
+__global__ void __launch_bounds__(256) k_dec_dH_reduce(const float* __restrict__ part, int64_t n, int V, int o,
+                                                       int split, const int32_t* __restrict__ inv,
+                                                       typename C::type* __restrict__ dYs) {
+  using T = typename C::type;
+  constexpr int TE = C::BM * C::BN;
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t t = idx / (TE / 4);
+  const int e = (int)(idx - t * (TE / 4)) * 4;
+  const TileCoord tc = tile_plain_at<C>(n, o, V, t);
+  const int i = e / C::BN, j = e % C::BN;
+  if (!tc.valid || i >= tc.m_rows || j >= tc.n_cols) return;
+  const float* p = part + t * split * TE + e;
+  floatx4 s = *reinterpret_cast<const floatx4*>(p);
+#pragma unroll 4
+  for (int c = 1; c < split; ++c) s += *reinterpret_cast<const floatx4*>(p + (int64_t)c * TE);
+  vec4<T> v;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = from_f32<T>(s[r]);
+  *reinterpret_cast<vec4<T>*>(dYs + (int64_t)inv[tc.m0 + i] * o + tc.n0 + j) = v;
 }
 
 // out [M][N] (fp32) = A^T B, reduction over `rows` rows (A [rows][M], B [rows][N], both
@@ -1003,6 +1041,28 @@ __global__ void __launch_bounds__(256) k_split_reduce(const float* __restrict__ 
   float s = 0.f;
   for (int c = 0; c < split; ++c) s += part[((int64_t)r * split + c) * TE + e];
   out[(tc.m0 + i) * (int64_t)N + tc.n0 + j] = s;
+}
+
+// Launches k_dec_dH.  Fewer tiles than half the CUs (o is narrow, V is not): each tile's reduction is
+// split so that the chunks fill the chip, in pieces of at least kChunk columns, below which writing
+// and adding the sums costs what the split saves.  5003 x 520, V = 10,008 bf16 (60 tiles): 165 us,
+// 66 and 11 for the sum in four chunks.  part: kMaxSplitItems tiles.
+template <class C, int GW = 0>
+static int launch_dH(const typename C::type* G, const typename C::type* D, int64_t n, int V, int o, const int32_t* inv,
+                     typename C::type* dYs, float* part, hipStream_t st) {
+  constexpr int kChunk = GW > 0 ? GW : (sizeof(typename C::type) == 4 ? 256 : 512);
+  const int64_t tiles = cdiv(n, C::BM) * cdiv(o, C::BN);
+  int64_t split = tiles > 0 ? device_cus() / tiles : 1;
+  if (split > cdiv(V, kChunk)) split = cdiv(V, kChunk);
+  if (split < 1) split = 1;
+  const int64_t chunk = cdiv(cdiv(V, split), kChunk) * kChunk;
+  split = cdiv(V, chunk);
+  HMOE_LAUNCH("decoder dH", (k_dec_dH<C, GW>), dim3((unsigned)(tiles * split)), dim3(C::THREADS), C::LDS, st, G, D, n, V,
+              o, inv, dYs, (int)split, (int)chunk, part);
+  if (split > 1)
+    HMOE_LAUNCH("decoder dH reduce", k_dec_dH_reduce<C>, dim3((unsigned)cdiv(tiles * (C::BM * C::BN / 4), 256)),
+                dim3(256), 0, st, (const float*)part, n, V, o, (int)split, inv, dYs);
+  return HMOE_OK;
 }
 
 // Launches k_gemm_tn_split (and its reduction) for out = A^T B; `part` holds kMaxSplitItems
@@ -1356,17 +1416,13 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
                 s.V, dbD);
   if constexpr (C::PIPE) {
     if (slab) {
-      HMOE_LAUNCH("decoder dH", (k_dec_dH<CK, GW>), dim3((unsigned)(mt * cdiv(s.o, C::BN))), dim3(C::THREADS),
-                  C::LDS, st, (const T*)G, D, n, s.V, s.o, inv, dYs);
+      HMOE_TRY((launch_dH<CK, GW>((const T*)G, D, n, s.V, s.o, inv, dYs, split_part, st)));
       HMOE_TRY(launch_tn_split<CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st, n * GW, GW));
     }
   }
   if (!slab) {
     HMOE_TRY(by_tile_count<T, CK>((int64_t)mt * cdiv(s.o, C::BN), [&](auto cfg) -> int {
-      using F = decltype(cfg);
-      HMOE_LAUNCH("decoder dH", k_dec_dH<F>, dim3((unsigned)(cdiv(n, F::BM) * cdiv(s.o, F::BN))), dim3(F::THREADS),
-                  F::LDS, st, (const T*)G, D, n, s.V, s.o, inv, dYs);
-      return HMOE_OK;
+      return launch_dH<decltype(cfg)>((const T*)G, D, n, s.V, s.o, inv, dYs, split_part, st);
     }));
     HMOE_TRY(launch_tn_split<CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st));
   }
