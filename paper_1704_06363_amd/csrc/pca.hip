@@ -220,7 +220,7 @@ struct SmallBufs {
   double *U, *dinv, *W, *de;  // kSmallN^2, kSmallN, kSmallN^2, 2 kSmallN
   SmallRot* rot;              // kRotGroups groups
   int32_t *k0, *order;
-  static constexpr int kRotGroups = 16384;
+  static constexpr int kRotGroups = 8192;
   explicit SmallBufs(Workspace ws)
       : U(ws.take<double>(kSmallN * kSmallN)), dinv(ws.take<double>(kSmallN)), W(ws.take<double>(kSmallN * kSmallN)),
         de(ws.take<double>(2 * kSmallN)), rot(ws.take<SmallRot>((size_t)kRotGroups * kRotGroup)),

@@ -49,6 +49,58 @@ __device__ __forceinline__ double small_lane(double v, int lane) {  // `lane` wa
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// 1 / sqrt(x) to fp64's last bits: the hardware's estimate and two Newton steps.
+__device__ __forceinline__ double small_rsqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double e = fma(-x * y, y, 1.0);
+    y = fma(0.5 * y, e, y);
+  }
+  return y;
+}
+
+struct CholLds {
+  double col[2][kSmallN], rroot[2];
+};
+
+// The columns of block kb (a constant, so that A stays in registers) and of those after it.
+template <int kb>
+__device__ __forceinline__ void chol_block(double (&A)[kSmallB][kSmallB], int r, double least, double* __restrict__ U,
+                                           double* __restrict__ dinv, int32_t* __restrict__ flag, CholLds& m) {
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
+  for (int kr = 0; kr < 32; ++kr) {
+    const int k = 32 * kb + kr;
+    if (k >= r) return;
+    double* c = m.col[k & 1];
+    if (tx == kr) {
+#pragma unroll
+      for (int a = kb; a < kSmallB; ++a) c[ty + 32 * a] = A[a][kb];
+      if (ty == kr) m.rroot[k & 1] = small_rsqrt(A[kb][kb]);
+    }
+    __syncthreads();  // the other buffer's readers are one barrier behind at most
+    const double piv = c[k];
+    if (!(piv > 0.0) || !(piv > least)) {
+      if (t == 0) *flag = 1;
+      return;
+    }
+    const double rs = m.rroot[k & 1];  // by one thread: by all, the root and its divisions were half of the step
+    if (t < kSmallN) U[(int64_t)k * kSmallN + t] = t > k ? c[t] * rs : 0.0;
+    if (t == 0) dinv[k] = rs;
+    const double w = -rs * rs;
+    double cj[kSmallB];
+#pragma unroll
+    for (int b = kb; b < kSmallB; ++b) cj[b] = c[tx + 32 * b];
+#pragma unroll
+    for (int a = kb; a < kSmallB; ++a) {
+      const double ci = c[ty + 32 * a] * w;
+#pragma unroll
+      for (int b = kb; b <= a; ++b) A[a][b] = fma(ci, cj[b], A[a][b]);
+    }
+  }
+  if constexpr (kb + 1 < kSmallB) chol_block<kb + 1>(A, r, least, U, dinv, flag, m);
+}
+
 // S (r x r, fp32) + shift I = L L^T, the shift 1e-12 of the mean diagonal: U[k][i] = L[i][k] (fp64,
 // ld kSmallN, 0 for i <= k and past r), dinv[k] = 1 / L[k][k].  A pivot (before its square root)
 // that is not above min_rel_pivot of the largest diagonal entry ends the factorisation and sets
@@ -57,7 +109,7 @@ __device__ __forceinline__ double small_lane(double v, int lane) {  // `lane` wa
 static __global__ void __launch_bounds__(1024) k_small_chol(const float* __restrict__ S, int r, double min_rel_pivot,
                                                             double* __restrict__ U, double* __restrict__ dinv,
                                                             int32_t* __restrict__ flag) {
-  __shared__ double col[2][kSmallN];
+  __shared__ CholLds m;
   __shared__ double s_tr, s_max;
   const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
   if (t < 64) {
@@ -87,36 +139,7 @@ static __global__ void __launch_bounds__(1024) k_small_chol(const float* __restr
       if (i < r && j < r) v = (double)S[(int64_t)(i > j ? i : j) * r + (i > j ? j : i)];
       A[a][b] = i == j ? v + shift : v;
     }
-#pragma unroll
-  for (int kb = 0; kb < kSmallB; ++kb)
-    for (int kr = 0; kr < 32; ++kr) {
-      const int k = 32 * kb + kr;
-      if (k >= r) return;
-      double* c = col[k & 1];
-      if (tx == kr) {
-#pragma unroll
-        for (int a = kb; a < kSmallB; ++a) c[ty + 32 * a] = A[a][kb];
-      }
-      __syncthreads();  // the other buffer's readers are one barrier behind at most
-      const double piv = c[k];
-      if (!(piv > 0.0) || !(piv > least)) {
-        if (t == 0) *flag = 1;
-        return;
-      }
-      const double root = sqrt(piv);
-      if (t < kSmallN) U[(int64_t)k * kSmallN + t] = t > k ? c[t] / root : 0.0;
-      if (t == 0) dinv[k] = 1.0 / root;
-      const double w = 1.0 / piv;
-      double cj[kSmallB];
-#pragma unroll
-      for (int b = kb; b < kSmallB; ++b) cj[b] = c[tx + 32 * b];
-#pragma unroll
-      for (int a = kb; a < kSmallB; ++a) {
-        const double ci = -c[ty + 32 * a] * w;
-#pragma unroll
-        for (int b = kb; b <= a; ++b) A[a][b] = fma(ci, cj[b], A[a][b]);
-      }
-    }
+  chol_block<0>(A, r, least, U, dinv, flag, m);
 }
 
 // Rinv (fp32, r x r) = R^-1 for R = L^T: its row j is column j of L^-1, by a wave each, lane l
@@ -126,21 +149,39 @@ static __global__ void __launch_bounds__(256) k_small_tri_inverse(const double* 
                                                                   float* __restrict__ Rinv) {
   const int j = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
   if (j >= r) return;
-  double x[4];
+  constexpr int P = 8;  // columns of L fetched ahead of their use (one by one: 72 us)
+  double x[4], dv[4], u[P][4], un[P][4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) x[q] = l + 64 * q == j ? 1.0 : 0.0;
-#pragma unroll
-  for (int kq = 0; kq < 4; ++kq) {
-    const int k1 = r - 64 * kq < 64 ? r - 64 * kq : 64;
-#pragma unroll 8
-    for (int kl = 0; kl < k1; ++kl) {
-      const int k = 64 * kq + kl;
-      const double xk = small_lane(x[kq], kl) * dinv[k];  // 0 until k = j
-#pragma unroll
-      for (int q = kq; q < 4; ++q) x[q] = fma(-U[(int64_t)k * kSmallN + l + 64 * q], xk, x[q]);
-      if (l == kl) x[kq] = xk;
-    }
+  for (int q = 0; q < 4; ++q) {
+    x[q] = l + 64 * q == j ? 1.0 : 0.0;
+    dv[q] = l + 64 * q < r ? dinv[l + 64 * q] : 0.0;
   }
+  const auto fetch = [&](double (&to)[P][4], int k0, int q0) {  // rows past r are not used
+#pragma unroll
+    for (int z = 0; z < P; ++z)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q >= q0) to[z][q] = U[(int64_t)(k0 + z < r ? k0 + z : r - 1) * kSmallN + l + 64 * q];
+  };
+  fetch(u, 0, 0);
+#pragma unroll
+  for (int kq = 0; kq < 4; ++kq)
+    for (int k0 = 0; k0 < 64; k0 += P) {
+      if (64 * kq + k0 >= r) break;
+      fetch(un, 64 * kq + k0 + P, kq);
+#pragma unroll
+      for (int z = 0; z < P; ++z) {
+        const int kl = k0 + z;
+        const double xk = small_lane(x[kq], kl) * small_lane(dv[kq], kl);  // 0 until k = j, and past r
+#pragma unroll
+        for (int q = kq; q < 4; ++q) x[q] = fma(-u[z][q], xk, x[q]);
+        if (l == kl) x[kq] = xk;
+      }
+#pragma unroll
+      for (int z = 0; z < P; ++z)
+#pragma unroll
+        for (int q = kq; q < 4; ++q) u[z][q] = un[z][q];
+    }
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     if (l + 64 * q < r) Rinv[(int64_t)j * r + l + 64 * q] = (float)x[q];
@@ -287,11 +328,19 @@ static __global__ void __launch_bounds__(1024) k_small_tridiag(const float* __re
 struct SmallRot {
   double c, s;
 };
-constexpr int kRotGroup = 8;  // rotations come in groups of consecutive k, the first k of each in k0
+constexpr int kRotGroup = 16;  // rotations come in groups of consecutive k, the first k of each in k0
 
 // Applies `groups` groups of rotations to the rows of V ([r][kSmallN], row k of column j at lane
 // j); `first` starts from the identity.  A wave per 64 columns, which sit in LDS; the rows past
-// r absorb the identity rotations that fill a group.
+// r absorb the identity rotations that fill a group.  Bound by the chain through a row that the
+// rotations of a step pass on: the coefficients are fetched two groups ahead (vector loads, the
+// same address in every lane: scalar ones could only be waited for together with the LDS
+// reads), and where a group follows on from the one before, its rows one group ahead.
+// r = 256: 1.8 ms (2.2 in groups of eight without that).
+struct RotCoef {
+  SmallRot q[kRotGroup];
+  int k;
+};
 static __global__ void __launch_bounds__(64) k_small_rotate(const SmallRot* __restrict__ rot,
                                                             const int32_t* __restrict__ k0, int groups, int r,
                                                             int first, double* __restrict__ V) {
@@ -300,35 +349,58 @@ static __global__ void __launch_bounds__(64) k_small_rotate(const SmallRot* __re
   const int l = threadIdx.x, j = blockIdx.x * 64 + l;
   for (int k = 0; k < kSmallN + kRotGroup; ++k)
     v[k * 64 + l] = first ? (k == j ? 1.0 : 0.0) : (k < r ? V[(int64_t)k * kSmallN + j] : 0.0);
-  // the next group's rotations are fetched ahead, as vector loads (the same address in every
-  // lane): scalar ones could only be waited for together with the LDS reads
   int zero = 0;
   asm volatile("" : "+v"(zero));
   rot += zero;
   k0 += zero;
-  SmallRot nq[kRotGroup];
+  const auto fetch = [&](RotCoef& c, int g) {
+    g = g < groups ? g : groups - 1;
 #pragma unroll
-  for (int z = 0; z < kRotGroup; ++z) nq[z] = rot[z];
-  int nk = k0[0];
-  for (int g = 0; g < groups; ++g) {
-    SmallRot q[kRotGroup];
+    for (int z = 0; z < kRotGroup; ++z) c.q[z] = rot[(int64_t)g * kRotGroup + z];
+    c.k = k0[g];
+  };
+  double x[kRotGroup + 1];
+  const auto step = [&](const RotCoef& c, const RotCoef& next) {
+    double* row = v + c.k * 64 + l;
+    const double* nrow = v + next.k * 64 + l;
+    const bool on = __builtin_amdgcn_readfirstlane(next.k - c.k) == kRotGroup;
+    double y[kRotGroup + 1];
+    if (on) {
 #pragma unroll
-    for (int z = 0; z < kRotGroup; ++z) q[z] = nq[z];
-    double* row = v + nk * 64 + l;
-    double x[kRotGroup + 1];
-#pragma unroll
-    for (int z = 0; z <= kRotGroup; ++z) x[z] = row[z * 64];
-    const int gn = g + 1 < groups ? g + 1 : g;
-#pragma unroll
-    for (int z = 0; z < kRotGroup; ++z) nq[z] = rot[(int64_t)gn * kRotGroup + z];
-    nk = k0[gn];
+      for (int z = 1; z <= kRotGroup; ++z) y[z] = nrow[z * 64];
+    }
 #pragma unroll
     for (int z = 0; z < kRotGroup; ++z) {
       const double a = x[z], b = x[z + 1];
-      row[z * 64] = q[z].c * a - q[z].s * b;
-      x[z + 1] = q[z].s * a + q[z].c * b;
+      row[z * 64] = c.q[z].c * a - c.q[z].s * b;
+      x[z + 1] = c.q[z].s * a + c.q[z].c * b;
     }
-    row[kRotGroup * 64] = x[kRotGroup];
+    if (!on) {
+      row[kRotGroup * 64] = x[kRotGroup];
+#pragma unroll
+      for (int z = 0; z <= kRotGroup; ++z) y[z] = nrow[z * 64];
+    } else {
+      y[0] = x[kRotGroup];
+    }
+#pragma unroll
+    for (int z = 0; z <= kRotGroup; ++z) x[z] = y[z];
+  };
+  if (groups > 0) {
+    RotCoef c0, c1, c2;
+    fetch(c0, 0);
+    fetch(c1, 1);
+#pragma unroll
+    for (int z = 0; z <= kRotGroup; ++z) x[z] = v[(c0.k + z) * 64 + l];
+    for (int g = 0; g < groups; g += 3) {  // past the last group c.k repeats: not followed on
+      fetch(c2, g + 2);
+      step(c0, c1);
+      if (g + 1 >= groups) break;
+      fetch(c0, g + 3);
+      step(c1, c2);
+      if (g + 2 >= groups) break;
+      fetch(c1, g + 4);
+      step(c2, c0);
+    }
   }
   for (int k = 0; k < r; ++k) V[(int64_t)k * kSmallN + j] = v[k * 64 + l];
 }
