@@ -88,7 +88,9 @@ int hmoe_kmeans_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, con
  *   C: float[K x d] in/out (fp32 master copy; a bf16 fit assigns against bf16(C)).
  *   assign: int32[n] out (final assignment).  min_dist: float[n] out or NULL.
  *   counts: int32[K] out or NULL.  objective: double[n_iter+1] out or NULL.
- *   init_idx: int32[K] out or NULL (k-means++ picks).  K <= n is required. */
+ *   init_idx: int32[K] out or NULL (k-means++ picks).  K <= n is required.
+ *   ws: the workspace size includes an 8-bit copy of X for the seeding of large data; a workspace
+ *     without those n (d + 20) bytes (d rounded up to 16) runs without it, with the same results. */
 size_t hmoe_kmeans_fit_workspace(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt);
 int hmoe_kmeans_fit(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t K,
                     int32_t n_iter, const double* init_uniforms, int32_t reseed_empty,

@@ -39,15 +39,61 @@ __device__ __forceinline__ float shfl_xor(float v, int m) { return __shfl_xor(v,
 __device__ __forceinline__ int shfl_xor(int v, int m) { return __shfl_xor(v, m, kWave); }
 __device__ __forceinline__ double shfl_xor(double v, int m) { return __shfl_xor(v, m, kWave); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
+// v of the lane that a DPP control names, within rows of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// v + v of the lane 32, or 16, away.
+template <bool HALVES>
+__device__ __forceinline__ float swap_add(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto x = HALVES ? __builtin_amdgcn_permlane32_swap(u, u, false, false)
+                        : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+}
+template <bool HALVES>
+__device__ __forceinline__ double swap_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+  const auto lo = HALVES ? __builtin_amdgcn_permlane32_swap(l, l, false, false)
+                         : __builtin_amdgcn_permlane16_swap(l, l, false, false);
+  const auto hi = HALVES ? __builtin_amdgcn_permlane32_swap(h, h, false, false)
+                         : __builtin_amdgcn_permlane16_swap(h, h, false, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+         __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+// The sum over a row of 16 lanes, in each of them: the rotations by 8, 4, 2, 1 pair the lanes as a
+// butterfly does (after a step the values repeat with its distance), so the bits are the same.
+template <typename V>
+__device__ __forceinline__ V row_sum(V v) {
+  v += dpp<0x128>(v);  // row_ror:8, 4, 2, 1
+  v += dpp<0x124>(v);
+  v += dpp<0x122>(v);
+  v += dpp<0x121>(v);
   return v;
 }
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += shfl_xor(v, m);
+// The same by distances 1, 2, 4, 8 (a quad's lanes swapped, then halves and rows mirrored).
+template <typename V>
+__device__ __forceinline__ V row_sum_up(V v) {
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0x141>(v);
+  v += dpp<0x140>(v);
   return v;
+}
+// The butterfly sum over a wave (distances 32 to 1) in registers: six trips through LDS took five
+// times as long.  Entered by whole waves.
+template <typename V>
+__device__ __forceinline__ V wave_sum(V v) {
+  return row_sum(swap_add<false>(swap_add<true>(v)));
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

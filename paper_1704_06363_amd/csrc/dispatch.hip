@@ -341,8 +341,9 @@ int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* 
     HMOE_TRY(launch_seg_plan(seg, G, SegPlan{{kSegPiece}, {own}, nullptr}, st));
     ts = own;
   }
-  HMOE_LAUNCH("segsum partial", k_segsum_partial<T>, dim3((unsigned)pieces), dim3(256), 0, st, X, ld, rowmap, seg, ts, G,
-                     w, part);
+  const int vecs = w / (16 / (int)sizeof(T));
+  const auto partial = vecs <= 256 ? k_segsum_partial<T, 1> : (vecs <= 512 ? k_segsum_partial<T, 2> : k_segsum_partial<T, kSegMaxVec>);
+  HMOE_LAUNCH("segsum partial", partial, dim3((unsigned)pieces), dim3(256), 0, st, X, ld, rowmap, seg, ts, G, w, part);
   HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
                      ts, G, w, out, accumulate);
   return HMOE_OK;

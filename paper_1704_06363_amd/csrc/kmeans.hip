@@ -351,9 +351,7 @@ __device__ __forceinline__ double kpp_dist(const T* __restrict__ x, const T* __r
       s += df * df;
     }
   }
-#pragma unroll
-  for (int m = 1; m < 16; m <<= 1) s += shfl_xor(s, m);
-  return s;
+  return row_sum_up(s);
 }
 
 // bsum[block] = sum of the block's D2 in row order, split over the first wave: lane l adds rows
@@ -376,7 +374,7 @@ __device__ __forceinline__ void kpp_block_sum(const double* rowv, double* __rest
 // same to the last bit: the margins below cover the rounding of the bound and of the distance.
 // Rows with entries that are not finite, or too large or small to square, have e = inf: they are
 // always measured.
-// 2^20 x 512 fp32, 64 centres: 23.4 ms -> 10.0 (142 us a pass, 1.06 ms for the first, which also writes
+// 2^20 x 512 fp32, 64 centres: 23.4 ms -> 8.5 (118 us a pass, 1.06 ms for the first, which also writes
 // the copy).
 struct KppMeta {
   float s, e;    // scale; upper bound of |x - s q|
@@ -459,31 +457,36 @@ __device__ __forceinline__ void kpp_quantise(const T* __restrict__ x, int64_t i,
   }
 }
 
-// Whether the bound says that row x is farther from centre c than sqrt(D2): P = q . q'.
-__device__ __forceinline__ bool kpp_far(const KppMeta& x, const KppMeta& c, int P, double D2) {
+// A lower bound of the distance of two rows by their copies, P = q . q'; negative, infinite or NaN
+// where there is none.
+__device__ __forceinline__ double kpp_bound(const KppMeta& x, const KppMeta& c, int P) {
   const double sx = x.s, sc = c.s;
   const double xx = sx * sx * (double)x.qq, cc = sc * sc * (double)c.qq;
   const double d2 = xx + cc - 2.0 * (sx * sc * (double)P) - 1e-12 * (xx + cc);
-  const double lb = (double)sqrtf((float)fmax(d2, 0.0)) * (1.0 - 1e-6) - (double)x.e - (double)c.e;
-  return lb > 1e-12 && lb * lb * (1.0 - 1e-6) > D2;  // false where a bound is inf or NaN
+  return (double)sqrtf((float)fmax(d2, 0.0)) * (1.0 - 1e-6) - (double)x.e - (double)c.e;
 }
+// Whether a distance of at least lb has a square above D2 (false for a bound that is none).
+__device__ __forceinline__ bool kpp_far(double lb, double D2) { return lb > 1e-12 && lb * lb * (1.0 - 1e-6) > D2; }
 
 // D2[i] = min(D2[i], |x_i - X[idx[t]]|^2) (fp64 direct differences; t == 0 initialises) and
 // bsum[b] = sum of D2 over the block's kKppRows rows, in a fixed order.  16 lanes share a row, so
-// each wave streams 4 rows at once and the block 16.  QUANT: also writes the rows' 8-bit copies.
-template <typename T, bool QUANT>
-__global__ void __launch_bounds__(256) k_kpp_update(const T* __restrict__ X, int64_t n, int d,
+// each wave streams 4 rows at once.  QUANT: also writes the rows' 8-bit copies.  THREADS: 256, or
+// 1024 where there are fewer blocks than CUs and a block's rows are a chain of memory latencies
+// (4096 x 64: 11 us, 4).
+template <typename T, bool QUANT, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_kpp_update(const T* __restrict__ X, int64_t n, int d,
                                                     const int32_t* __restrict__ idx, int t,
                                                     double* __restrict__ D2, double* __restrict__ bsum,
-                                                    int8_t* __restrict__ Xq, KppMeta* __restrict__ meta) {
+                                                    int8_t* __restrict__ Xq, KppMeta* __restrict__ meta,
+                                                    int32_t* __restrict__ near) {
   __shared__ double rowv[kKppRows];
   const int lane = threadIdx.x & 15;        // position inside the row group
-  const int grp = threadIdx.x >> 4;         // 16 row groups per block
+  const int grp = threadIdx.x >> 4;         // row groups per block
   const T* c = X + (int64_t)idx[t] * d;
   const int64_t r0 = (int64_t)blockIdx.x * kKppRows;
 #pragma unroll 2
-  for (int q = 0; q < kKppRows / 16; ++q) {
-    const int lr = q * 16 + grp;
+  for (int q = 0; q < kKppRows / (THREADS / 16); ++q) {
+    const int lr = q * (THREADS / 16) + grp;
     const int64_t i = r0 + lr;
     double s = 0.0;
     if (i < n) {
@@ -499,6 +502,7 @@ __global__ void __launch_bounds__(256) k_kpp_update(const T* __restrict__ X, int
           v = old < s ? old : s;
         }
         D2[i] = v;
+        if constexpr (QUANT) near[i] = 0;
       }
       rowv[lr] = v;
     }
@@ -507,48 +511,78 @@ __global__ void __launch_bounds__(256) k_kpp_update(const T* __restrict__ X, int
   kpp_block_sum(rowv, bsum);
 }
 
-// Pass t > 0 over the copy: the block's rows are sifted first, four at a time by each group of 16
-// lanes, and those that remain are measured by all groups.
+// cc[s] = lower bound of the distance of centres t and s < t, by 64 groups of 16 lanes.
+__device__ __forceinline__ void kpp_centre_bounds(const int8_t* __restrict__ Xq, const KppMeta* __restrict__ meta,
+                                                  const int32_t* __restrict__ idx, int64_t ct, int t, int d,
+                                                  float* __restrict__ cc) {
+  const int lane = threadIdx.x & 15;
+  const int64_t rb = kpp_row_bytes(d);
+  for (int s = threadIdx.x >> 4; s < t; s += 64) {
+    const int64_t c = idx[s];
+    int P = 0;
+    for (int v = lane; v < rb / 16; v += 16) {
+      const i32x4 x = *reinterpret_cast<const i32x4*>(Xq + c * rb + v * 16);
+      const i32x4 y = *reinterpret_cast<const i32x4*>(Xq + ct * rb + v * 16);
+#pragma unroll
+      for (int z = 0; z < 4; ++z) P = __builtin_amdgcn_sdot4(x[z], y[z], P, false);
+    }
+    P = row16_sum(P);
+    if (lane == 0) cc[s] = (float)(kpp_bound(meta[c], meta[ct], P) * (1.0 - 1e-6));
+  }
+}
+
+// Pass t > 0 over the copy.  A row whose nearest centre so far (near) is at least twice as far from
+// the new one as from the row keeps its D^2 without a look at it; the block's other rows are
+// sifted by the copy, four at a time by each group of 16 lanes, and those that remain are
+// measured by all groups.
 template <typename T>
 __global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const int8_t* __restrict__ Xq,
-                                                  const KppMeta* __restrict__ meta, int64_t n, int d,
-                                                  const int32_t* __restrict__ idx, int t, double* __restrict__ D2,
+                                                  const KppMeta* __restrict__ meta, const float* __restrict__ cc,
+                                                  int64_t n, int d, const int32_t* __restrict__ idx, int t,
+                                                  double* __restrict__ D2, int32_t* __restrict__ near,
                                                   double* __restrict__ bsum) {
   constexpr int U = 4;
   __shared__ double rowv[kKppRows];
-  __shared__ int32_t list[kKppRows];
-  __shared__ int32_t left;
-  if (threadIdx.x == 0) left = 0;
+  __shared__ int32_t list[2][kKppRows];
+  __shared__ int32_t left[2];
+  if (threadIdx.x < 2) left[threadIdx.x] = 0;
   __syncthreads();
   const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const int64_t r0 = (int64_t)blockIdx.x * kKppRows;
   const int64_t ci = idx[t];
+  static_assert(kKppRows == 256, "a thread per row");
+  double old = 0.0;  // past the last row
+  if (r0 + threadIdx.x < n) {
+    old = D2[r0 + threadIdx.x];
+    if (!kpp_far(cc[near[r0 + threadIdx.x]], 4.0 * old)) list[0][atomicAdd(&left[0], 1)] = threadIdx.x;
+  }
+  rowv[threadIdx.x] = old;
+  __syncthreads();
+  const int todo = left[0];
   const KppMeta cm = meta[ci];
   const int64_t rb = kpp_row_bytes(d);
   const int qv = (int)(rb / 16);
   const int8_t* cq = Xq + ci * rb;
-  for (int q = 0; q < kKppRows / 16; q += U) {
-    const int mine = (q + (lane & (U - 1))) * 16 + grp;  // the row this lane decides on
-    const int64_t im = r0 + mine;
-    KppMeta xm = cm;
-    double old = 0.0;
-    if (im < n) {
-      xm = meta[im];
-      old = D2[im];
-    }
+  for (int q = 0; q < todo; q += 16 * U) {
+    const int own = q + (lane & (U - 1)) * 16 + grp;  // the entry this lane decides on
+    const int mine = list[0][own < todo ? own : 0];
+    const KppMeta xm = meta[r0 + mine];
     int acc[U] = {0, 0, 0, 0};
+    const int8_t* x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int at = q + u * 16 + grp;
+      x[u] = Xq + (r0 + list[0][at < todo ? at : 0]) * rb;
+    }
     for (int v = lane; v < qv; v += 16) {
       const i32x4 c = *reinterpret_cast<const i32x4*>(cq + v * 16);
-      i32x4 x[U];
+      i32x4 xv[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t i = r0 + (q + u) * 16 + grp;
-        x[u] = *reinterpret_cast<const i32x4*>(Xq + (i < n ? i : ci) * rb + v * 16);
-      }
+      for (int u = 0; u < U; ++u) xv[u] = *reinterpret_cast<const i32x4*>(x[u] + v * 16);
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int z = 0; z < 4; ++z) acc[u] = __builtin_amdgcn_sdot4(x[u][z], c[z], acc[u], false);
+        for (int z = 0; z < 4; ++z) acc[u] = __builtin_amdgcn_sdot4(xv[u][z], c[z], acc[u], false);
     }
     int P = 0;
 #pragma unroll
@@ -556,22 +590,21 @@ __global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const
       const int a = row16_sum(acc[u]);
       P = (lane & (U - 1)) == u ? a : P;
     }
-    if (lane < U) {
-      rowv[mine] = old;  // 0 past the last row
-      if (im < n && !kpp_far(xm, cm, P, old)) list[atomicAdd(&left, 1)] = mine;
-    }
+    if (lane < U && own < todo && !kpp_far(kpp_bound(xm, cm, P), rowv[mine])) list[1][atomicAdd(&left[1], 1)] = mine;
   }
   __syncthreads();
-  const int cnt = left;
+  const int cnt = left[1];
   const T* c = X + ci * d;
   for (int q = grp; q < cnt; q += 16) {
-    const int lr = list[q];
+    const int lr = list[1][q];
     const double s = kpp_dist(X + (r0 + lr) * d, c, d, lane);
     if (lane == 0) {
-      const double old = rowv[lr];
-      const double v = old < s ? old : s;
-      D2[r0 + lr] = v;
-      rowv[lr] = v;
+      const double v = rowv[lr];
+      if (!(v < s)) {  // as min(): a NaN takes its place, too
+        D2[r0 + lr] = s;
+        near[r0 + lr] = t;
+        rowv[lr] = s;
+      }
     }
   }
   __syncthreads();
@@ -579,11 +612,14 @@ __global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const
 }
 
 // Picks centre t: the first row whose running D^2 sum exceeds u[t] * total (lowest unchosen row
-// if the total is zero).  One block of 1024 threads.
+// if the total is zero).  With the 8-bit copy, also bounds the centre's distances to the earlier ones
+// (cc).  One block of 1024 threads.
 __global__ void __launch_bounds__(1024) k_kpp_select(const double* __restrict__ D2, int64_t n,
                                                      const double* __restrict__ bsum, int nb,
                                                      const double* __restrict__ u, int t,
-                                                     int32_t* __restrict__ idx) {
+                                                     int32_t* __restrict__ idx, const int8_t* __restrict__ Xq,
+                                                     const KppMeta* __restrict__ meta, int d,
+                                                     float* __restrict__ cc) {
   __shared__ double sh[17], rowd[kKppRows], before;
   __shared__ int32_t pick;
   __shared__ int who, block;
@@ -657,6 +693,7 @@ __global__ void __launch_bounds__(1024) k_kpp_select(const double* __restrict__ 
     __syncthreads();
   }
   if (threadIdx.x == 0) idx[t] = pick;
+  if (Xq) kpp_centre_bounds(Xq, meta, idx, pick, t, d, cc);
 }
 
 // C[k][:] = X[idx[k]][:] as fp32, and Cd (the data-precision copy) when given.
@@ -954,15 +991,17 @@ int launch_update(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t 
 
 size_t update_ws_bytes(int64_t n, int32_t d, int32_t K) { return update_scratch(n, d, K); }
 
-// The seeding's 8-bit copy pays where a pass over X is a trip to memory, and the copy is read at
-// least twice.  Below 32 MB a pass over X runs out of the caches and the copy's first pass costs more.
+// The seeding's 8-bit copy pays where a pass over X is a trip to memory, and over enough passes to earn
+// its first one.  Seeding with the copy and without: 32 MB (90,000 x 96 fp32) 16 centres 347 / 450 us,
+// 16 MB 301 / 230, 8 MB 299 / 231; 2 GB (2^20 x 512) 64 centres 9.9 / 24.7 ms, 16 centres 5.0 / 6.7,
+// 8 centres 3.8 / 3.6.
 static bool kpp_copies(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
-  return K >= 4 && n * d * (int64_t)dtype_size(dt) >= (int64_t(32) << 20);
+  return K >= 16 && n * d * (int64_t)dtype_size(dt) >= (int64_t(32) << 20);
 }
 
 // What a fit needs, and the 8-bit copy on top of it (a fit in a smaller workspace goes without).
 size_t fit_ws_copy_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
-  return kpp_copies(n, d, K, dt) ? (size_t)n * (kpp_row_bytes(d) + sizeof(KppMeta)) + 512 : 0;
+  return kpp_copies(n, d, K, dt) ? (size_t)n * (kpp_row_bytes(d) + sizeof(KppMeta) + 4) + 4 * (size_t)K + 1024 : 0;
 }
 
 size_t fit_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
@@ -1001,26 +1040,34 @@ static int fit_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t n_iter, co
     // the copy lies past everything else in the workspace
     int8_t* Xq = nullptr;
     KppMeta* meta = nullptr;
+    int32_t* near = nullptr;
+    float* cc = nullptr;
     if (fit_ws_copy_bytes(n, d, K, DT<T>::id) > 0) {
       Workspace w(ws.base, ws.cap);
       w.off = fit_ws_bytes(n, d, K, DT<T>::id);
       Xq = w.take<int8_t>((size_t)n * kpp_row_bytes(d));
       meta = w.take<KppMeta>(n);
+      near = w.take<int32_t>(n);
+      cc = w.take<float>(K);
       if (!w.fits()) Xq = nullptr;
     }
     HMOE_LAUNCH("kmeans++ first", k_kpp_first, dim3(1), dim3(64), 0, st, u, n, idx);
     for (int t = 0; t < K; ++t) {
       if (Xq && t == 0)
-        HMOE_LAUNCH("kmeans++ D2", (k_kpp_update<T, true>), dim3((unsigned)nb), dim3(256), 0, st, X, n, d, idx, t, D2,
-                    bsum, Xq, meta);
+        HMOE_LAUNCH("kmeans++ D2", (k_kpp_update<T, true, 256>), dim3((unsigned)nb), dim3(256), 0, st, X, n, d, idx, t, D2,
+                    bsum, Xq, meta, near);
       else if (Xq)
         HMOE_LAUNCH("kmeans++ D2", k_kpp_sift<T>, dim3((unsigned)nb), dim3(256), 0, st, X, (const int8_t*)Xq,
-                    (const KppMeta*)meta, n, d, idx, t, D2, bsum);
-      else
-        HMOE_LAUNCH("kmeans++ D2", (k_kpp_update<T, false>), dim3((unsigned)nb), dim3(256), 0, st, X, n, d, idx, t, D2,
-                    bsum, (int8_t*)nullptr, (KppMeta*)nullptr);
+                    (const KppMeta*)meta, (const float*)cc, n, d, idx, t, D2, near, bsum);
+      else {
+        const bool few = nb < device_cus();
+        const auto update = few ? k_kpp_update<T, false, 1024> : k_kpp_update<T, false, 256>;
+        HMOE_LAUNCH("kmeans++ D2", update, dim3((unsigned)nb), dim3(few ? 1024 : 256), 0, st, X, n, d, idx, t, D2, bsum,
+                    (int8_t*)nullptr, (KppMeta*)nullptr, (int32_t*)nullptr);
+      }
       if (t + 1 < K) {
-        HMOE_LAUNCH("kmeans++ select", k_kpp_select, dim3(1), dim3(1024), 0, st, D2, n, bsum, nb, u, t + 1, idx);
+        HMOE_LAUNCH("kmeans++ select", k_kpp_select, dim3(1), dim3(1024), 0, st, D2, n, bsum, nb, u, t + 1, idx,
+                    (const int8_t*)Xq, (const KppMeta*)meta, d, cc);
       }
     }
     HMOE_LAUNCH("gather centres", k_gather_centres<T>, dim3((unsigned)cdiv(Kd, 256)), dim3(256), 0, st, X, d, idx, K, C,
