@@ -244,6 +244,35 @@ __device__ __forceinline__ void gemm_tile_reg(const typename C::type* __restrict
   }
   const int nk = (int)cdiv(k_len, C::BK);
   if (nk == 0) return;
+  if constexpr (C::BM * C::BN <= 64 * 64) {
+    // small tiles: a stage's MFMAs take less than the trip to memory, so loads run two stages ahead
+    static_assert(!ROWNORM, "row norms: larger tiles");
+    SA sa[2];
+    SB sb[2];
+    const auto load = [&](int s, int p) {
+      sa[p].load(A, lda, a_rows, s * C::BK, k_len);
+      sb[p].load(B, ldb, b_rows, s * C::BK, k_len);
+    };
+    const auto store = [&](int p) {
+      sa[p].store(smem + p * C::A_BYTES);
+      sb[p].store(smem + 2 * C::A_BYTES + p * C::B_BYTES);
+    };
+    load(0, 0);
+    if (nk > 1) load(1, 1);
+    store(0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; kt += 2) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {  // stage kt + p in buffer p; registers p are free, 1 - p hold the next
+        if (kt + p >= nk) break;
+        if (kt + p + 2 < nk) load(kt + p + 2, p);
+        mfma_stage<C>(smem + p * C::A_BYTES, smem + 2 * C::A_BYTES + p * C::B_BYTES, acc);
+        if (kt + p + 1 < nk) store(1 - p);
+        __syncthreads();
+      }
+    }
+    return;
+  }
   SA sa;
   SB sb;
   lds<char>* const bufA0 = smem;

@@ -1424,7 +1424,10 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
     HMOE_TRY(by_tile_count<T, CK>((int64_t)mt * cdiv(s.o, C::BN), [&](auto cfg) -> int {
       return launch_dH<decltype(cfg)>((const T*)G, D, n, s.V, s.o, inv, dYs, split_part, st);
     }));
-    HMOE_TRY(launch_tn_split<CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st));
+    // few chunks of whole tiles: quarter tiles, as above
+    HMOE_TRY(by_tile_count<T, CK>(cdiv(s.V, C::BM) * cdiv(s.o, C::BN) * cdiv(n, 256), [&](auto cfg) -> int {
+      return launch_tn_split<decltype(cfg)>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st);
+    }));
   }
   }
   // experts
