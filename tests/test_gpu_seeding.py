@@ -26,13 +26,13 @@ def _both(X, K, n_iter, seed):
     return with_copy, u
 
 
-# widths of one vector, of no whole 16-entry vector, and odd in both dtypes; 8 MB and up
-@pytest.mark.parametrize("n,d,K,dtype", [(20001, 120, 33, "f32"), (40000, 264, 16, "f32"), (20011, 1000, 17, "bf16"),
-                                         (131073, 128, 40, "bf16"), (300001, 8, 17, "f32")])
+# widths of one vector, of no whole 16-entry vector, and odd in both dtypes; 32 MB and up
+@pytest.mark.parametrize("n,d,K,dtype", [(70001, 120, 33, "f32"), (40000, 264, 16, "f32"), (20011, 1000, 17, "bf16"),
+                                         (131073, 128, 40, "bf16"), (1048577, 8, 17, "f32")])
 def test_copy_changes_nothing(n, d, K, dtype):
     X = W.gmm_features(n, d, 24, seed=n, dtype=dtype, device="cuda")
     out, u = _both(X, K, 2, n)
-    if n * K < 2_000_000:
+    if n * K < 3_000_000:
         assert out["init_idx"].tolist() == O.kmeanspp(np64(X), K, u).tolist()
 
 
