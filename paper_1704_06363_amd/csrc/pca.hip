@@ -229,7 +229,7 @@ struct SmallBufs {
 };
 
 // orthonormalise() without a trip to the host, r <= kSmallN: a block that loses rank sets *flag
-// (and leaves Q undefined).  r = 256, d = 512: 0.35 ms a pass (1.0 with the factor and the inverse on the host).
+// (and leaves Q undefined).  r = 256, d = 512: 0.26 ms a pass (1.0 with the factor and the inverse on the host).
 static int orthonormalise_gpu(float*& Q, float*& Z, int d, int r, float* S, float* Rinv, int passes, int32_t* flag,
                               Workspace& ws, hipStream_t st) {
   const SmallBufs b(ws);
@@ -248,7 +248,7 @@ static int orthonormalise_gpu(float*& Q, float*& Z, int d, int r, float* S, floa
 }
 
 // The eigenvectors of (S + S^T) / 2, r <= kSmallN, as the columns of V (fp32, r x r) in decreasing
-// order of their eigenvalues, which go to eigvals.  r = 256: 3.9 ms, 0.8 of it on the host (16 ms there).
+// order of their eigenvalues, which go to eigvals.  r = 256: 2.9 ms (16 on the host).
 static int ritz_gpu(const float* S, int r, float* V, float* eigvals, Workspace& ws, hipStream_t st) {
   const SmallBufs b(ws);
   if (!b.fits) return HMOE_EWORKSPACE;
@@ -257,34 +257,59 @@ static int ritz_gpu(const float* S, int r, float* V, float* eigvals, Workspace& 
   HMOE_TRY(d2h(de.data(), b.de, de.size() * sizeof(double), st));
   std::vector<double> d(de.begin(), de.begin() + r), e(r, 0.0);
   for (int i = 0; i + 1 < r; ++i) e[i] = de[kSmallN + i];
+  // the rotations go out in pieces while the next ones are formed; the host's copies of them stay
+  // until the device has read them (the vectors never grow past their room)
+  constexpr int kPiece = 1024;
+  constexpr int kRotLds = (kSmallN + kRotGroup) * 64 * (int)sizeof(double);
   std::vector<SmallRot> rot;
   std::vector<int32_t> k0;
-  rot.reserve((size_t)r * r * 2);
+  rot.reserve((size_t)SmallBufs::kRotGroups * kRotGroup);
+  k0.reserve(SmallBufs::kRotGroups);
+  size_t sent = 0;
+  bool first = true;
   const auto close = [&] { rot.resize(k0.size() * kRotGroup, SmallRot{1.0, 0.0}); };
+  const auto send = [&]() -> int {
+    const int m = (int)(k0.size() - sent);
+    if (m > 0) {
+      HMOE_TRY(hip_check(hipMemcpyAsync(b.rot + sent * kRotGroup, rot.data() + sent * kRotGroup,
+                                        (size_t)m * kRotGroup * sizeof(SmallRot), hipMemcpyHostToDevice, st),
+                         "pca: copy to device"));
+      HMOE_TRY(hip_check(hipMemcpyAsync(b.k0 + sent, k0.data() + sent, (size_t)m * sizeof(int32_t),
+                                        hipMemcpyHostToDevice, st),
+                         "pca: copy to device"));
+    }
+    HMOE_LAUNCH("pca rotations", k_small_rotate, dim3(kSmallN / 64), dim3(64), kRotLds, st,
+                (const SmallRot*)(b.rot + sent * kRotGroup), (const int32_t*)(b.k0 + sent), m, r, (int)first, b.W);
+    first = false;
+    sent = k0.size();
+    return HMOE_OK;
+  };
+  int rc = HMOE_OK;
   const bool ok = tridiag_eigen(
-      d, e, r, [&](int, int) { close(); },
+      d, e, r,
+      [&](int lo, int hi) {
+        close();
+        if (rc == HMOE_OK && k0.size() - sent >= kPiece) rc = send();
+        if (k0.size() + (hi - lo + kRotGroup - 1) / kRotGroup > SmallBufs::kRotGroups) {  // no room for this step
+          if (rc == HMOE_OK) rc = send();
+          if (rc == HMOE_OK) rc = hip_check(hipStreamSynchronize(st), "pca: synchronise");
+          rot.clear();
+          k0.clear();
+          sent = 0;
+        }
+      },
       [&](int k, double c, double s) {
         if (rot.size() == k0.size() * kRotGroup) k0.push_back(k);
         rot.push_back(SmallRot{c, s});
       });
-  if (!ok) {
+  close();
+  if (rc == HMOE_OK) rc = send();
+  if (rc != HMOE_OK || !ok) {
+    const int drained = hip_check(hipStreamSynchronize(st), "pca: synchronise");  // before the copies go
+    if (rc != HMOE_OK || drained != HMOE_OK) return rc != HMOE_OK ? rc : drained;
     set_error("pca: the eigensolve of the %d x %d Rayleigh-Ritz matrix did not converge", r, r);
     return HMOE_ENUMERIC;
   }
-  close();
-  constexpr int kRotLds = (kSmallN + kRotGroup) * 64 * (int)sizeof(double);
-  const size_t groups = k0.size();
-  size_t g = 0;
-  do {
-    const int m = (int)std::min(groups - g, (size_t)SmallBufs::kRotGroups);
-    if (m > 0) {
-      HMOE_TRY(h2d(b.rot, rot.data() + g * kRotGroup, (size_t)m * kRotGroup * sizeof(SmallRot), st));
-      HMOE_TRY(h2d(b.k0, k0.data() + g, (size_t)m * sizeof(int32_t), st));
-    }
-    HMOE_LAUNCH("pca rotations", k_small_rotate, dim3(kSmallN / 64), dim3(64), kRotLds, st, (const SmallRot*)b.rot,
-                (const int32_t*)b.k0, m, r, (int)(g == 0), b.W);
-    g += m;
-  } while (g < groups);
   std::vector<int32_t> ord(r);
   for (int i = 0; i < r; ++i) ord[i] = i;
   std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return d[x] > d[y]; });

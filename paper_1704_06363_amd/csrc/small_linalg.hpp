@@ -12,36 +12,6 @@ namespace hmoe {
 constexpr int kSmallN = 256;  // largest r, and the leading dimension of the fp64 scratch matrices
 constexpr int kSmallB = kSmallN / 32;
 
-// Sums over 16 lanes (DPP rotations) and over a wave (register swaps), without trips through LDS.
-__device__ __forceinline__ double small_pair(double v, uint32_t lo, uint32_t hi) {
-  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-template <int CTRL>
-__device__ __forceinline__ double small_ror(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  return small_pair(v, __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true),
-                    __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double small_sum32(double v) {  // over 32 lanes, in each of them
-  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
-  v = small_ror<0x128>(v);  // row_ror:8, 4, 2, 1
-  v = small_ror<0x124>(v);
-  v = small_ror<0x122>(v);
-  v = small_ror<0x121>(v);
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const u2v lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
-  const u2v hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-  return small_pair(__builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]), lo[1], hi[1]);
-}
-__device__ __forceinline__ double small_halves(double v) {  // lanes l and l ^ 32
-  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const u2v lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
-  const u2v hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-  return small_pair(__builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]), lo[1], hi[1]);
-}
-__device__ __forceinline__ double small_sum64(double v) { return small_halves(small_sum32(v)); }
-
 __device__ __forceinline__ double small_lane(double v, int lane) {  // `lane` wave-uniform
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
@@ -84,7 +54,7 @@ __device__ __forceinline__ void chol_block(double (&A)[kSmallB][kSmallB], int r,
       if (t == 0) *flag = 1;
       return;
     }
-    const double rs = m.rroot[k & 1];  // by one thread: by all, the root and its divisions were half of the step
+    const double rs = m.rroot[k & 1];  // by one thread: with root and divisions in all of them 216 us
     if (t < kSmallN) U[(int64_t)k * kSmallN + t] = t > k ? c[t] * rs : 0.0;
     if (t == 0) dinv[k] = rs;
     const double w = -rs * rs;
@@ -104,8 +74,9 @@ __device__ __forceinline__ void chol_block(double (&A)[kSmallB][kSmallB], int r,
 // S (r x r, fp32) + shift I = L L^T, the shift 1e-12 of the mean diagonal: U[k][i] = L[i][k] (fp64,
 // ld kSmallN, 0 for i <= k and past r), dinv[k] = 1 / L[k][k].  A pivot (before its square root)
 // that is not above min_rel_pivot of the largest diagonal entry ends the factorisation and sets
-// *flag.  One workgroup, right-looking, a barrier per column; bound by that chain and by the LDS
-// reads of the column.  r = 256: 216 us.
+// *flag.  One workgroup, right-looking, a barrier per column; bound by the LDS
+// reads of the column (publishing the next column before the other updates changes nothing;
+// two entries to a read needs registers that are not there: 251 us).  r = 256: 190 us.
 static __global__ void __launch_bounds__(1024) k_small_chol(const float* __restrict__ S, int r, double min_rel_pivot,
                                                             double* __restrict__ U, double* __restrict__ dinv,
                                                             int32_t* __restrict__ flag) {
@@ -223,7 +194,7 @@ __device__ __forceinline__ void tridiag_block(double (&A)[kSmallB][kSmallB], int
         s += x[q] * x[q];
       }
       const double x0 = m.u[k + 1];
-      const double xn = sqrt(small_sum64(s));
+      const double xn = sqrt(wave_sum(s));
       if (k + 2 >= r) {  // the last off-diagonal entry as it is
         if (l == 0) de[kSmallN + k] = x0;
       } else {
@@ -234,7 +205,7 @@ __device__ __forceinline__ void tridiag_block(double (&A)[kSmallB][kSmallB], int
           if (l + 64 * q == k + 1) x[q] -= alpha;
           s += x[q] * x[q];
         }
-        s = small_sum64(s);
+        s = wave_sum(s);
         const double sc = xn == 0.0 ? 0.0 : sqrt(2.0 / s);
         if (l == 0) de[kSmallN + k] = xn == 0.0 ? 0.0 : alpha;
 #pragma unroll
@@ -264,12 +235,12 @@ __device__ __forceinline__ void tridiag_block(double (&A)[kSmallB][kSmallB], int
         rs = fma(A[a][b], uj[b], rs);
         if (b < a) cs[b] = fma(A[a][b], ui, cs[b]);
       }
-      rs = small_sum32(rs);
+      rs = swap_add<false>(row_sum(rs));
       if (tx == 0) m.row[ty + 32 * a] = rs;
     }
 #pragma unroll
     for (int b = kb; b < kSmallB; ++b) {
-      cs[b] = small_halves(cs[b]);  // the wave's two rows ty
+      cs[b] = swap_add<true>(cs[b]);  // the wave's two rows ty
       if (l < 32) m.col[w][tx + 32 * b] = cs[b];
     }
     __syncthreads();
@@ -286,7 +257,7 @@ __device__ __forceinline__ void tridiag_block(double (&A)[kSmallB][kSmallB], int
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (l + 64 * q >= 32 * kb) s = fma(m.u[l + 64 * q], m.q[l + 64 * q], s);
-      s = small_sum64(s);
+      s = wave_sum(s);
       if (l == 0) m.half = 0.5 * s;
     }
     __syncthreads();
@@ -332,15 +303,11 @@ constexpr int kRotGroup = 16;  // rotations come in groups of consecutive k, the
 
 // Applies `groups` groups of rotations to the rows of V ([r][kSmallN], row k of column j at lane
 // j); `first` starts from the identity.  A wave per 64 columns, which sit in LDS; the rows past
-// r absorb the identity rotations that fill a group.  Bound by the chain through a row that the
-// rotations of a step pass on: the coefficients are fetched two groups ahead (vector loads, the
-// same address in every lane: scalar ones could only be waited for together with the LDS
-// reads), and where a group follows on from the one before, its rows one group ahead.
-// r = 256: 1.8 ms (2.2 in groups of eight without that).
-struct RotCoef {
-  SmallRot q[kRotGroup];
-  int k;
-};
+// r absorb the identity rotations that fill a group.  Bound by the one wave's instructions: a lane
+// fetches one of four groups' rotations, the next four while these run, and each is handed to all
+// lanes through scalar registers (a load of its own for each rotation, the same in every lane, took
+// longer than the rotation); where a group follows on from the one before, its rows are read ahead.
+// r = 256: 1.7 ms.
 static __global__ void __launch_bounds__(64) k_small_rotate(const SmallRot* __restrict__ rot,
                                                             const int32_t* __restrict__ k0, int groups, int r,
                                                             int first, double* __restrict__ V) {
@@ -349,57 +316,55 @@ static __global__ void __launch_bounds__(64) k_small_rotate(const SmallRot* __re
   const int l = threadIdx.x, j = blockIdx.x * 64 + l;
   for (int k = 0; k < kSmallN + kRotGroup; ++k)
     v[k * 64 + l] = first ? (k == j ? 1.0 : 0.0) : (k < r ? V[(int64_t)k * kSmallN + j] : 0.0);
-  int zero = 0;
-  asm volatile("" : "+v"(zero));
-  rot += zero;
-  k0 += zero;
-  const auto fetch = [&](RotCoef& c, int g) {
+  constexpr int GS = 64 / kRotGroup;  // groups per fetch
+  const auto fetch = [&](int g, SmallRot& q, int& k) {  // past the end: the last group again
+    g += l / kRotGroup;
     g = g < groups ? g : groups - 1;
-#pragma unroll
-    for (int z = 0; z < kRotGroup; ++z) c.q[z] = rot[(int64_t)g * kRotGroup + z];
-    c.k = k0[g];
+    q = rot[(int64_t)g * kRotGroup + l % kRotGroup];
+    k = k0[g];
   };
   double x[kRotGroup + 1];
-  const auto step = [&](const RotCoef& c, const RotCoef& next) {
-    double* row = v + c.k * 64 + l;
-    const double* nrow = v + next.k * 64 + l;
-    const bool on = __builtin_amdgcn_readfirstlane(next.k - c.k) == kRotGroup;
-    double y[kRotGroup + 1];
-    if (on) {
-#pragma unroll
-      for (int z = 1; z <= kRotGroup; ++z) y[z] = nrow[z * 64];
-    }
-#pragma unroll
-    for (int z = 0; z < kRotGroup; ++z) {
-      const double a = x[z], b = x[z + 1];
-      row[z * 64] = c.q[z].c * a - c.q[z].s * b;
-      x[z + 1] = c.q[z].s * a + c.q[z].c * b;
-    }
-    if (!on) {
-      row[kRotGroup * 64] = x[kRotGroup];
-#pragma unroll
-      for (int z = 0; z <= kRotGroup; ++z) y[z] = nrow[z * 64];
-    } else {
-      y[0] = x[kRotGroup];
-    }
-#pragma unroll
-    for (int z = 0; z <= kRotGroup; ++z) x[z] = y[z];
-  };
   if (groups > 0) {
-    RotCoef c0, c1, c2;
-    fetch(c0, 0);
-    fetch(c1, 1);
+    SmallRot q, nq;
+    int k, nk;
+    fetch(0, q, k);
+    const int f = __builtin_amdgcn_readlane(k, 0);
 #pragma unroll
-    for (int z = 0; z <= kRotGroup; ++z) x[z] = v[(c0.k + z) * 64 + l];
-    for (int g = 0; g < groups; g += 3) {  // past the last group c.k repeats: not followed on
-      fetch(c2, g + 2);
-      step(c0, c1);
-      if (g + 1 >= groups) break;
-      fetch(c0, g + 3);
-      step(c1, c2);
-      if (g + 2 >= groups) break;
-      fetch(c1, g + 4);
-      step(c2, c0);
+    for (int z = 0; z <= kRotGroup; ++z) x[z] = v[(f + z) * 64 + l];
+    for (int g = 0; g < groups; g += GS) {
+      fetch(g + GS, nq, nk);
+#pragma unroll
+      for (int i = 0; i < GS; ++i) {
+        if (g + i >= groups) break;
+        const int kc = __builtin_amdgcn_readlane(k, i * kRotGroup);
+        const int kn = i + 1 < GS ? __builtin_amdgcn_readlane(k, (i + 1) % GS * kRotGroup) : __builtin_amdgcn_readlane(nk, 0);
+        const bool on = kn - kc == kRotGroup;
+        double* row = v + kc * 64 + l;
+        const double* nrow = v + kn * 64 + l;
+        double y[kRotGroup + 1];
+        if (on) {
+#pragma unroll
+          for (int z = 1; z <= kRotGroup; ++z) y[z] = nrow[z * 64];
+        }
+#pragma unroll
+        for (int z = 0; z < kRotGroup; ++z) {
+          const double c = small_lane(q.c, i * kRotGroup + z), s = small_lane(q.s, i * kRotGroup + z);
+          const double a = x[z], b = x[z + 1];
+          row[z * 64] = c * a - s * b;
+          x[z + 1] = s * a + c * b;
+        }
+        if (on) {
+          y[0] = x[kRotGroup];
+        } else {
+          row[kRotGroup * 64] = x[kRotGroup];
+#pragma unroll
+          for (int z = 0; z <= kRotGroup; ++z) y[z] = nrow[z * 64];
+        }
+#pragma unroll
+        for (int z = 0; z <= kRotGroup; ++z) x[z] = y[z];
+      }
+      q = nq;
+      k = nk;
     }
   }
   for (int k = 0; k < r; ++k) V[(int64_t)k * kSmallN + j] = v[k * 64 + l];
@@ -425,7 +390,7 @@ static __global__ void __launch_bounds__(256) k_small_back(const double* __restr
       u[q] = refl[(int64_t)k * kSmallN + l + 64 * q];
       s = fma(u[q], x[q], s);
     }
-    s = small_sum64(s);
+    s = wave_sum(s);
 #pragma unroll
     for (int q = 0; q < 4; ++q) x[q] = fma(-u[q], s, x[q]);
   }
