@@ -342,8 +342,10 @@ int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* 
     ts = own;
   }
   const int vecs = w / (16 / (int)sizeof(T));
-  const auto partial = vecs <= 256 ? k_segsum_partial<T, 1> : (vecs <= 512 ? k_segsum_partial<T, 2> : k_segsum_partial<T, kSegMaxVec>);
-  HMOE_LAUNCH("segsum partial", partial, dim3((unsigned)pieces), dim3(256), 0, st, X, ld, rowmap, seg, ts, G, w, part);
+  const int nv = vecs <= 256 ? 1 : (vecs <= 512 ? 2 : kSegMaxVec);
+  const auto partial = nv == 1 ? k_segsum_partial<T, 1> : (nv == 2 ? k_segsum_partial<T, 2> : k_segsum_partial<T, kSegMaxVec>);
+  HMOE_LAUNCH("segsum partial", partial, dim3((unsigned)pieces, (unsigned)cdiv(vecs, 256 * nv)), dim3(256), 0, st, X, ld,
+              rowmap, seg, ts, G, w, part);
   HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
                      ts, G, w, out, accumulate);
   return HMOE_OK;

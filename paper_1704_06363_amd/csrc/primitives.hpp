@@ -120,9 +120,10 @@ __device__ __forceinline__ int find_segment(const int32_t* __restrict__ tile_sta
 // the pieces of each segment are added in a fixed order (k_segsum_final).
 
 constexpr int kSegPiece = 256;
-constexpr int kSegMaxVec = 4;  // vectors per thread: w <= 1024 * 16 / sizeof(T)
+constexpr int kSegMaxVec = 4;  // most vectors per thread
 
-// NV: vectors of a row per thread (a row of at most 256 NV).  With one, a thread's sums leave
+// NV: vectors of a row per thread.  Block (b, y) sums the 256 NV vectors of piece b's rows from vector
+// 256 NV y on (wider rows take several y).  With one, a thread's sums leave
 // registers for more waves and rows in flight: 5003 x 520 and x 2056
 // bf16 70 -> 61 us, 2^20 x 512 fp32 389 either way.
 template <typename T, int NV>
@@ -138,7 +139,9 @@ __global__ void __launch_bounds__(256) k_segsum_partial(const T* __restrict__ X,
   const int e = find_segment(tile_start, G, b);
   const int64_t r0 = seg[e] + (b - tile_start[e]) * kSegPiece;
   const int64_t r1 = (r0 + kSegPiece < seg[e + 1]) ? r0 + kSegPiece : seg[e + 1];
-  const int VPR = w / EPV;
+  const int first = blockIdx.y * 256 * NV;  // of this block's vectors
+  const int VPR = w / EPV - first;
+  X += first * EPV;
   const int t = threadIdx.x;
   const int RG = VPR >= 256 ? 1 : 256 / VPR;
   const int rg = VPR >= 256 ? 0 : t / VPR;
@@ -176,7 +179,7 @@ __global__ void __launch_bounds__(256) k_segsum_partial(const T* __restrict__ X,
       }
     }
   }
-  double* dst = part + b * (int64_t)w;
+  double* dst = part + b * (int64_t)w + first * EPV;
   if (RG == 1) {
     if (rg > 0) return;  // fewer than 256 vectors: the last threads have no column
 #pragma unroll
