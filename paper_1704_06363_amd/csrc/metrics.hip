@@ -72,28 +72,26 @@ __device__ __forceinline__ void emit_topm(float (&lv)[M], int (&li)[M], int m, i
   }
 }
 
-// The m-th largest over the lanes of x (with multiplicity): a bitonic sort of the 64 lanes in
-// registers, each merge starting with the mirrored pair (so that every step keeps the larger
-// value in the lower lane).  About 90 instructions; m rounds of a wave maximum take 16 m.
+// The m-th largest over the lanes of x (with multiplicity), m <= 16: each row of 16 lanes is sorted
+// (bitonic, each merge starting with the mirrored pair, so that every step keeps the larger value
+// in the lower lane), then the 16 largest of two rows are the larger ones of one row and the other
+// reversed, sorted again.  A step is a lane move and a median with +inf or -inf: about 50
+// instructions (130 in a full sort by selects of minima and maxima).
 template <int CTRL>
 __device__ __forceinline__ float dpp_of(float x) {
   return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
 }
+__device__ __forceinline__ float max_of(float a, float b) {  // one instruction, any NaN passed over
+  return __builtin_amdgcn_fmed3f(a, b, INFINITY);
+}
 __device__ __forceinline__ float mth_lane_value(float x, int m, int l) {
-  typedef unsigned int u2v __attribute__((ext_vector_type(2)));
-  const auto step = [&](float y, int bit) { x = (l & bit) ? fminf(x, y) : fmaxf(x, y); };
+  const auto step = [&](float y, int bit) {
+    x = __builtin_amdgcn_fmed3f(x, y, (l & bit) ? -INFINITY : INFINITY);  // the smaller : the larger
+  };
   const auto xor1 = [&] { step(dpp_of<0xB1>(x), 1); };           // quad_perm [1,0,3,2]
   const auto xor2 = [&] { step(dpp_of<0x4E>(x), 2); };           // quad_perm [2,3,0,1]
   const auto xor4 = [&] { step(dpp_of<0x1B>(dpp_of<0x141>(x)), 4); };  // half mirror, quad mirror
   const auto xor8 = [&] { step(dpp_of<0x128>(x), 8); };          // row_ror:8
-  const auto rows16 = [&](float y) {  // y from the lane 16 away
-    const u2v a = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-    return __uint_as_float((l & 16) ? a[0] : a[1]);
-  };
-  const auto rows32 = [&](float y) {  // y from the lane 32 away
-    const u2v a = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
-    return __uint_as_float((l & 32) ? a[0] : a[1]);
-  };
   xor1();
   step(dpp_of<0x1B>(x), 2);  // quad mirror
   xor1();
@@ -104,13 +102,16 @@ __device__ __forceinline__ float mth_lane_value(float x, int m, int l) {
   xor4();
   xor2();
   xor1();
-  step(rows16(dpp_of<0x140>(x)), 16);
+  // rows 0 and 2 take the best of rows 0, 1 and 2, 3
+  unsigned y = __float_as_uint(dpp_of<0x140>(x));
+  x = max_of(x, __uint_as_float(__builtin_amdgcn_permlane16_swap(y, y, false, false)[1]));
   xor8();
   xor4();
   xor2();
   xor1();
-  step(rows16(rows32(dpp_of<0x140>(x))), 32);
-  step(rows16(x), 16);
+  // row 0 the best of all
+  y = __float_as_uint(dpp_of<0x140>(x));
+  x = max_of(x, __uint_as_float(__builtin_amdgcn_permlane32_swap(y, y, false, false)[1]));
   xor8();
   xor4();
   xor2();
@@ -129,13 +130,15 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// One row's t_m by one wave, reading the whole row: r its entries, arow its anchors' four-slot
-// tiles (tile t at arow[t n]; NULL: the stored values are the entries).  U vectors in flight.
-template <typename T, int M, int U>
-__device__ __forceinline__ void topm_row(const T* __restrict__ r, const floatx4* __restrict__ arow, int64_t n, int V,
-                                         int m, int l, int64_t row, int32_t* __restrict__ idx,
-                                         float* __restrict__ val) {
+template <typename T, int M>
+__global__ void __launch_bounds__(256) k_topm(const T* __restrict__ L, int64_t n, int V, int m,
+                                              int32_t* __restrict__ idx, float* __restrict__ val) {
   constexpr int EPV = 16 / sizeof(T);
+  constexpr int U = 4;  // vectors in flight
+  const int l = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n) return;
+  const T* r = L + row * (int64_t)V;
   float lv[M];
   int li[M];
 #pragma unroll
@@ -153,18 +156,10 @@ __device__ __forceinline__ void topm_row(const T* __restrict__ r, const floatx4*
   int step = 0;
   for (int b0 = 0; b0 < nvec; b0 += 64 * U, ++step) {
     i32x4 raw[U];
-    float an[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int v = b0 + 64 * u + l;
-      an[u] = 0.f;
-      if (v < nvec) {
-        raw[u] = *reinterpret_cast<const i32x4*>(r + (int64_t)v * EPV);
-        if (arow) {
-          const int c = v * EPV;
-          an[u] = reinterpret_cast<const float*>(arow + (int64_t)(c / kAnchorTile) * n)[(c % kAnchorTile) / kAnchorCols];
-        }
-      }
+      if (v < nvec) raw[u] = *reinterpret_cast<const i32x4*>(r + (int64_t)v * EPV);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -175,17 +170,13 @@ __device__ __forceinline__ void topm_row(const T* __restrict__ r, const floatx4*
       float vmax = -INFINITY;
 #pragma unroll
       for (int z = 0; z < EPV; ++z) {
-        f[z] = arow ? an[u] + to_f32(e[z]) : to_f32(e[z]);
+        f[z] = to_f32(e[z]);
         vmax = fmaxf(vmax, f[z]);
       }
-      // the common case: nothing here enters (an unfilled slot also takes a -inf entry of
-      // anchored logits, whose rows may have fewer than m finite ones)
-      const bool open = arow && li[M - 1] == 0x7fffffff;
-      if (!(vmax >= thr && (vmax > lv[M - 1] || open))) continue;
+      if (!(vmax >= thr && vmax > lv[M - 1])) continue;  // the common case: nothing here enters
 #pragma unroll
       for (int z = 0; z < EPV; ++z)
-        if (f[z] >= thr && (f[z] > lv[M - 1] || (arow && f[z] == lv[M - 1] && li[M - 1] == 0x7fffffff)))
-          list_carry(lv, li, f[z], v * EPV + z);
+        if (f[z] >= thr && f[z] > lv[M - 1]) list_carry(lv, li, f[z], v * EPV + z);
     }
     // the m-th largest of the lanes' maxima: m lanes each hold an entry at least that large
     // (refreshed on the first steps, then every 4th: it settles quickly, and any value it
@@ -196,38 +187,36 @@ __device__ __forceinline__ void topm_row(const T* __restrict__ r, const floatx4*
   emit_topm(lv, li, m, l, row, idx, val);
 }
 
-template <typename T, int M>
-__global__ void __launch_bounds__(256) k_topm(const T* __restrict__ L, int64_t n, int V, int m,
-                                              int32_t* __restrict__ idx, float* __restrict__ val) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;
-  topm_row<T, M, 4>(L + row * (int64_t)V, nullptr, n, V, m, threadIdx.x & 63, row, idx, val);
-}
-
 // Anchored logits, one wave per row and eight adjacent rows per workgroup.  Block b (columns
 // [64 b, 64 b + 64)) of row i has its anchor at anc[((b / 4) n + i) 4 + b % 4], and every entry
 // of it is at most that anchor; the four anchors of a 256-column tile are one 16-byte vector, and
 // the eight rows' vectors one 128-byte line, which the workgroup's waves read at about the same
 // time.
-//   1. Lane l reads the tiles l, l + 64, ... of its row.  t0 = the m-th largest of the lanes'
-//      largest anchors: at least m blocks have an anchor >= t0.  Those blocks are listed in LDS
-//      (a few more than m: a lane that holds two of the largest lowers t0 a little).
-//   2. The listed blocks are read, a 16-byte vector per lane, several blocks at once.  t1 = the
+//   1. The workgroup stages the rows' anchors in LDS, whole lines, and lane l takes the tiles l, l + 64,
+//      ... of its wave's row.  The m-th largest of the lanes' largest anchors is a bound t0 that at
+//      least m blocks reach, and those are listed.  Neighbouring blocks are in one lane, so a
+//      vocabulary in order of frequency lists up to 4 m: with more than whole reads of m blocks need,
+//      t0 becomes the m-th largest of the listed anchors, and the blocks below it are dropped.
+//   2. The blocks are read, a 16-byte vector per lane, several blocks at once.  t1 = the
 //      m-th largest of the lanes' largest entries; the entries >= t1 (m and a few more) are
 //      collected in LDS, one per lane, and ranked by (value desc, index asc).
-//   3. Every entry outside the listed blocks is below t0, so t_m is among the listed ones when
-//      the m-th of them is >= t0.  With the forward's anchors (each its block's maximum, so each
-//      listed block holds an entry equal to its anchor) this is always the case.  Otherwise, and
-//      when the lists overflow (many equal anchors or entries), the wave reads the whole row.
+//   3. Every entry outside those blocks is below t0, so t_m is among theirs when the m-th of them is
+//      >= t0.  With the forward's anchors (each its block's maximum, so each block holds an entry
+//      equal to its anchor) this is always the case.
+//   4. Otherwise, and where a list overflows (equal anchors or entries, best entries in few blocks),
+//      the wave goes through the blocks in order, reads those whose anchor ranks before the
+//      m-th best entry so far, and keeps the entries that do (k_topm_anchored's `stream`).
 // The work per row is under a thousand vector instructions and two trips to memory (290 MB at
-// 65,536 x 50,000 bf16 logits and m = 10): 0.36 -> 0.11 ms there against a lane per row with
-// sorted lists of anchors, whose insertions every lane of a wave waits for, and 0.19 -> 0.01 ms
-// for 512 rows, which gave that kernel 8 workgroups.  Six waves per SIMD: four (no bound) take
-// 0.14 ms, eight 0.11 ms but spill the lists of the whole-row pass, which then takes 295 ms
-// instead of 2.5 on anchors above their blocks' entries (6.0 ms with sorted lists per lane).
+// 65,536 x 50,000 bf16 logits and m = 10).
+//   At 65,536 x 50,000 bf16, in us (a lane per row with sorted lists of anchors / a wave per row that
+//   reads its own anchors, a lane's 16 bytes a line apart / this): m = 10 on i.i.d. logits
+//   375 / 141 / 111, m = 1 69 / 84 / 54; logits -1.1 ln(rank) + 0.5 N(0, 1) m = 10 400 / 1540 / 124,
+//   and 1.0 N(0, 1) m = 16 659 / 2046 / 157 (whole rows where the candidates outnumbered a list of
+//   32); logits in steps of 4 (many equal anchors) 1431 / 3662 / 438; 512 rows 194 / 17 / 14.
 constexpr int kTopmWaves = 8;    // rows per workgroup
-constexpr int kTopmBlocks = 32;  // listed blocks at most
-constexpr int kTopmRegTiles = 4;  // anchor tiles a lane keeps between its two looks at them
+constexpr int kTopmBlocks = 32;  // blocks read at once at most
+constexpr int kTopmRegTiles = 4;  // anchor tiles of a lane in registers
+constexpr int kTopmLd = 64 * kTopmRegTiles + 2;  // 16 lanes' stores (8 rows of 2 tiles) in 16 bank groups
 
 template <typename T>
 __global__ void __launch_bounds__(64 * kTopmWaves, 6)
@@ -238,49 +227,63 @@ __global__ void __launch_bounds__(64 * kTopmWaves, 6)
   constexpr int BPR = 64 / VPB;                    // blocks a wave reads at once
   constexpr int ROUNDS = kTopmBlocks / BPR;
   static_assert(kAnchorSlots == 4, "one 16-byte anchor vector per tile");
-  __shared__ int32_t s_blk[kTopmWaves][kTopmBlocks];
-  __shared__ float s_anc[kTopmWaves][kTopmBlocks];
-  __shared__ float s_val[kTopmWaves][64];
-  __shared__ int32_t s_idx[kTopmWaves][64];
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * kTopmWaves + w;
-  if (row >= n) return;
+  __shared__ floatx4 s_tile[kTopmWaves][kTopmLd];
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t row0 = (int64_t)blockIdx.x * kTopmWaves, row = row0 + w;
   const int nb = (int)cdiv(V, kAnchorCols);
   const int nt = (int)cdiv(V, kAnchorTile);
   const floatx4* arow = reinterpret_cast<const floatx4*>(anc) + row;  // tile t at arow[t n]
-  const T* r = L + row * (int64_t)V;
-  // a tile's anchors, absent blocks as -inf
-  auto tile = [&](int t) {
-    floatx4 q = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    if (t < nt) {
-      q = arow[(int64_t)t * n];
+  {
+    const int sr = threadIdx.x % kTopmWaves, st = threadIdx.x / kTopmWaves;
+    const floatx4* from = reinterpret_cast<const floatx4*>(anc) + row0 + (row0 + sr < n ? sr : 0) + (int64_t)st * n;
+    floatx4 x[kTopmRegTiles];
 #pragma unroll
-      for (int sl = 0; sl < 4; ++sl)
-        if (4 * t + sl >= nb) q[sl] = -INFINITY;
-    }
-    return q;
+    for (int u = 0; u < kTopmRegTiles; ++u)
+      if (st + 64 * u < nt) x[u] = from[(int64_t)(64 * u) * n];
+#pragma unroll
+    for (int u = 0; u < kTopmRegTiles; ++u)
+      if (st + 64 * u < nt) s_tile[sr][st + 64 * u] = x[u];
+  }
+  __syncthreads();
+  if (row >= n) return;
+  const T* r = L + row * (int64_t)V;
+  const auto present = [&](floatx4 x, int t) {
+#pragma unroll
+    for (int sl = 1; sl < 4; ++sl) x[sl] = 4 * t + sl < nb ? x[sl] : NAN;
+    return x;
+  };
+  const auto tile = [&](int t) { return present(t < nt ? arow[(int64_t)t * n] : floatx4{NAN, NAN, NAN, NAN}, t); };
+  const auto top_of = [](float x, const floatx4& q) {
+    return max_of(max_of(max_of(max_of(x, q[0]), q[1]), q[2]), q[3]);
   };
   floatx4 q[kTopmRegTiles];
 #pragma unroll
-  for (int u = 0; u < kTopmRegTiles; ++u) q[u] = tile(l + 64 * u);
+  for (int u = 0; u < kTopmRegTiles; ++u) {
+    q[u] = s_tile[w][l + 64 * u];
+    q[u][0] = l + 64 * u < nt ? q[u][0] : NAN;
+    q[u] = present(q[u], l + 64 * u);
+  }
+  wave_lds_fence();
+  // the row's tiles are in registers: their place holds the lists
+  int32_t* s_blk = reinterpret_cast<int32_t*>(s_tile[w]);  // blocks: 64, in `stream` 256
+  float* s_anc = reinterpret_cast<float*>(s_blk + 256);
+  float* s_val = s_anc + 256;  // entries
+  int32_t* s_idx = reinterpret_cast<int32_t*>(s_val + 64);
   float top = -INFINITY;
 #pragma unroll
-  for (int u = 0; u < kTopmRegTiles; ++u) top = fmaxf(fmaxf(fmaxf(top, q[u][0]), fmaxf(q[u][1], q[u][2])), q[u][3]);
-  for (int t = 64 * kTopmRegTiles; t < nt; t += 64) {
-    const floatx4 x = tile(t + l);
-    top = fmaxf(fmaxf(fmaxf(top, x[0]), fmaxf(x[1], x[2])), x[3]);
-  }
-  const float t0 = mth_lane_value(top, m, l);
+  for (int u = 0; u < kTopmRegTiles; ++u) top = top_of(top, q[u]);
+  for (int t = 64 * kTopmRegTiles; t < nt; t += 64) top = top_of(top, tile(t + l));
+  float t0 = mth_lane_value(top, m, l);
   int listed = 0;  // wave-uniform
   auto list = [&](const floatx4& x, int t) {
 #pragma unroll
     for (int sl = 0; sl < 4; ++sl) {
-      const uint64_t hit = __ballot(4 * t + sl < nb && x[sl] >= t0);
+      const uint64_t hit = __ballot(x[sl] >= t0);
       if (hit == 0) continue;
       const int at = listed + lanes_below(hit);
-      if (((hit >> l) & 1) && at < kTopmBlocks) {
-        s_blk[w][at] = 4 * t + sl;
-        s_anc[w][at] = x[sl];
+      if (((hit >> l) & 1) && at < 64) {
+        s_blk[at] = 4 * t + sl;
+        s_anc[at] = x[sl];
       }
       listed += __popcll(hit);
     }
@@ -288,10 +291,51 @@ __global__ void __launch_bounds__(64 * kTopmWaves, 6)
 #pragma unroll
   for (int u = 0; u < kTopmRegTiles; ++u) list(q[u], l + 64 * u);
   for (int t = 64 * kTopmRegTiles; t < nt; t += 64) list(tile(t + l), t + l);
-  bool found = false;
-  if (listed <= kTopmBlocks) {
+  wave_lds_fence();
+  if (listed > (m + BPR - 1) / BPR * BPR && listed <= 64) {
+    const float a = l < listed ? s_anc[l] : -INFINITY;
+    const int32_t b = l < listed ? s_blk[l] : 0;
+    t0 = mth_lane_value(a, m, l);
+    const uint64_t keep = __ballot(l < listed && a >= t0);
     wave_lds_fence();
-    // the listed blocks, BPR at a time: lane l takes vector l % VPB of block l / VPB
+    if ((keep >> l) & 1) {
+      s_blk[lanes_below(keep)] = b;
+      s_anc[lanes_below(keep)] = a;
+    }
+    listed = __popcll(keep);
+    wave_lds_fence();
+  }
+  // The m-th of the `count` <= 64 entries listed, ranked by (value desc, index asc), as (vb, ib); `rank`
+  // of this lane's entry (v, i).
+  float vb = t0, v = 0.f;
+  int ib = INT32_MAX, i = 0, rank = 0;
+  const auto rank_entries = [&](int count) {
+    wave_lds_fence();
+    v = l < count ? s_val[l] : -INFINITY;
+    i = l < count ? s_idx[l] : INT32_MAX;
+    rank = 0;
+    for (int k = 0; k < count; ++k) {
+      const float ov = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), k));
+      const int oi = __builtin_amdgcn_readlane(i, k);
+      rank += (ov > v || (ov == v && oi < i)) ? 1 : 0;
+    }
+    const uint64_t last = __ballot(l < count && rank == m - 1);
+    if (last == 0) return false;
+    const int at = 63 - __builtin_clzll(last);
+    vb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), at));
+    ib = __builtin_amdgcn_readlane(i, at);
+    return true;
+  };
+  const auto emit = [&](int count) {
+    const int at = l < count ? rank : l;  // past the entries (a row with NaN): no index
+    if (at < m) {
+      idx[row * (int64_t)m + at] = i;
+      if (val) val[row * (int64_t)m + at] = v;
+    }
+  };
+  bool bounded = false;  // m entries rank at or before (vb, ib)
+  if (listed <= kTopmBlocks) {
+    // the blocks, BPR at a time: lane l takes vector l % VPB of block l / VPB
     float f[ROUNDS][EPV];
     int c0[ROUNDS];
     i32x4 raw[ROUNDS];
@@ -300,7 +344,7 @@ __global__ void __launch_bounds__(64 * kTopmWaves, 6)
       const int k = u * BPR + l / VPB;
       c0[u] = V;
       if (u * BPR < listed && k < listed) {
-        c0[u] = s_blk[w][k] * kAnchorCols + (l % VPB) * EPV;
+        c0[u] = s_blk[k] * kAnchorCols + (l % VPB) * EPV;
         if (c0[u] < V) raw[u] = *reinterpret_cast<const i32x4*>(r + c0[u]);
       }
     }
@@ -309,12 +353,12 @@ __global__ void __launch_bounds__(64 * kTopmWaves, 6)
     for (int u = 0; u < ROUNDS; ++u) {
       if (u * BPR >= listed) break;
       const int k = u * BPR + l / VPB;
-      const float a = k < listed ? s_anc[w][k] : 0.f;
+      const float a = k < listed ? s_anc[k] : 0.f;
       const T* e = reinterpret_cast<const T*>(&raw[u]);
 #pragma unroll
       for (int z = 0; z < EPV; ++z) {
-        f[u][z] = c0[u] < V ? a + to_f32(e[z]) : -INFINITY;
-        best = fmaxf(best, f[u][z]);
+        f[u][z] = c0[u] < V ? a + to_f32(e[z]) : NAN;  // absent: never listed
+        best = max_of(best, f[u][z]);
       }
     }
     const float t1 = mth_lane_value(best, m, l);
@@ -324,36 +368,96 @@ __global__ void __launch_bounds__(64 * kTopmWaves, 6)
       if (u * BPR >= listed) break;
 #pragma unroll
       for (int z = 0; z < EPV; ++z) {
-        const uint64_t hit = __ballot(c0[u] < V && f[u][z] >= t1);
+        const uint64_t hit = __ballot(f[u][z] >= t1);
         if (hit == 0) continue;
         const int at = kept + lanes_below(hit);
         if (((hit >> l) & 1) && at < 64) {
-          s_val[w][at] = f[u][z];
-          s_idx[w][at] = c0[u] + z;
+          s_val[at] = f[u][z];
+          s_idx[at] = c0[u] + z;
         }
         kept += __popcll(hit);
       }
     }
-    if (kept >= m && kept <= 64) {
-      wave_lds_fence();
-      const float v = l < kept ? s_val[w][l] : -INFINITY;
-      const int i = l < kept ? s_idx[w][l] : 0x7fffffff;
-      int rank = 0;
-      for (int k = 0; k < kept; ++k) {
-        const float ov = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), k));
-        const int oi = __builtin_amdgcn_readlane(i, k);
-        rank += (ov > v || (ov == v && oi < i)) ? 1 : 0;
+    if (kept <= 64) {
+      bounded = rank_entries(kept);
+      if (bounded && vb >= t0) {
+        emit(kept);
+        return;
       }
-      // the m-th found entry settles whether anything outside the listed blocks could rank
-      const uint64_t last = __ballot(l < kept && rank == m - 1 && v >= t0);
-      found = last != 0;
-      if (found && l < kept && rank < m) {
-        idx[row * (int64_t)m + rank] = i;
-        if (val) val[row * (int64_t)m + rank] = v;
-      }
+    } else {
+      vb = t1;
+      bounded = true;
     }
   }
-  if (!found) topm_row<T, 16, 1>(r, arow, n, V, m, l, row, idx, val);
+  // Goes through the blocks in order and lists the entries that rank before (vb, ib), which the m-th best
+  // one becomes whenever the list is full.  False when there are fewer than m (written if `last`).
+  const auto stream = [&](bool last) {
+    int count = 0;
+    const auto before = [&](float x, int j) { return x > vb || (x == vb && j < ib); };
+    for (int t = 0; t < nt; t += 64) {
+      const floatx4 x = tile(t + l);
+      uint64_t hit[4];
+      int total = 0, at = 0;
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl) {
+        hit[sl] = __ballot(before(x[sl], (4 * (t + l) + sl) * kAnchorCols));
+        at += lanes_below(hit[sl]);
+        total += __popcll(hit[sl]);
+      }
+      wave_lds_fence();
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl)
+        if ((hit[sl] >> l) & 1) {
+          s_blk[at] = 4 * (t + l) + sl;
+          s_anc[at++] = x[sl];
+        }
+      wave_lds_fence();
+      for (int k0 = 0; k0 < total; k0 += BPR) {
+        const int k = k0 + l / VPB;
+        const int b = k < total ? s_blk[k] : 0;
+        const float a = k < total ? s_anc[k] : NAN;
+        const int c = b * kAnchorCols + (l % VPB) * EPV;
+        const bool in = before(a, b * kAnchorCols) && c < V;
+        if (__ballot(in) == 0) continue;
+        i32x4 raw = {0, 0, 0, 0};
+        if (in) raw = *reinterpret_cast<const i32x4*>(r + c);
+        for (int z = 0; z < EPV; ++z) {
+          const int q = z * (int)sizeof(T) / 4;
+          const uint32_t word = (uint32_t)(q < 2 ? (q == 0 ? raw[0] : raw[1]) : (q == 2 ? raw[2] : raw[3]));
+          const uint32_t bits = sizeof(T) == 4 ? word : ((z & 1) ? word & 0xffff0000u : word << 16);
+          float f = in ? a + __uint_as_float(bits) : NAN;
+          for (;;) {
+            const uint64_t enter = __ballot(before(f, c + z));
+            const int at = count + lanes_below(enter), full = count + __popcll(enter);
+            if (((enter >> l) & 1) && at < 64) {
+              s_val[at] = f;
+              s_idx[at] = c + z;
+              f = NAN;
+            }
+            count = full < 64 ? full : 64;
+            if (full <= 64) break;
+            rank_entries(count);
+            wave_lds_fence();
+            if (rank < m) {
+              s_val[rank] = v;
+              s_idx[rank] = i;
+            }
+            count = m;
+          }
+        }
+      }
+    }
+    const bool found = rank_entries(count);
+    if (found || last) emit(count);
+    return found;
+  };
+  // entries equal to the bound count, but those of it that are behind the m-th one known
+  if (bounded && ib < INT32_MAX) ++ib;
+  if (stream(bounded) || bounded) return;
+  // t0 bounds anchors that are their blocks' maxima: here they are not
+  vb = -INFINITY;
+  ib = INT32_MAX;
+  stream(true);
 }
 
 // hits[0 .. m) for p, hits[m .. 2m) for q; must start at zero.

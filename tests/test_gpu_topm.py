@@ -91,6 +91,68 @@ def test_topm_anchored_forward_layout(n, V, m):
     np.testing.assert_array_equal(np64(val), np.take_along_axis(full, ref.astype(np.int64), axis=1))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,m", [(4096, 10), (4096, 16), (50000, 12), (50000, 16)])
+def test_topm_anchored_reads_only_blocks_that_can_reach(dtype, V, m):
+    """The best blocks are neighbours (a vocabulary in order of frequency), so whole tiles of four
+    lie above the m-th tile's maximum.  The entries of blocks whose anchor is below the m-th largest
+    one are poisoned with large offsets (which no forward writes): a pass that reads them shows."""
+    n = 70
+    rng = np.random.default_rng(V + m)
+    nb = (V + 63) // 64
+    L = rng.standard_normal((n, V)) * 0.01 - 1.1 * np.log1p(np.arange(V))[None, :]
+    A = np.full((n, nb), -np.inf)
+    for b in range(nb):
+        A[:, b] = L[:, b * 64:(b + 1) * 64].max(axis=1)
+    far = A < np.sort(A, axis=1)[:, -m][:, None] - 1e-3
+    assert far.sum() >= n * (nb - 2 * m)
+    Lg, An = anchored(L, torch.bfloat16 if dtype == "bf16" else torch.float32)
+    full = unanchored(Lg, An)
+    poison = torch.from_numpy(np.repeat(far, 64, axis=1)[:, :V]).cuda()
+    Lp = torch.where(poison, torch.full_like(Lg, 1000.0), Lg)
+    idx, val = hmoe.topm(Lp, m, want_values=True, anchor=An)
+    ref = O.topm(full, m)
+    assert np.array_equal(npi(idx), ref)
+    np.testing.assert_array_equal(np64(val), np.take_along_axis(full, ref.astype(np.int64), axis=1))
+
+
+@pytest.mark.parametrize("V,m,equal", [(8192, 10, 1), (50000, 16, 1), (50000, 16, 40), (50000, 10, 70),
+                                       (50000, 16, 782), (100000, 16, 1)])
+def test_topm_anchored_neighbouring_blocks(V, m, equal):
+    """Anchors that fall along the row, `equal` blocks on each level, in both directions: more
+    candidates than one per lane, ties at the m-th anchor, and (all equal) nothing to tell them by."""
+    n = 40
+    rng = np.random.default_rng(V + m + equal)
+    level = -(np.arange(V) // 64 // equal).astype(np.float64)
+    L = level[None, :] - rng.integers(0, 8, (n, V)) * 0.25
+    L[: n // 2] = L[: n // 2, ::-1]
+    Lg, An = anchored(L, torch.bfloat16)
+    idx, val = hmoe.topm(Lg, m, want_values=True, anchor=An)
+    full = unanchored(Lg, An)
+    ref = O.topm(full, m)
+    assert np.array_equal(npi(idx), ref)
+    np.testing.assert_array_equal(np64(val), np.take_along_axis(full, ref.astype(np.int64), axis=1))
+
+
+def test_topm_anchored_rows_with_too_few_numbers():
+    # NaN ranks nowhere: a row with fewer than m numbers lists those, then no index and -inf
+    n, V, m = 9, 1000, 6
+    L, A = anchored(np.random.default_rng(1).standard_normal((n, V)), torch.bfloat16)
+    keep = torch.zeros(n, V, dtype=torch.bool)
+    for row in range(1, n):
+        keep[row, torch.randperm(V, generator=torch.Generator().manual_seed(row))[: row - 1]] = True
+    keep[n - 1] = True
+    full = unanchored(L, A)
+    L[~keep.cuda()] = float("nan")
+    idx, val = hmoe.topm(L, m, want_values=True, anchor=A)
+    for row in range(n):
+        have = np.flatnonzero(keep[row].numpy())
+        ref = have[np.lexsort((have, -full[row][have]))][:m]
+        k = len(ref)
+        assert npi(idx)[row].tolist() == ref.tolist() + [2 ** 31 - 1] * (m - k)
+        assert np64(val)[row].tolist() == full[row][ref].astype(np.float64).tolist() + [-np.inf] * (m - k)
+
+
 def test_topm_anchored_full_size_sampled_rows():
     """The inference workload's shape and launch (65,536 x 50,000 bf16 logits in the forward's
     anchored layout, m = 10): 512 seeded rows against the oracle on their own entries, plus
