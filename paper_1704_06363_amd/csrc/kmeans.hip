@@ -994,9 +994,10 @@ size_t update_ws_bytes(int64_t n, int32_t d, int32_t K) { return update_scratch(
 // The seeding's 8-bit copy pays where a pass over X is a trip to memory, and over enough passes to earn
 // its first one.  Seeding with the copy and without: 32 MB (90,000 x 96 fp32) 16 centres 347 / 450 us,
 // 16 MB 301 / 230, 8 MB 299 / 231; 2 GB (2^20 x 512) 64 centres 9.9 / 24.7 ms, 16 centres 5.0 / 6.7,
-// 8 centres 3.8 / 3.6.
+// 8 centres 3.8 / 3.6.  Wider rows than kKppMaxWidth would overflow the integer sums.
+constexpr int32_t kKppMaxWidth = INT32_MAX / (127 * 127);  // 133,144
 static bool kpp_copies(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
-  return K >= 16 && n * d * (int64_t)dtype_size(dt) >= (int64_t(32) << 20);
+  return K >= 16 && d <= kKppMaxWidth && n * d * (int64_t)dtype_size(dt) >= (int64_t(32) << 20);
 }
 
 // What a fit needs, and the 8-bit copy on top of it (a fit in a smaller workspace goes without).

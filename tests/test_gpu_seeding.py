@@ -50,3 +50,22 @@ def test_copy_with_rows_it_cannot_hold():
     _both(X, K, 0, 8)
     X[900, 3] = float("nan")
     _both(X, K, 0, 9)
+
+
+@pytest.mark.parametrize("d", [133144, 133152, 140000])
+def test_rows_past_the_integer_sums_of_the_copy(d):
+    """From 133,152 columns on the squares of a row of 8-bit entries near 127 pass 2^31.  16 far
+    families of four rows, of which two have one larger entry and so smaller 8-bit entries (whose
+    squares do not): a family is picked twice only when the passes miss a distance."""
+    K, n = 16, 64
+    g = torch.Generator(device="cuda").manual_seed(d)
+    sign = torch.randint(0, 2, (K, 1, d), generator=g, device="cuda").float() * 2 - 1
+    X = (sign * (1 - 0.005 * torch.rand(K, 1, d, generator=g, device="cuda"))
+         + 1e-4 * torch.randn(K, 4, d, generator=g, device="cuda"))
+    X[:, 2:, 7] = 1.04
+    X = X.reshape(n, d).contiguous()
+    u = W.uniforms(K, 3)
+    ws = torch.empty(hmoe.kmeans_fit_workspace(n, d, K, X.dtype), dtype=torch.uint8, device="cuda")
+    out = hmoe.kmeans_fit(X, K, 0, init_uniforms=u, ws=ws)
+    assert out["init_idx"].tolist() == O.kmeanspp(np64(X), K, u).tolist()
+    assert len(set(i // 4 for i in out["init_idx"].tolist())) == K
