@@ -376,11 +376,19 @@ __device__ __forceinline__ void kpp_block_sum(const double* rowv, double* __rest
 // always measured.
 // 2^20 x 512 fp32, 64 centres: 23.4 ms -> 8.5 (118 us a pass, 1.06 ms for the first, which also writes
 // the copy).
+// Rows with a few entries far above the rest keep little of the others in 8 bits: e is of the order of the
+// distances, the bounds rule out nothing, and a pass that reads the copy and then X took 30% longer than
+// X alone (the same rows with one column at 300: 33.1 ms, 25.5 without a copy).  So a block of rows
+// is sifted only while that pays: it makes no copy (all e = inf but the first centre's) when most of its
+// first 16 rows have e > |x - c| / 8 against the first centre c, and after two passes in a row (the
+// third and later) in which the copy left too many of its rows, it skips 2, 4, ... 32 before it tries again.
+// (33.1 -> 24.1 ms there; mixtures and i.i.d. rows take the same as with the copy throughout.)
 struct KppMeta {
   float s, e;    // scale; upper bound of |x - s q|
   int32_t qq;    // |q|^2
-  int32_t pad;
+  int32_t wait;  // of a block's first row: 8 (first pass that is sifted) + passes in vain before it, up to 6
 };
+constexpr int32_t kKppNever = INT32_MAX;
 static_assert(sizeof(KppMeta) == 16, "one 16-byte load");
 
 __host__ __device__ __forceinline__ int64_t kpp_row_bytes(int d) { return (int64_t)((d + 15) & ~15); }
@@ -395,9 +403,9 @@ __device__ __forceinline__ int row16_sum(int v) {
 }
 
 // Row i's 8-bit copy; 16 lanes of a wave share the row, lane taking vectors lane, lane + 16, ...
-// of 16 entries (absent ones 0, up to the padded row).
+// of 16 entries (absent ones 0, up to the padded row).  Returns e.
 template <typename T>
-__device__ __forceinline__ void kpp_quantise(const T* __restrict__ x, int64_t i, int d, int lane,
+__device__ __forceinline__ float kpp_quantise(const T* __restrict__ x, int64_t i, int d, int lane,
                                              int8_t* __restrict__ Xq, KppMeta* __restrict__ meta) {
   constexpr int EPV = 16 / sizeof(T);
   constexpr int PER = 16 / EPV;  // source vectors per destination vector
@@ -447,14 +455,9 @@ __device__ __forceinline__ void kpp_quantise(const T* __restrict__ x, int64_t i,
 #pragma unroll
   for (int m = 1; m < 16; m <<= 1) r2 += shfl_xor(r2, m);
   qq = row16_sum(qq);
-  if (lane == 0) {
-    KppMeta mt;
-    mt.s = s;
-    mt.e = ok ? (float)(sqrt(r2) * (1.0 + 1e-6)) : INFINITY;
-    mt.qq = qq;
-    mt.pad = 0;
-    meta[i] = mt;
-  }
+  const float e = ok ? (float)(sqrt(r2) * (1.0 + 1e-6)) : INFINITY;
+  if (lane == 0) meta[i] = KppMeta{s, e, qq, 0};
+  return e;
 }
 
 // A lower bound of the distance of two rows by their copies, P = q . q'; negative, infinite or NaN
@@ -480,18 +483,38 @@ __global__ void __launch_bounds__(THREADS) k_kpp_update(const T* __restrict__ X,
                                                     int8_t* __restrict__ Xq, KppMeta* __restrict__ meta,
                                                     int32_t* __restrict__ near) {
   __shared__ double rowv[kKppRows];
+  __shared__ int poor;  // rows among the first 16 whose copy is of no use
   const int lane = threadIdx.x & 15;        // position inside the row group
   const int grp = threadIdx.x >> 4;         // row groups per block
   const T* c = X + (int64_t)idx[t] * d;
   const int64_t r0 = (int64_t)blockIdx.x * kKppRows;
-#pragma unroll 2
+  bool copies = true;
+  if constexpr (QUANT) {
+    if (threadIdx.x == 0) poor = 0;
+    __syncthreads();
+  }
+#pragma unroll(QUANT ? 1 : 2)
   for (int q = 0; q < kKppRows / (THREADS / 16); ++q) {
     const int lr = q * (THREADS / 16) + grp;
     const int64_t i = r0 + lr;
     double s = 0.0;
     if (i < n) {
       s = kpp_dist(X + i * d, c, d, lane);
-      if constexpr (QUANT) kpp_quantise(X + i * d, i, d, lane, Xq, meta);
+      if constexpr (QUANT) {
+        if (copies || i == idx[t]) {
+          const float e = kpp_quantise(X + i * d, i, d, lane, Xq, meta);
+          if (q == 0 && lane == 0 && !(64.0 * (double)e * (double)e <= s)) atomicAdd(&poor, 1);
+        } else if (lane == 0) {
+          meta[i] = KppMeta{0.f, INFINITY, 0, 0};
+        }
+      }
+    }
+    if constexpr (QUANT) {
+      if (q == 0) {
+        __syncthreads();
+        const int rows = n - r0 < THREADS / 16 ? (int)(n - r0) : THREADS / 16;
+        copies = 4 * poor < 3 * rows;
+      }
     }
     if (lane == 0) {
       double v = 0.0;
@@ -506,6 +529,9 @@ __global__ void __launch_bounds__(THREADS) k_kpp_update(const T* __restrict__ X,
       }
       rowv[lr] = v;
     }
+  }
+  if constexpr (QUANT) {
+    if (threadIdx.x == 0 && !copies) meta[r0].wait = kKppNever;  // the thread that wrote meta[r0]
   }
   __syncthreads();
   kpp_block_sum(rowv, bsum);
@@ -533,11 +559,12 @@ __device__ __forceinline__ void kpp_centre_bounds(const int8_t* __restrict__ Xq,
 
 // Pass t > 0 over the copy.  A row whose nearest centre so far (near) is at least twice as far from
 // the new one as from the row keeps its D^2 without a look at it; the block's other rows are
-// sifted by the copy, four at a time by each group of 16 lanes, and those that remain are
-// measured by all groups.
+// sifted by the copy, four at a time by each group of 16 lanes, unless the block waits or the centre
+// has no copy, and those that remain are measured by all groups.  The copy has paid when it left at most
+// the share of the rows read whose bytes it saved: 3/4 of fp32 rows, 1/2 of bf16 rows.
 template <typename T>
 __global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const int8_t* __restrict__ Xq,
-                                                  const KppMeta* __restrict__ meta, const float* __restrict__ cc,
+                                                  KppMeta* __restrict__ meta, const float* __restrict__ cc,
                                                   int64_t n, int d, const int32_t* __restrict__ idx, int t,
                                                   double* __restrict__ D2, int32_t* __restrict__ near,
                                                   double* __restrict__ bsum) {
@@ -560,10 +587,12 @@ __global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const
   __syncthreads();
   const int todo = left[0];
   const KppMeta cm = meta[ci];
+  const int32_t wait = meta[r0].wait;
+  const bool sift = t >= wait / 8 && cm.e < INFINITY;
   const int64_t rb = kpp_row_bytes(d);
   const int qv = (int)(rb / 16);
   const int8_t* cq = Xq + ci * rb;
-  for (int q = 0; q < todo; q += 16 * U) {
+  for (int q = 0; sift && q < todo; q += 16 * U) {
     const int own = q + (lane & (U - 1)) * 16 + grp;  // the entry this lane decides on
     const int mine = list[0][own < todo ? own : 0];
     const KppMeta xm = meta[r0 + mine];
@@ -593,10 +622,17 @@ __global__ void __launch_bounds__(256) k_kpp_sift(const T* __restrict__ X, const
     if (lane < U && own < todo && !kpp_far(kpp_bound(xm, cm, P), rowv[mine])) list[1][atomicAdd(&left[1], 1)] = mine;
   }
   __syncthreads();
-  const int cnt = left[1];
+  const int cnt = sift ? left[1] : todo;
+  const int32_t* rows = list[sift ? 1 : 0];
+  if (threadIdx.x == 0 && sift && todo >= 64) {
+    const bool vain = t > 2 && cnt * (int)sizeof(T) > todo * ((int)sizeof(T) - 1);
+    const int32_t tries = !vain ? 0 : (wait % 8 < 6 ? wait % 8 + 1 : 6);
+    const int32_t next = (t + (tries < 2 ? 1 : 1 + (1 << (tries - 1)))) * 8 + tries;
+    if (vain || wait % 8 != 0) meta[r0].wait = next;
+  }
   const T* c = X + ci * d;
   for (int q = grp; q < cnt; q += 16) {
-    const int lr = list[1][q];
+    const int lr = rows[q];
     const double s = kpp_dist(X + (r0 + lr) * d, c, d, lane);
     if (lane == 0) {
       const double v = rowv[lr];
@@ -1059,7 +1095,7 @@ static int fit_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t n_iter, co
                     bsum, Xq, meta, near);
       else if (Xq)
         HMOE_LAUNCH("kmeans++ D2", k_kpp_sift<T>, dim3((unsigned)nb), dim3(256), 0, st, X, (const int8_t*)Xq,
-                    (const KppMeta*)meta, (const float*)cc, n, d, idx, t, D2, near, bsum);
+                    meta, (const float*)cc, n, d, idx, t, D2, near, bsum);
       else {
         const bool few = nb < device_cus();
         const auto update = few ? k_kpp_update<T, false, 1024> : k_kpp_update<T, false, 256>;

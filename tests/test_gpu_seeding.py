@@ -52,6 +52,39 @@ def test_copy_with_rows_it_cannot_hold():
     _both(X, K, 0, 9)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["spikes", "half spikes", "far first centre"])
+def test_copy_that_cannot_help(dtype, kind):
+    """One large entry in each row leaves nothing of the others in 8 bits: no copy is made past the first
+    16 rows of each block of 256 that has such rows, and the outputs are the same.  Against a first centre
+    far from all others the copies look useful, and no pass is helped by them."""
+    n, d, K = 40000, 264 if dtype == "f32" else 520, 40
+    g = torch.Generator(device="cuda").manual_seed(4)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    u = W.uniforms(K, 5)
+    u[0] = 0.1  # the first centre: a row with a large entry
+    spiky = torch.zeros(n, dtype=torch.bool, device="cuda")
+    if kind == "far first centre":
+        X = 100.0 + 0.01 * X if dtype == "f32" else X.sign() + 0.01 * X
+        X[int(u[0] * n)] = 0.0 if dtype == "f32" else 300.0
+    else:
+        spiky[: n if kind == "spikes" else 20224] = True  # whole blocks
+        X[spiky, 3] = 300.0
+    X = X.to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    d16 = -(-d // 16) * 16
+    size = hmoe.kmeans_fit_workspace(n, d, K, X.dtype)
+    ws = torch.full((size,), 0xAB, dtype=torch.uint8, device="cuda")
+    first = -(-(size - n * (d16 + 20) - 4 * K - 1024) // 256) * 256  # the copy lies past all else
+    out = hmoe.kmeans_fit(X, K, 0, init_uniforms=u, ws=ws)
+    written = (ws[first:first + n * d16].view(n, d16) != 0xAB).any(1)
+    row = torch.arange(n, device="cuda")
+    assert bool(written[~spiky].all())
+    assert int(written[spiky & (row % 256 >= 16)].sum()) <= 1  # the first centre
+    without = hmoe.kmeans_fit(X, K, 0, init_uniforms=u, ws=ws[: size - n * (d16 + 20)])
+    for k in out:
+        assert torch.equal(out[k].view(torch.uint8), without[k].view(torch.uint8)), k
+
+
 @pytest.mark.parametrize("d", [133144, 133152, 140000])
 def test_rows_past_the_integer_sums_of_the_copy(d):
     """From 133,152 columns on the squares of a row of 8-bit entries near 127 pass 2^31.  16 far
