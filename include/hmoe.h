@@ -14,7 +14,9 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Every call is
  *     asynchronous on that stream and performs no host synchronisation.
  *   - Scratch memory comes from the caller through (ws, ws_bytes); the matching *_workspace()
- *     call returns the number of bytes needed (0 is a valid answer; ws may then be NULL).
+ *     call returns the number of bytes to give (0 is a valid answer; ws may then be NULL).
+ *     hmoe_kmeans_fit, hmoe_moe_forward and hmoe_moe_backward also run in less, down to what they
+ *     cannot do without, only slower: the rest holds copies and tables that save time.
  *   - Matrices are row-major.  Real tensors are HMOE_F32 (float) or HMOE_BF16 (bfloat16,
  *     round-to-nearest-even on store); accumulation is always fp32 or wider.
  *   - Row widths (d, d_hid, d_out, vocab for the decoder) must be multiples of 8 and device
@@ -52,7 +54,7 @@ enum {
   HMOE_EINVAL = -1,     /* NULL required pointer, negative size, K out of range */
   HMOE_EDTYPE = -2,     /* unknown dtype */
   HMOE_ESHAPE = -3,     /* width not a multiple of 8, misaligned pointer */
-  HMOE_EWORKSPACE = -4, /* ws_bytes smaller than the *_workspace() answer */
+  HMOE_EWORKSPACE = -4, /* ws_bytes smaller than the call can do with */
   HMOE_EHIP = -5,       /* a HIP launch or runtime call failed */
   HMOE_ENUMERIC = -6    /* a host-side factorisation did not converge (hmoe_pca_fit) */
 };

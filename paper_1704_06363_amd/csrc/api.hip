@@ -353,7 +353,7 @@ static int check_params(const hmoe_moe_params_t* p) {
 
 size_t hmoe_moe_workspace(const hmoe_moe_params_t* p, int64_t n) {
   if (!p || n < 0) return 0;
-  return moe_ws_bytes(p, n);
+  return moe_ws_bytes(p, n, true);
 }
 
 int hmoe_moe_forward(const hmoe_moe_params_t* p, int64_t n, const void* X_sorted, const int32_t* offsets,
@@ -379,7 +379,7 @@ int hmoe_moe_forward(const hmoe_moe_params_t* p, int64_t n, const void* X_sorted
   HMOE_TRY(check_ptr("lse", lse, false));
   HMOE_TRY(check_ptr("loss", loss, false));
   HMOE_TRY(check_ptr("loss_mean", loss_mean, false));
-  HMOE_TRY(check_ws(moe_ws_bytes(p, n), ws_bytes, ws));
+  HMOE_TRY(check_ws(moe_ws_bytes(p, n, false), ws_bytes, ws));
   Workspace w(ws, ws_bytes);
   return launch_moe_forward(p, n, X_sorted, offsets, perm, y, H1_sorted, H, logits, logit_anchor, lse, loss,
                             loss_mean, w, (hipStream_t)stream);
@@ -425,7 +425,7 @@ int hmoe_moe_backward(const hmoe_moe_params_t* p, int64_t n, const void* X_sorte
   } else if (p->decoders > 1)
     return fail(HMOE_EINVAL, "with one decoder per expert the backward needs the forward's saved logits");
   if (dX) HMOE_TRY(check_ptr("dX", dX));
-  HMOE_TRY(check_ws(moe_ws_bytes(p, n), ws_bytes, ws));
+  HMOE_TRY(check_ws(moe_ws_bytes(p, n, false), ws_bytes, ws));
   Workspace w(ws, ws_bytes);
   return launch_moe_backward(p, n, X_sorted, offsets, perm, inv, y, H1_sorted, H, logits, logit_anchor, lse, dW1,
                              db1, dW2, db2, dD, dbD, dX, w, (hipStream_t)stream);

@@ -334,7 +334,7 @@ template <typename T, typename O>
 int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* seg, int G, int w,
                   int64_t n, O* out, int accumulate, Workspace& ws, hipStream_t st, const int32_t* ts) {
   const int64_t pieces = cdiv(n, kSegPiece) + G;
-  int32_t* own = ws.take<int32_t>(G + 1);
+  int32_t* own = ts ? nullptr : ws.take<int32_t>(G + 1);
   double* part = ws.take<double>((size_t)pieces * w);
   if (!ws.fits()) return HMOE_EWORKSPACE;
   if (!ts) {

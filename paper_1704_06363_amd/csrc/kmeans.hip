@@ -275,11 +275,10 @@ static size_t assign_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) 
 
 template <class C>
 static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typename C::type* Cn, int32_t K,
-                    int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st, const float* norms) {
+                    int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st, float* norms, bool normed) {
   using T = typename C::type;
   const int nt = (int)cdiv(K, C::BN);
-  float* own = ws.take<float>(K);
-  const float* cn = norms ? norms : own;
+  float* cn = norms ? norms : ws.take<float>(K);
   float *pv = nullptr, *xn = nullptr;
   int32_t* pi = nullptr;
   if (nt > 1) {
@@ -288,8 +287,8 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
     xn = ws.take<float>(n);
   }
   if (!ws.fits()) return HMOE_EWORKSPACE;
-  if (!norms)
-    HMOE_LAUNCH("centre norms", k_cnorm<T>, dim3((unsigned)cdiv(K, 4)), dim3(256), 0, st, Cn, K, d, own);
+  if (!normed)
+    HMOE_LAUNCH("centre norms", k_cnorm<T>, dim3((unsigned)cdiv(K, 4)), dim3(256), 0, st, Cn, K, d, cn);
   if (n == 0) return HMOE_OK;
   const int64_t tiles = cdiv(n, C::BM) * nt;
   if constexpr (C::DMA)
@@ -305,21 +304,21 @@ static int assign_t(const typename C::type* X, int64_t n, int32_t d, const typen
 }
 
 int launch_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, const void* C, int32_t K, int32_t* assign,
-                  float* min_dist, Workspace& ws, hipStream_t st, const float* norms) {
+                  float* min_dist, Workspace& ws, hipStream_t st, float* norms, bool normed) {
   const bool pipe = assign_pipe(d, dt, K);
   const bool few = cdiv(n, CfgDmaNarrow::BM) < device_cus();
   if (dt == HMOE_BF16) {
     const bf16 *x = (const bf16*)X, *c = (const bf16*)C;
-    if (K <= 64 && few) return assign_t<CfgDmaNarrowFew>(x, n, d, c, K, assign, min_dist, ws, st, norms);
-    if (K <= 64) return assign_t<CfgDmaNarrow>(x, n, d, c, K, assign, min_dist, ws, st, norms);
-    if (pipe) return assign_t<CfgPipe>(x, n, d, c, K, assign, min_dist, ws, st, norms);
-    return assign_t<CfgSmall<bf16>>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+    if (K <= 64 && few) return assign_t<CfgDmaNarrowFew>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
+    if (K <= 64) return assign_t<CfgDmaNarrow>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
+    if (pipe) return assign_t<CfgPipe>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
+    return assign_t<CfgSmall<bf16>>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
   }
   const float *x = (const float*)X, *c = (const float*)C;
-  if (K <= 64 && few) return assign_t<CfgDmaF32NarrowFew>(x, n, d, c, K, assign, min_dist, ws, st, norms);
-  if (K <= 64) return assign_t<CfgDmaF32Narrow>(x, n, d, c, K, assign, min_dist, ws, st, norms);
-  if (pipe) return assign_t<CfgPipeF32>(x, n, d, c, K, assign, min_dist, ws, st, norms);
-  return assign_t<CfgSmall<float>>(x, n, d, c, K, assign, min_dist, ws, st, norms);
+  if (K <= 64 && few) return assign_t<CfgDmaF32NarrowFew>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
+  if (K <= 64) return assign_t<CfgDmaF32Narrow>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
+  if (pipe) return assign_t<CfgPipeF32>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
+  return assign_t<CfgSmall<float>>(x, n, d, c, K, assign, min_dist, ws, st, norms, normed);
 }
 
 // ------------------------------------------------------------------ k-means++ seeding
@@ -988,9 +987,9 @@ static size_t update_scratch(int64_t n, int32_t d, int32_t K) {
   Workspace ws(nullptr, 0);
   ws.take<int32_t>(K);
   ws.take<int32_t>(K + 1);
-  ws.take<int32_t>(K + 1);
   ws.take<int32_t>(n);
   ws.take<int32_t>(n);
+  // the pieces' table, which the sort leaves, is the one that the segmented sums have room for
   size_t s = ws.off + dispatch_ws(n, K) + segsum_ws(n, K, d) +
              (size_t)kReseedBlocks * (sizeof(float) + sizeof(int64_t)) + 4096;
   return s;
@@ -1050,8 +1049,7 @@ size_t fit_ws_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt) {
   ws.take<double>(n);                       // D^2 for k-means++
   ws.take<double>(cdiv(n, kKppRows));       // block sums
   ws.take<int32_t>(K);                      // picks when the caller passes none
-  ws.take<float>(K);                        // centre norms
-  size_t s = ws.off + update_scratch(n, d, K) + assign_ws_bytes(n, d, K, dt) + 4096;
+  size_t s = ws.off + update_scratch(n, d, K) + assign_ws_bytes(n, d, K, dt) + 4096;  // centre norms: the assignment's
   return s;
 }
 
@@ -1126,7 +1124,7 @@ static int fit_t(const T* X, int64_t n, int32_t d, int32_t K, int32_t n_iter, co
   const size_t mark = ws.off;
   for (int t = 0; t <= n_iter; ++t) {
     ws.off = mark;
-    HMOE_TRY(launch_assign(X, DT<T>::id, n, d, Cuse, K, assign, d1, ws, st, t > 0 ? norms : nullptr));
+    HMOE_TRY(launch_assign(X, DT<T>::id, n, d, Cuse, K, assign, d1, ws, st, norms, t > 0));
     if (objective) HMOE_TRY(launch_sum_f32(d1, n, 1.0, objective + t, nullptr, ws, st));
     if (t == n_iter) break;
     HMOE_TRY(update_core<T>(X, n, d, K, assign, d1, sums, c64, 0, reseed, b, ws, st));

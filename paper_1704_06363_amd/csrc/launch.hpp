@@ -53,7 +53,8 @@ size_t fit_ws_copy_bytes(int64_t n, int32_t d, int32_t K, hmoe_dtype_t dt);
 size_t update_ws_bytes(int64_t n, int32_t d, int32_t K);
 int launch_assign(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, const void* C, int32_t K,
                   int32_t* assign, float* min_dist, Workspace& ws, hipStream_t st,
-                  const float* norms = nullptr);  // |c_k|^2 as k_cnorm gives it
+                  float* norms = nullptr,   // room for the K |c_k|^2 (from ws without it),
+                  bool normed = false);     // which are there already, as k_cnorm gives them
 int launch_fit(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t K, int32_t n_iter,
                const double* u, int32_t reseed, float* C, int32_t* assign, float* min_dist,
                int32_t* counts, double* objective, int32_t* init_idx, Workspace& ws, hipStream_t st);
@@ -62,7 +63,7 @@ int launch_update(const void* X, hmoe_dtype_t dt, int64_t n, int32_t d, int32_t 
                   int32_t reseed, Workspace& ws, hipStream_t st);
 
 // moe.hip
-size_t moe_ws_bytes(const hmoe_moe_params_t* p, int64_t n);
+size_t moe_ws_bytes(const hmoe_moe_params_t* p, int64_t n, bool more);  // what is needed, or what is asked for
 int launch_moe_forward(const hmoe_moe_params_t* p, int64_t n, const void* Xs, const int32_t* offsets,
                        const int32_t* perm, const hmoe_labels_t* y, void* H1s, void* H, void* logits,
                        float* anc, float* lse, float* loss, float* loss_mean, Workspace& ws, hipStream_t st);

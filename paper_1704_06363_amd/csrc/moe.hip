@@ -1193,69 +1193,84 @@ static int grad_rows(int64_t n, int V) {
   return rows;
 }
 
+// Workspace of the forward and of the backward, without and with (`more`) what makes small problems
+// faster: the tables of quarter tiles and of the sums' pieces, and the column sums of a gradient in
+// blocks of fewer than kGradRows rows.  A call in a workspace without that runs whole tiles and blocks.
 template <typename T, class P>
-static size_t fwd_ws(const MoeShape& s) {
+static size_t fwd_ws(const MoeShape& s, bool more) {
   using C = typename P::C;
   Workspace ws(nullptr, 0);
   const int64_t ntv = cdiv(s.V, C::BN);
-  ws.take<int32_t>(s.K + 1);
   ws.take<int32_t>(s.K + 1);
   ws.take<float>((size_t)ntv * s.n);
   ws.take<float>((size_t)ntv * s.n);
   if (s.nd > 1) ws.take<T>((size_t)s.n * s.o);
   ws.take<double>(kSumBlocks);
+  if (more) ws.take<int32_t>(s.K + 1);
   return ws.off;
 }
 
+// Rows of column sums of the gradient, in blocks of `brows`.
+template <class C>
+static size_t grad_sums(const MoeShape& s, int brows) {
+  const int64_t mt = cdiv(s.n, C::BM), gr = cdiv(s.n, brows);
+  return (size_t)((mt > gr ? mt : gr) + s.K) * s.V;
+}
+
+// ... and in the blocks that fill the chip, where those are smaller.
+template <typename T, class C>
+static size_t grad_sums_few(const MoeShape& s) {
+  const int rows = grad_rows<T>(s.n, s.V);
+  return rows < kGradRows ? grad_sums<C>(s, rows) : 0;
+}
+
 template <typename T, class P>
-static size_t bwd_ws(const MoeShape& s) {
+static size_t bwd_ws(const MoeShape& s, bool more) {
   using C = typename P::C;
   Workspace ws(nullptr, 0);
-  ws.take<int32_t>(s.K + 1);
-  ws.take<int32_t>(s.K + 1);
   ws.take<int32_t>(s.K + 1);
   ws.take<int32_t>(s.K);
   constexpr int GW = 256 * (16 / (int)sizeof(T));  // G padded to whole slabs (backward_t)
   ws.take<T>(C::PIPE && s.nd == 1 ? (size_t)s.n * cdiv(s.V, GW) * GW : (size_t)s.n * s.V);
   ws.take<T>((size_t)s.n * s.o);
   ws.take<T>((size_t)s.n * s.h);
-  const int64_t gr = cdiv(s.n, grad_rows<T>(s.n, s.V));
-  const int64_t prow = cdiv(s.n, C::BM) > gr ? cdiv(s.n, C::BM) : gr;
-  ws.take<float>((size_t)(prow + s.K) * s.V);
+  ws.take<float>(grad_sums<C>(s, kGradRows));
   ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   if (s.nd > 1) {
     ws.take<T>((size_t)s.n * s.o);
     ws.take<int32_t>(s.K + 1);
   }
   const int w = s.h > s.o ? s.h : s.o;
-  return ws.off + segsum_ws(s.n, s.K, w) + 256;
+  ws.off += segsum_ws(s.n, s.K, w) + 256;
+  if (more) {
+    ws.take<int32_t>(s.K + 1);
+    ws.take<int32_t>(s.K + 1);
+    ws.take<float>(grad_sums_few<T, C>(s));
+  }
+  return ws.off;
 }
 
-size_t moe_ws_bytes(const hmoe_moe_params_t* p, int64_t n) {
-  const MoeShape s = shape_of(p, n);
-  size_t a, b;
-  if (p->dt != HMOE_BF16) {
-    a = fwd_ws<float, Pick<float>>(s);
-    b = bwd_ws<float, Pick<float>>(s);
-  } else if (wide_rows(s)) {
-    a = fwd_ws<bf16, Pick<bf16, true>>(s);
-    b = bwd_ws<bf16, Pick<bf16, true>>(s);
-  } else {
-    a = fwd_ws<bf16, Pick<bf16>>(s);
-    b = bwd_ws<bf16, Pick<bf16>>(s);
-  }
+template <typename T, class P>
+static size_t both_ws(const MoeShape& s, bool more) {
+  const size_t a = fwd_ws<T, P>(s, more), b = bwd_ws<T, P>(s, more);
   return a > b ? a : b;
+}
+
+size_t moe_ws_bytes(const hmoe_moe_params_t* p, int64_t n, bool more) {
+  const MoeShape s = shape_of(p, n);
+  if (p->dt != HMOE_BF16) return both_ws<float, Pick<float>>(s, more);
+  return wide_rows(s) ? both_ws<bf16, Pick<bf16, true>>(s, more) : both_ws<bf16, Pick<bf16>>(s, more);
 }
 
 // fp32 products of few tiles run quarter tiles (CfgQuarter): with fewer tiles than CUs a product
 // lasts as long as one tile's reduction, and a quarter of the tile takes a quarter of the time per
 // stage on four times the CUs; each element's sum runs in the same order.  4096 x 64 -> 128 -> 64,
 // V = 1000, 8 experts: dH 83 -> 50 us, the weight gradients 99 -> 61.  Measured at up to a tile per CU; with more the larger tile
-// reads less.  body(configuration) launches; `tiles` counts C's.
+// reads less.  body(configuration) launches; `tiles` counts C's; `table` is that of the quarter tiles.
 template <typename T, class C, class Body>
-static int by_tile_count(int64_t tiles, Body body) {
+static int by_tile_count(int64_t tiles, bool table, Body body) {
   if constexpr (sizeof(T) == 4)
-    if (tiles < device_cus()) return body(CfgQuarter<T>{});
+    if (table && tiles < device_cus()) return body(CfgQuarter<T>{});
   return body(C{});
 }
 
@@ -1280,26 +1295,32 @@ static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const i
   const MoeShape s = shape_of(p, n);
   const int ntv = (int)cdiv(s.V, C::BN);
   int32_t* ts = ws.take<int32_t>(s.K + 1);
-  int32_t* tsq = ws.take<int32_t>(s.K + 1);  // of quarter tiles
   float* pm = ws.take<float>((size_t)ntv * n);
   float* ps = ws.take<float>((size_t)ntv * n);
   T* Hs = s.nd > 1 ? ws.take<T>((size_t)n * s.o) : nullptr;  // H in slot order
   if (!ws.fits()) return HMOE_EWORKSPACE;
+  int32_t* tsq = nullptr;  // of quarter tiles
+  if (sizeof(T) == 4) {
+    Workspace x(ws.base, ws.cap);
+    x.off = fwd_ws<T, P>(s, false);
+    tsq = x.take<int32_t>(s.K + 1);
+    if (!x.fits()) tsq = nullptr;
+  }
   const T* W1 = (const T*)p->W1;
   const T* W2 = (const T*)p->W2;
   const T* D = (const T*)p->D;
   if (!Lg) anc = nullptr;
-  HMOE_TRY(launch_seg_plan(offsets, s.K, SegPlan{{C::BM, CfgQuarter<T>::BM}, {ts, sizeof(T) == 4 ? tsq : nullptr}, nullptr},
+  HMOE_TRY(launch_seg_plan(offsets, s.K, SegPlan{{C::BM, CfgQuarter<T>::BM}, {ts, tsq}, nullptr},
                            st));
   const int64_t mt_bound = cdiv(n, C::BM) + s.K;
-  HMOE_TRY(by_tile_count<T, C>(mt_bound * cdiv(s.h, C::BN), [&](auto cfg) -> int {
+  HMOE_TRY(by_tile_count<T, C>(mt_bound * cdiv(s.h, C::BN), tsq, [&](auto cfg) -> int {
     using F = decltype(cfg);
     HMOE_LAUNCH("expert layer 1", (k_expert_fwd<F, 1>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.h, F::BN))),
                 dim3(F::THREADS), F::LDS, st, Xs, W1, (const T*)p->b1, offsets, F::BM == C::BM ? ts : tsq, s.K, s.h,
                 s.d, perm, H1s);
     return HMOE_OK;
   }));
-  HMOE_TRY(by_tile_count<T, C>(mt_bound * cdiv(s.o, C::BN), [&](auto cfg) -> int {
+  HMOE_TRY(by_tile_count<T, C>(mt_bound * cdiv(s.o, C::BN), tsq, [&](auto cfg) -> int {
     using F = decltype(cfg);
     HMOE_LAUNCH("expert layer 2", (k_expert_fwd<F, 2>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.o, F::BN))),
                 dim3(F::THREADS), F::LDS, st, (const T*)H1s, W2, (const T*)p->b2, offsets, F::BM == C::BM ? ts : tsq,
@@ -1344,8 +1365,6 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   using CK = typename P::CK;  // K-strided second operand
   const MoeShape s = shape_of(p, n);
   int32_t* ts = ws.take<int32_t>(s.K + 1);
-  int32_t* tsq = ws.take<int32_t>(s.K + 1);  // of quarter tiles
-  int32_t* tss = ws.take<int32_t>(s.K + 1);  // of the segmented sums' pieces
   int32_t* order = ws.take<int32_t>(s.K);
   constexpr int EPV = 16 / sizeof(T);
   // bf16 logits through the shared decoder: G slab-major, [V / GW slabs][n][GW] (see
@@ -1356,9 +1375,8 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   T* dYs = ws.take<T>((size_t)n * s.o);
   T* dZ = ws.take<T>((size_t)n * s.h);
   const int mt = (int)cdiv(n, C::BM);
-  const int brows = grad_rows<T>(n, s.V);
-  const int gr = (int)cdiv(n, brows);
-  float* pdb = ws.take<float>((size_t)((mt > gr ? mt : gr) + s.K) * s.V);
+  int brows = kGradRows;
+  float* pdb = ws.take<float>(grad_sums<C>(s, kGradRows));
   float* split_part = ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   T* Hs = nullptr;
   int32_t* gts = nullptr;
@@ -1367,6 +1385,21 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
     gts = ws.take<int32_t>(s.K + 1);   // first gradient piece of each expert
   }
   if (!ws.fits()) return HMOE_EWORKSPACE;
+  int32_t *tsq = nullptr, *tss = nullptr;  // tables of quarter tiles, of the segmented sums' pieces
+  {
+    Workspace x(ws.base, ws.cap);
+    x.off = bwd_ws<T, P>(s, false);
+    int32_t* const q = x.take<int32_t>(s.K + 1);
+    int32_t* const pieces = x.take<int32_t>(s.K + 1);
+    float* const sums = x.take<float>(grad_sums_few<T, C>(s));
+    if (x.fits()) {
+      tsq = sizeof(T) == 4 ? q : nullptr;
+      tss = pieces;
+      brows = grad_rows<T>(n, s.V);
+      if (brows < kGradRows) pdb = sums;
+    }
+  }
+  const int gr = (int)cdiv(n, brows);
   const T* W1 = (const T*)p->W1;
   const T* W2 = (const T*)p->W2;
   const T* D = (const T*)p->D;
@@ -1376,9 +1409,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   static_assert(sizeof(T) == 4 || P::WIDE || C::BM == kSegPiece, "one table for both");
   if (C::BM == kSegPiece) tss = ts;
   HMOE_TRY(launch_seg_plan(offsets, s.K,
-                           SegPlan{{C::BM, CfgQuarter<T>::BM, kSegPiece},
-                                   {ts, sizeof(T) == 4 ? tsq : nullptr, tss != ts ? tss : nullptr},
-                                   order},
+                           SegPlan{{C::BM, CfgQuarter<T>::BM, kSegPiece}, {ts, tsq, tss != ts ? tss : nullptr}, order},
                            st));
   if (s.nd > 1) {
     // One decoder per expert, everything in slot order (the API guarantees saved logits):
@@ -1421,11 +1452,11 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
     }
   }
   if (!slab) {
-    HMOE_TRY(by_tile_count<T, CK>((int64_t)mt * cdiv(s.o, C::BN), [&](auto cfg) -> int {
+    HMOE_TRY(by_tile_count<T, CK>((int64_t)mt * cdiv(s.o, C::BN), true, [&](auto cfg) -> int {
       return launch_dH<decltype(cfg)>((const T*)G, D, n, s.V, s.o, inv, dYs, split_part, st);
     }));
     // few chunks of whole tiles: quarter tiles, as above
-    HMOE_TRY(by_tile_count<T, CK>(cdiv(s.V, C::BM) * cdiv(s.o, C::BN) * cdiv(n, 256), [&](auto cfg) -> int {
+    HMOE_TRY(by_tile_count<T, CK>(cdiv(s.V, C::BM) * cdiv(s.o, C::BN) * cdiv(n, 256), true, [&](auto cfg) -> int {
       return launch_tn_split<decltype(cfg)>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st);
     }));
   }
@@ -1433,7 +1464,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   // experts
   const size_t mark = ws.off;
   const auto wgrad = [&](const char* label, const T* A, int M, const T* B, int N, float* out) -> int {
-    return by_tile_count<T, CK>((int64_t)s.K * cdiv(M, C::BM) * cdiv(N, C::BN), [&](auto cfg) -> int {
+    return by_tile_count<T, CK>((int64_t)s.K * cdiv(M, C::BM) * cdiv(N, C::BN), true, [&](auto cfg) -> int {
       using F = decltype(cfg);
       HMOE_LAUNCH(label, k_expert_wgrad<F>, dim3((unsigned)((int64_t)s.K * cdiv(M, F::BM) * cdiv(N, F::BN))),
                   dim3(F::THREADS), F::LDS, st, A, B, offsets, order, s.K, M, N, out);
@@ -1443,7 +1474,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   if (db2) HMOE_TRY(launch_segsum<T, float>(dYs, s.o, nullptr, offsets, s.K, s.o, n, db2, 0, ws, st, tss));
   ws.off = mark;
   HMOE_TRY(wgrad("expert dW2", dYs, s.o, H1s, s.h, dW2));
-  HMOE_TRY(by_tile_count<T, CK>(mt_bound * cdiv(s.h, C::BN), [&](auto cfg) -> int {
+  HMOE_TRY(by_tile_count<T, CK>(mt_bound * cdiv(s.h, C::BN), tsq, [&](auto cfg) -> int {
     using F = decltype(cfg);
     HMOE_LAUNCH("expert dH1", (k_expert_dgrad<F, true>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.h, F::BN))),
                 dim3(F::THREADS), F::LDS, st, (const T*)dYs, W2, offsets, F::BM == C::BM ? ts : tsq, s.K, s.h, s.o,
@@ -1454,7 +1485,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
   ws.off = mark;
   HMOE_TRY(wgrad("expert dW1", dZ, s.h, Xs, s.d, dW1));
   if (dX)
-    HMOE_TRY(by_tile_count<T, CK>(mt_bound * cdiv(s.d, C::BN), [&](auto cfg) -> int {
+    HMOE_TRY(by_tile_count<T, CK>(mt_bound * cdiv(s.d, C::BN), tsq, [&](auto cfg) -> int {
       using F = decltype(cfg);
       HMOE_LAUNCH("expert dX", (k_expert_dgrad<F, false>), dim3((unsigned)((cdiv(n, F::BM) + s.K) * cdiv(s.d, F::BN))),
                   dim3(F::THREADS), F::LDS, st, (const T*)dZ, W1, offsets, F::BM == C::BM ? ts : tsq, s.K, s.d, s.h,

@@ -176,11 +176,11 @@ def _expect(t, shape, dtype, what):
 
 
 def _workspace(nbytes, ws, device):
+    """ws or a new tensor of nbytes.  The library refuses one that is too small; it needs less than it
+    asks for where that only makes a call faster."""
     if nbytes == 0:
         return None, 0
     if ws is not None:
-        if ws.numel() * ws.element_size() < nbytes:
-            raise HmoeError(f"workspace of {ws.numel() * ws.element_size()} bytes, {nbytes} needed")
         return ws, ws.numel() * ws.element_size()
     return torch.empty(nbytes, dtype=torch.uint8, device=device), nbytes
 
@@ -232,12 +232,7 @@ def kmeans_fit(X, K, n_iter, init_uniforms=None, C=None, reseed=True, ws=None):
            "counts": torch.empty(K, dtype=torch.int32, device=dev),
            "objective": torch.empty(n_iter + 1, dtype=torch.float64, device=dev),
            "init_idx": torch.empty(K, dtype=torch.int32, device=dev) if u is not None else None}
-    # the library refuses a workspace that is too small; one without room for the seeding's 8-bit
-    # copy of X is enough
-    if ws is None:
-        w, wb = _workspace(kmeans_fit_workspace(n, d, K, X.dtype), None, dev)
-    else:
-        w, wb = ws, ws.numel() * ws.element_size()
+    w, wb = _workspace(kmeans_fit_workspace(n, d, K, X.dtype), ws, dev)
     _chk(lib().hmoe_kmeans_fit(_ptr(X), _dt(X), n, d, K, n_iter, _ptr(u), 1 if reseed else 0,
                                _ptr(Cout), _ptr(out["assign"]), _ptr(out["min_dist"]),
                                _ptr(out["counts"]), _ptr(out["objective"]), _ptr(out["init_idx"]),
