@@ -330,7 +330,8 @@ __global__ void __launch_bounds__(C::THREADS)
 // writes before the merge's reads and the merge's reads before the buffer is written again.
 constexpr int kDecStatLds = 2 * 4 * 256 * (int)sizeof(float);
 // This lane's bias of a tile, packed; the loads are unconditional (a column past the tile reads
-// the tile's first ones, for outputs that are neither stored nor counted).
+// the tile's first ones, for outputs that are neither stored nor counted).  The bias may start at any
+// element: unlike the matrices' its alignment is not checked.
 template <class C>
 __device__ __forceinline__ void dec_bias_packed(const TileCoord& tc, const bf16* __restrict__ bD,
                                                 uint2 (&bp)[C::NJ]) {
@@ -339,11 +340,13 @@ __device__ __forceinline__ void dec_bias_packed(const TileCoord& tc, const bf16*
     for (int j = 0; j < C::NJ; ++j) bp[j] = uint2{0u, 0u};
     return;
   }
+  typedef unsigned int u2v __attribute__((ext_vector_type(2), aligned(2)));
   const Frag<C> f;
 #pragma unroll
   for (int j = 0; j < C::NJ; ++j) {
     const int col = f.col(j, 0);  // four consecutive columns; n_cols is a multiple of 8
-    bp[j] = *reinterpret_cast<const uint2*>(bD + tc.n0 + (col < tc.n_cols ? col : 0));
+    const u2v b = *reinterpret_cast<const u2v*>(bD + tc.n0 + (col < tc.n_cols ? col : 0));
+    bp[j] = uint2{b[0], b[1]};
   }
 }
 // Waits for the bias here: among loads that a fixed count can tell apart.  Behind the stores, of

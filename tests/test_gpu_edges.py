@@ -246,3 +246,24 @@ def test_column_sums_around_one_vector_per_thread(dtype, d):
     ref = torch.zeros_like(sums).index_add_(0, a.long(), X.double())
     # fp64 sums of 600 terms: n eps times their magnitude
     assert (sums - ref).abs().max() <= n * 2.0 ** -53 * X.double().abs().sum(0).max()
+
+
+@pytest.mark.parametrize("at", [1, 2, 3, 5])
+@pytest.mark.parametrize("n,V", [(300, 264), (700, 1000)])
+def test_biases_at_any_element(n, V, at):
+    # biases as views into one parameter buffer, at odd elements of it: the same bits
+    K, d, h, o = 3, 64, 72, 136
+    inp = W.skewed_inputs(device="cuda", seed=n, n=n, d=d, h=h, o=o, V=V, K=K, bias=True)
+    p = inp["params"]
+    q = dict(p)
+    for k in ("b1", "b2", "bD"):
+        buf = torch.zeros(p[k].numel() + 8, dtype=p[k].dtype, device="cuda")
+        q[k] = buf[at:at + p[k].numel()].view(p[k].shape)
+        q[k].copy_(p[k])
+    ids = torch.from_numpy(np.random.default_rng(n).integers(0, K, n).astype(np.int32)).cuda()
+    dd = hmoe.moe_dispatch(ids, K, rows=inp["X"])
+    row_ptr, tag = torch.tensor(inp["row_ptr"], device="cuda"), torch.tensor(inp["tag"], device="cuda")
+    a, b = (hmoe.moe_forward(x, dd["rows_sorted"], dd["offsets"], dd["perm"], row_ptr, tag, save_logits=True)
+            for x in (p, q))
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
