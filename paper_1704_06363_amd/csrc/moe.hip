@@ -1070,15 +1070,17 @@ static int launch_dH(const typename C::type* G, const typename C::type* D, int64
 
 // Launches k_gemm_tn_split (and its reduction) for out = A^T B; `part` holds kMaxSplitItems
 // tiles of fp32 partials.  rows > 0.  a_sw > 0: A is slab-major (see k_gemm_tn_split).
-template <class C, bool SYM = false>
+// L: the configuration whose chunks are taken.  Quarter tiles (C) take those of whole ones (L),
+// fewer than a round of which there are: every sum is the same, over four times the workgroups.
+template <class C, bool SYM = false, class L = C>
 static int launch_tn_split(const char* label, const typename C::type* A, const typename C::type* B, int64_t rows,
                            int M, int N, float* out, float* part, hipStream_t st, int64_t a_sstride = 0,
                            int a_sw = 0) {
   // rounds of `slots` concurrent tiles (one workgroup per 160 KB of LDS per CU)
-  const int64_t tiles = tn_tiles<C, SYM>(M, N);
-  int64_t slots = (int64_t)device_cus() * ((160 * 1024) / C::LDS);
+  const int64_t tiles = tn_tiles<L, SYM>(M, N);
+  int64_t slots = (int64_t)device_cus() * ((160 * 1024) / L::LDS);
   if (slots > kMaxSplitItems) slots = kMaxSplitItems;
-  const int64_t R = tiles % slots;
+  int64_t R = tiles % slots;
   const int64_t t_full = tiles - R;
   int split = R > 0 ? (int)(slots / R) : 1;
   // chunks of a multiple of 64 rows and at least 256 (fewer chunks when rows are few); split is
@@ -1086,6 +1088,11 @@ static int launch_tn_split(const char* label, const typename C::type* A, const t
   int64_t chunk = cdiv(cdiv(rows, split), 64) * 64;
   if (chunk < 256) chunk = 256;
   split = (int)cdiv(rows, chunk);
+  if constexpr (!std::is_same<C, L>::value) {
+    static_assert(C::BM * C::BN * 4 == L::BM * L::BN, "quarter tiles");  // so that `part` holds their chunks
+    if (t_full > 0) return launch_tn_split<L, SYM>(label, A, B, rows, M, N, out, part, st, a_sstride, a_sw);
+    R = tn_tiles<C, SYM>(M, N);
+  }
   HMOE_LAUNCH(label, (k_gemm_tn_split<C, SYM>), dim3((unsigned)(t_full + R * split)), dim3(C::THREADS), C::LDS, st, A, B,
               rows, M, N, out, t_full, split, chunk, part, a_sstride, a_sw);
   if (R > 0)
@@ -1460,7 +1467,7 @@ static int backward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const 
     }));
     // few chunks of whole tiles: quarter tiles, as above
     HMOE_TRY(by_tile_count<T, CK>(cdiv(s.V, C::BM) * cdiv(s.o, C::BN) * cdiv(n, 256), true, [&](auto cfg) -> int {
-      return launch_tn_split<decltype(cfg)>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st);
+      return launch_tn_split<decltype(cfg), false, CK>("decoder dD", (const T*)G, H, n, s.V, s.o, dD, split_part, st);
     }));
   }
   }
@@ -1530,10 +1537,9 @@ int launch_gemm_tn(const T* A, const T* B, int64_t rows, int M, int N, float* ou
   if (!ws.fits()) return HMOE_EWORKSPACE;
   if (rows <= 0) return launch_zero_f32(out, (int64_t)M * N, st);
   if constexpr (sizeof(T) == 4) {
-    // a short reduction over few tiles (the PCA's Gram matrices: 4 tiles, two chunks): quarter
-    // tiles in the same chunks, so the same sums
+    // a short reduction over few tiles (the PCA's Gram matrices: 4 tiles, two chunks): quarter tiles
     if (rows <= 4096 && cdiv(M, C::BM) * cdiv(N, C::BN) * cdiv(rows, 256) < device_cus())
-      return launch_tn_split<CfgQuarter<T>>(label, A, B, rows, M, N, out, part, st);
+      return launch_tn_split<CfgQuarter<T>, false, C>(label, A, B, rows, M, N, out, part, st);
   }
   return launch_tn_split<C>(label, A, B, rows, M, N, out, part, st);
 }
