@@ -72,3 +72,19 @@ def test_rows_beyond_the_offset_range():
     ref = dZ.T @ X[:, -4096:].double()
     err = (b["dW1"][0][:, -4096:].double() - ref).norm() / ref.norm()
     assert err <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("dtype,K,d", [("f32", 65, 1 << 22), ("bf16", 129, 1 << 23), ("f32", 65, (1 << 22) - 8)])
+def test_assign_around_the_offset_range(dtype, K, d):
+    # the last row width on the pipelined engine and the first past it, against fp64 by column chunks
+    n, tdt = 9, torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(K)
+    C = torch.randn(K, d, generator=g, device="cuda", dtype=tdt)
+    pick = torch.tensor([0, 1, 31, 63, 64, K - 1, 40, 2, K - 2], device="cuda")
+    X = (C[pick].float() + 0.5 * torch.randn(n, d, generator=g, device="cuda")).to(tdt)
+    a, md = hmoe.kmeans_assign(X, C)
+    d2 = sum(torch.cdist(x.double(), c.double()) ** 2 for x, c in zip(X.split(1 << 18, 1), C.split(1 << 18, 1)))
+    assert torch.equal(a.long(), pick) and torch.equal(d2.argmin(1), pick)
+    # fp32 sums of d squares and products: at most d / 64 eps of their magnitude in sums of 64 lanes
+    mag = (X.double() ** 2).sum(1) + (C.double() ** 2).sum(1).max()
+    assert ((md.double() - d2.min(1).values).abs() <= d / 64 * 2.0 ** -24 * mag).all()
