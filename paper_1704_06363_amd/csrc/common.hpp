@@ -95,11 +95,6 @@ template <typename V>
 __device__ __forceinline__ V wave_sum(V v) {
   return row_sum(swap_add<false>(swap_add<true>(v)));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, shfl_xor(v, m));
-  return v;
-}
 
 // The four lanes 16 apart (l % 16 alike) combined by `op` without a trip through LDS: two register
 // swaps, of odd with even 16-lane rows and of the wave's halves, leave each lane with its own

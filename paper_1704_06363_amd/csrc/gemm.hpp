@@ -1,7 +1,8 @@
 // gemm.hpp -- the MFMA tile engines shared by every dense contraction of the hot path: the
-// register-staged engine described first (Cfg) and the direct-to-LDS engine further down
-// (CfgD), which runs the bf16 MoE contractions, the larger assignments and the fp32
-// contractions with K-contiguous operands.
+// register-staged engine described first (Cfg: the fp32 MoE products, the PCA fit's, the bf16
+// assignment to 65 .. 128 centres and rows too wide for the others), the direct-to-LDS ring (CfgD:
+// assignments to up to 64 centres) and the pipelined engine (CfgP: the bf16 MoE products, the larger
+// assignments and the PCA's projection).
 //
 // C[m, n] = sum_k A(m, k) * B(n, k) over one BM x BN output tile per workgroup, split into
 // (BM/WM) x (BN/WN) wavefronts of WM x WN.  Operands are staged through LDS in a row-major,
@@ -300,31 +301,21 @@ __device__ __forceinline__ void gemm_tile_reg(const typename C::type* __restrict
   }
 }
 
-// ------------------------------------------------------------------ direct-to-LDS engine
+// ------------------------------------------------------------------ direct-to-LDS ring
 //
-// The same BM x BN tile and wave split (bf16; fp32 for K-contiguous operands, see CfgD), but
-// operands travel from HBM to LDS without passing through registers: global_load_lds_dwordx4 writes lane l's 16 bytes to LDS at (wave-uniform
-// base) + 16 l, so the LDS layout -- including its bank swizzle -- is chosen by the global
+// NT products with few columns (the gater's assignment to up to 64 centres).  Operands travel from
+// HBM to LDS without passing through registers: global_load_lds_dwordx4 writes lane l's 16 bytes to LDS at
+// (wave-uniform base) + 16 l, so the LDS layout -- including its bank swizzle -- is chosen by the global
 // address each lane loads.  A stage covers 32 K (64 bytes per row); NS stages form a ring and
 // the loads for stage kt + NS - 1 are issued while stage kt feeds the MFMAs, each wave waiting
-// (vmcnt) only for its own loads of the stage it is about to read.
-//   K-contiguous operand: LDS [rows][32 K] (64-byte rows, chunk c of row r at c ^ ((r >> 1) & 3));
-//                         MFMA operands come from one ds_read_b128 per 16 x 32 fragment.
-//   K-strided operand:    LDS [32 K][rows] as in HBM (rows contiguous, 16-byte chunk c of K-row
-//                         k at c ^ 2 ((k & 3) | ((k >> 1) & 4))); MFMA operands come from two
-//                         ds_read_b64_tr_b16 per fragment.  Within each 16-lane group that read
-//                         returns to lane i, slot s, element i % 4 of the 8 bytes addressed by lane
-//                         4 s + i / 4 (verified on gfx950), so lane j addressing K-row
-//                         8 (l / 16) + 4 h + j / 4, rows 4 (j % 4) .. + 3 gives every lane the 4
-//                         consecutive K of its own row that the MFMA layout expects.
-// Both swizzles make the MFMA operand reads conflict-free (checked with the LDS bank-conflict
-// counter).  Rows past the valid range load a clamped (valid) address -- they only feed
-// output rows / columns that are never stored -- and a last partial K stage is staged through
-// registers with zero fill.  Needs every row width (ld) and valid row count in the row
-// direction of a K-strided operand to be a multiple of 8 elements.
+// (vmcnt) only for its own loads of the stage it is about to read.  LDS holds [rows][32 K] (64-byte
+// rows, chunk c of row r at c ^ ((r >> 1) & 3)); MFMA operands come from one ds_read_b128 per 16 x 32
+// fragment, conflict-free (checked with the LDS bank-conflict counter).  Rows past the valid range
+// load a clamped (valid) address -- they only feed output rows / columns that are never stored -- and
+// a last partial K stage is staged through registers with zero fill.  Needs every row width (ld) to be
+// a multiple of 8 elements.
 
-// fp32 operands (F32) take the same path for contractions with both operands K-contiguous: the
-// engine stages 16-bit units (a float is two, every ld and K doubled), so a 64-byte row still
+// fp32 operands (F32) take the same path: the engine stages 16-bit units (a float is two, every ld and K doubled), so a 64-byte row still
 // holds one stage, and each 16-byte fragment -- four consecutive K of one row -- feeds four
 // v_mfma_f32_16x16x4_f32, the lane group g supplying K = 4 g + q to the q-th of them.
 template <typename T, int BM_, int BN_, int WM_, int WN_, int NS_>
@@ -362,6 +353,12 @@ typedef CfgD<bf16, 64, 64, 32, 32, 5> CfgDmaNarrowFew;
 // swizzle, r & 3, (r >> 2) & 3, (r ^ (r >> 2)) & 3 and (r >> 3) & 3 are all 2-way conflicted.
 __device__ __forceinline__ int kc_swz(int row) { return (row >> 1) & 3; }
 __device__ __forceinline__ int kc_off(int row, int chunk) { return row * 64 + ((chunk ^ kc_swz(row)) << 4); }
+// K-strided operands (pipelined engine): LDS [K][R rows] as in HBM (rows contiguous, 16-byte chunk c of
+// K-row k at c ^ 2 ((k & 3) | ((k >> 1) & 4))); MFMA operands come from two ds_read_b64_tr_b16 per
+// fragment, conflict-free.  Within each 16-lane group that read returns to lane i, slot s, element i % 4
+// of the 8 bytes addressed by lane 4 s + i / 4 (verified on gfx950), so lane j addressing K-row
+// 8 (l / 16) + 4 h + j / 4, rows 4 (j % 4) .. + 3 gives every lane the 4 consecutive K of its own row
+// that the MFMA layout expects.
 template <int R>
 __device__ __forceinline__ int ks_off(int k, int byte) {
   const int sw = ((k & 3) | ((k >> 1) & 4)) << 1;
@@ -376,83 +373,52 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "mem
 __device__ __forceinline__ void wg_barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // One operand of R rows: per-thread slot offsets and the per-stage DMA / tail staging.
-template <int R, int THREADS, bool KC>
+template <int R, int THREADS>
 struct DmaOperand {
-  static constexpr int SLOTS = KC ? R * 4 : 32 * (R / 8);  // 16-byte slots per stage
+  static constexpr int SLOTS = R * 4;  // 16-byte slots per stage
   static constexpr int NQ = SLOTS / THREADS;
   static_assert(SLOTS % THREADS == 0, "slots/threads");
-  int64_t off[NQ];   // element offset of the slot's source for k0 = 0
-  bool live[NQ];     // KC: chunk K-position tracking is per stage; KS: column valid
-  int kk[NQ];        // KC: K offset of the chunk (0..31); KS: K-row within the stage
+  int64_t off[NQ];  // element offset of the slot's source for k0 = 0
+  int kk[NQ];       // K offset of the chunk (0..31)
 
-  // KC: element (r, k) at base + r * ld + k.  KS: element (r, k) at base + k * ld + r.
+  // element (r, k) at base + r * ld + k
   __device__ __forceinline__ void init(int64_t ld, int rows_valid) {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int slot = (q * (THREADS / 64) + w) * 64 + l;
-      if constexpr (KC) {
-        const int r = slot >> 2, p = slot & 3;
-        const int c = p ^ kc_swz(r);
-        const int gr = r < rows_valid ? r : rows_valid - 1;
-        off[q] = (int64_t)gr * ld + c * 8;
-        kk[q] = c * 8;
-        live[q] = r < rows_valid;
-      } else {
-        constexpr int CPR = R / 8;  // chunks per K-row
-        const int k = slot / CPR, p = slot % CPR;
-        const int sw = ((k & 3) | ((k >> 1) & 4)) << 1;
-        const int col = (p ^ sw) * 8;
-        live[q] = col < rows_valid;
-        off[q] = (int64_t)k * ld + (live[q] ? col : 0);
-        kk[q] = k;
-      }
+      const int r = slot >> 2, p = slot & 3;
+      const int c = p ^ kc_swz(r);
+      const int gr = r < rows_valid ? r : rows_valid - 1;
+      off[q] = (int64_t)gr * ld + c * 8;
+      kk[q] = c * 8;
     }
   }
 
-  __device__ __forceinline__ void issue(const bf16* __restrict__ base, int64_t ld, int k0, lds<char>* buf) const {
+  __device__ __forceinline__ void issue(const bf16* __restrict__ base, int k0, lds<char>* buf) const {
     const int w = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const int64_t o = off[q] + (KC ? (int64_t)k0 : (int64_t)k0 * ld);
       lds<char>* dst = buf + (q * (THREADS / 64) + w) * 1024;
-      __builtin_amdgcn_global_load_lds((const void*)(base + o), (lds<void>*)dst, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)(base + off[q] + k0), (lds<void>*)dst, 16, 0, 0);
     }
   }
 
   // Last partial stage [k0, k_len): through registers, zero outside the valid range.
-  __device__ __forceinline__ void tail(const bf16* __restrict__ base, int64_t ld, int k0, int k_len,
-                                       lds<char>* buf) const {
+  __device__ __forceinline__ void tail(const bf16* __restrict__ base, int k0, int k_len, lds<char>* buf) const {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int slot = (q * (THREADS / 64) + w) * 64 + l;
       i32x4 v = i32x4{0, 0, 0, 0};
-      const bool ok = KC ? (k0 + kk[q] < k_len) : (live[q] && k0 + kk[q] < k_len);
-      if (ok) v = *reinterpret_cast<const i32x4*>(base + off[q] + (KC ? (int64_t)k0 : (int64_t)k0 * ld));
+      if (k0 + kk[q] < k_len) v = *reinterpret_cast<const i32x4*>(base + off[q] + k0);
       *reinterpret_cast<lds<i32x4>*>(buf + slot * 16) = v;
     }
   }
 };
 
-template <bool KC, int R>
-__device__ __forceinline__ bf16x8 dma_frag(const lds<char>* buf, int r0, int lr, int lg) {
-  if constexpr (KC) {
-    return *reinterpret_cast<const lds<bf16x8>*>(buf + kc_off(r0 + lr, lg));
-  } else {
-    typedef short s4 __attribute__((ext_vector_type(4)));
-    const int byte = (r0 + 4 * (lr & 3)) * 2;
-    const int k = 8 * lg + (lr >> 2);
-    const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds<s4>*)(buf + ks_off<R>(k, byte)));
-    const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds<s4>*)(buf + ks_off<R>(k + 4, byte)));
-    typedef short s8 __attribute__((ext_vector_type(8)));
-    const s8 v = s8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
-  }
-}
-
 // A stage's MFMA operands for this wave: fragments of its WM rows of A and WN rows of B.
-template <class C, bool A_KC, bool B_KC>
+template <class C>
 __device__ __forceinline__ void dma_read_frags(const lds<char>* bA, const lds<char>* bB, bf16x8 (&a)[C::MI],
                                                bf16x8 (&b)[C::NJ]) {
   const int l = threadIdx.x & 63;
@@ -460,9 +426,11 @@ __device__ __forceinline__ void dma_read_frags(const lds<char>* bA, const lds<ch
   const int wm = w / C::WAVES_N, wn = w % C::WAVES_N;
   const int lr = l & 15, lg = l >> 4;
 #pragma unroll
-  for (int i = 0; i < C::MI; ++i) a[i] = dma_frag<A_KC, C::BM>(bA, wm * C::WM + 16 * i, lr, lg);
+  for (int i = 0; i < C::MI; ++i)
+    a[i] = *reinterpret_cast<const lds<bf16x8>*>(bA + kc_off(wm * C::WM + 16 * i + lr, lg));
 #pragma unroll
-  for (int j = 0; j < C::NJ; ++j) b[j] = dma_frag<B_KC, C::BN>(bB, wn * C::WN + 16 * j, lr, lg);
+  for (int j = 0; j < C::NJ; ++j)
+    b[j] = *reinterpret_cast<const lds<bf16x8>*>(bB + kc_off(wn * C::WN + 16 * j + lr, lg));
 }
 
 // The stage's MFMAs.  B is the MFMA's first operand: the 16 x 16 result is the transposed
@@ -514,89 +482,42 @@ __device__ __forceinline__ void dma_mfmas(const bf16x8 (&a)[C::MI], const bf16x8
   }
 }
 
-template <class C, bool A_KC, bool B_KC, bool ROWNORM = false>
-__device__ __forceinline__ void dma_mfma_stage(const lds<char>* bA, const lds<char>* bB,
-                                               floatx4 (&acc)[C::MI][C::NJ], float* xs = nullptr) {
-  bf16x8 a[C::MI], b[C::NJ];
-  dma_read_frags<C, A_KC, B_KC>(bA, bB, a, b);
-  // all of the stage's fragment reads go out before its MFMAs (measured faster than letting
-  // the scheduler interleave them)
-  __builtin_amdgcn_sched_barrier(0);
-  dma_mfmas<C, ROWNORM>(a, b, acc, xs);
-}
-
 // Waits for this wave's loads of the stage that has `pending_stages` later stages in flight
-// behind it, plus X more memory operations issued after those (vmcnt counts loads and stores
-// alike, in issue order).
-template <class C, int LOADS, int X = 0>
+// behind it (vmcnt counts in issue order).
+template <class C, int LOADS>
 __device__ __forceinline__ void wait_stage(int pending_stages) {
-  static_assert(C::NS <= 5 && LOADS * (C::NS - 2) + X <= 63, "vmcnt range");
+  static_assert(C::NS <= 5 && LOADS * (C::NS - 2) <= 63, "vmcnt range");
   switch (pending_stages) {
-    case 0: wait_vmcnt<X>(); break;
-    case 1: wait_vmcnt<LOADS + X>(); break;
-    case 2: wait_vmcnt<2 * LOADS + X>(); break;
-    default: wait_vmcnt<3 * LOADS + X>(); break;
+    case 0: wait_vmcnt<0>(); break;
+    case 1: wait_vmcnt<LOADS>(); break;
+    case 2: wait_vmcnt<2 * LOADS>(); break;
+    default: wait_vmcnt<3 * LOADS>(); break;
   }
 }
 
-// The K loop of one tile, split in two so that a persistent kernel can start the next tile's
-// loads before it runs the current tile's epilogue:
-//   prime()  issues stages 0 .. NS-2 of a tile into the LDS ring (the ring must be free: after
-//            run()'s closing barrier, or at kernel start);
-//   run()    the main loop over the primed tile and a partial last stage; it ends with a barrier
-//            after which the ring is free again.  run<.., X>(.., after_prime) is for a caller
-//            that issued exactly X further memory operations (per wave) between prime() and
-//            run() when after_prime is true: the waits for the primed stages let those X stay
-//            in flight instead of draining them first.
-// A_SW > 0: A is K-contiguous and stored slab-major -- K split into slabs of A_SW columns,
-// slab s of every row at A + s a_sstride (a_sstride = rows x A_SW), lda = A_SW within a slab
-// -- so each stage's loads start from the base of the slab that holds it (A_SW is a multiple
-// of BK, so no stage straddles two slabs).  Set the stride with slab_a() before prime().
-template <class C, bool A_KC, bool B_KC, int A_SW = 0>
+// The K loop of one tile: prime() issues stages 0 .. NS-2 into the LDS ring, run() is the main loop
+// and a partial last stage; it ends with a barrier after which the ring is free again.
+template <class C>
 struct DmaTile {
-  using OA = DmaOperand<C::BM, C::THREADS, A_KC>;
-  using OB = DmaOperand<C::BN, C::THREADS, B_KC>;
+  using OA = DmaOperand<C::BM, C::THREADS>;
+  using OB = DmaOperand<C::BN, C::THREADS>;
   static constexpr int LOADS = OA::NQ + OB::NQ;
-  static constexpr bool SLAB_A = A_SW > 0;
-  static_assert(!SLAB_A || (A_KC && A_SW % C::BK == 0), "slab-major A: K-contiguous, whole stages per slab");
   OA oa;
   OB ob;
   const bf16* A;
   const bf16* B;
-  int64_t lda, ldb;
   int k_len;
-  int64_t a_sstride = 0;
-
-  __device__ __forceinline__ void slab_a(int64_t stride) { a_sstride = stride; }
-  __device__ __forceinline__ void issue_a(int k0, lds<char>* buf) const {
-    if constexpr (SLAB_A) {
-      const int sl = k0 / A_SW;
-      oa.issue(A + sl * a_sstride, lda, k0 - sl * A_SW, buf);
-    } else {
-      oa.issue(A, lda, k0, buf);
-    }
-  }
-  __device__ __forceinline__ void tail_a(int k0, lds<char>* buf) const {
-    if constexpr (SLAB_A) {
-      const int sl = k0 / A_SW;
-      oa.tail(A + sl * a_sstride, lda, k0 - sl * A_SW, k_len - sl * A_SW, buf);
-    } else {
-      oa.tail(A, lda, k0, k_len, buf);
-    }
-  }
 
   __device__ __forceinline__ static lds<char>* bufA(lds<char>* smem, int s) { return smem + s * C::STAGE; }
   __device__ __forceinline__ static lds<char>* bufB(lds<char>* smem, int s) {
     return smem + s * C::STAGE + C::A_BYTES;
   }
 
-  __device__ __forceinline__ void prime(const bf16* __restrict__ A_, int64_t lda_, int a_rows,
-                                        const bf16* __restrict__ B_, int64_t ldb_, int b_rows, int k_len_,
+  __device__ __forceinline__ void prime(const bf16* __restrict__ A_, int64_t lda, int a_rows,
+                                        const bf16* __restrict__ B_, int64_t ldb, int b_rows, int k_len_,
                                         lds<char>* smem) {
     A = A_;
     B = B_;
-    lda = lda_;
-    ldb = ldb_;
     k_len = k_len_;
     oa.init(lda, a_rows);
     ob.init(ldb, b_rows);
@@ -604,15 +525,13 @@ struct DmaTile {
 #pragma unroll
     for (int s = 0; s < C::NS - 1; ++s)
       if (s < nfull) {
-        issue_a(s * C::BK, bufA(smem, s));
-        ob.issue(B, ldb, s * C::BK, bufB(smem, s));
+        oa.issue(A, s * C::BK, bufA(smem, s));
+        ob.issue(B, s * C::BK, bufB(smem, s));
       }
   }
 
-  template <bool ROWNORM = false, int X = 0>
-  __device__ __forceinline__ void run(lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ], float* xs = nullptr,
-                                      bool after_prime = false) {
-    static_assert(!ROWNORM || A_KC, "row norms need a K-contiguous A");
+  template <bool ROWNORM = false>
+  __device__ __forceinline__ void run(lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ], float* xs = nullptr) {
     if constexpr (ROWNORM) {
 #pragma unroll
       for (int i = 0; i < (C::MI + C::WAVES_N - 1) / C::WAVES_N; ++i) xs[i] = 0.f;
@@ -622,74 +541,53 @@ struct DmaTile {
 #pragma unroll
       for (int j = 0; j < C::NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int nfull = k_len / C::BK;
-    // Ping-pong schedule for contractions with at least one K-contiguous operand.  With both
-    // operands K-strided (two ds_read_b64_tr_b16 per fragment) the read phase outlasts the
-    // MFMA phase and the single-group schedule below measured faster (dD, weight gradients).
-    constexpr bool PP = A_KC || B_KC;
     auto wait_own = [&](int k) {  // this wave's loads of stage k
       const int ahead = nfull - 1 - k;
-      const int pend = ahead < C::NS - 2 ? ahead : C::NS - 2;
-      if (X > 0 && after_prime && k < C::NS - 1)
-        wait_stage<C, LOADS, X>(pend);  // stage k was primed: the caller's X operations are younger
-      else
-        wait_stage<C, LOADS>(pend);
+      wait_stage<C, LOADS>(ahead < C::NS - 2 ? ahead : C::NS - 2);
     };
-    if constexpr (PP) {
-      // Two wave groups (waves 0 .. WAVES/2-1 and the rest; each SIMD holds one wave of each)
-      // run the same stage sequence  [barrier] read fragments + issue loads [barrier] MFMAs
-      // with group 1 one phase behind group 0, so that while one group reads, the other feeds
-      // the SIMD's matrix unit.  The offset comes from one extra barrier, taken by group 1
-      // before the loop and by group 0 after it (the group index is wave-uniform, so those are
-      // scalar branches and both groups execute the same number of barriers).  Stage kt is
-      // read first by group 0, after barrier 2 kt + 1, which for group 1 is the second barrier
-      // of its stage kt - 1 (or the extra one): each wave waits for its own loads of stage kt
-      // before that barrier; the count of its younger loads is the same in both places.  The
-      // slot of stage kt - 1 gets new loads only after barrier 2 kt + 1, when both groups'
-      // reads of it have completed (lgkmcnt(0) before every second barrier).
-      static_assert(C::WAVES % 2 == 0, "two wave groups");
-      const bool g1 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) >= C::WAVES / 2;
-      if (nfull > 0 && g1) {
-        wait_own(0);
-        wg_barrier();
-      }
-      for (int kt = 0; kt < nfull; ++kt) {
-        if (!g1) wait_own(kt);
-        wg_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        bf16x8 fa[C::MI], fb[C::NJ];
-        const int sc = kt % C::NS;
-        dma_read_frags<C, A_KC, B_KC>(bufA(smem, sc), bufB(smem, sc), fa, fb);
-        const int nx = kt + C::NS - 1;
-        if (nx < nfull) {
-          issue_a(nx * C::BK, bufA(smem, nx % C::NS));
-          ob.issue(B, ldb, nx * C::BK, bufB(smem, nx % C::NS));
-        }
-        if (g1 && kt + 1 < nfull) wait_own(kt + 1);
-        wg_barrier_lds();
-        __builtin_amdgcn_sched_barrier(0);
-        dma_mfmas<C, ROWNORM>(fa, fb, acc, xs);
-      }
-      if (nfull > 0 && !g1) wg_barrier();
-    } else {
-      for (int kt = 0; kt < nfull; ++kt) {
-        wait_own(kt);
-        wg_barrier();
-        const int nx = kt + C::NS - 1;
-        if (nx < nfull) {
-          const int sb = nx % C::NS;
-          issue_a(nx * C::BK, bufA(smem, sb));
-          ob.issue(B, ldb, nx * C::BK, bufB(smem, sb));
-        }
-        const int sc = kt % C::NS;
-        dma_mfma_stage<C, A_KC, B_KC, ROWNORM>(bufA(smem, sc), bufB(smem, sc), acc, xs);
-      }
+    // Two wave groups (waves 0 .. WAVES/2-1 and the rest) run the same stage sequence  [barrier]
+    // read fragments + issue loads [barrier] MFMAs  with group 1 one phase behind group 0, so that
+    // while one group reads, the other feeds the matrix units.  The offset comes from one extra
+    // barrier, taken by group 1 before the loop and by group 0 after it (the group index is
+    // wave-uniform, so those are scalar branches and both groups execute the same number of
+    // barriers).  Stage kt is read first by group 0, after barrier 2 kt + 1, which for group 1 is the
+    // second barrier of its stage kt - 1 (or the extra one): each wave waits for its own loads of
+    // stage kt before that barrier; the count of its younger loads is the same in both places.  The
+    // slot of stage kt - 1 gets new loads only after barrier 2 kt + 1, when both groups'
+    // reads of it have completed (lgkmcnt(0) before every second barrier).
+    static_assert(C::WAVES % 2 == 0, "two wave groups");
+    const bool g1 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) >= C::WAVES / 2;
+    if (nfull > 0 && g1) {
+      wait_own(0);
+      wg_barrier();
     }
+    for (int kt = 0; kt < nfull; ++kt) {
+      if (!g1) wait_own(kt);
+      wg_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8 fa[C::MI], fb[C::NJ];
+      const int sc = kt % C::NS;
+      dma_read_frags<C>(bufA(smem, sc), bufB(smem, sc), fa, fb);
+      const int nx = kt + C::NS - 1;
+      if (nx < nfull) {
+        oa.issue(A, nx * C::BK, bufA(smem, nx % C::NS));
+        ob.issue(B, nx * C::BK, bufB(smem, nx % C::NS));
+      }
+      if (g1 && kt + 1 < nfull) wait_own(kt + 1);
+      wg_barrier_lds();
+      __builtin_amdgcn_sched_barrier(0);
+      dma_mfmas<C, ROWNORM>(fa, fb, acc, xs);
+    }
+    if (nfull > 0 && !g1) wg_barrier();
     if (nfull * C::BK < k_len) {
       const int sb = nfull % C::NS;
-      tail_a(nfull * C::BK, bufA(smem, sb));
-      ob.tail(B, ldb, nfull * C::BK, k_len, bufB(smem, sb));
+      oa.tail(A, nfull * C::BK, k_len, bufA(smem, sb));
+      ob.tail(B, nfull * C::BK, k_len, bufB(smem, sb));
       wg_barrier_lds();
-      dma_mfma_stage<C, A_KC, B_KC, ROWNORM>(bufA(smem, sb), bufB(smem, sb), acc, xs);
+      bf16x8 fa[C::MI], fb[C::NJ];
+      dma_read_frags<C>(bufA(smem, sb), bufB(smem, sb), fa, fb);
+      __builtin_amdgcn_sched_barrier(0);  // all of the fragment reads go out before the MFMAs
+      dma_mfmas<C, ROWNORM>(fa, fb, acc, xs);
     }
     wg_barrier_lds();
   }
@@ -1177,13 +1075,13 @@ struct PipeTile {
 };
 
 // The tile loop of a direct-to-LDS configuration.
-template <class C, bool A_KC, bool B_KC, int A_SW = 0, bool PIPE = C::PIPE>
+template <class C, bool A_KC, bool B_KC, bool PIPE = C::PIPE>
 struct TileLoop {
-  using type = PipeTile<C, A_KC, B_KC, A_SW>;
+  using type = PipeTile<C, A_KC, B_KC>;
 };
-template <class C, bool A_KC, bool B_KC, int A_SW>
-struct TileLoop<C, A_KC, B_KC, A_SW, false> {
-  using type = DmaTile<C, A_KC, B_KC>;
+template <class C>
+struct TileLoop<C, true, true, false> {
+  using type = DmaTile<C>;
 };
 
 template <class C, bool A_KC, bool B_KC, bool ROWNORM = false>

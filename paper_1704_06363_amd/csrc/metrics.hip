@@ -77,10 +77,6 @@ __device__ __forceinline__ void emit_topm(float (&lv)[M], int (&li)[M], int m, i
 // in the lower lane), then the 16 largest of two rows are the larger ones of one row and the other
 // reversed, sorted again.  A step is a lane move and a median with +inf or -inf: about 50
 // instructions (130 in a full sort by selects of minima and maxima).
-template <int CTRL>
-__device__ __forceinline__ float dpp_of(float x) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
-}
 __device__ __forceinline__ float max_of(float a, float b) {  // one instruction, any NaN passed over
   return __builtin_amdgcn_fmed3f(a, b, INFINITY);
 }
@@ -88,29 +84,29 @@ __device__ __forceinline__ float mth_lane_value(float x, int m, int l) {
   const auto step = [&](float y, int bit) {
     x = __builtin_amdgcn_fmed3f(x, y, (l & bit) ? -INFINITY : INFINITY);  // the smaller : the larger
   };
-  const auto xor1 = [&] { step(dpp_of<0xB1>(x), 1); };           // quad_perm [1,0,3,2]
-  const auto xor2 = [&] { step(dpp_of<0x4E>(x), 2); };           // quad_perm [2,3,0,1]
-  const auto xor4 = [&] { step(dpp_of<0x1B>(dpp_of<0x141>(x)), 4); };  // half mirror, quad mirror
-  const auto xor8 = [&] { step(dpp_of<0x128>(x), 8); };          // row_ror:8
+  const auto xor1 = [&] { step(dpp<0xB1>(x), 1); };           // quad_perm [1,0,3,2]
+  const auto xor2 = [&] { step(dpp<0x4E>(x), 2); };           // quad_perm [2,3,0,1]
+  const auto xor4 = [&] { step(dpp<0x1B>(dpp<0x141>(x)), 4); };  // half mirror, quad mirror
+  const auto xor8 = [&] { step(dpp<0x128>(x), 8); };          // row_ror:8
   xor1();
-  step(dpp_of<0x1B>(x), 2);  // quad mirror
+  step(dpp<0x1B>(x), 2);  // quad mirror
   xor1();
-  step(dpp_of<0x141>(x), 4);  // half mirror
+  step(dpp<0x141>(x), 4);  // half mirror
   xor2();
   xor1();
-  step(dpp_of<0x140>(x), 8);  // row mirror
+  step(dpp<0x140>(x), 8);  // row mirror
   xor4();
   xor2();
   xor1();
   // rows 0 and 2 take the best of rows 0, 1 and 2, 3
-  unsigned y = __float_as_uint(dpp_of<0x140>(x));
+  unsigned y = __float_as_uint(dpp<0x140>(x));
   x = max_of(x, __uint_as_float(__builtin_amdgcn_permlane16_swap(y, y, false, false)[1]));
   xor8();
   xor4();
   xor2();
   xor1();
   // row 0 the best of all
-  y = __float_as_uint(dpp_of<0x140>(x));
+  y = __float_as_uint(dpp<0x140>(x));
   x = max_of(x, __uint_as_float(__builtin_amdgcn_permlane32_swap(y, y, false, false)[1]));
   xor8();
   xor4();

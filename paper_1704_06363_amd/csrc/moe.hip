@@ -1536,11 +1536,10 @@ int launch_gemm_tn(const T* A, const T* B, int64_t rows, int M, int N, float* ou
   float* part = ws.take<float>((size_t)kMaxSplitItems * C::BM * C::BN);
   if (!ws.fits()) return HMOE_EWORKSPACE;
   if (rows <= 0) return launch_zero_f32(out, (int64_t)M * N, st);
-  if constexpr (sizeof(T) == 4) {
-    // a short reduction over few tiles (the PCA's Gram matrices: 4 tiles, two chunks): quarter tiles
-    if (rows <= 4096 && cdiv(M, C::BM) * cdiv(N, C::BN) * cdiv(rows, 256) < device_cus())
-      return launch_tn_split<CfgQuarter<T>, false, C>(label, A, B, rows, M, N, out, part, st);
-  }
+  static_assert(sizeof(T) == 4, "fp32 products");
+  // a short reduction over few tiles (the PCA's Gram matrices: 4 tiles, two chunks): quarter tiles
+  if (rows <= 4096 && cdiv(M, C::BM) * cdiv(N, C::BN) * cdiv(rows, 256) < device_cus())
+    return launch_tn_split<CfgQuarter<T>, false, C>(label, A, B, rows, M, N, out, part, st);
   return launch_tn_split<C>(label, A, B, rows, M, N, out, part, st);
 }
 
@@ -1578,8 +1577,6 @@ template size_t gemm_tn_ws<float>();
 template size_t gemm_tn_ws<bf16>();
 template int launch_gemm_tn<float>(const float*, const float*, int64_t, int, int, float*, Workspace&, hipStream_t,
                                    const char*);
-template int launch_gemm_tn<bf16>(const bf16*, const bf16*, int64_t, int, int, float*, Workspace&, hipStream_t,
-                                  const char*);
 template int launch_gemm_nn<float>(const float*, const float*, int64_t, int, int, float*, hipStream_t);
 
 int launch_moe_forward(const hmoe_moe_params_t* p, int64_t n, const void* Xs, const int32_t* offsets,

@@ -450,14 +450,9 @@ static int pca_project_t(const T* X, int64_t n, int d, const float* mean, const 
 
 int launch_pca_project(const void* X, hmoe_dtype_t dt, int64_t n, int d, const float* mean, const float* comps,
                        int r, void* Z, Workspace& ws, hipStream_t st) {
-  // both operands K-contiguous: the pipelined engine in either dtype (fp32 rows count twice)
-  if (dt == HMOE_BF16) {
-    if (d >= kPipeMaxLd)
-      return pca_project_t<bf16, CfgSmall<bf16>>((const bf16*)X, n, d, mean, comps, r, (bf16*)Z, ws, st);
-    return pca_project_t<bf16, CfgPipe>((const bf16*)X, n, d, mean, comps, r, (bf16*)Z, ws, st);
-  }
-  if (2 * (int64_t)d >= kPipeMaxLd)
-    return pca_project_t<float, CfgSmall<float>>((const float*)X, n, d, mean, comps, r, (float*)Z, ws, st);
+  // both operands K-contiguous: the pipelined engine in either dtype (the workspace has room for d^2
+  // floats, so d is far below kPipeMaxLd / 2)
+  if (dt == HMOE_BF16) return pca_project_t<bf16, CfgPipe>((const bf16*)X, n, d, mean, comps, r, (bf16*)Z, ws, st);
   return pca_project_t<float, CfgPipeF32>((const float*)X, n, d, mean, comps, r, (float*)Z, ws, st);
 }
 

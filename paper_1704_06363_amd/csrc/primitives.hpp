@@ -38,6 +38,14 @@ __device__ __forceinline__ V block_excl_scan(V v, V* sh, V* total) {
   return res;
 }
 
+// How many of the `m` segments f0, f0 + 1, ..., whose lengths are at len, come before segment e of
+// length `mine`: longest first, equal lengths by lower index.
+__device__ __forceinline__ int seg_rank(const int32_t* len, int m, int f0, int32_t mine, int e) {
+  int rank = 0;
+  for (int q = 0; q < m; ++q) rank += (len[q] > mine) || (len[q] == mine && f0 + q < e);
+  return rank;
+}
+
 // What the grouped kernels need to know of the segments, in one launch: for each of up to three tile
 // heights tile_start[q][e] = sum_{e' < e} ceil((seg[e'+1] - seg[e']) / tile[q]), e = 0..G, and the
 // order of k_seg_order (G <= 256; NULL: not wanted).  One block of 1024 threads; G <= 4096.
@@ -74,14 +82,11 @@ static __global__ void __launch_bounds__(1024) k_seg_plan(const int32_t* __restr
   const int e = threadIdx.x;  // per = 1
   if (e < G) len_s[e] = len[0];
   __syncthreads();
-  if (e >= G) return;
-  int rank = 0;
-  for (int f = 0; f < G; ++f) rank += (len_s[f] > len[0]) || (len_s[f] == len[0] && f < e);
-  plan.order[rank] = e;
+  if (e < G) plan.order[seg_rank(len_s, G, 0, len[0], e)] = e;
 }
 
-// order[r] = the segment of rank r when segments are ranked by length, longest first, equal
-// lengths by lower index (a stable descending sort, so `order` is a permutation of 0..G-1).
+// order[r] = the segment of rank r (seg_rank: a stable descending sort, so `order` is a permutation of
+// 0..G-1).
 // Each thread ranks one segment against all G lengths, staged through LDS 256 at a time.
 static __global__ void __launch_bounds__(256) k_seg_order(const int32_t* __restrict__ seg, int G,
                                                         int32_t* __restrict__ order) {
@@ -94,11 +99,7 @@ static __global__ void __launch_bounds__(256) k_seg_order(const int32_t* __restr
     __syncthreads();
     len_s[threadIdx.x] = f < G ? seg[f + 1] - seg[f] : 0;
     __syncthreads();
-    const int m = (G - f0) < 256 ? (G - f0) : 256;
-    for (int q = 0; q < m; ++q) {
-      const int32_t c = len_s[q];
-      rank += (c > mine) || (c == mine && f0 + q < e);
-    }
+    rank += seg_rank(len_s, (G - f0) < 256 ? (G - f0) : 256, f0, mine, e);
   }
   if (e < G) order[rank] = e;
 }
