@@ -683,6 +683,8 @@ __device__ __forceinline__ const char* uniform(const char* p) {
   return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
 
+static __device__ const i32x4 kZeros = {0, 0, 0, 0};
+
 // Half panels of an operand of R tile rows, W per wave strip.
 //   K-contiguous: slot [R / 2 rows][64 K], 16-byte chunk c of slot row r at c ^ ((r ^ (r >> 2)) & 7).
 //   K-strided:    slot [64 K][R / 2 rows], chunk swizzle of ks_off<R / 2>.
@@ -699,22 +701,26 @@ struct HalfPanels {
     constexpr int G = W / 2;
     return (q / G) * W + h * G + q % G;
   }
-  // byte offset and K position (within the stage) of 16-byte slot piece `piece` of half h; rows
-  // past the valid range take a valid row's bytes (they only feed outputs that are not stored)
-  __device__ __forceinline__ static uint32_t source(int h, int piece, int64_t ld, int rows_valid, int& kk) {
+  // K position (within the stage) of 16-byte slot piece `piece`
+  __device__ __forceinline__ static int k_of(int piece) {
     if constexpr (KC) {
-      const int r = piece >> 3, p = piece & 7;
-      const int c = p ^ ((r ^ (r >> 2)) & 7);
-      int tr = tile_row(h, r);
-      tr = tr < rows_valid ? tr : rows_valid - 1;
-      kk = c * 8;
-      return (uint32_t)((tr * ld + c * 8) * 2);
+      const int r = piece >> 3;
+      return ((piece & 7) ^ ((r ^ (r >> 2)) & 7)) * 8;
     } else {
-      constexpr int CPR = HR / 8;
-      const int k = piece / CPR, p = piece % CPR;
+      return piece / (HR / 8);
+    }
+  }
+  // byte offset of piece `piece` of half h; rows past the valid range take a valid row's bytes (they
+  // only feed outputs that are not stored)
+  __device__ __forceinline__ static uint32_t source(int h, int piece, int64_t ld, int rows_valid) {
+    const int k = k_of(piece);
+    if constexpr (KC) {
+      int tr = tile_row(h, piece >> 3);
+      tr = tr < rows_valid ? tr : rows_valid - 1;
+      return (uint32_t)((tr * ld + k) * 2);
+    } else {
       const int sw = ((k & 3) | ((k >> 1) & 4)) << 1;
-      const int col = tile_row(h, (p ^ sw) * 8);
-      kk = k;
+      const int col = tile_row(h, ((piece % (HR / 8)) ^ sw) * 8);
       return (uint32_t)((k * ld + (col < rows_valid ? col : 0)) * 2);
     }
   }
@@ -723,10 +729,7 @@ struct HalfPanels {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        int kk;
-        off[h][q] = source(h, q * THREADS + t, ld, rows_valid, kk);
-      }
+      for (int q = 0; q < NQ; ++q) off[h][q] = source(h, q * THREADS + t, ld, rows_valid);
   }
   template <int H>
   __device__ __forceinline__ void issue(const char* __restrict__ base, lds<char>* slot) const {
@@ -734,22 +737,36 @@ struct HalfPanels {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       uint32_t o = off[H][q];
-      asm volatile("" : "+v"(o));  // keeps base + o an SGPR base with a 32-bit offset
+      asm("" : "+v"(o));  // keeps base + o an SGPR base with a 32-bit offset (volatile: dD 1.5% slower)
       __builtin_amdgcn_global_load_lds((const void*)(base + o), (lds<void>*)(slot + (q * (THREADS / 64) + w) * 1024),
                                        16, 0, 0);
     }
   }
-  // The last, partial stage of k_left K positions, through registers; zero past them.
+  // The last, partial stage of k_left K positions: the pieces past them come from a piece of zeros.
+  template <int H>
+  __device__ __forceinline__ void issue_last(const char* __restrict__ base, int k_left, lds<char>* slot) const {
+    const int t = thread_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t b = reinterpret_cast<uint64_t>(base), z = reinterpret_cast<uint64_t>(&kZeros);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const bool in = k_of(q * THREADS + t) < k_left;
+      // 32-bit halves: as 64-bit sums the offsets would be kept in register pairs
+      const uint32_t lo = (uint32_t)b + off[H][q], hi = (uint32_t)(b >> 32) + (lo < off[H][q] ? 1u : 0u);
+      const uint64_t from = (uint64_t)(in ? hi : (uint32_t)(z >> 32)) << 32 | (in ? lo : (uint32_t)z);
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(from),
+                                       (lds<void>*)(slot + (q * (THREADS / 64) + w) * 1024), 16, 0, 0);
+    }
+  }
+  // The same through registers, after the loop.
   __device__ __forceinline__ static void tail(int h, const char* __restrict__ base, int64_t ld, int rows_valid,
                                               int k_left, lds<char>* slot) {
     const int t = thread_id();
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int piece = q * THREADS + t;
-      int kk;
-      const uint32_t o = source(h, piece, ld, rows_valid, kk);
+      const uint32_t o = source(h, piece, ld, rows_valid);
       i32x4 v = i32x4{0, 0, 0, 0};
-      if (kk < k_left)
+      if (k_of(piece) < k_left)
         v = *reinterpret_cast<const __attribute__((address_space(1))) i32x4*>(
             (const __attribute__((address_space(1))) char*)base + o);
       *reinterpret_cast<lds<i32x4>*>(slot + piece * 16) = v;
@@ -804,14 +821,17 @@ struct HalfFrags {
 // loads before it runs the current tile's epilogue:
 //   prime()  issues the first loads of a tile (LDS must be free: after run()'s closing barrier,
 //            or at kernel start);
-//   run()    the main loop and a partial last stage; it ends with a barrier after which LDS is
-//            free again.  run<.., X>(.., after_prime) is for a caller that issued exactly X
+//   run()    the main loop; it ends with a barrier after which LDS is free again.  run<.., X>(.., after_prime) is for a caller that issued exactly X
 //            further memory operations (per wave) between prime() and run() when after_prime is
 //            true: the waits for the primed loads let those X stay in flight.
 // A_SW > 0: A is K-contiguous and stored slab-major -- K split into slabs of A_SW columns,
 // slab s of every row at A + s a_sstride, lda = A_SW within a slab (A_SW a multiple of BK).
 // Set the stride with slab_a() before prime().
-template <class C, bool A_KC, bool B_KC, int A_SW = 0>
+// A partial last stage is one more stage of the loop, its pieces past the end loaded from zeros; with
+// REG_TAIL it goes through registers after the loop: the row norms leave no registers for the other
+// (48 spilled, 200,000 x 2048 bf16 against 256 centres 319 -> 570 us), and the loop of long reductions
+// over rows (dD) comes out 2% slower with it.
+template <class C, bool A_KC, bool B_KC, int A_SW = 0, bool REG_TAIL = false>
 struct PipeTile {
   using OA = HalfPanels<C::BM, C::WM, C::THREADS, A_KC, false>;
   using OB = HalfPanels<C::BN, C::WN, C::THREADS, B_KC, C::SPLIT>;
@@ -825,9 +845,11 @@ struct PipeTile {
   HalfFrags<B_KC, C::BN / 2, HJ> fb;
   const char* A;
   const char* B;
-  int64_t lda, ldb, step_a, step_b;  // bytes per stage
+  int64_t step_a, step_b;  // bytes per stage
   int64_t slab_bytes = 0;
-  int a_rows, b_rows, k_len;
+  int nk, k_last;  // stages, and K positions of the last one (REG_TAIL: of the tail)
+  int64_t lda, ldb;
+  int a_rows, b_rows;
 
   __device__ __forceinline__ void slab_a(int64_t stride) { slab_bytes = stride * 2; }
   __device__ __forceinline__ const char* a_at(int k) const {  // stage k of A
@@ -846,10 +868,22 @@ struct PipeTile {
     return smem + par * C::STAGE + 2 * C::A_HALF + h * C::B_HALF;
   }
 
-  // LONG: the reduction has at least two whole stages (no branches among the loads)
+  // Loads of half H of stage k, which may be the last.
+  template <int H>
+  __device__ __forceinline__ void load_a(int k, lds<char>* slot) const {
+    if (!REG_TAIL && k == nk - 1 && k_last < C::BK) oa.template issue_last<H>(a_at(k), k_last, slot);
+    else oa.template issue<H>(a_at(k), slot);
+  }
+  template <int H>
+  __device__ __forceinline__ void load_b(int k, lds<char>* slot) const {
+    if (!REG_TAIL && k == nk - 1 && k_last < C::BK) ob.template issue_last<H>(b_at(k), k_last, slot);
+    else ob.template issue<H>(b_at(k), slot);
+  }
+
+  // LONG: the reduction has at least two stages (no branches among the first one's loads)
   template <bool LONG = false>
   __device__ __forceinline__ void prime(const bf16* __restrict__ A_, int64_t lda_, int a_rows_,
-                                        const bf16* __restrict__ B_, int64_t ldb_, int b_rows_, int k_len_,
+                                        const bf16* __restrict__ B_, int64_t ldb_, int b_rows_, int k_len,
                                         lds<char>* smem) {
     A = uniform(reinterpret_cast<const char*>(A_));
     B = uniform(reinterpret_cast<const char*>(B_));
@@ -857,24 +891,29 @@ struct PipeTile {
     ldb = ldb_;
     a_rows = a_rows_;
     b_rows = b_rows_;
-    k_len = __builtin_amdgcn_readfirstlane(k_len_);
+    k_len = __builtin_amdgcn_readfirstlane(k_len);
+    nk = (REG_TAIL ? k_len : k_len + C::BK - 1) / C::BK;
+    k_last = k_len - (REG_TAIL ? nk : nk - 1) * C::BK;
     step_a = A_KC ? C::BK * 2 : C::BK * 2 * lda;
     step_b = B_KC ? C::BK * 2 : C::BK * 2 * ldb;
     oa.init(lda, a_rows);
     ob.init(ldb, b_rows);
-    const int nk = k_len / C::BK;
-    if (LONG || nk > 0) {
+    if constexpr (LONG) {
       const char *pa = a_at(0), *pb = b_at(0);
       ob.template issue<0>(pb, slot_b(smem, 0, 0));
       oa.template issue<0>(pa, slot_a(smem, 0, 0));
       ob.template issue<1>(pb, slot_b(smem, 0, 1));
       oa.template issue<1>(pa, slot_a(smem, 0, 1));
+    } else if (nk > 0) {
+      load_b<0>(0, slot_b(smem, 0, 0));
+      load_a<0>(0, slot_a(smem, 0, 0));
+      load_b<1>(0, slot_b(smem, 0, 1));
+      load_a<1>(0, slot_a(smem, 0, 1));
     }
     if (LONG || nk > 1) {
-      const char *pa = a_at(1), *pb = b_at(1);
-      ob.template issue<0>(pb, slot_b(smem, 1, 0));
-      oa.template issue<0>(pa, slot_a(smem, 1, 0));
-      ob.template issue<1>(pb, slot_b(smem, 1, 1));
+      load_b<0>(1, slot_b(smem, 1, 0));
+      load_a<0>(1, slot_a(smem, 1, 0));
+      load_b<1>(1, slot_b(smem, 1, 1));
     }
   }
 
@@ -957,8 +996,13 @@ struct PipeTile {
     bf16x8 a[HI][2], b1[HJ][2];
     read_a(a, slot_a(smem, 0, 0));  // fa and fb carry the stage's parity
     read_b(b1, slot_b(smem, 0, 1));
-    if (STEADY || left >= 1) oa.template issue<1>(a_at(s + 1), slot_a(smem, PAR ^ 1, 1));
-    if (STEADY || left >= 2) ob.template issue<0>(b_at(s + 2), slot_b(smem, PAR, 0));
+    if constexpr (STEADY) {
+      oa.template issue<1>(a_at(s + 1), slot_a(smem, PAR ^ 1, 1));
+      ob.template issue<0>(b_at(s + 2), slot_b(smem, PAR, 0));
+    } else {
+      if (left >= 1) load_a<1>(s + 1, slot_a(smem, PAR ^ 1, 1));
+      if (left >= 2) load_b<0>(s + 2, slot_b(smem, PAR, 0));
+    }
     if (X > 0 && extra) {
       if (STEADY || left >= 2) wait_vmcnt<2 * AL + 2 * BL + X>();
       else if (left == 1) wait_vmcnt<2 * AL + BL + X>();
@@ -977,9 +1021,12 @@ struct PipeTile {
     fa.move(kFlip);
     fb.move(kFlip);
     if (STEADY || left >= 1) read_b(b0n, slot_b(smem, 0, 0));
-    if (STEADY || left >= 2) {
+    if constexpr (STEADY) {
       oa.template issue<0>(a_at(s + 2), slot_a(smem, PAR, 0));
       ob.template issue<1>(b_at(s + 2), slot_b(smem, PAR, 1));
+    } else if (left >= 2) {
+      load_a<0>(s + 2, slot_a(smem, PAR, 0));
+      load_b<1>(s + 2, slot_b(smem, PAR, 1));
     }
     if (X > 0 && extra) {
       if (STEADY || left >= 2) wait_vmcnt<2 * AL + 2 * BL + X>();
@@ -1011,7 +1058,6 @@ struct PipeTile {
 #pragma unroll
         for (int j = 0; j < C::NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    const int nk = k_len / C::BK;
     const int l = thread_id() & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = w / C::WAVES_N, wn = w % C::WAVES_N;
     fa.init(wm * (C::WM / 2), l & 15, l >> 4);
@@ -1037,7 +1083,8 @@ struct PipeTile {
       asm volatile("" : "+s"(first));
       return X > 0 && after_prime && first == 0;
     };
-    for (; s + 3 < nk; s += 2) {
+    const int whole = !REG_TAIL && k_last < C::BK ? nk - 1 : nk;  // stages that may be loaded without a look at their end
+    for (; s + 3 < whole; s += 2) {  // loads up to stage s + 3
       stage<0, true, ROWNORM, X>(smem, acc, be, bo, s, 0, wn, xs, extra());
       stage<1, true, ROWNORM, 0>(smem, acc, bo, be, s + 1, 0, wn, xs, false);
     }
@@ -1046,17 +1093,16 @@ struct PipeTile {
       if (s + 1 < nk) stage<1, false, ROWNORM, 0>(smem, acc, bo, be, s + 1, nk - 2 - s, wn, xs, false);
     }
     if (nk > 0 && !g1) wg_barrier();
-    if (nk * C::BK < k_len) {
+    if (REG_TAIL && k_last > 0) {
       bf16x8 a[HI][2];
-      const int left = k_len - nk * C::BK;
       const char *pa = a_at(nk), *pb = b_at(nk);
       fa.init(wm * (C::WM / 2), l & 15, l >> 4);
       fb.init(wn * (C::WN / 2), l & 15, l >> 4);
       wg_barrier_lds();
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        OA::tail(h, pa, lda, a_rows, left, slot_a(smem, 0, h));
-        OB::tail(h, pb, ldb, b_rows, left, slot_b(smem, 0, h));
+        OA::tail(h, pa, lda, a_rows, k_last, slot_a(smem, 0, h));
+        OB::tail(h, pb, ldb, b_rows, k_last, slot_b(smem, 0, h));
       }
       wg_barrier_lds();
       read_b(be, slot_b(smem, 0, 0));
@@ -1075,21 +1121,21 @@ struct PipeTile {
 };
 
 // The tile loop of a direct-to-LDS configuration.
-template <class C, bool A_KC, bool B_KC, bool PIPE = C::PIPE>
+template <class C, bool A_KC, bool B_KC, bool REG_TAIL = false, bool PIPE = C::PIPE>
 struct TileLoop {
-  using type = PipeTile<C, A_KC, B_KC>;
+  using type = PipeTile<C, A_KC, B_KC, 0, REG_TAIL>;
 };
-template <class C>
-struct TileLoop<C, true, true, false> {
+template <class C, bool REG_TAIL>
+struct TileLoop<C, true, true, REG_TAIL, false> {
   using type = DmaTile<C>;
 };
 
-template <class C, bool A_KC, bool B_KC, bool ROWNORM = false>
+template <class C, bool A_KC, bool B_KC, bool ROWNORM = false, bool REG_TAIL = false>
 __device__ __forceinline__ void gemm_tile_dma(const bf16* __restrict__ A, int64_t lda, int a_rows,
                                               const bf16* __restrict__ B, int64_t ldb, int b_rows, int k_len,
                                               lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ],
                                               float* xs = nullptr) {
-  typename TileLoop<C, A_KC, B_KC>::type t;
+  typename TileLoop<C, A_KC, B_KC, REG_TAIL>::type t;
   t.prime(A, lda, a_rows, B, ldb, b_rows, k_len, smem);
   t.template run<ROWNORM>(smem, acc, xs);
 }
@@ -1104,17 +1150,17 @@ __device__ __host__ constexpr bool dma_f32() {
 }
 
 // Full K loop for one tile on whichever engine the configuration names.
-template <class C, bool A_KC, bool B_KC, bool ROWNORM = false>
+template <class C, bool A_KC, bool B_KC, bool ROWNORM = false, bool REG_TAIL = false>
 __device__ __forceinline__ void gemm_tile(const typename C::type* __restrict__ A, int64_t lda, int a_rows,
                                           const typename C::type* __restrict__ B, int64_t ldb, int b_rows,
                                           int k_len, lds<char>* smem, floatx4 (&acc)[C::MI][C::NJ],
                                           float* xs = nullptr) {
   if constexpr (dma_f32<C>()) {
     static_assert(A_KC && B_KC, "fp32 on the direct-to-LDS engine: K-contiguous operands only");
-    gemm_tile_dma<C, A_KC, B_KC, ROWNORM>(reinterpret_cast<const bf16*>(A), 2 * lda, a_rows,
+    gemm_tile_dma<C, A_KC, B_KC, ROWNORM, REG_TAIL>(reinterpret_cast<const bf16*>(A), 2 * lda, a_rows,
                                           reinterpret_cast<const bf16*>(B), 2 * ldb, b_rows, 2 * k_len, smem, acc, xs);
   } else if constexpr (C::DMA) {
-    gemm_tile_dma<C, A_KC, B_KC, ROWNORM>(A, lda, a_rows, B, ldb, b_rows, k_len, smem, acc, xs);
+    gemm_tile_dma<C, A_KC, B_KC, ROWNORM, REG_TAIL>(A, lda, a_rows, B, ldb, b_rows, k_len, smem, acc, xs);
   } else {
     gemm_tile_reg<C, A_KC, B_KC, ROWNORM>(A, lda, a_rows, B, ldb, b_rows, k_len, smem, acc, xs);
   }

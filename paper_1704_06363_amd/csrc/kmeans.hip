@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(C::THREADS)
   constexpr int U = C::F32 ? 2 : 1;
   const bf16* Xu = reinterpret_cast<const bf16*>(X);
   const bf16* Cu = reinterpret_cast<const bf16*>(Cn);
-  typename TileLoop<C, true, true>::type pipe;
+  typename TileLoop<C, true, true, true>::type pipe;
   lds<float>* hn = reinterpret_cast<lds<float>*>(smem + C::LDS);  // [BN]
   static_assert(C::BN <= C::THREADS, "one thread per centre");
   float h = INFINITY;

@@ -356,7 +356,8 @@ __device__ __forceinline__ void dec_bias_arrived(uint2 (&bp)[C::NJ]) {
 #pragma unroll
   for (int j = 0; j < C::NJ; ++j) asm volatile("" : "+v"(bp[j].x), "+v"(bp[j].y));
 }
-template <class C>
+// LONG: the reduction has at least two stages.
+template <class C, bool LONG>
 __global__ void __launch_bounds__(C::THREADS)
     k_dec_fwd_stream(const bf16* __restrict__ H, const bf16* __restrict__ D, const bf16* __restrict__ bD, int64_t n,
                      int V, int o, float* __restrict__ pm, float* __restrict__ ps, bf16* __restrict__ L,
@@ -373,7 +374,7 @@ __global__ void __launch_bounds__(C::THREADS)
   if (t >= tiles) return;
   TileCoord tc = uniform(tile_plain_at<C>(n, V, o, t));
   typename TileLoop<C, true, true>::type pipe;
-  pipe.template prime<true>(H + tc.m0 * o, o, tc.m_rows, D + (int64_t)tc.n0 * o, o, tc.n_cols, o, smem);
+  pipe.template prime<LONG>(H + tc.m0 * o, o, tc.m_rows, D + (int64_t)tc.n0 * o, o, tc.n_cols, o, smem);
   uint2 bp[C::NJ];
   dec_bias_packed<C>(tc, bD, bp);
   dec_bias_arrived<C>(bp);
@@ -404,7 +405,7 @@ __global__ void __launch_bounds__(C::THREADS)
     if (more) {
       nc = uniform(tile_plain_at<C>(n, V, o, tn));
       dec_bias_packed<C>(nc, bD, bp);
-      pipe.template prime<true>(H + nc.m0 * o, o, nc.m_rows, D + (int64_t)nc.n0 * o, o, nc.n_cols, o, smem);
+      pipe.template prime<LONG>(H + nc.m0 * o, o, nc.m_rows, D + (int64_t)nc.n0 * o, o, nc.n_cols, o, smem);
     }
     // the waves' row partials, then the logits stores, then the previous tile's merge:
     // measured faster than merging before the stores.  The merge's stores are younger than
@@ -1012,7 +1013,8 @@ __global__ void __launch_bounds__(C::THREADS)
   if (b < t_full) {
     const TileCoord tc = tn_tile_at<C, SYM>(M, N, (int)rows, b);
     if (!tc.valid) return;
-    gemm_tile<C, false, false>(a_at(tc.m0), lda, tc.m_rows, B + tc.n0, N, tc.n_cols, (int)rows, smem, acc);
+    gemm_tile<C, false, false, false, true>(a_at(tc.m0), lda, tc.m_rows, B + tc.n0, N, tc.n_cols, (int)rows, smem,
+                                            acc);
     store_out<C, float>(tc, acc, smem, out, N, Ident{}, RowId{tc.m0}, NoVec{});
     return;
   }
@@ -1023,8 +1025,8 @@ __global__ void __launch_bounds__(C::THREADS)
   const TileCoord tc = tn_tile_at<C, SYM>(M, N, (int)rows, t);
   const int64_t k0 = c * chunk;
   const int klen = (int)(rows - k0 < chunk ? rows - k0 : chunk);
-  gemm_tile<C, false, false>(a_at(tc.m0) + k0 * lda, lda, tc.m_rows, B + tc.n0 + k0 * N, N, tc.n_cols, klen, smem,
-                             acc);
+  gemm_tile<C, false, false, false, true>(a_at(tc.m0) + k0 * lda, lda, tc.m_rows, B + tc.n0 + k0 * N, N, tc.n_cols,
+                                          klen, smem, acc);
   TileCoord lt = tc;
   lt.m0 = 0;
   lt.n0 = 0;
@@ -1345,23 +1347,18 @@ static int forward_t(const hmoe_moe_params_t* p, int64_t n, const T* Xs, const i
     HMOE_TRY(launch_loss<T>(pm, ps, ntv, Hs, D, (const T*)p->bD, n, s.o, s.V, perm, offsets, s.K, y, lse, loss, st));
     return launch_sum_f32(loss, n, 1.0 / (double)n, nullptr, loss_mean, ws, st);
   }
-  // persistent, one workgroup per resident slot, when a tile's reduction has the two stages its
-  // priming takes; shorter ones have no loop to hide an epilogue behind
-  bool streamed = false;
-  if constexpr (C::PIPE) {
-    if (s.o >= 2 * C::BK) {
-      const int64_t tiles = cdiv(n, C::BM) * ntv;
-      constexpr int lds_bytes = C::LDS + 2 * kDecStatLds;
-      int64_t slots = (int64_t)device_cus() * ((160 * 1024) / lds_bytes);
-      if (slots > tiles) slots = tiles;
-      HMOE_LAUNCH("decoder forward", k_dec_fwd_stream<C>, dim3((unsigned)slots), dim3(C::THREADS), lds_bytes, st,
-                  (const bf16*)H, (const bf16*)D, (const bf16*)p->bD, n, s.V, s.o, pm, ps, (bf16*)Lg, anc);
-      streamed = true;
-    }
-  }
-  if (!streamed)
+  if constexpr (C::PIPE) {  // persistent, one workgroup per resident slot
+    const int64_t tiles = cdiv(n, C::BM) * ntv;
+    constexpr int lds_bytes = C::LDS + 2 * kDecStatLds;
+    int64_t slots = (int64_t)device_cus() * ((160 * 1024) / lds_bytes);
+    if (slots > tiles) slots = tiles;
+    const auto stream = s.o > C::BK ? k_dec_fwd_stream<C, true> : k_dec_fwd_stream<C, false>;
+    HMOE_LAUNCH("decoder forward", stream, dim3((unsigned)slots), dim3(C::THREADS), lds_bytes, st, (const bf16*)H,
+                (const bf16*)D, (const bf16*)p->bD, n, s.V, s.o, pm, ps, (bf16*)Lg, anc);
+  } else {
     HMOE_LAUNCH("decoder forward", k_dec_fwd<C>, dim3((unsigned)(cdiv(n, C::BM) * ntv)), dim3(C::THREADS), C::LDS,
                 st, (const T*)H, D, (const T*)p->bD, n, s.V, s.o, pm, ps, Lg, anc);
+  }
   HMOE_TRY(launch_loss<T>(pm, ps, ntv, H, D, (const T*)p->bD, n, s.o, s.V, nullptr, nullptr, 0, y, lse, loss, st));
   return launch_sum_f32(loss, n, 1.0 / (double)n, nullptr, loss_mean, ws, st);
 }

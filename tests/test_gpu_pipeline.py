@@ -8,7 +8,7 @@ import torch
 from oracle import oracle as O
 from paper_1704_06363_amd import hmoe
 from paper_1704_06363_amd import workloads as W
-from tests.parity import assert_assign, np64
+from tests.parity import anchor_of_columns, assert_assign, np64
 from tests.test_gpu_bf16 import _check_step
 
 pytestmark = pytest.mark.gpu
@@ -23,6 +23,28 @@ def test_step_at_stage_edges(d, h, o, V, n, saved):
     inp = W.skewed_inputs(device="cuda", seed=d + n, n=n, d=d, h=h, o=o, V=V, K=K, bias=True)
     ids = np.random.default_rng(n).integers(0, K, n).astype(np.int32)
     _check_step(inp["X"], ids, K, inp["params"], inp["row_ptr"], inp["tag"], saved=saved)
+
+
+# more tiles than the persistent forward has workgroups, with reductions of one and two stages, whole and not
+@pytest.mark.parametrize("o", [8, 40, 64, 72, 120, 128])
+def test_short_reductions_over_many_tiles(o):
+    n, V, K = 4400, 4360, 3
+    inp = W.skewed_inputs(device="cuda", seed=o, n=n, d=64, h=72, o=o, V=V, K=K, bias=True)
+    p = inp["params"]
+    p["bD"] = torch.randn(V, generator=torch.Generator().manual_seed(o)).to(torch.bfloat16).cuda()
+    ids = torch.from_numpy(np.random.default_rng(o).integers(0, K, n).astype(np.int32)).cuda()
+    dd = hmoe.moe_dispatch(ids, K, rows=inp["X"])
+    row_ptr, tag = torch.tensor(inp["row_ptr"], device="cuda"), torch.tensor(inp["tag"], device="cuda")
+    f = hmoe.moe_forward(p, dd["rows_sorted"], dd["offsets"], dd["perm"], row_ptr, tag, save_logits=True)
+    H, D = f["H"].double(), p["D"].double()  # from the stored H: no rounding of it in between
+    L = H @ D.T + p["bD"].double()
+    # fp32 sums of o products and the bias, and the offset from the anchor rounded to bf16
+    sums = (o + 2) * 2.0 ** -24 * (H.abs() @ D.abs().T + p["bD"].double().abs())
+    A = torch.from_numpy(anchor_of_columns(f["logit_anchor"], V)).cuda().double()
+    got = A + f["logits"].double()
+    assert ((got - L).abs() <= 3 * sums + 2.0 ** -8 * (L - A).abs()).all()
+    # the exponentials' own error, a few units of 2^-23
+    assert (f["lse"].double() - L.logsumexp(1)).abs().max() <= 3 * sums.max() + 2e-6
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
