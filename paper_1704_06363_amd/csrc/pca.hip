@@ -247,6 +247,11 @@ static int orthonormalise_gpu(float*& Q, float*& Z, int d, int r, float* S, floa
   return HMOE_OK;
 }
 
+// Up to this r the final eigensolve runs on the host: its r^3 steps take less there than the GPU's chain
+// of launches and copies.  A fit of 2000 x 256 without iterations, GPU / host: r = 32 0.56 / 0.35 ms, 64
+// 0.94 / 0.70, 96 1.37 / 1.32, 128 1.93 / 2.47.
+constexpr int kRitzHost = 96;
+
 // The eigenvectors of (S + S^T) / 2, r <= kSmallN, as the columns of V (fp32, r x r) in decreasing
 // order of their eigenvalues, which go to eigvals.  r = 256: 2.9 ms (16 on the host).
 static int ritz_gpu(const float* S, int r, float* V, float* eigvals, Workspace& ws, hipStream_t st) {
@@ -394,7 +399,7 @@ static int pca_fit_t(const T* X, int64_t n, int d, int r, int n_iter, uint64_t s
   HMOE_TRY(launch_gemm_nn<float>(Cv, Q, d, d, r, Z, st));
   HMOE_TRY(launch_gemm_tn<float>(Q, Z, d, r, r, S, ws, st));
   ws.off = mark;
-  if (small) {
+  if (small && r > kRitzHost) {
     HMOE_TRY(ritz_gpu(S, r, Rinv, eigvals, ws, st));
     HMOE_TRY(launch_gemm_nn<float>(Q, Rinv, d, r, r, Z, st));
     HMOE_LAUNCH("pca components", k_pca_comps, dim3((unsigned)r), dim3(256), 0, st, (const float*)Z, d, r, comps);
