@@ -441,6 +441,9 @@ size_t pca_project_ws(int d, int r, hmoe_dtype_t dt) {
   return ws.off;
 }
 
+// Up to 64 components run the narrow tiles of the ring engine (a 256 x 256 tile would be padding, and a
+// reduction of one short stage nothing but its latency: 300,000 x 16 fp32 to 8 components 64 us, 20
+// on these; x 512 to 64 645 and 252), half as high where there are fewer of those than CUs.
 template <typename T, class C>
 static int pca_project_t(const T* X, int64_t n, int d, const float* mean, const float* comps, int r, T* Zo,
                          Workspace& ws, hipStream_t st) {
@@ -455,10 +458,17 @@ static int pca_project_t(const T* X, int64_t n, int d, const float* mean, const 
 
 int launch_pca_project(const void* X, hmoe_dtype_t dt, int64_t n, int d, const float* mean, const float* comps,
                        int r, void* Z, Workspace& ws, hipStream_t st) {
-  // both operands K-contiguous: the pipelined engine in either dtype (the workspace has room for d^2
-  // floats, so d is far below kPipeMaxLd / 2)
-  if (dt == HMOE_BF16) return pca_project_t<bf16, CfgPipe>((const bf16*)X, n, d, mean, comps, r, (bf16*)Z, ws, st);
-  return pca_project_t<float, CfgPipeF32>((const float*)X, n, d, mean, comps, r, (float*)Z, ws, st);
+  // both operands K-contiguous: the direct-to-LDS engines in either dtype (the workspace has room for
+  // d^2 floats, so d is far below kPipeMaxLd / 2)
+  const bool few = cdiv(n, CfgDmaNarrow::BM) < device_cus();
+  if (dt == HMOE_BF16) {
+    const auto run = r > 64 ? pca_project_t<bf16, CfgPipe>
+                            : (few ? pca_project_t<bf16, CfgDmaNarrowFew> : pca_project_t<bf16, CfgDmaNarrow>);
+    return run((const bf16*)X, n, d, mean, comps, r, (bf16*)Z, ws, st);
+  }
+  const auto run = r > 64 ? pca_project_t<float, CfgPipeF32>
+                          : (few ? pca_project_t<float, CfgDmaF32NarrowFew> : pca_project_t<float, CfgDmaF32Narrow>);
+  return run((const float*)X, n, d, mean, comps, r, (float*)Z, ws, st);
 }
 
 }  // namespace hmoe

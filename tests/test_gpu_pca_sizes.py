@@ -22,7 +22,7 @@ def _rows(n, d, seed, dtype):
 
 @pytest.mark.parametrize("n,d,r,n_iter,dtype", [
     (900, 8, 8, 0, "f32"), (900, 16, 16, 1, "f32"), (900, 32, 32, 2, "f32"), (1500, 40, 40, 2, "bf16"),
-    (1500, 64, 64, 0, "f32"), (1500, 72, 72, 3, "f32"), (3000, 136, 136, 2, "f32"), (3000, 248, 248, 2, "bf16"),
+    (1500, 64, 64, 0, "f32"), (1500, 72, 72, 3, "f32"), (2000, 96, 96, 2, "f32"), (2000, 104, 104, 2, "f32"), (3000, 136, 136, 2, "f32"), (3000, 248, 248, 2, "bf16"),
     (3000, 256, 256, 0, "f32"), (3000, 256, 256, 5, "f32"), (3000, 264, 264, 2, "f32"), (4000, 520, 520, 2, "bf16")])
 def test_whole_spectrum(n, d, r, n_iter, dtype):
     X = _rows(n, d, d + n_iter, dtype)
@@ -53,6 +53,23 @@ def test_lost_rank_goes_to_the_host(r, n_iter):
     w = np.linalg.eigvalsh(Cov)[::-1]
     assert (w[:k] > 1e-3 * w[0]).all() and np.abs(w[k:]).max() <= 1e-9 * w[0]
     assert np.abs(np64(ev) - w[:r]).max() <= EV_RT * w[0]
+
+
+# 256 x 128 rows: the last of the half-height tiles and the first of the others; 64 and 72 components
+@pytest.mark.parametrize("n", [1, 65, 32640, 32769])
+@pytest.mark.parametrize("d,r", [(8, 8), (72, 16), (136, 64), (136, 72)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_projection_tiles(n, d, r, dtype):
+    X = _rows(n, d, n + d, dtype)
+    g = torch.Generator().manual_seed(r)
+    U, mean = torch.randn(r, d, generator=g).cuda() * d ** -0.5, torch.randn(d, generator=g).cuda()
+    Z = hmoe.pca_project(X, mean, U)
+    lo = U.to(X.dtype).double()
+    ref = X.double() @ lo.T - (U.double() @ mean.double())
+    # fp32 sums of d products and the bias, and in bf16 the rounding of the result
+    mag = X.double().abs() @ lo.abs().T + (U.double().abs() @ mean.double().abs())
+    bound = (d + 2) * 2.0 ** -24 * mag + (2.0 ** -8 if dtype == "bf16" else 2.0 ** -24) * ref.abs()
+    assert ((Z.double() - ref).abs() <= bound).all()
 
 
 def test_not_a_number_is_refused():
