@@ -346,8 +346,13 @@ int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* 
   const auto partial = nv == 1 ? k_segsum_partial<T, 1> : (nv == 2 ? k_segsum_partial<T, 2> : k_segsum_partial<T, kSegMaxVec>);
   HMOE_LAUNCH("segsum partial", partial, dim3((unsigned)pieces, (unsigned)cdiv(vecs, 256 * nv)), dim3(256), 0, st, X, ld,
               rowmap, seg, ts, G, w, part);
-  HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
-                     ts, G, w, out, accumulate);
+  // more than eight pieces a segment: their sum is a chain worth splitting
+  if (n > 8 * (int64_t)kSegPiece * G)
+    HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
+                ts, G, w, out, accumulate);
+  else
+    HMOE_LAUNCH("segsum final", k_segsum_final_few<O>, dim3((unsigned)cdiv((int64_t)G * w, 256)), dim3(256), 0, st,
+                part, ts, G, w, out, accumulate);
   return HMOE_OK;
 }
 

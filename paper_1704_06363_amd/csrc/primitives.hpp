@@ -233,6 +233,27 @@ __global__ void __launch_bounds__(256) k_segsum_final(const double* __restrict__
   else out[idx] = (O)s;
 }
 
+// The same sums with a thread for each output, eight loads in flight: for segments of few pieces, where
+// the eight threads above have nothing to share (1000 segments of 2048 bf16 columns over 5000 rows: the
+// centre sums take 97 us, 122 with those).
+template <typename O>
+__global__ void __launch_bounds__(256) k_segsum_final_few(const double* __restrict__ part,
+                                                          const int32_t* __restrict__ tile_start, int G,
+                                                          int w, O* __restrict__ out, int accumulate) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (int64_t)G * w) return;
+  const int e = (int)(idx / w), j = (int)(idx % w);
+  const int32_t q1 = tile_start[e + 1];
+  double p[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int32_t q = tile_start[e]; q < q1; q += 8)
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (q + u < q1) p[u] += part[(int64_t)(q + u) * w + j];
+  const double s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+  if (accumulate) out[idx] = (O)((double)out[idx] + s);
+  else out[idx] = (O)s;
+}
+
 // ------------------------------------------------------------------ row permutation
 
 // out[r] = in[index[r]] for rows of `vpr` 16-byte vectors; a negative index writes zeros.
