@@ -311,8 +311,9 @@ __global__ void __launch_bounds__(64) k_sum_final(const double* __restrict__ par
 }
 
 // The same sum in one launch, for n <= kSumSmall: the 256 slices have at most 64 entries, so a wave adds
-// a slice as k_sum_partial does (its other three waves there have none), and one wave adds the
-// slices' sums as k_sum_final does.  One workgroup of 16 waves.
+// a slice as k_sum_partial does (its other three waves there have none) -- four slices at once where
+// they have at most 16, the butterfly's first two steps adding nothing but zeros --, and one wave adds
+// the slices' sums as k_sum_final does.  One workgroup of 16 waves.
 constexpr int64_t kSumSmall = 64 * kSumBlocks;
 template <typename S, typename O>
 __global__ void __launch_bounds__(1024) k_sum_small(const S* __restrict__ x, int n, double scale,
@@ -320,11 +321,20 @@ __global__ void __launch_bounds__(1024) k_sum_small(const S* __restrict__ x, int
   __shared__ double part[kSumBlocks];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int per = (n + kSumBlocks - 1) / kSumBlocks;
+  if (per <= 16) {
+#pragma unroll
+    for (int b = 4 * w + l / 16; b < kSumBlocks; b += 64) {
+      const int i = b * per + l % 16;
+      const double s = row_sum(l % 16 < per && i < n ? (double)x[i] : 0.0);
+      if (l % 16 == 0) part[b] = s;
+    }
+  } else {
 #pragma unroll 4
-  for (int b = w; b < kSumBlocks; b += 16) {
-    const int i = b * per + l;
-    const double s = wave_sum(l < per && i < n ? (double)x[i] : 0.0);
-    if (l == 0) part[b] = s;
+    for (int b = w; b < kSumBlocks; b += 16) {
+      const int i = b * per + l;
+      const double s = wave_sum(l < per && i < n ? (double)x[i] : 0.0);
+      if (l == 0) part[b] = s;
+    }
   }
   __syncthreads();
   if (w != 0) return;

@@ -1,6 +1,6 @@
 """The one-launch forms of short steps on both sides of the sizes where they end: the counting sort
-(8192 ids, 512 buckets), the objective's sum (16,384 rows), the reseeding's search (16,384 rows)
-and the centre norms that a fit's update leaves for its next assignment."""
+(8192 ids, 512 buckets), the objective's sum (4096 and 16,384 rows), the segments' few pieces, the
+reseeding's search (16,384 rows) and the centre norms that a fit's update leaves for its next assignment."""
 import numpy as np
 import pytest
 import torch
@@ -31,7 +31,22 @@ def test_dispatch(n, K):
     assert int(out["offsets"][K]) == int((key < K).sum())
 
 
-@pytest.mark.parametrize("n,d,K,dtype", [(40, 16, 9, "f32"), (8192, 72, 50, "bf16"), (8193, 64, 300, "f32"),
+# up to eight pieces of 256 rows a segment a thread adds an output's pieces, above that eight threads
+@pytest.mark.parametrize("K", [1, 5])
+@pytest.mark.parametrize("more", [0, 1])
+def test_column_sums_around_eight_pieces(K, more):
+    n, d = 8 * 256 * K + more, 40
+    X = W.gmm_features(n, d, 8, seed=n, dtype="f32", device="cuda")
+    a = torch.zeros(n, dtype=torch.int32, device="cuda")
+    a[: n // 3] = K - 1  # uneven segments, most of them empty
+    sums, counts = torch.ones(K, d, dtype=torch.float64, device="cuda"), torch.zeros(K, dtype=torch.int64, device="cuda")
+    hmoe.kmeans_update(X, K, a, None, sums, counts, torch.zeros(K, d, device="cuda"), mode=hmoe.UPDATE_ACCUMULATE)
+    ref = torch.ones_like(sums).index_add_(0, a.long(), X.double())
+    assert (sums - ref).abs().max() <= n * 2.0 ** -53 * X.double().abs().sum(0).max()
+    assert counts.tolist() == torch.bincount(a.long(), minlength=K).tolist()
+
+
+@pytest.mark.parametrize("n,d,K,dtype", [(40, 16, 9, "f32"), (4096, 8, 2, "f32"), (4097, 8, 2, "f32"), (8192, 72, 50, "bf16"), (8193, 64, 300, "f32"),
                                          (16384, 40, 64, "f32"), (16385, 40, 600, "bf16"), (20000, 1032, 3, "bf16")])
 def test_fit_is_its_steps(n, d, K, dtype):
     """A fit and the same iterations through assign and update: the same bits (reseeding included: two
