@@ -346,8 +346,11 @@ int launch_segsum(const T* X, int64_t ld, const int32_t* rowmap, const int32_t* 
   const auto partial = nv == 1 ? k_segsum_partial<T, 1> : (nv == 2 ? k_segsum_partial<T, 2> : k_segsum_partial<T, kSegMaxVec>);
   HMOE_LAUNCH("segsum partial", partial, dim3((unsigned)pieces, (unsigned)cdiv(vecs, 256 * nv)), dim3(256), 0, st, X, ld,
               rowmap, seg, ts, G, w, part);
-  // more than eight pieces a segment: their sum is a chain worth splitting
-  if (n > 8 * (int64_t)kSegPiece * G)
+  // A thread per output from 2^20 outputs on and up to four pieces a segment on average.  Eight threads / one,
+  // in us, segments of equal length and of Zipf(1) lengths (the longest has an eighth of the rows):
+  // 1000 x 2048 outputs, 0.3 pieces 47 / 15 and 51 / 15, three 54 / 19 and 55 / 32, 7.5 61 / 30 and 65 / 62;
+  // 1000 x 1024, three 30 / 12 and 29 / 29, 7.5 33 / 17 and 34 / 57; 500 x 1024, three 17 / 8 and 17 / 19.
+  if ((int64_t)G * w < (1 << 20) || n > 4 * (int64_t)kSegPiece * G)
     HMOE_LAUNCH("segsum final", k_segsum_final<O>, dim3((unsigned)cdiv((int64_t)G * w, 32)), dim3(256), 0, st, part,
                 ts, G, w, out, accumulate);
   else

@@ -233,9 +233,9 @@ __global__ void __launch_bounds__(256) k_segsum_final(const double* __restrict__
   else out[idx] = (O)s;
 }
 
-// The same sums with a thread for each output, eight loads in flight: for segments of few pieces, where
-// the eight threads above have nothing to share (1000 segments of 2048 bf16 columns over 5000 rows: the
-// centre sums take 97 us, 122 with those).
+// The same sums with a thread for each output: many outputs of few pieces, where the eight threads above
+// have nothing to share and their blocks are too many.  A segment's pieces go 32 loads at a time, so that
+// a long one among the short (one of 250 pieces: 113 us with eight loads, 19) holds nothing up.
 template <typename O>
 __global__ void __launch_bounds__(256) k_segsum_final_few(const double* __restrict__ part,
                                                           const int32_t* __restrict__ tile_start, int G,
@@ -243,12 +243,21 @@ __global__ void __launch_bounds__(256) k_segsum_final_few(const double* __restri
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (int64_t)G * w) return;
   const int e = (int)(idx / w), j = (int)(idx % w);
-  const int32_t q1 = tile_start[e + 1];
-  double p[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int32_t q = tile_start[e]; q < q1; q += 8)
+  int32_t m = tile_start[e + 1] - tile_start[e];
+  const double* src = part + (int64_t)tile_start[e] * w + j;
+  double p[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, v[32];
+  for (; m >= 32; m -= 32, src += (int64_t)32 * w) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (q + u < q1) p[u] += part[(int64_t)(q + u) * w + j];
+    for (int u = 0; u < 32; ++u) v[u] = src[(int64_t)u * w];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) p[u & 7] += v[u];
+  }
+  for (; m > 0; m -= 8, src += (int64_t)8 * w) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = u < m ? src[(int64_t)u * w] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) p[u] += v[u];
+  }
   const double s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
   if (accumulate) out[idx] = (O)((double)out[idx] + s);
   else out[idx] = (O)s;

@@ -31,19 +31,24 @@ def test_dispatch(n, K):
     assert int(out["offsets"][K]) == int((key < K).sum())
 
 
-# up to eight pieces of 256 rows a segment a thread adds an output's pieces, above that eight threads
-@pytest.mark.parametrize("K", [1, 5])
-@pytest.mark.parametrize("more", [0, 1])
-def test_column_sums_around_eight_pieces(K, more):
-    n, d = 8 * 256 * K + more, 40
-    X = W.gmm_features(n, d, 8, seed=n, dtype="f32", device="cuda")
-    a = torch.zeros(n, dtype=torch.int32, device="cuda")
-    a[: n // 3] = K - 1  # uneven segments, most of them empty
-    sums, counts = torch.ones(K, d, dtype=torch.float64, device="cuda"), torch.zeros(K, dtype=torch.int64, device="cuda")
-    hmoe.kmeans_update(X, K, a, None, sums, counts, torch.zeros(K, d, device="cuda"), mode=hmoe.UPDATE_ACCUMULATE)
-    ref = torch.ones_like(sums).index_add_(0, a.long(), X.double())
-    assert (sums - ref).abs().max() <= n * 2.0 ** -53 * X.double().abs().sum(0).max()
-    assert counts.tolist() == torch.bincount(a.long(), minlength=K).tolist()
+# segments of no, one, a few, 8, 9, 31 .. 33 and 40 pieces of 256 rows: from 2^20 outputs on a thread adds an
+# output's pieces, below that eight threads do, in the same order
+def test_column_sums_of_uneven_segments():
+    K, d = 4096, 256
+    pieces = {0: 1, 3: 40, 4: 31, 5: 32, 700: 33, 701: 8, 702: 9, 4094: 3, 4095: 16}
+    a = torch.cat([torch.full((256 * p - (e % 2) * 5,), e, dtype=torch.int32, device="cuda") for e, p in pieces.items()])
+    a = a[torch.randperm(a.numel(), generator=torch.Generator().manual_seed(1)).cuda()].contiguous()
+    X = W.gmm_features(a.numel(), d, 8, seed=3, dtype="f32", device="cuda")
+    got = []
+    for w in (d, d - 8):
+        x = X[:, :w].contiguous()
+        sums, counts = torch.ones(K, w, dtype=torch.float64, device="cuda"), torch.zeros(K, dtype=torch.int64, device="cuda")
+        hmoe.kmeans_update(x, K, a, None, sums, counts, torch.zeros(K, w, device="cuda"), mode=hmoe.UPDATE_ACCUMULATE)
+        ref = torch.ones_like(sums).index_add_(0, a.long(), x.double())
+        assert (sums - ref).abs().max() <= a.numel() * 2.0 ** -53 * x.double().abs().sum(0).max()
+        assert counts.tolist() == torch.bincount(a.long(), minlength=K).tolist()
+        got.append(sums)
+    assert torch.equal(got[0][:, : d - 8], got[1])
 
 
 @pytest.mark.parametrize("n,d,K,dtype", [(40, 16, 9, "f32"), (4096, 8, 2, "f32"), (4097, 8, 2, "f32"), (8192, 72, 50, "bf16"), (8193, 64, 300, "f32"),
