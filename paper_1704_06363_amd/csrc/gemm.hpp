@@ -1,8 +1,8 @@
 // gemm.hpp -- the MFMA tile engines shared by every dense contraction of the hot path: the
 // register-staged engine described first (Cfg: the fp32 MoE products, the PCA fit's, the bf16
-// assignment to 65 .. 128 centres and rows too wide for the others), the direct-to-LDS ring (CfgD:
-// assignments to up to 64 centres) and the pipelined engine (CfgP: the bf16 MoE products, the larger
-// assignments and the PCA's projection).
+// assignment to 65 .. 128 centres and rows too wide for the pipelined engine), the direct-to-LDS ring
+// (CfgD: assignments to up to 64 centres, projections to up to 64 components) and the pipelined engine
+// (CfgP: the bf16 MoE products, the larger assignments and projections).
 //
 // C[m, n] = sum_k A(m, k) * B(n, k) over one BM x BN output tile per workgroup, split into
 // (BM/WM) x (BN/WN) wavefronts of WM x WN.  Operands are staged through LDS in a row-major,
@@ -303,11 +303,12 @@ __device__ __forceinline__ void gemm_tile_reg(const typename C::type* __restrict
 
 // ------------------------------------------------------------------ direct-to-LDS ring
 //
-// NT products with few columns (the gater's assignment to up to 64 centres).  Operands travel from
-// HBM to LDS without passing through registers: global_load_lds_dwordx4 writes lane l's 16 bytes to LDS at
-// (wave-uniform base) + 16 l, so the LDS layout -- including its bank swizzle -- is chosen by the global
-// address each lane loads.  A stage covers 32 K (64 bytes per row); NS stages form a ring and
-// the loads for stage kt + NS - 1 are issued while stage kt feeds the MFMAs, each wave waiting
+// NT products with few columns (the gater's assignment to up to 64 centres, the PCA's projection to up
+// to 64 components).  Operands travel from HBM to LDS without passing through registers:
+// global_load_lds_dwordx4 writes lane l's 16 bytes to LDS at (wave-uniform base) + 16 l, so the LDS
+// layout -- including its bank swizzle -- is chosen by the global address each lane loads.  A stage
+// covers 32 K (64 bytes per row); NS stages form a ring and the loads for stage kt + NS - 1 are
+// issued while stage kt feeds the MFMAs, each wave waiting
 // (vmcnt) only for its own loads of the stage it is about to read.  LDS holds [rows][32 K] (64-byte
 // rows, chunk c of row r at c ^ ((r >> 1) & 3)); MFMA operands come from one ds_read_b128 per 16 x 32
 // fragment, conflict-free (checked with the LDS bank-conflict counter).  Rows past the valid range
@@ -336,8 +337,8 @@ struct CfgD {
   static_assert(sizeof(T) == 2 || sizeof(T) == 4, "bf16 or fp32 operands");
 };
 
-// fp32 with at most 64 columns (the gater's assignment, K <= 64): 128 x 64 tiles of four waves
-// and a 3-stage ring (36 KB), four workgroups per CU -- measured against 256 x 64 (4 stages:
+// At most 64 columns: 128 x 64 tiles of four waves
+// and a 3-stage ring (36 KB), four workgroups per CU -- on fp32 rows against 256 x 64 (4 stages:
 // 11% slower; 3 stages: 15%), 128 x 64 with 2 or 4 stages (10%, 8%) and 64 x 64 (17%)
 typedef CfgD<float, 128, 64, 32, 64, 3> CfgDmaF32Narrow;
 typedef CfgD<bf16, 128, 64, 32, 64, 3> CfgDmaNarrow;
@@ -821,16 +822,19 @@ struct HalfFrags {
 // loads before it runs the current tile's epilogue:
 //   prime()  issues the first loads of a tile (LDS must be free: after run()'s closing barrier,
 //            or at kernel start);
-//   run()    the main loop; it ends with a barrier after which LDS is free again.  run<.., X>(.., after_prime) is for a caller that issued exactly X
-//            further memory operations (per wave) between prime() and run() when after_prime is
-//            true: the waits for the primed loads let those X stay in flight.
+//   run()    the main loop; it ends with a barrier after which LDS is free again.
+//            run<.., X>(.., after_prime) is for a caller that issued exactly X further memory
+//            operations (per wave) between prime() and run() when after_prime is true: the waits
+//            for the primed loads let those X stay in flight.
 // A_SW > 0: A is K-contiguous and stored slab-major -- K split into slabs of A_SW columns,
 // slab s of every row at A + s a_sstride, lda = A_SW within a slab (A_SW a multiple of BK).
 // Set the stride with slab_a() before prime().
 // A partial last stage is one more stage of the loop, its pieces past the end loaded from zeros; with
 // REG_TAIL it goes through registers after the loop: the row norms leave no registers for the other
 // (48 spilled, 200,000 x 2048 bf16 against 256 centres 319 -> 570 us), and the loop of long reductions
-// over rows (dD) comes out 2% slower with it.
+// over rows (dD) comes out 2% slower with it.  The experts' weight gradients take the stage: dW1 of few
+// long segments loses 3% (58,224 x 112, six experts 927 -> 955 us), of many gains 8% and more (skewed
+// step 685 -> 630, 5003 x 1000 and 50 experts 131 -> 119).
 template <class C, bool A_KC, bool B_KC, int A_SW = 0, bool REG_TAIL = false>
 struct PipeTile {
   using OA = HalfPanels<C::BM, C::WM, C::THREADS, A_KC, false>;
